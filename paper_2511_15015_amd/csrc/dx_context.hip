@@ -500,7 +500,7 @@ extern "C" dx_status dx_router_logits(dx_ctx *c, const void *x, const void *w_ro
     if (((uintptr_t)x & 15) || ((uintptr_t)w_router & 15) || ((uintptr_t)logits & 3) || ((uintptr_t)bias & 3))
         DX_FAIL(c, DX_ERR_INVALID, "dx_router_logits: misaligned pointer");
     DX_HIP(c, dxk_router_gemm(static_cast<const dx_bf16 *>(x), static_cast<const dx_bf16 *>(w_router), bias, T, c->cfg.E,
-                              c->cfg.d, logits, c->compute));
+                              c->cfg.d, logits, c->n_cu, c->compute));
     return DX_OK;
 }
 

@@ -230,48 +230,116 @@ __global__ void k_store_handle(dx_handle *slot, dx_handle h)
     if (threadIdx.x == 0 && blockIdx.x == 0) *slot = h;
 }
 
-// Router gate: logits = x . W_r^T (+ bias).  One block per 32 tokens x 32 experts; its 4 wavefronts
-// take the K-steps of 16 in turn (step s to wavefront s % 4), each multiplying with
-// v_mfma_f32_32x32x16_bf16 straight from global memory (lane l: row l % 32, 8 consecutive k from
-// 8 * (l / 32)); the four partial tiles meet in LDS and are added in wavefront order.
+// Router gate: logits = x . W_r^T (+ bias).  Bound by latency for decode batches (2 MB of W_r at most: a fraction
+// of a microsecond at the HBM rate) and by what a compute unit can take in for prefill batches.  A block
+// computes 16*MT tokens x 16*NT experts and its WAVES wavefronts split K, so every operand byte of the tile
+// enters the compute unit once and no second kernel or atomic is needed; the partial tiles meet in LDS and are
+// added in the order of the wavefronts.
+// A compute unit takes in 120 GB/s from L2 when eight neighbouring lanes read one 128-byte line, but only 37 GB/s
+// in the operand order of v_mfma_f32_16x16x32_bf16 (lane (r, q): row r, 16 bytes at 64 bytes of 16 rows per
+// instruction; the same for lines of 8 rows whose lanes are not neighbours).  So a wavefront loads whole lines
+// (8 rows x 128 bytes per instruction, two lines of every row in flight), passes each line through a stage of
+// LDS of its own (piece p of row r in slot p ^ ((r >> 1) & 7): no bank conflicts) and reads the operands there.
+// Per call, d = 2048: 32 tokens x 512 experts 3.4 us, 4096 x 128 8.9 us (13.4 and 17.6 us with 32 x 32 tiles of 4
+// wavefronts straight from global memory).
 typedef __attribute__((ext_vector_type(8))) __bf16 rt_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float rt_f32x16;
+typedef __attribute__((ext_vector_type(4))) float rt_f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t rt_u32x4;
 
-__global__ __launch_bounds__(256) void k_router_gemm(const dx_bf16 *__restrict__ x, const dx_bf16 *__restrict__ w_r,
-                                                     const float *__restrict__ bias, int T, int E, int d,
-                                                     float *__restrict__ logits)
+template <int MT, int NT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_router_gemm(const dx_bf16 *__restrict__ x, const dx_bf16 *__restrict__ w_r,
+                                                            const float *__restrict__ bias, int T, int E, int d,
+                                                            int by_xcd, float *__restrict__ logits)
 {
-    __shared__ float part[4][32][33];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.y * 32, e0 = blockIdx.x * 32;
-    const int r = lane & 31, kq = lane >> 5;
-    const int t = min(t0 + r, T - 1), e = min(e0 + r, E - 1); // rows past the end repeat the last one; never stored
-    const dx_bf16 *xrow = x + (size_t)t * d + kq * 8;
-    const dx_bf16 *wrow = w_r + (size_t)e * d + kq * 8;
-    rt_f32x16 acc;
+    constexpr int ROWS = 16 * MT, COLS = 16 * NT, LOADS = 2 * (MT + NT); // LOADS: eight-row groups of a line
+    constexpr int kStage = LOADS * 1024;
+    constexpr int kPart = MT * NT * 1024;
+    __shared__ __attribute__((aligned(128))) char lds[WAVES * (kStage > kPart ? kStage : kPart)];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // by_xcd: block b runs on XCD b % 8; the column tiles of a row tile go to one XCD, so that its x rows are read
+    // into one L2 only (row tiles are padded to a multiple of 8).
+    const int ncol = (E + COLS - 1) / COLS, at_xcd = blockIdx.x >> 3;
+    const int t0 = (by_xcd ? (at_xcd / ncol) * 8 + (blockIdx.x & 7) : blockIdx.x / ncol) * ROWS;
+    const int e0 = (by_xcd ? at_xcd % ncol : blockIdx.x % ncol) * COLS;
+    if (t0 >= T) return;
+    // loader: piece lane % 8 of row lane / 8 of every group.  Rows past the end repeat the last one; never stored.
+    const int piece = lane & 7;
+    const dx_bf16 *row[LOADS];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int i = 0; i < LOADS; ++i) {
+        const int rr = 8 * i + (lane >> 3);
+        row[i] = i < 2 * MT ? x + (size_t)min(t0 + rr, T - 1) * d : w_r + (size_t)min(e0 + rr - ROWS, E - 1) * d;
+    }
+    const int nlines = (d + 63) / 64, nsteps = d / 32; // the last line may be half a line: its second step is left out
+    const int per = (nlines + WAVES - 1) / WAVES;      // consecutive lines of a row to a wavefront
+    const int l0 = wave * per, l1 = min(nlines, l0 + per);
+    auto load_line = [&](int l, rt_u32x4 (&v)[LOADS]) {
+        l = max(min(l, l1 - 1), 0);
+        const int at = l * 64 + (2 * l + 1 < nsteps ? piece : piece & 3) * 8;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) v[i] = *reinterpret_cast<const rt_u32x4 *>(row[i] + at);
+    };
+    char *stage = lds + wave * kStage;
+    const int put = (lane >> 3) * 128 + (piece ^ ((lane >> 4) & 3)) * 16; // + 1024 per group, the swizzle's third bit below
+    const int r = lane & 15, q = lane >> 4;
+    rt_f32x4 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[m][n] = rt_f32x4{0.f, 0.f, 0.f, 0.f};
     union frag {
         rt_u32x4 u;
         rt_bf16x8 v;
     };
-    for (int s = wave; s < d / 16; s += 4) {
-        frag a, b;
-        a.u = *reinterpret_cast<const rt_u32x4 *>(xrow + s * 16);
-        b.u = *reinterpret_cast<const rt_u32x4 *>(wrow + s * 16);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, acc, 0, 0, 0);
-    }
-    // accumulator element v: token row (v/4)*8 + (lane/32)*4 + v%4, expert column lane%32
+    auto multiply_line = [&](int l, const rt_u32x4 (&v)[LOADS]) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) part[wave][(v >> 2) * 8 + kq * 4 + (v & 3)][r] = acc[v];
+        for (int i = 0; i < LOADS; ++i) // row 8 * i + lane / 8: bit 2 of (row >> 1) & 7 is i & 1
+            *reinterpret_cast<rt_u32x4 *>(stage + i * 1024 + (put ^ ((i & 1) * 64))) = v[i];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (2 * l + h >= nsteps) break; // wavefront-uniform
+            frag a[MT], b[NT];
+            const int slot = ((q + 4 * h) ^ ((r >> 1) & 7)) * 16;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) a[m].u = *reinterpret_cast<const rt_u32x4 *>(stage + (16 * m + r) * 128 + slot);
+#pragma unroll
+            for (int n = 0; n < NT; ++n) b[n].u = *reinterpret_cast<const rt_u32x4 *>(stage + (ROWS + 16 * n + r) * 128 + slot);
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m].v, b[n].v, acc[m][n], 0, 0, 0);
+        }
+    };
+    rt_u32x4 v[2][LOADS];
+    if (l0 < l1) { // wavefront-uniform
+        load_line(l0, v[0]);
+        load_line(l0 + 1, v[1]);
+        for (int l = l0; l < l1; l += 2) { // loads past the end are duplicates that are not multiplied
+            multiply_line(l, v[0]);
+            load_line(l + 2, v[0]);
+            if (l + 1 < l1) multiply_line(l + 1, v[1]);
+            load_line(l + 3, v[1]);
+        }
+    }
+    __syncthreads(); // the stages are free
+    float *part = reinterpret_cast<float *>(lds); // [WAVES][MT * NT][4][64]
+    // accumulator element v of lane (r, q): token row 4q + v, expert column r
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[((wave * MT * NT + m * NT + n) * 4 + i) * 64 + lane] = acc[m][n][i];
     __syncthreads();
-    for (int i = threadIdx.x; i < 32 * 32; i += 256) {
-        const int tr = i >> 5, ec = i & 31;
+    for (int i = threadIdx.x; i < ROWS * COLS; i += WAVES * 64) { // in the order of `part`: no bank conflicts
+        const int tile = i >> 8, tr = 16 * (tile / NT) + 4 * ((i & 63) >> 4) + ((i >> 6) & 3), ec = 16 * (tile % NT) + (i & 15);
         if (t0 + tr >= T || e0 + ec >= E) continue;
-        float v = ((part[0][tr][ec] + part[1][tr][ec]) + part[2][tr][ec]) + part[3][tr][ec];
-        if (bias) v += bias[e0 + ec];
-        logits[(size_t)(t0 + tr) * E + e0 + ec] = v;
+        float s = part[i];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) s += part[w * ROWS * COLS + i];
+        if (bias) s += bias[e0 + ec];
+        logits[(size_t)(t0 + tr) * E + e0 + ec] = s;
     }
 }
 
@@ -316,10 +384,25 @@ hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, flo
 }
 
 hipError_t dxk_router_gemm(const dx_bf16 *x, const dx_bf16 *w_r, const float *bias, int T, int E, int d, float *logits,
-                           hipStream_t s)
+                           int n_cu, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_router_gemm, dim3((E + 31) / 32, (T + 31) / 32), dim3(256), 0, s, x, w_r, bias, T, E, d, logits);
+    // The smallest tile whose blocks run in one round on the chip; beyond that the tile that moves the fewest bytes
+    // into the compute units (an x row is read E / 16*NT times, a W_r row T / 16*MT times).  Measured, d = 2048:
+    // T = 300, E = 128: 4.0 us (16 x 16), 5.7 (32 x 32); T = 1000, E = 512: 16.8, 9.4, 8.5 (32 x 64), 11.9 (64 x 64);
+    // T = 4096, E = 512: 27.0, 28.4 and 18.9 us from 32 x 32 up.
+    const long cu = n_cu;
+    auto blocks = [&](int rows, int cols) { return (long)((T + rows - 1) / rows) * ((E + cols - 1) / cols); };
+    auto run = [&](auto kernel, int rows, int cols, int threads) {
+        const int nrow = (T + rows - 1) / rows, ncol = (E + cols - 1) / cols;
+        const int by_xcd = nrow >= 16 && ncol > 1;
+        hipLaunchKernelGGL(kernel, dim3((by_xcd ? (nrow + 7) / 8 * 8 : nrow) * ncol), dim3(threads), 0, s, x, w_r, bias, T, E,
+                           d, by_xcd, logits);
+    };
+    if (blocks(16, 16) <= cu) run(k_router_gemm<1, 1, 8>, 16, 16, 512);
+    else if (blocks(32, 32) <= cu) run(k_router_gemm<2, 2, 8>, 32, 32, 512);
+    else if (blocks(32, 64) <= cu) run(k_router_gemm<2, 4, 8>, 32, 64, 512);
+    else run(k_router_gemm<4, 4, 4>, 64, 64, 256);
     return hipGetLastError();
 }
 

@@ -215,6 +215,33 @@ def test_router_logits_match_oracle(B, LY, dxo, T, E, d, with_bias):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,E,d,with_bias", [
+    (20, 20, 32, False),      # 16 x 16 tiles, half a line, more wavefronts than lines
+    (16, 16, 2080, True),     # an odd number of lines per wavefront and half a line at the end
+    (4097, 17, 64, True),     # 32 x 32 tiles, remainders of one, the XCD order with padded row tiles
+    (1000, 500, 96, True),    # 32 x 64 tiles
+    (2049, 500, 160, False),  # 64 x 64 tiles
+])
+def test_router_logits_tile_edges(B, LY, dxo, T, E, d, with_bias):
+    """Every tile of the router gate at remainders of rows, columns and K.  Bound per element: fp32 sums of d exact
+    products, each addition at most 2^-24 of the sum of the magnitudes."""
+    g = np.random.default_rng(T * E + d)
+    x = W.f32_to_bf16_bits(g.standard_normal((T, d)).astype(np.float32))
+    wr = W.f32_to_bf16_bits((0.02 * g.standard_normal((E, d))).astype(np.float32))
+    bias = (g.standard_normal(E) * 3).astype(np.float32) if with_bias else None
+    ctx = B.Context(L=1, E=E, d=d, f=64, top_k=2, group=32, max_tokens=T)
+    out = torch.full((T, E), float("nan"), dtype=torch.float32, device="cuda")
+    ctx.dx_router_logits(LY.bits_to_device(x), LY.bits_to_device(wr),
+                         torch.from_numpy(bias).cuda() if with_bias else None, T, out)
+    sync()
+    ref = dxo.router_logits(x, wr, bias)
+    mag = np.abs(W.bf16_bits_to_f32(x)).astype(np.float64) @ np.abs(W.bf16_bits_to_f32(wr)).astype(np.float64).T
+    if with_bias:
+        mag = mag + np.abs(bias)[None, :]
+    assert (np.abs(out.cpu().numpy() - ref) <= (d + 1) * 2.0 ** -24 * mag).all()
+    ctx.close()
+
+
 # ------------------------------------------------------------------ the layer
 class Layer:
     """One layer set up on both sides from the same master bits."""
