@@ -29,16 +29,14 @@
 //     the expert and the K-chunk, so each wavefront keeps its fragments in
 //     registers for all strips of a run: after the first strip, weights are
 //     the only global traffic.
-//   - Lane (r = lane%16, q = lane/16) owns tile row r.  bf16: step j of a
-//     chunk takes elements 32j + 8q .. +7.  int4 / int2: the lane takes the
-//     LK consecutive elements at q*LK (one 16-byte / 8-byte piece for LK =
-//     32).  Token fragments use the same K ownership, which makes either
-//     order valid.  Where the sizes allow it the loads themselves cover whole
-//     128-byte lines of 8 rows and a DPP move sorts the pieces into this
-//     ownership (see kLines).
-//   - Quantized weights are expanded to exact small bf16 integers; a K-chunk
-//     never crosses a quantization group, so the group's scale multiplies the
-//     chunk's fp32 partial sums once (q*s is never rounded).
+//   - Lane (r = lane%16, q = lane/16) owns tile row r in the matrix instruction.  Weights and token rows are
+//     loaded in another order, eight neighbouring lanes to a 128-byte line, and pass through a small area of
+//     LDS of the wavefront on their way to the operands (see line_load).  Contractions that are no multiple
+//     of 128 load in operand order (LK = 16, 8).
+//   - Quantized weights are expanded to exact small bf16 integers; a step of
+//     the matrix instruction never crosses a quantization group, so the
+//     group's scale multiplies the group's fp32 partial sums once (q*s is
+//     never rounded).
 // Batches of up to 128 tokens run here alone (segments above 32 tokens in
 // blocks of 32); larger ones hand the big segments to the tile kernels.
 #include "dx_internal.h"
@@ -47,6 +45,7 @@
 #include <hip/hip_ext.h>
 
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -189,94 +188,286 @@ struct wstage {
     uint32_t wq[CPW][NQ];       // int4: JN words of 8 nibbles; int2: JN/2 words of 16 codes
 };
 
-// The cache policy of the weight stream.  With the non-temporal hint a read-only stream of whole 128-byte
-// lines is faster on this chip (7.0 against 6.2 TB/s), but only when a load instruction covers whole lines.
-// The operand layout of the matrix instruction wants, per instruction, 16 bytes per lane of the lane's own
-// row: 64 bytes of each of 16 rows, the other half of every line in the next instruction -- hinted loads of
-// that shape measured slower than plain ones (gate/up 46.5 against 44.4 us on the 30B-shaped layer).
-// kLines<...> chooses the other shape where the sizes allow it: an instruction covers 128 bytes of each of 8
-// rows (lane (r, q) fetches row r % 8 of the strip's lower or upper half, 16-byte piece q + 4 * (r / 8) of
-// the line), so half of what a lane receives belongs to the lane 8 places away in its 16-lane row; one DPP
-// move per register (row rotation by 8, written to half of the row) puts it there when the stage is used.
-// The K order of the operands does not change.
-template <typename T>
-__device__ __forceinline__ T stream_load(const DX_GLOBAL T *p)
-{
-    return *p;
-}
+// The weight stream of chunks of 128 elements (LK = 32), and the token rows of all formats.  Three measurements on
+// this chip decide its shape (a 192 MB stream of cold strips, one 8-wavefront block per compute unit):
+//   - a compute unit takes in 120 GB/s (from L2) when eight neighbouring lanes read one 128-byte line, 37 GB/s
+//     when the lanes of a line are spread over the wavefront, as the operand order of the matrix instruction
+//     (lane (r, q): 16 bytes of row r) wants them;
+//   - with the non-temporal hint whole lines in neighbour order stream at 6.2 TB/s, in the spread order (8 rows
+//     x 128 bytes per instruction all the same) at 5.75, without the hint at 5.2 to 5.6;
+//   - loads to LDS stream at 5.2 TB/s whatever the hint.
+// So lane l fetches 16-byte piece l % 8 of row l / 8 into registers, and when a stage is used it passes through a
+// small area of LDS that belongs to the wavefront (no barrier; the area is the wavefront's part of the `red`
+// buffer that is next to be filled, unused until the sums are parked), from where the operands are read in the
+// order they are needed.  Reading from LDS also lets every step of the matrix instruction take its elements
+// from one quantization group, whatever the group size: GPC = groups per chunk (1, 2, 4 for groups of 128, 64, 32).
+//   Area: bf16 [line][16 rows][128 B], a chunk at a time; int4 [16 rows][64 * CPW B]; int2 [16 rows][32 * CPW B].
+//   16-byte piece p of row r sits in slot p ^ ((r >> 1) & 7) of a 128-byte row, p ^ ((r >> 2) & 3) of a 64-byte
+//   row: the 16 lanes that read one piece index of 16 rows hit 16 different bank groups.
 template <typename T>
 __device__ __forceinline__ T line_load(const DX_GLOBAL T *p)
 {
     return __builtin_nontemporal_load(p);
 }
 
-// bf16: a chunk of 128 elements is two lines per row; int4: two chunks side by side are one line per row
-template <int LK, int CPW, int FMT, bool FAST>
-constexpr bool kLines = LK == 32 && (FMT == 0 || (FMT == 1 && CPW == 2 && FAST));
+typedef __attribute__((address_space(3))) char *lds_bytes;
+template <typename T>
+__device__ __forceinline__ T lds_get(lds_bytes p)
+{
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(p);
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(lds_bytes p, T v)
+{
+    *reinterpret_cast<__attribute__((address_space(3))) T *>(p) = v;
+}
 
-// Line-shaped loads of one strip: `row_lo` is row r % 8 of the strip's lower eight rows, `row_hi` row r % 8
-// of its upper eight (in a gate/up strip another matrix), `piece` = q + 4 * (r / 8).  Stage register n of
-// chunk i then holds load (line n / 2, half n % 2) (bf16) resp. chunk register i holds the load of half i
-// (int4) until settle_lines sorts them out.
-template <int LK, int CPW, int FMT>
-__device__ __forceinline__ void issue_weight_lines(wstage<LK, CPW, FMT> &st, gbytes row_lo, gbytes row_hi, int c0,
-                                                   int nc, int piece)
+// weight registers of one wavefront for one 16-row strip of CPW chunks, in the order they were loaded
+template <int CPW, int FMT>
+struct line_stage {
+    static constexpr int N = FMT == 0 ? 4 * CPW : (FMT == 1 ? CPW : 1);
+    u32x4 w[N];
+};
+
+// `lo`: the strip's first eight rows at the wavefront's first chunk, `hi`: its other eight (in a gate/up strip
+// another matrix); `two`: the second chunk of a CPW = 2 stage exists.
+template <int CPW, int FMT>
+__device__ __forceinline__ void issue_lines(line_stage<CPW, FMT> &st, gbytes lo, gbytes hi, uint32_t row_bytes, bool one,
+                                            bool two, int lane)
 {
     if constexpr (FMT == 0) {
+        const uint32_t off = (uint32_t)(lane >> 3) * row_bytes + (lane & 7) * 16;
 #pragma unroll
         for (int i = 0; i < CPW; ++i) {
-            if (c0 + i < nc) { // wavefront-uniform
+            if (i ? two : one) { // wavefront-uniform
 #pragma unroll
                 for (int n = 0; n < 4; ++n)
-                    st.w[i][n] = line_load(reinterpret_cast<gvec16>(((n & 1) ? row_hi : row_lo) + (size_t)(c0 + i) * 256 +
-                                                                   128 * (n >> 1) + 16 * piece));
+                    st.w[i * 4 + n] = line_load(reinterpret_cast<gvec16>(((n & 1) ? hi : lo) + (i * 256 + 128 * (n >> 1)) + off));
             }
         }
-    } else {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u32x4 t = line_load(reinterpret_cast<gvec16>((h ? row_hi : row_lo) + (size_t)c0 * 64 + 16 * piece));
-            st.wq[h][0] = t.x; st.wq[h][1] = t.y; st.wq[h][2] = t.z; st.wq[h][3] = t.w;
+    } else if constexpr (FMT == 1 && CPW == 2) {
+        // (without the second chunk the lanes of its half re-read the first)
+        const uint32_t off = (uint32_t)(lane >> 3) * row_bytes + (lane & (two ? 7 : 3)) * 16;
+        if (one) {
+            st.w[0] = line_load(reinterpret_cast<gvec16>(lo + off));
+            st.w[1] = line_load(reinterpret_cast<gvec16>(hi + off));
+        }
+    } else if (one) {
+        // all 16 rows in one instruction: 64 (int2, one chunk: 32) bytes of each
+        const gbytes base = (lane < 32 ? lo : hi) + (uint32_t)((lane >> 2) & 7) * row_bytes;
+        if constexpr (FMT == 2 && CPW == 1) {
+            const u32x2 t = line_load(reinterpret_cast<gvec8>(base + (lane & 3) * 8));
+            st.w[0] = u32x4{t.x, t.y, 0u, 0u};
+        } else {
+            st.w[0] = line_load(reinterpret_cast<gvec16>(base + (lane & (CPW == 1 || two ? 3 : 1)) * 16));
         }
     }
 }
 
-// register pair (a, b) = loads (lower half rows, upper half rows) of the same line: afterwards a holds the
-// lane's own row's first piece, b its second (lanes 0..7 of a row keep a and receive b from 8 places up,
-// lanes 8..15 keep b and receive a from 8 places down)
-__device__ __forceinline__ void settle_pair(uint32_t &a, uint32_t &b)
+// byte addresses in the wavefront's area, computed once per run
+struct line_lanes {
+    int put, get, get64, get32; // 128-byte rows: the loaded piece; pieces q, q / 2 (8 bytes), 0 (4 bytes) of row r
+    int put_s, get_s, get64_s, get32_s; // the same for 64-byte rows
+    int tok1, tok2;             // tokens: piece 4 * (q % 2) of line q / 2; piece 2q
+};
+__device__ __forceinline__ line_lanes line_lanes_of(int lane)
 {
-    const int a0 = (int)a, b0 = (int)b;
-    a = (uint32_t)__builtin_amdgcn_update_dpp(a0, b0, 0x128 /* row_ror:8 */, 0xF, 0xC, false);
-    b = (uint32_t)__builtin_amdgcn_update_dpp(b0, a0, 0x128, 0xF, 0x3, false);
+    const int r = lane & 15, q = lane >> 4, s = (r >> 1) & 7, f = (r >> 2) & 3;
+    line_lanes ll;
+    ll.put = (lane >> 3) * 128 + ((lane & 7) ^ ((lane >> 4) & 3)) * 16; // rows 8..15: ^ 64 on top
+    ll.get = r * 128 + (q ^ s) * 16;
+    ll.get64 = r * 128 + ((q >> 1) ^ s) * 16 + 8 * (q & 1);
+    ll.get32 = r * 128 + s * 16 + 4 * q;
+    ll.put_s = (lane >> 2) * 64 + ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
+    ll.get_s = r * 64 + (q ^ f) * 16;
+    ll.get64_s = r * 64 + ((q >> 1) ^ f) * 16 + 8 * (q & 1);
+    ll.get32_s = r * 64 + f * 16 + 4 * q;
+    ll.tok1 = r * 128 + ((4 * (q & 1)) ^ s) * 16 + (q >> 1) * 2048;
+    ll.tok2 = r * 128 + ((2 * q) ^ s) * 16;
+    return ll;
 }
 
-template <int LK, int CPW, int FMT>
-__device__ __forceinline__ wstage<LK, CPW, FMT> settle_lines(const wstage<LK, CPW, FMT> &in, int c0, int nc)
+// Which 8 elements of a chunk lane (r, q) takes in step j: bf16 and GPC = 4: 32j + 8q; else
+// (128 / GPC) * (j / SPG) + (32 / GPC) * q + 8 * (j % SPG) with SPG = 4 / GPC steps per group.
+template <int GPC, int CPW, int FMT, int MT>
+__device__ __forceinline__ void load_token_lines(u32x4 (&x)[CPW][MT][4], const gbf16 (&row)[2][2], int c0, int nc, int lane,
+                                                 const line_lanes &ll, lds_bytes area)
 {
-    wstage<LK, CPW, FMT> st = in;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        if (c0 + i < nc) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    x[i][mt][n] = *reinterpret_cast<gvec16>(row[mt][n & 1] + (c0 + i) * 128 + 64 * (n >> 1) + (lane & 7) * 8);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        if (c0 + i < nc) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    lds_put(area + (n >> 1) * 2048 + (n & 1) * 1024 + (ll.put ^ ((n & 1) * 64)), x[i][mt][n]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (FMT == 0 || GPC == 4) x[i][mt][j] = lds_get<u32x4>(area + (j >> 1) * 2048 + (ll.get ^ ((j & 1) * 64)));
+                    else if constexpr (GPC == 2) x[i][mt][j] = lds_get<u32x4>(area + (j >> 1) * 2048 + (ll.tok2 ^ ((j & 1) * 16)));
+                    else x[i][mt][j] = lds_get<u32x4>(area + (ll.tok1 ^ (j * 16)));
+                }
+            }
+        }
+    }
+}
+
+// Quantized runs: bring the token fragments into the element order of the expanded codes and compute
+// nbias[i][g][mt] = -bias * sum over group g of chunk i of the token row (one MFMA against all-ones per step), laid
+// out like an accumulator (every column holds the row's sum): what the group's products start from.
+template <int GPC, int CPW, int MT, int FMT>
+__device__ __forceinline__ void prepare_line_tokens(u32x4 (&x)[CPW][MT][4], f32x4 (&nbias)[CPW][GPC][MT], int c0, int nc)
+{
+    constexpr int SPG = 4 / GPC;
+    frag8 ones;
+    ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        if (c0 + i < nc) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int g = 0; g < GPC; ++g) {
+                    f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = g * SPG; j < (g + 1) * SPG; ++j) {
+                        frag8 a;
+                        a.u = x[i][mt][j];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, sum, 0, 0, 0);
+                        if constexpr (FMT == 1) x[i][mt][j] = interleave_halves(x[i][mt][j]);
+                    }
+                    nbias[i][g][mt] = sum * (FMT == 1 ? -kNibbleBias : -kCrumbBias);
+                }
+                if constexpr (FMT == 2) {
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2) zip_fragments(x[i][mt][j], x[i][mt][j + 1]);
+                }
+            }
+        }
+    }
+}
+
+template <int GPC, int CPW, int FMT, int MT>
+__device__ __forceinline__ void multiply_lines(const line_stage<CPW, FMT> &st, const u32x4 (&x)[CPW][MT][4],
+                                               const f32x4 (&nbias)[CPW][GPC][MT], const uint32_t (&scales)[(CPW * GPC + 1) / 2],
+                                               bool one, bool two, const line_lanes &ll, int lane, lds_bytes area,
+                                               f32x4 (&acc)[MT])
+{
+    constexpr int SPG = 4 / GPC;
+    if (!one) return; // wavefront-uniform
     if constexpr (FMT == 0) {
+        frag8 wv[CPW][4];
 #pragma unroll
         for (int i = 0; i < CPW; ++i) {
-            if (c0 + i < nc) {
+            if (i == 0 || two) {
 #pragma unroll
-                for (int l = 0; l < 2; ++l)
+                for (int n = 0; n < 4; ++n)
+                    lds_put(area + (n >> 1) * 2048 + (n & 1) * 1024 + (ll.put ^ ((n & 1) * 64)), st.w[i * 4 + n]);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        uint32_t a = st.w[i][2 * l][k], b = st.w[i][2 * l + 1][k];
-                        settle_pair(a, b);
-                        st.w[i][2 * l][k] = a;
-                        st.w[i][2 * l + 1][k] = b;
+                for (int j = 0; j < 4; ++j) wv[i][j].u = lds_get<u32x4>(area + (j >> 1) * 2048 + (ll.get ^ ((j & 1) * 64)));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            if (i == 0 || two) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        frag8 a;
+                        a.u = x[i][mt][j];
+                        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, wv[i][j].v, acc[mt], 0, 0, 0);
                     }
             }
         }
     } else {
+        constexpr bool wide = FMT == 1 && CPW == 2; // 128-byte rows in the area
+        if constexpr (wide) {
+            lds_put(area + ll.put, st.w[0]);
+            lds_put(area + 1024 + (ll.put ^ 64), st.w[1]);
+        } else if constexpr (FMT == 2 && CPW == 1) {
+            lds_put(area + lane * 8, u32x2{st.w[0].x, st.w[0].y}); // 32-byte rows
+        } else {
+            lds_put(area + ll.put_s, st.w[0]);
+        }
+        uint32_t wq[CPW][4]; // int4: a word of 8 codes per step; int2: a word of 16 codes per two steps
 #pragma unroll
-        for (int k = 0; k < 4; ++k) settle_pair(st.wq[0][k], st.wq[1][k]);
+        for (int i = 0; i < CPW; ++i) {
+            if (i && !two) continue;
+            if constexpr (FMT == 1) {
+                if constexpr (GPC == 1) {
+                    const u32x4 t = lds_get<u32x4>(area + (wide ? ll.get ^ (i * 64) : ll.get_s));
+                    wq[i][0] = t.x; wq[i][1] = t.y; wq[i][2] = t.z; wq[i][3] = t.w;
+                } else if constexpr (GPC == 2) {
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        const u32x2 t = lds_get<u32x2>(area + (wide ? ll.get64 ^ (i * 64) ^ (g * 32) : ll.get64_s ^ (g * 32)));
+                        wq[i][2 * g] = t.x; wq[i][2 * g + 1] = t.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        wq[i][j] = lds_get<uint32_t>(area + (wide ? ll.get32 ^ (i * 64) ^ (j * 16) : ll.get32_s ^ (j * 16)));
+                }
+            } else {
+                const int r = lane & 15, q = lane >> 4;
+                if constexpr (GPC == 1) {
+                    const u32x2 t = lds_get<u32x2>(area + (CPW == 2 ? ll.get64_s ^ (i * 32) : r * 32 + 8 * q));
+                    wq[i][0] = t.x; wq[i][1] = t.y;
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+                        wq[i][g] = lds_get<uint32_t>(area + (CPW == 2 ? ll.get32_s ^ (i * 32) ^ (g * 16) : r * 32 + 16 * g + 4 * q));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            if (i && !two) continue;
+#pragma unroll
+            for (int g = 0; g < GPC; ++g) {
+                f32x4 part[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) part[mt] = nbias[i][g][mt];
+#pragma unroll
+                for (int j = g * SPG; j < (g + 1) * SPG; ++j) {
+                    bf16x8 wv;
+                    if constexpr (FMT == 1) wv = nibbles_to_biased_bf16(wq[i][j]);
+                    else wv = (j & 1) ? crumbs_to_biased_bf16<1>(wq[i][j / 2]) : crumbs_to_biased_bf16<0>(wq[i][j / 2]);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        frag8 a;
+                        a.u = x[i][mt][j];
+                        part[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, wv, part[mt], 0, 0, 0);
+                    }
+                }
+                // (the bf16 scales of the wavefront's groups, two to a word: even ones in the low half)
+                const uint32_t sw = scales[(i * GPC + g) >> 1];
+                const float scale = __uint_as_float(((i * GPC + g) & 1) ? sw & 0xFFFF0000u : sw << 16);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[mt] += part[mt] * scale;
+            }
+        }
     }
-    return st;
 }
 
+template <typename T>
+__device__ __forceinline__ T stream_load(const DX_GLOBAL T *p)
+{
+    return *p;
+}
+
+// ---- chunks of 64 or 32 elements (LK = 16, 8): contractions that are no multiple of 128, operand order ----
 template <int LK, int CPW, int FMT>
 __device__ __forceinline__ void issue_weights(wstage<LK, CPW, FMT> &st, gbytes row, int c0, int nc, int q)
 {
@@ -337,7 +528,7 @@ __device__ __forceinline__ void load_tokens(u32x4 (&x)[CPW][MT][LK / 8], gbf16 a
 // bias[i][mt] = 136 * sum over chunk i of the token row (one MFMA against all-ones per step), laid out
 // like an accumulator (every column holds the row's sum).
 template <int LK, int CPW, int MT, int FMT>
-__device__ __forceinline__ void prepare_quant_tokens(u32x4 (&x)[CPW][MT][LK / 8], f32x4 (&bias)[CPW][MT], int c0, int nc)
+__device__ __forceinline__ void prepare_quant_tokens(u32x4 (&x)[CPW][MT][LK / 8], f32x4 (&bias)[CPW][1][MT], int c0, int nc)
 {
     constexpr int JN = LK / 8;
     frag8 ones;
@@ -359,7 +550,7 @@ __device__ __forceinline__ void prepare_quant_tokens(u32x4 (&x)[CPW][MT][LK / 8]
 #pragma unroll
                     for (int j = 0; j + 1 < JN; j += 2) zip_fragments(x[i][mt][j], x[i][mt][j + 1]);
                 }
-                bias[i][mt] = sum * (FMT == 1 ? kNibbleBias : kCrumbBias);
+                bias[i][0][mt] = sum * (FMT == 1 ? kNibbleBias : kCrumbBias);
             }
         }
     }
@@ -367,7 +558,7 @@ __device__ __forceinline__ void prepare_quant_tokens(u32x4 (&x)[CPW][MT][LK / 8]
 
 template <int LK, int CPW, int FMT, int MT>
 __device__ __forceinline__ void multiply(const wstage<LK, CPW, FMT> &st, const u32x4 (&x)[CPW][MT][LK / 8],
-                                         const f32x4 (&bias)[CPW][MT], uint32_t scales, int c0, int nc, f32x4 (&acc)[MT])
+                                         const f32x4 (&bias)[CPW][1][MT], uint32_t scales, int c0, int nc, f32x4 (&acc)[MT])
 {
     constexpr int JN = LK / 8;
 #pragma unroll
@@ -392,7 +583,7 @@ __device__ __forceinline__ void multiply(const wstage<LK, CPW, FMT> &st, const u
                 // (the bf16 scales of the wavefront's chunks, two to a word: chunk 0 in the low half)
                 const float scale = __uint_as_float(i == 0 ? scales << 16 : scales & 0xFFFF0000u);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt] += (part[mt] - bias[i][mt]) * scale;
+                for (int mt = 0; mt < MT; ++mt) acc[mt] += (part[mt] - bias[i][0][mt]) * scale;
             } else {
 #pragma unroll
                 for (int j = 0; j < JN; ++j) {
@@ -507,7 +698,7 @@ __device__ __forceinline__ void finish_batch(const dx_fwd_args &a, const expert_
 // is straight-line code -- every iteration issues the next strip pair's loads unconditionally (the
 // strip index is clamped, so the last iterations of a ragged run fetch a duplicate) -- which lets the
 // compiler wait for exactly the loads it is about to use and keep the prefetch in flight.
-template <int LK, int CPW, bool DOWN, int FMT, int MT, bool FAST>
+template <int LK, int GPC, int CPW, bool DOWN, int FMT, int MT, bool FAST>
 __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ctx &ex, int mb, int h_lo, int h_hi,
                                            f32x4 (*red)[kWaves][4][64], int &pb)
 {
@@ -526,7 +717,6 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     const bool idle = g >= SPP;
     const int npairs = (h_hi - h_lo + 1) / 2;
     const int nbatch = (npairs + SPP - 1) / SPP;
-    const int nsteps = nbatch * rounds;
 
     int fin_slot, fin_orow;
     finish_target<DOWN, MT>(a, ex, mb, fin_slot, fin_orow);
@@ -547,39 +737,60 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
 
     // FAST: nc counts as "unbounded" so that every chunk predicate folds away
     const int ncp = FAST ? 0x7fffffff : nc;
+    constexpr bool LINES = LK == 32;
+    constexpr int NSW = (CPW * GPC + 1) / 2; // words of group scales per strip
     u32x4 x[CPW][MT][LK / 8];
-    f32x4 bias[CPW][MT];
-    gbf16 arow0 = nullptr, arow1 = nullptr; // token rows of this run, looked up after the weight prologue
+    f32x4 bias[CPW][GPC][MT];
+    // token rows of this run, looked up after the weight prologue: LINES: the rows the lane loads (lane / 8 and
+    // 8 + lane / 8 of every 16-token tile), else row r of tile mt in [mt][0]
+    gbf16 arow[2][2];
+    const line_lanes ll = line_lanes_of(lane);
+    // the wavefront's area of LDS: its part of the half of `red` that is filled next
+    auto area = [&]() { return (lds_bytes)(__attribute__((address_space(3))) void *)&red[pb][wave][0][0]; };
     auto fetch_tokens = [&](int c0) {
-        load_tokens<LK, CPW, FMT, MT>(x, arow0, arow1, c0, ncp, q);
-        if constexpr (FMT != 0) prepare_quant_tokens<LK, CPW, MT, FMT>(x, bias, c0, ncp);
+        if constexpr (LINES) {
+            load_token_lines<GPC, CPW, FMT, MT>(x, arow, c0, ncp, lane, ll, area());
+            if constexpr (FMT != 0) prepare_line_tokens<GPC, CPW, MT, FMT>(x, bias, c0, ncp);
+        } else {
+            load_tokens<LK, CPW, FMT, MT>(x, arow[0][0], arow[1][0], c0, ncp, q);
+            if constexpr (FMT != 0) prepare_quant_tokens<LK, CPW, MT, FMT>(x, bias, c0, ncp);
+        }
     };
 
-    // A step is one strip: step t = (batch * rounds + round) * 2 + b, b = 0 the first strip of the pair,
-    // b = 1 the second; the last pair of a run may lack its second strip (no load, no multiply).  NST
-    // register stages: the strip of step t + NST - 1 is fetched while step t is multiplied.  A quantized
+    // A step is one strip: b = 0 the first strip of a pair, b = 1 the second; the last pair of a run may lack its
+    // second strip (no load, no multiply).  FAST: step t = 2 * batch + b.  Otherwise K goes in rounds of 8 * CPW chunks
+    // and the tokens are fetched anew in every round, so NB pairs share a round's tokens, each with accumulators
+    // of its own: step t = (((batch / NB) * rounds + round) * NB + batch % NB) * 2 + b.  (One pair per fetch moved as
+    // many token bytes as weight bytes: 8 tokens of 16 experts of 4096 x 6400 225 us, with NB = 4 185 us.)
+    // NST register stages: the strip of step t + NST - 1 is fetched while step t is multiplied.  A quantized
     // strip is a quarter of the bytes or less, so it gets a deeper pipeline (four stages; with six or eight
     // the runs of a decode batch, a dozen steps each, spend most of their steps outside the steady loop,
     // which measured slower).
+    constexpr int NB = FAST ? 1 : 4;
     constexpr int NST = FMT ? 4 : 2;
-    const int nhalf = 2 * nsteps;
-    wstage<LK, CPW, FMT> st[NST];
+    const int nhalf = (nbatch + NB - 1) / NB * NB * rounds * 2; // steps
+    using stage_t = std::conditional_t<LINES, line_stage<CPW, FMT>, wstage<LK, CPW, FMT>>;
+    stage_t st[NST];
     const gbytes weight_rows0 = ex.w0, weight_rows1 = ex.w1;
     const uint32_t lane_row8 = (uint32_t)(r & 7) * ex.row_bytes, lane_row16 = (uint32_t)r * ex.row_bytes; // per-lane byte offsets
     // the strip of step t (past the end of the run for the missing half of the last pair and for the pairs of
-    // wavefront groups without one in the last batch)
-    auto strip_of = [&](int t) { return h_lo + 2 * (((t >> 1) / rounds) * SPP + g) + (t & 1); };
+    // wavefront groups without one in the last batch) and its K round
+    auto strip_of = [&](int t) {
+        if constexpr (FAST) return h_lo + 2 * ((t >> 1) * SPP + g) + (t & 1);
+        else return h_lo + 2 * (((t / (2 * NB) / rounds) * NB + ((t >> 1) % NB)) * SPP + g) + (t & 1);
+    };
+    auto chunk_of_step = [&](int t) { return FAST ? kw * CPW : (((t / (2 * NB)) % rounds) * WPS + kw) * CPW; };
     // row r of a strip's tile in the weight (scale) matrices: row index and which of the two matrices
-    auto issue_step = [&](int t, wstage<LK, CPW, FMT> &dst) {
-        const int sr = t >> 1;
+    auto issue_step = [&](int t, stage_t &dst) {
         int s = strip_of(t);
         s = s < h_hi ? s : h_hi - 1; // ragged tail: fetch a duplicate rather than branch
-        const int c0 = ((sr % rounds) * WPS + kw) * CPW;
+        const int c0 = chunk_of_step(t);
         const size_t strip_at = (size_t)((DOWN ? 16 : 8) * s) * ex.row_bytes; // scalar
-        if constexpr (kLines<LK, CPW, FMT, FAST>) {
-            const gbytes p_lo = weight_rows0 + strip_at + lane_row8;
-            const gbytes p_hi = DOWN ? weight_rows0 + (strip_at + 8 * ex.row_bytes) + lane_row8 : weight_rows1 + strip_at + lane_row8;
-            issue_weight_lines<LK, CPW, FMT>(dst, p_lo, p_hi, c0, ncp, q + 4 * (r >> 3));
+        if constexpr (LINES) {
+            constexpr int CB = FMT == 0 ? 256 : (FMT == 1 ? 64 : 32); // bytes of a chunk in a row
+            const gbytes lo = weight_rows0 + strip_at + c0 * CB;
+            const gbytes hi = (DOWN ? weight_rows0 + 8 * (size_t)ex.row_bytes : weight_rows1) + strip_at + c0 * CB;
+            issue_lines<CPW, FMT>(dst, lo, hi, ex.row_bytes, c0 < ncp, c0 + 1 < ncp, lane);
         } else {
             const gbytes p = DOWN ? weight_rows0 + strip_at + lane_row16
                                   : (r < 8 ? weight_rows0 + strip_at : weight_rows1 + strip_at) + lane_row8;
@@ -592,28 +803,36 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     // at the end of every iteration, and the completion counter is in order -- a copy of a load issued
     // last would wait for every load in flight, a copy of the oldest ones waits for nothing.
     static_assert(CPW <= 2, "two chunk scales to a word");
-    uint32_t sc_cur[NST], sc_next[NST];
+    uint32_t sc_cur[NST][NSW], sc_next[NST][NSW];
     const gbf16 scale_rows0 = ex.s0, scale_rows1 = ex.s1;
-    auto issue_scales = [&](int t0 /* even */, uint32_t (&dst)[NST]) __attribute__((always_inline)) {
+    auto issue_scales = [&](int t0 /* even */, uint32_t (&dst)[NST][NSW]) __attribute__((always_inline)) {
         if constexpr (FMT != 0) {
 #pragma unroll
             for (int u = 0; u < NST; ++u) {
-                const int sr = (t0 >> 1) + (u >> 1); // step t0 + u
                 int s = strip_of(t0 + u);
                 s = s < h_hi ? s : h_hi - 1;
                 const size_t strip_at = (size_t)((DOWN ? 16 : 8) * s) * ex.G; // scalar
                 const gbf16 sp = DOWN ? scale_rows0 + strip_at + (uint32_t)(r * ex.G)
                                       : (r < 8 ? scale_rows0 + strip_at : scale_rows1 + strip_at) + (uint32_t)((r & 7) * ex.G);
-                const int c0 = ((sr % rounds) * WPS + kw) * CPW;
-                if (CPW == 2 && a.group == CHUNK && c0 + 1 < ncp) {
+                const int c0 = chunk_of_step(t0 + u);
+                if constexpr (GPC > 1) {
+                    // the groups of the wavefront's chunks are neighbours, GPC (even) of them per chunk
+#pragma unroll
+                    for (int i = 0; i < CPW; ++i)
+                        if (c0 + i < ncp) {
+#pragma unroll
+                            for (int g = 0; g < GPC; g += 2)
+                                dst[u][(i * GPC + g) >> 1] = *reinterpret_cast<gvec4>(sp + (c0 + i) * GPC + g);
+                        }
+                } else if (CPW == 2 && a.group == CHUNK && c0 + 1 < ncp) {
                     // the two chunks' scales are neighbours (c0 is even, a scale row starts 4-byte aligned)
-                    dst[u] = *reinterpret_cast<gvec4>(sp + c0);
+                    dst[u][0] = *reinterpret_cast<gvec4>(sp + c0);
                 } else {
                     uint32_t v = 0;
 #pragma unroll
                     for (int i = 0; i < CPW; ++i)
                         if (c0 + i < ncp) v |= (uint32_t)sp[((c0 + i) * CHUNK) / a.group] << (16 * i);
-                    dst[u] = v;
+                    dst[u][0] = v;
                 }
             }
         }
@@ -621,22 +840,22 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     auto rotate_scales = [&]() {
         if constexpr (FMT != 0) {
 #pragma unroll
-            for (int u = 0; u < NST; ++u) sc_cur[u] = sc_next[u];
+            for (int u = 0; u < NST; ++u)
+#pragma unroll
+                for (int i = 0; i < NSW; ++i) sc_cur[u][i] = sc_next[u][i];
         }
     };
 
-    f32x4 acc[2][MT];
+    f32x4 acc[NB][2][MT];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int p = 0; p < NB; ++p)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[b][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[p][b][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto do_step = [&](int t, const wstage<LK, CPW, FMT> &cur, uint32_t sc,
-                       int b /* = t & 1, compile-time at every call */) {
-        const int sr = t >> 1;
-        const int batch = sr / rounds, rnd = sr % rounds;
-        const int c0 = (rnd * WPS + kw) * CPW;
-        if (rounds > 1 && b == 0) fetch_tokens(c0);
+    auto multiply_step = [&](int t, const stage_t &cur, const uint32_t (&sc)[NSW], f32x4 (&to)[MT]) __attribute__((always_inline)) {
+        const int c0 = chunk_of_step(t);
 #ifdef DX_TRACE_STEPS
         if (threadIdx.x == 0 && (blockIdx.x & 63) == 37) {
             const unsigned int n = g_nsteps[DOWN][blockIdx.x >> 6]++;
@@ -644,18 +863,19 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
         }
 #endif
         if (strip_of(t) < h_hi) { // wavefront-uniform; a strip past the end was not fetched either, or is a duplicate
-            if constexpr (kLines<LK, CPW, FMT, FAST>) multiply<LK, CPW, FMT, MT>(settle_lines<LK, CPW, FMT>(cur, c0, ncp), x, bias, sc, c0, ncp, acc[b]);
-            else multiply<LK, CPW, FMT, MT>(cur, x, bias, sc, c0, ncp, acc[b]);
+            if constexpr (LINES) multiply_lines<GPC, CPW, FMT, MT>(cur, x, bias, sc, c0 < ncp, c0 + 1 < ncp, ll, lane, area(), to);
+            else multiply<LK, CPW, FMT, MT>(cur, x, bias, sc[0], c0, ncp, to);
         }
-        if (b == 0 || rnd != rounds - 1) return;
-        // the strip pairs of this batch are complete: park the partial sums (zeros for a missing second strip)
-        const bool live = strip_of(t - 1) < h_hi;
+    };
+    // a batch's strip pairs are complete: park the partial sums (zeros for a missing second strip)
+    auto park_and_finish = [&](int batch, f32x4 (&sums)[2][MT]) __attribute__((always_inline)) {
+        const bool live = h_lo + 2 * (batch * SPP + g) < h_hi;
 #pragma unroll
         for (int bb = 0; bb < 2; ++bb)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                if (live) red[pb][wave][bb * 2 + mt][lane] = acc[bb][mt];
-                acc[bb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (live) red[pb][wave][bb * 2 + mt][lane] = sums[bb][mt];
+                sums[bb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         finish(batch);
     };
@@ -667,52 +887,77 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
         if (i < nhalf && strip_of(i) < h_hi) issue_step(i, st[i]);
     issue_scales(0, sc_cur);
 
-    // token rows of this run (A operand): row r of tile mt
-    {
-        gbf16 arow[2];
+    // token rows of this run (A operand)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            int slot = mb * 32 + 16 * mt + r;
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int h = 0; h < (LINES ? 2 : 1); ++h) {
+            int slot = mb * 32 + 16 * mt + (LINES ? 8 * h + (lane >> 3) : r);
             slot = slot < ex.m ? slot : ex.m - 1;
             if constexpr (DOWN) {
-                arow[mt] = (gbf16)a.h + (size_t)(ex.seg0 + slot) * a.fmax;
+                arow[mt][h] = (gbf16)a.h + (size_t)(ex.seg0 + slot) * a.fmax;
             } else {
                 int tok = slot;
                 if (!ex.shared) {
                     const int p = ex.perm_lds ? ex.perm_lds[ex.seg0 + slot] : a.perm[ex.seg0 + slot];
                     tok = p / a.k;
                 }
-                arow[mt] = (gbf16)a.x + (size_t)tok * ex.K;
+                arow[mt][h] = (gbf16)a.x + (size_t)tok * ex.K;
             }
         }
-        arow0 = arow[0];
-        arow1 = arow[1];
-    }
-    if (rounds == 1) fetch_tokens(kw * CPW);
-    int t = 0;
-    // steady state: NST strips per iteration, every prefetch unconditional (NST is even, so stage i always
-    // holds a strip with b = i & 1)
-    for (; t + 2 * NST - 2 < nhalf; t += NST) {
-        issue_scales(t + NST, sc_next);
+    if constexpr (FAST) {
+        fetch_tokens(kw * CPW);
+        auto do_step = [&](int t, const stage_t &cur, const uint32_t (&sc)[NSW],
+                           int b /* = t & 1, compile-time at every call */) __attribute__((always_inline)) {
+            multiply_step(t, cur, sc, acc[0][b]);
+            if (b) park_and_finish(t >> 1, acc[0]);
+        };
+        int t = 0;
+        // steady state: NST strips per iteration, every prefetch unconditional (NST is even, so stage i always
+        // holds a strip with b = i & 1)
+        for (; t + 2 * NST - 2 < nhalf; t += NST) {
+            issue_scales(t + NST, sc_next);
 #pragma unroll
-        for (int i = 0; i < NST; ++i) {
-            issue_step(t + i + NST - 1, st[(i + NST - 1) % NST]);
-            do_step(t + i, st[i], sc_cur[i], i & 1);
-        }
-        rotate_scales();
-    }
-    // drain: the same, with the prefetch guarded (an unconditional prefetch of duplicates past the end of
-    // the run was measured: the next run then starts behind those loads, 72.6 -> 79.1 us per C2 step)
-    for (; t < nhalf; t += NST) {
-        if (t + NST < nhalf) issue_scales(t + NST, sc_next);
-#pragma unroll
-        for (int i = 0; i < NST; ++i) {
-            if (t + i < nhalf) {
-                if (t + i + NST - 1 < nhalf && strip_of(t + i + NST - 1) < h_hi) issue_step(t + i + NST - 1, st[(i + NST - 1) % NST]);
+            for (int i = 0; i < NST; ++i) {
+                issue_step(t + i + NST - 1, st[(i + NST - 1) % NST]);
                 do_step(t + i, st[i], sc_cur[i], i & 1);
             }
+            rotate_scales();
         }
-        rotate_scales();
+        // drain: the same, with the prefetch guarded (an unconditional prefetch of duplicates past the end of
+        // the run was measured: the next run then starts behind those loads, 72.6 -> 79.1 us per C2 step)
+        for (; t < nhalf; t += NST) {
+            if (t + NST < nhalf) issue_scales(t + NST, sc_next);
+#pragma unroll
+            for (int i = 0; i < NST; ++i) {
+                if (t + i < nhalf) {
+                    if (t + i + NST - 1 < nhalf && strip_of(t + i + NST - 1) < h_hi) issue_step(t + i + NST - 1, st[(i + NST - 1) % NST]);
+                    do_step(t + i, st[i], sc_cur[i], i & 1);
+                }
+            }
+            rotate_scales();
+        }
+    } else {
+        // one iteration: NB pairs in one K round (2 * NB steps, a multiple of NST)
+        static_assert((2 * NB) % NST == 0, "the stages come round with every iteration");
+        for (int t = 0; t < nhalf; t += 2 * NB) {
+            fetch_tokens(chunk_of_step(t));
+#pragma unroll
+            for (int i = 0; i < 2 * NB; ++i) {
+                if (i % NST == 0 && t + i + NST < nhalf) issue_scales(t + i + NST, sc_next);
+                if (t + i + NST - 1 < nhalf && strip_of(t + i + NST - 1) < h_hi) issue_step(t + i + NST - 1, st[(i + NST - 1) % NST]);
+                multiply_step(t + i, st[i % NST], sc_cur[i % NST], acc[i >> 1][i & 1]);
+                if (i % NST == NST - 1) rotate_scales();
+            }
+            const int it = t / (2 * NB);
+            if (it % rounds == rounds - 1) {
+#pragma unroll
+                for (int p = 0; p < NB; ++p) {
+                    const int batch = it / rounds * NB + p;
+                    if (batch < nbatch) park_and_finish(batch, acc[p]);
+                }
+            }
+        }
     }
 }
 
@@ -790,7 +1035,7 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
 }
 
 // This block's share: the strips whose first unit lies in [ub0, ub1), run by run.
-template <int LK, int CPW, bool DOWN, bool FAST>
+template <int LK, int GPC, int CPW, bool DOWN, bool FAST>
 __device__ __forceinline__ void run_share(const dx_fwd_args &a, const partition_lds &pl, uint32_t ub0, uint32_t ub1,
                                           lds_ints perm_lds, f32x4 (*red)[kWaves][4][64])
 {
@@ -837,24 +1082,24 @@ __device__ __forceinline__ void run_share(const dx_fwd_args &a, const partition_
             }
 #endif
             if (ex.fmt == DX_FMT_INT4G) {
-                if (two) run_strips<LK, CPW, DOWN, 1, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                else run_strips<LK, CPW, DOWN, 1, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                if (two) run_strips<LK, GPC, CPW, DOWN, 1, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                else run_strips<LK, GPC, CPW, DOWN, 1, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
             } else if (ex.fmt == DX_FMT_INT2G) {
-                // (16 codes per word: the library refuses int2 handles when the group is 32, i.e. LK = 8)
-                if constexpr (LK >= 16) {
-                    if (two) run_strips<LK, CPW, DOWN, 2, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                    else run_strips<LK, CPW, DOWN, 2, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                // (16 codes per word: the library refuses int2 handles when the group is 32)
+                if constexpr (LK >= 16 && GPC < 4) {
+                    if (two) run_strips<LK, GPC, CPW, DOWN, 2, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                    else run_strips<LK, GPC, CPW, DOWN, 2, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
                 }
             } else {
-                if (two) run_strips<LK, CPW, DOWN, 0, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                else run_strips<LK, CPW, DOWN, 0, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                if (two) run_strips<LK, GPC, CPW, DOWN, 0, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                else run_strips<LK, GPC, CPW, DOWN, 0, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
             }
             i = iend;
         }
     }
 }
 
-template <int LK, int CPW, bool DOWN, bool FAST>
+template <int LK, int GPC, int CPW, bool DOWN, bool FAST>
 __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
 {
     __shared__ f32x4 red[2][kWaves][4][64]; // 64 KB: partial sums, double buffered
@@ -867,7 +1112,7 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
 #ifdef DX_TRACE
     const unsigned long long trace_t1 = wall_clock64();
 #endif
-    run_share<LK, CPW, DOWN, FAST>(a, pl, ub0, ub1, nullptr, red);
+    run_share<LK, GPC, CPW, DOWN, FAST>(a, pl, ub0, ub1, nullptr, red);
 #ifdef DX_TRACE
     if (threadIdx.x == 0 && blockIdx.x < 8192) {
         g_trace[DOWN ? 1 : 0][blockIdx.x][0] = trace_t0;
@@ -888,7 +1133,7 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
 // Each thread also owns EPT consecutive experts for the counts, offsets and cost units.
 constexpr int kRoutedTokens = DX_ROUTED_MAX_TOKENS, kRoutedExperts = DX_ROUTED_MAX_EXPERTS, kRoutedTopK = DX_ROUTED_MAX_TOPK;
 
-template <int LK, int CPW, int NV>
+template <int LK, int GPC, int CPW, int NV>
 __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_route_io r)
 {
     constexpr int kE = 16 * NV;                 // experts this instance takes
@@ -1048,7 +1293,7 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 #ifdef DX_TRACE
     trace_t3 = wall_clock64();
 #endif
-    run_share<LK, CPW, false, true>(a, pl, ub0, ub1, (lds_ints)lds_perm, red);
+    run_share<LK, GPC, CPW, false, true>(a, pl, ub0, ub1, (lds_ints)lds_perm, red);
 #ifdef DX_TRACE
     if (threadIdx.x == 0 && blockIdx.x < 8192) {
         g_trace[0][blockIdx.x][0] = trace_t0;
@@ -1161,7 +1406,7 @@ split_choice pick_split(int nc_a, int nc_b)
         }
     }
     if (best) return {best, true};
-    return {2, false};
+    return {1, false};
 }
 
 // A launch, optionally with events that take the start and stop time stamps of the kernel's own dispatch
@@ -1173,17 +1418,57 @@ void launch(void (*kernel)(Args...), dim3 grid, dim3 block, hipStream_t s, hipEv
     else hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
 }
 
-template <int LK, bool DOWN>
-void launch_stream(const dx_fwd_args &a, split_choice c, dim3 grid, hipStream_t s, hipEvent_t start = nullptr,
-                   hipEvent_t stop = nullptr)
+// How a projection's contraction is cut into chunks.  Multiples of 128: chunks of 128 elements in whole lines, with
+// 128 / group quantization groups each; other sizes (the group, 32 or 64, still divides them): chunks of one
+// group in operand order.
+template <int LK_, int GPC_>
+struct chunking {
+    static constexpr int LK = LK_, GPC = GPC_;
+};
+template <typename F>
+void with_chunking(int group, int K_a, int K_b, F f)
+{
+    if (K_a % 128 == 0 && K_b % 128 == 0) {
+        if (group == 128) f(chunking<32, 1>{});
+        else if (group == 64) f(chunking<32, 2>{});
+        else f(chunking<32, 4>{});
+    } else {
+        if (group == 64) f(chunking<16, 1>{});
+        else f(chunking<8, 1>{});
+    }
+}
+int chunk_of(int group, int K_a, int K_b) { return K_a % 128 == 0 && K_b % 128 == 0 ? 128 : group; }
+
+// gate/up or down over the streamed experts; r: the gate/up kernel routes in its prologue (K a fast split)
+template <bool DOWN>
+void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
+                   const dx_route_io *r = nullptr)
 {
     const dim3 block(kThreads);
-    if (c.fast) {
-        if (c.cpw == 2) launch(k_stream<LK, 2, DOWN, true>, grid, block, s, start, stop, a);
-        else launch(k_stream<LK, 1, DOWN, true>, grid, block, s, start, stop, a);
-    } else {
-        launch(k_stream<LK, 2, DOWN, false>, grid, block, s, start, stop, a);
-    }
+    const int K_a = DOWN ? a.f : a.d, K_b = DOWN && a.shared ? a.shared_f : K_a;
+    const int chunk = chunk_of(a.group, K_a, K_b);
+    const split_choice c = pick_split(K_a / chunk, K_b / chunk);
+    with_chunking(a.group, K_a, K_b, [&](auto ch) {
+        constexpr int LK = decltype(ch)::LK, GPC = decltype(ch)::GPC;
+        if constexpr (!DOWN) {
+            if (r) {
+                if (a.E <= 128) {
+                    if (c.cpw == 2) launch(k_stream_routed<LK, GPC, 2, 8>, grid, block, s, start, stop, a, *r);
+                    else launch(k_stream_routed<LK, GPC, 1, 8>, grid, block, s, start, stop, a, *r);
+                } else {
+                    if (c.cpw == 2) launch(k_stream_routed<LK, GPC, 2, 32>, grid, block, s, start, stop, a, *r);
+                    else launch(k_stream_routed<LK, GPC, 1, 32>, grid, block, s, start, stop, a, *r);
+                }
+                return;
+            }
+        }
+        if (c.fast) {
+            if (c.cpw == 2) launch(k_stream<LK, GPC, 2, DOWN, true>, grid, block, s, start, stop, a);
+            else launch(k_stream<LK, GPC, 1, DOWN, true>, grid, block, s, start, stop, a);
+        } else {
+            launch(k_stream<LK, GPC, 1, DOWN, false>, grid, block, s, start, stop, a);
+        }
+    });
 }
 
 // Up to this many tokens per call the streaming kernels alone are faster than the three-chain prefill
@@ -1192,11 +1477,9 @@ constexpr int kStreamOnlyTokens = 128;
 
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
 // then tells whether it did (if not, nothing has been launched).
-template <int LK>
 hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx_fwd_streams *side, dx_marks *mk,
                       const dx_route_io *r, bool *routed)
 {
-    constexpr int CHUNK = 4 * LK;
     dx_fwd_args a = a_in;
     // Few tokens per call (decode): the streaming kernels take every expert.  Otherwise experts above
     // 32 tokens go to the tiled MFMA kernels (when the shapes fit their tiles).
@@ -1211,10 +1494,9 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx
     // its int4 path reads a row's scales as aligned pairs: an even number of groups along both contractions
     a.big_int4 = a.m_big && (a.d / a.group) % 2 == 0 && (a.f / a.group) % 2 == 0;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
-    const split_choice gu = pick_split(a.d / CHUNK, a.d / CHUNK);
-    const split_choice dn = pick_split(a.f / CHUNK, (a.shared ? a.shared_f : a.f) / CHUNK);
     if (r) {
-        *routed = !mixed && gu.fast && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
+        const int nc = a.d / chunk_of(a.group, a.d, a.d);
+        *routed = !mixed && pick_split(nc, nc).fast && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
@@ -1226,22 +1508,14 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx
         hipEvent_t ev[8] = {};
         if (marks)
             for (int i = 0; i < 8; ++i) ev[i] = marks[i];
-        if (r && a.E <= 128) {
-            if (gu.cpw == 2) launch(k_stream_routed<LK, 2, 8>, grid, dim3(kThreads), s, ev[0], ev[1], a, *r);
-            else launch(k_stream_routed<LK, 1, 8>, grid, dim3(kThreads), s, ev[0], ev[1], a, *r);
-        } else if (r) {
-            if (gu.cpw == 2) launch(k_stream_routed<LK, 2, 32>, grid, dim3(kThreads), s, ev[0], ev[1], a, *r);
-            else launch(k_stream_routed<LK, 1, 32>, grid, dim3(kThreads), s, ev[0], ev[1], a, *r);
-        } else {
-            launch_stream<LK, false>(a, gu, grid, s, ev[0], ev[1]);
-        }
-        launch_stream<LK, true>(a, dn, grid, s, ev[5], ev[2]);
+        launch_stream<false>(a, grid, s, ev[0], ev[1], r);
+        launch_stream<true>(a, grid, s, ev[5], ev[2]);
         combine_start = ev[6];
         combine_stop = ev[3];
     } else if (!side) {
         const dim3 grid(n_cu);
-        launch_stream<LK, false>(a, gu, grid, s);
-        launch_stream<LK, true>(a, dn, grid, s);
+        launch_stream<false>(a, grid, s);
+        launch_stream<true>(a, grid, s);
         if (marks) (void)hipEventRecord(marks[0], s);
         const hipError_t e = dxk_moe_forward_tiled(a, s, s, marks ? &marks[1] : nullptr);
         if (e != hipSuccess) return e;
@@ -1262,8 +1536,8 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx
         if (marks) (void)hipEventRecord(marks[2], s);
         const bool tiles_dominate = (long)a.T * a.k >= 256L * a.E; // mean segment of 256 tokens or more
         const dim3 grid(tiles_dominate && n_cu >= 8 ? n_cu / 4 : n_cu);
-        launch_stream<LK, false>(a, gu, grid, side->aux[0]);
-        launch_stream<LK, true>(a, dn, grid, side->aux[0]);
+        launch_stream<false>(a, grid, side->aux[0]);
+        launch_stream<true>(a, grid, side->aux[0]);
         for (int i = 0; i < 2; ++i) {
             if ((e = hipEventRecord(side->join[i], side->aux[i])) != hipSuccess) return e;
             if ((e = hipStreamWaitEvent(s, side->join[i], 0)) != hipSuccess) return e;
@@ -1310,10 +1584,7 @@ extern "C" int dx_debug_read_steps(void *dst, void *counts)
 hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, const dx_fwd_streams *side, dx_marks *marks)
 {
     if (a.T == 0) return hipSuccess;
-    // K-chunk = min(group, 128) so that a chunk never crosses a quantization group
-    if (a.group >= 128) return launch_all<32>(a, n_cu, s, side, marks, nullptr, nullptr);
-    if (a.group == 64) return launch_all<16>(a, n_cu, s, side, marks, nullptr, nullptr);
-    return launch_all<8>(a, n_cu, s, side, marks, nullptr, nullptr);
+    return launch_all(a, n_cu, s, side, marks, nullptr, nullptr);
 }
 
 hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_cu, hipStream_t s, dx_marks *marks,
@@ -1321,7 +1592,5 @@ hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_c
 {
     *routed = false;
     if (a.T == 0) return hipSuccess;
-    if (a.group >= 128) return launch_all<32>(a, n_cu, s, nullptr, marks, &r, routed);
-    if (a.group == 64) return launch_all<16>(a, n_cu, s, nullptr, marks, &r, routed);
-    return launch_all<8>(a, n_cu, s, nullptr, marks, &r, routed);
+    return launch_all(a, n_cu, s, nullptr, marks, &r, routed);
 }

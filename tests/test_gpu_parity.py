@@ -1152,6 +1152,41 @@ def test_forward_random_shapes_int4_int2_pair(B, LY, dxo):
         ctx.close()
 
 
+@pytest.mark.parametrize("pair,T,d,f,group", [
+    ("bf16-int4", 33, 2048, 256, 64),     # two groups per chunk, the self-routing kernel at the 30B layer's K
+    ("bf16-int4", 20, 1152, 2176, 32),    # four groups per chunk; 9 and 17 chunks: K in rounds, a last chunk without a pair
+    ("bf16-int4", 34, 1920, 1152, 128),   # 15 and 9 chunks
+    ("bf16-int4", 7, 128, 896, 32),       # one and seven chunks: a chunk per wavefront
+    ("int4-int2", 20, 1152, 2176, 64),
+    ("int4-int2", 33, 1920, 2048, 128),
+    ("int4-int2", 3, 128, 896, 64),
+    ("int4-int2", 18, 2048, 896, 64),
+])
+def test_decode_groups_and_chunk_counts(B, LY, dxo, pair, T, d, f, group):
+    """Group sizes below the chunk of 128 elements, and numbers of chunks that leave a wavefront with half of its
+    chunks or none: route_forward against the oracle, token by token within twice the bar."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=4, k=2, d=d, f=f, group=group)
+    x, logits = W.layer_inputs(wl, seed=51)
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, [0, 2], 51, T)
+    else:
+        ly = Layer(B, LY, dxo, wl, [0, 2], seed=51)
+        ctx, keep, versions = ly.ctx, ly, ly.versions
+    rb = LY.RoutingBuffers(T, wl.E, wl.k)
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    rb.route_forward(ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+    sync()
+    ids, w, counts, offsets, perm = dxo.route(logits, wl.k)
+    assert np.array_equal(rb.ids.cpu().numpy(), ids) and np.array_equal(rb.perm.cpu().numpy(), perm)
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w)
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(LY.device_to_bits(y), y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    del keep
+    ctx.close()
+
+
 def test_probe_read_runs_and_checks_its_arguments(B):
     ctx = B.Context(L=1, E=8, d=64, f=64, top_k=2, group=32, max_tokens=4)
     buf = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
