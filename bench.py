@@ -384,11 +384,8 @@ def main():
             # decode, whole layer call: all three matrices of every activated expert (+ the shared expert) once,
             # x and the logits in, y and the routing arrays out
             step_bytes += n_hi_act * b_hi + n_lo_act * b_lo + b_sh + 2 * T * d * 2 + T * E * 4 + T * k * 12 + E * 8
-            # prefill: the 256-row tile kernel multiplies the leading multiple of 256 rows of every bf16 and
-            # every int4 segment (not of int2 segments): 2 * rows * d * 2f each
-            big = hi if quant_pair else np.ones_like(hi)
-            rows = (counts[big] // 256 * 256).sum()
-            alg_flops += float(rows) * 2.0 * d * 2 * f
+            # prefill, gate/up phase (streamed experts, then tiles): 2 * rows * d * 2f over all routed rows
+            alg_flops += float(counts.sum()) * 2.0 * d * 2 * f
         alg_per_launch, flops_per_launch, step_bytes_per_call = alg_bytes / L, alg_flops / L, step_bytes / L
 
         # second pass over the same steps with HIP events around each forward kernel
@@ -448,16 +445,16 @@ def main():
         routed = False
         achieved = flops_per_launch / (gate_up_us * 1e-6) / 1e12
         step_flops = float(T * k) * 2.0 * d * 3 * f      # all routed pairs through gate, up and down
-        roofline = {"bound": "mfma", "kernel": "k_big<gate/up>", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS,
+        roofline = {"bound": "mfma", "kernel": "gate/up phase: k_stream<gate/up> + k_tiled<gate/up>", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                     "algorithmic_flops_per_launch": flops_per_launch, "avg_launch_us": gate_up_us,
-                    "note": "timed while the 128-row tile and streaming kernels of the same pass run beside it "
-                            "on the side streams, as in the timed steps",
+                    "note": "both kernels of the phase, the streamed experts (up to 32 tokens) and the tiled ones, with "
+                            "the kernel boundary between them",
                     "whole_step_tflops": step_flops / (ms_per_step * 1e-3) / 1e12}
     # HBM traffic of the dominant kernel from the committed counter summary; the summary names the commit
     # whose kernels it was taken on, printed next to it (this tree may have moved on since)
     tpath = os.path.join(ROOT, "profiles", "k_stream_gate_up_C2_decode_pmc.txt" if decode
-                         else "k_big_gate_up_C3_prefill_pmc.txt")
+                         else "k_tiled_gate_up_C3_prefill_pmc.txt")
     if os.path.exists(tpath) and not quant_pair and args.workload != "C4":
         for line in open(tpath):
             if line.startswith("traffic_bytes_per_launch:"):

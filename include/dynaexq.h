@@ -109,8 +109,8 @@ typedef struct {
 /* Creates a context on the current HIP device.  `hip_compute_stream` is a
  * hipStream_t (NULL = the null stream).  Allocates the handle tables
  * (L*E routed + L shared entries), the window counters, the routing and
- * forward scratch for max_tokens, a migration stream and two side streams
- * (all at default priority).  A context is not thread-safe: one host thread
+ * forward scratch for max_tokens and a migration stream (at default
+ * priority).  A context is not thread-safe: one host thread
  * at a time.  DX_ERR_INVALID for a configuration outside the supported
  * range: E <= 1024, top_k <= min(E, 64), group in {32, 64, 128} dividing d, f
  * and shared_f, d, f, shared_f multiples of 32, an expert matrix smaller than
@@ -185,12 +185,10 @@ dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router
  * for `layer`.  x_bf16 dev [T,d]; y_bf16 dev [T,d]; routing arrays as written
  * by dx_route for the same T.  Weights are read through the handles as they
  * are when the kernels run on the compute stream.
- * Stream order: the call is asynchronous and ordered on the compute stream.
- * Above 128 tokens it forks part of its kernels onto two side streams of the
- * context and joins them before the combine, so the work is still complete
- * in compute-stream order (and can be captured in a HIP graph with the
- * compute stream as origin).  The H and O scratch buffers belong to the
- * context: calls on one context must not overlap. */
+ * Stream order: the call is asynchronous, all its kernels run on the compute
+ * stream (and can be captured in a HIP graph with it as origin).  The H and O
+ * scratch buffers belong to the context: calls on one context must not
+ * overlap. */
 dx_status dx_moe_forward(dx_ctx *ctx, int layer, const dx_handle *handle_table,
                          const void *x_bf16, int T,
                          const int32_t *topk_ids, const float *topk_w,
@@ -295,7 +293,7 @@ dx_status dx_get_pool(dx_ctx *ctx, int which, void **base, uint64_t *block_bytes
  * (measurement aid, off by default).  While enabled, every forward call
  * (dx_moe_forward, dx_route_forward) times its kernels: decode batches attach
  * events to each kernel's own dispatch (start and stop stamps of the launch),
- * larger batches record events around the concurrent kernel chains.
+ * larger batches record events around the phases (streamed experts and tiles).
  * dx_get_profile synchronises the compute stream, adds the elapsed times of all
  * calls since the last read and clears them.  Keep profiling off while the
  * compute stream is being captured into a graph (timing events do not belong

@@ -273,11 +273,6 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
         return fail(e, "hipDeviceGetAttribute");
     if (c->n_cu <= 0) c->n_cu = 256;
     if ((e = hipStreamCreateWithFlags(&c->mig, hipStreamNonBlocking)) != hipSuccess) return fail(e, "migration stream");
-    for (int i = 0; i < 2; ++i) {
-        if ((e = hipStreamCreateWithFlags(&c->aux[i], hipStreamNonBlocking)) != hipSuccess) return fail(e, "side stream");
-        if ((e = hipEventCreateWithFlags(&c->join[i], hipEventDisableTiming)) != hipSuccess) return fail(e, "join event");
-    }
-    if ((e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming)) != hipSuccess) return fail(e, "fork event");
     if ((e = hipMalloc(&c->d_table, n_entries * sizeof(dx_handle))) != hipSuccess) return fail(e, "handle table");
     if ((e = hipMalloc(&c->d_counters, (size_t)g.L * g.E * 8)) != hipSuccess) return fail(e, "counters");
     if ((e = hipHostMalloc(&c->h_counters, (size_t)g.L * g.E * 8, hipHostMallocDefault)) != hipSuccess)
@@ -286,6 +281,9 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
     if ((e = hipMalloc(&c->d_chunk_base, (size_t)c->n_chunks_max * g.E * 4)) != hipSuccess) return fail(e, "route bases");
     if ((e = hipMalloc(&c->d_h, n_rows * c->fmax * sizeof(dx_bf16))) != hipSuccess) return fail(e, "H scratch");
     if ((e = hipMalloc(&c->d_o, n_rows * (size_t)g.d * sizeof(float))) != hipSuccess) return fail(e, "O scratch");
+    // (for the smallest m_small a call can have)
+    const size_t n_tile_rows = 1 + (size_t)dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0);
+    if ((e = hipMalloc(&c->d_tile_rows, n_tile_rows * sizeof(dx_tile_row))) != hipSuccess) return fail(e, "tile list");
     // zero the table and the counters with fill kernels on the compute stream
     if ((e = dxk_fill_u64(reinterpret_cast<unsigned long long *>(c->d_table), n_entries * sizeof(dx_handle) / 8, 0ull,
                           c->compute)) != hipSuccess)
@@ -316,14 +314,6 @@ extern "C" void dx_destroy(dx_ctx *c)
         (void)hipStreamSynchronize(c->mig);
         (void)hipStreamDestroy(c->mig);
     }
-    for (int i = 0; i < 2; ++i) {
-        if (c->aux[i]) {
-            (void)hipStreamSynchronize(c->aux[i]);
-            (void)hipStreamDestroy(c->aux[i]);
-        }
-        if (c->join[i]) (void)hipEventDestroy(c->join[i]);
-    }
-    if (c->fork) (void)hipEventDestroy(c->fork);
     for (auto &t : c->inflight) (void)hipEventDestroy(t.done);
     for (auto ev : c->event_pool) (void)hipEventDestroy(ev);
     for (auto ev : c->timing_pool) (void)hipEventDestroy(ev);
@@ -342,6 +332,7 @@ extern "C" void dx_destroy(dx_ctx *c)
     if (c->d_chunk_base) (void)hipFree(c->d_chunk_base);
     if (c->d_h) (void)hipFree(c->d_h);
     if (c->d_o) (void)hipFree(c->d_o);
+    if (c->d_tile_rows) (void)hipFree(c->d_tile_rows);
     delete c;
 }
 
@@ -394,6 +385,7 @@ dx_status forward_args(dx_ctx *c, const char *who, int layer, const dx_handle *t
     a.perm = perm;
     a.h = c->d_h;
     a.o = c->d_o;
+    a.tile_rows = c->d_tile_rows;
     a.T = T;
     a.E = g.E;
     a.k = g.top_k;
@@ -438,14 +430,13 @@ extern "C" dx_status dx_moe_forward(dx_ctx *c, int layer, const dx_handle *table
     dx_fwd_args a;
     dx_status st = forward_args(c, "dx_moe_forward", layer, table, x, T, ids, w, offsets, perm, y, a);
     if (st != DX_OK) return st;
-    const dx_fwd_streams side{{c->aux[0], c->aux[1]}, c->fork, {c->join[0], c->join[1]}};
     if (!c->profiling) {
-        DX_HIP(c, dxk_moe_forward(a, c->n_cu, c->compute, &side, nullptr));
+        DX_HIP(c, dxk_moe_forward(a, c->n_cu, c->compute, nullptr));
         return DX_OK;
     }
     dx_marks m;
     if ((st = take_marks(c, m)) != DX_OK) return st;
-    hipError_t e = dxk_moe_forward(a, c->n_cu, c->compute, &side, &m);
+    hipError_t e = dxk_moe_forward(a, c->n_cu, c->compute, &m);
     c->marks.push_back(m);
     if (e != hipSuccess) DX_FAIL(c, DX_ERR_HIP, "dx_moe_forward: %s", hipGetErrorString(e));
     return DX_OK;

@@ -49,8 +49,8 @@ struct dx_transition {
 // Timing events of one profiled forward call.  ev[0..3]: before gate/up, after it, after down, after
 // combine; ev[7], ev[4]: two records back to back (what an event pair itself adds).  Decode batches set
 // per_kernel: there ev[0]/ev[1], ev[5]/ev[2] and ev[6]/ev[3] are the start and stop stamps of the three
-// kernels' own dispatches (attached to the launches), not records between them.  Prefill: records around
-// the chain on the caller's stream.
+// kernels' own dispatches (attached to the launches), not records between them.  Prefill: records between
+// the phases.
 struct dx_marks {
     hipEvent_t ev[8];
     bool per_kernel;
@@ -62,9 +62,6 @@ struct dx_ctx {
     int n_cu = 0; // compute units of the device: size of the persistent grids
     hipStream_t compute = nullptr;
     hipStream_t mig = nullptr;
-    // side streams and fork/join events of the prefill forward pass (independent kernel chains)
-    hipStream_t aux[2] = {nullptr, nullptr};
-    hipEvent_t fork = nullptr, join[2] = {nullptr, nullptr};
     std::string err;
 
     // handle tables: routed [L*E] then shared [L]
@@ -84,6 +81,7 @@ struct dx_ctx {
     // forward scratch
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
     float *d_o = nullptr;   // [max_tokens*(k+1), d]
+    struct dx_tile_row *d_tile_rows = nullptr; // row tiles of the tiled experts of one call
     int fmax = 0;
 
     // pools / budget tracker / transitions
@@ -141,6 +139,19 @@ hipError_t dxk_quantize(const dx_bf16 *w, int rows, int K, int group, uint8_t *q
 hipError_t dxk_quantize2(const dx_bf16 *w, int rows, int K, int group, uint8_t *q, dx_bf16 *sc, hipStream_t s); // 2-bit
 
 // dx_moe_decode.hip / dx_moe_prefill.hip
+// One row tile of an expert above m_small tokens; in element 0 of the list e is the number of routed row tiles that
+// follow and mt the number of the shared expert's after them.
+constexpr int DX_TILE_ROWS = 128;
+struct dx_tile_row {
+    int e, mt;   // expert (E = shared), row tile of its segment
+    int m, seg0; // rows and first pair slot of the segment
+};
+// most row tiles a call of T tokens can have (a routed expert has ceil(m / 128) of them, and none up to m_small tokens)
+inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)
+{
+    const long pairs = (long)T * k, with = pairs / ((long)m_small + 1) < E ? pairs / ((long)m_small + 1) : E;
+    return pairs / DX_TILE_ROWS + with + (shared ? (T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0);
+}
 struct dx_fwd_args {
     const dx_handle *table;  // E routed entries of the layer
     const dx_handle *shared; // one entry or null
@@ -155,8 +166,7 @@ struct dx_fwd_args {
     int T, E, k, d, f, group, shared_f, fmax;
     int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
-    int m_big;   // non-zero: the leading multiple of 256 rows of a bf16 expert takes the 256 x 256 tile kernel
-    int big_int4; // non-zero (with m_big): so does the leading multiple of 256 rows of an int4 expert
+    dx_tile_row *tile_rows; // mixed batches: the row tiles of the tiled experts (element 0: their number), else null
 };
 // Decode batches that the gate/up kernel routes itself (dx_route_forward): what its first block reads and
 // writes on top of dx_fwd_args (whose ids, w, offsets and perm point at the same arrays for the kernels
@@ -171,19 +181,12 @@ struct dx_route_io {
     int32_t *perm;       // [T * k]
     unsigned long long *hotness; // the layer's window counters, or null
 };
-// Side streams for the prefill pass: its kernel chains (streamed small experts; 128-row tiles; 256-row
-// tiles) touch disjoint rows of H and O and run concurrently between `fork` and the joins.
-struct dx_fwd_streams {
-    hipStream_t aux[2];
-    hipEvent_t fork, join[2];
-};
-hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, const dx_fwd_streams *side, dx_marks *marks);
+hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, dx_marks *marks);
 // Routing and forward pass in one call.  Returns true in *routed when the gate/up kernel did the routing
 // (small decode batches whose shapes fit); otherwise nothing was launched and the caller runs dxk_route
 // and dxk_moe_forward.
 hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_cu, hipStream_t s, dx_marks *marks,
                              bool *routed);
-// dx_moe_prefill.hip: gate/up then down for the experts above a.m_small tokens.  The 256-row tile
-// kernels (when a.m_big) go to s_big, the 128-row ones to s_tiled (the two may be the same stream).
-hipError_t dxk_moe_forward_tiled(const dx_fwd_args &a, hipStream_t s_big, hipStream_t s_tiled,
-                                 hipEvent_t *mark_after_gate_up);
+// dx_moe_prefill.hip: gate/up, and down, of the experts above a.m_small tokens
+void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s);
+void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s);

@@ -1034,6 +1034,41 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
     __syncthreads();
 }
 
+// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot is free).  Experts above m_small tokens.
+__device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int R = (a.E + kThreads - 1) / kThreads; // experts per thread, consecutive
+    auto tokens_of = [&](int e) {
+        const int m = a.offsets[e + 1] - a.offsets[e];
+        return m > a.m_small ? m : 0;
+    };
+    uint32_t local = 0;
+    for (int i = 0; i < R; ++i) {
+        const int e = tid * R + i;
+        if (e < a.E) local += (uint32_t)((tokens_of(e) + DX_TILE_ROWS - 1) / DX_TILE_ROWS);
+    }
+    const uint32_t inc = dx_route_core::wave_scan_inclusive(local);
+    if (lane == 63) pl.wave_tot[wave] = inc;
+    __syncthreads();
+    uint32_t base = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t t = pl.wave_tot[w];
+        if (w < wave) base += t;
+        total += t;
+    }
+    dx_tile_row *out = a.tile_rows + 1 + base + inc - local;
+    for (int i = 0; i < R; ++i) {
+        const int e = tid * R + i;
+        const int m = e < a.E ? tokens_of(e) : 0;
+        for (int mt = 0; mt * DX_TILE_ROWS < m; ++mt) *out++ = dx_tile_row{e, mt, m, a.offsets[e]};
+    }
+    const int n_shared = a.shared && a.T > a.m_small ? (a.T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0;
+    for (int mt = tid; mt < n_shared; mt += kThreads) a.tile_rows[1 + total + mt] = dx_tile_row{a.E, mt, a.T, a.T * a.k};
+    if (tid == 0) a.tile_rows[0] = dx_tile_row{(int)total, n_shared, 0, 0};
+}
+
 // This block's share: the strips whose first unit lies in [ub0, ub1), run by run.
 template <int LK, int GPC, int CPW, bool DOWN, bool FAST>
 __device__ __forceinline__ void run_share(const dx_fwd_args &a, const partition_lds &pl, uint32_t ub0, uint32_t ub1,
@@ -1112,6 +1147,9 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
 #ifdef DX_TRACE
     const unsigned long long trace_t1 = wall_clock64();
 #endif
+    if constexpr (!DOWN) {
+        if (a.tile_rows && blockIdx.x + 1 == gridDim.x) write_tile_rows(a, pl);
+    }
     run_share<LK, GPC, CPW, DOWN, FAST>(a, pl, ub0, ub1, nullptr, red);
 #ifdef DX_TRACE
     if (threadIdx.x == 0 && blockIdx.x < 8192) {
@@ -1471,14 +1509,14 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
     });
 }
 
-// Up to this many tokens per call the streaming kernels alone are faster than the three-chain prefill
-// pass (measured on the 30B-shaped layer: 140 us against 171 us at T = 128, equal at T = 256).
+// Up to this many tokens per call the streaming kernels alone are faster than streamed experts and tiles (30B-shaped
+// layer: T = 100 106 us against 110, T = 128 117 against 114; 80B-shaped: T = 128 106 against 116).
 constexpr int kStreamOnlyTokens = 128;
 
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
 // then tells whether it did (if not, nothing has been launched).
-hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx_fwd_streams *side, dx_marks *mk,
-                      const dx_route_io *r, bool *routed)
+hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks *mk, const dx_route_io *r,
+                      bool *routed)
 {
     dx_fwd_args a = a_in;
     // Few tokens per call (decode): the streaming kernels take every expert.  Otherwise experts above
@@ -1486,13 +1524,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx
     const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0);
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
-    // the 256 x 256 kernel addresses rows with 32-bit byte offsets from the matrix base
-    const uint64_t span_x = (uint64_t)a.T * a.d * 2, span_h = (uint64_t)a.T * (a.k + 1) * a.fmax * 2;
-    const bool big_fit = a.d % 256 == 0 && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0) &&
-                         span_x < (1ull << 32) && span_h < (1ull << 32) && (uint64_t)a.d * a.fmax * 2 < (1ull << 32);
-    a.m_big = mixed && big_fit ? 256 : 0;
-    // its int4 path reads a row's scales as aligned pairs: an even number of groups along both contractions
-    a.big_int4 = a.m_big && (a.d / a.group) % 2 == 0 && (a.f / a.group) % 2 == 0;
+    if (!mixed) a.tile_rows = nullptr;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
@@ -1512,36 +1544,19 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, const dx
         launch_stream<true>(a, grid, s, ev[5], ev[2]);
         combine_start = ev[6];
         combine_stop = ev[3];
-    } else if (!side) {
-        const dim3 grid(n_cu);
-        launch_stream<false>(a, grid, s);
-        launch_stream<true>(a, grid, s);
-        if (marks) (void)hipEventRecord(marks[0], s);
-        const hipError_t e = dxk_moe_forward_tiled(a, s, s, marks ? &marks[1] : nullptr);
-        if (e != hipSuccess) return e;
-        if (marks) (void)hipEventRecord(marks[2], s);
     } else {
-        // Three chains on three streams.  The streamed experts are bound by memory, the tiles by the
-        // matrix cores, and the tail of each tiled grid leaves compute units idle: run together they
-        // fill each other's gaps.  Once the tiles carry most of the work the streaming grid shrinks to
-        // a quarter of the chip, so that the 256-row tile kernel (whose LDS footprint does not share a
-        // compute unit with it) keeps the rest; measured better from a mean segment of 256 tokens up.
-        hipError_t e;
-        if ((e = hipEventRecord(side->fork, s)) != hipSuccess) return e;
-        for (int i = 0; i < 2; ++i)
-            if ((e = hipStreamWaitEvent(side->aux[i], side->fork, 0)) != hipSuccess) return e;
+        // Each phase's streamed experts, then its tiles, one kernel after the other.  (Side by side on three streams they
+        // are no faster: 300 tokens of the 30B-shaped layer 159 us against 139, 1000 tokens 220 against 204,
+        // 4096 tokens 576 against 516; the streamed experts
+        // and the tiles ask for the same memory, and a fork and a join cost more than a kernel boundary.)
+        const dim3 grid(n_cu);
         if (marks) (void)hipEventRecord(marks[0], s);
-        hipStream_t s_tiled = a.m_big ? side->aux[1] : s;
-        if ((e = dxk_moe_forward_tiled(a, s, s_tiled, marks ? &marks[1] : nullptr)) != hipSuccess) return e;
+        launch_stream<false>(a, grid, s);
+        dxk_tiles_gate_up(a, s);
+        if (marks) (void)hipEventRecord(marks[1], s);
+        launch_stream<true>(a, grid, s);
+        dxk_tiles_down(a, s);
         if (marks) (void)hipEventRecord(marks[2], s);
-        const bool tiles_dominate = (long)a.T * a.k >= 256L * a.E; // mean segment of 256 tokens or more
-        const dim3 grid(tiles_dominate && n_cu >= 8 ? n_cu / 4 : n_cu);
-        launch_stream<false>(a, grid, side->aux[0]);
-        launch_stream<true>(a, grid, side->aux[0]);
-        for (int i = 0; i < 2; ++i) {
-            if ((e = hipEventRecord(side->join[i], side->aux[i])) != hipSuccess) return e;
-            if ((e = hipStreamWaitEvent(s, side->join[i], 0)) != hipSuccess) return e;
-        }
     }
     if (a.o_bf16) {
         launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
@@ -1581,10 +1596,10 @@ extern "C" int dx_debug_read_steps(void *dst, void *counts)
 }
 #endif
 
-hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, const dx_fwd_streams *side, dx_marks *marks)
+hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, dx_marks *marks)
 {
     if (a.T == 0) return hipSuccess;
-    return launch_all(a, n_cu, s, side, marks, nullptr, nullptr);
+    return launch_all(a, n_cu, s, marks, nullptr, nullptr);
 }
 
 hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_cu, hipStream_t s, dx_marks *marks,
@@ -1592,5 +1607,5 @@ hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_c
 {
     *routed = false;
     if (a.T == 0) return hipSuccess;
-    return launch_all(a, n_cu, s, nullptr, marks, &r, routed);
+    return launch_all(a, n_cu, s, marks, &r, routed);
 }
