@@ -76,7 +76,6 @@ struct dx_ctx {
     // routing scratch (chunks of 64 tokens)
     int n_chunks_max = 0;
     unsigned long long *d_mask = nullptr; // [n_chunks_max, E]
-    int32_t *d_chunk_base = nullptr;      // [n_chunks_max, E]
 
     // forward scratch
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
@@ -125,7 +124,7 @@ struct dx_ctx {
 // ---- kernel launchers (each validates nothing; callers validate) ----------
 // dx_route.hip
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
-                     int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *chunk_base,
+                     int32_t *offsets, int32_t *perm, unsigned long long *mask,
                      unsigned long long *hotness /* window counters of the layer, or null */, hipStream_t s);
 hipError_t dxk_router_gemm(const dx_bf16 *x, const dx_bf16 *w_r, const float *bias, int T, int E, int d, float *logits,
                            int n_cu, hipStream_t s);

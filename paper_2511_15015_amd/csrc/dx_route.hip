@@ -77,7 +77,12 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_topk(
             dx_route_core::load_logits_rows16<NV>(logits + (size_t)(t < T ? t : T - 1) * E, c, E, v);
             int my_id;
             float my_w;
-            dx_route_core::topk_rows16<NV>(v, k, lane, my_id, my_w);
+            if constexpr (NV <= 8) {
+                dx_route_core::topk_rows16<NV>(v, k, lane, my_id, my_w);
+            } else { // wide layers: a threshold first, then the selections over the few entries at or above it
+                auto scratch = (__attribute__((address_space(3))) int *)(lds_tot + kWaves + (E + 3) / 4 * 4) + wave * 64 * NV;
+                dx_route_core::topk_rows16_filtered<NV, 6>(v, k, lane, my_id, my_w, scratch);
+            }
             if (t < T && c < k) {
                 ids[(size_t)t * k + c] = my_id;
                 w[(size_t)t * k + c] = my_w;
@@ -139,53 +144,63 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_topk(
     }
 }
 
-// counts/offsets and per-chunk bases from the chunk masks (one block)
-__global__ __launch_bounds__(kRouteThreads) void k_route_scan(
-    const unsigned long long *__restrict__ mask, int n_chunks, int E, int32_t *__restrict__ chunk_base,
-    int32_t *__restrict__ counts, int32_t *__restrict__ offsets, unsigned long long *__restrict__ hotness)
+// Batches of several chunks: a block per chunk places the chunk's pairs.  It needs every expert's count and what the
+// chunks before its own hold of it, i.e. the population counts of all chunk masks; every block adds them up by
+// itself (64 KB from L2 for 4096 tokens on 128 experts), S threads to an expert so that one round of loads in flight covers
+// them, because a scan kernel in between costs more (30B-shaped layer: a pass of 4096 tokens 492 us with it, 482 without; of
+// 300 tokens 140 and 138).
+__global__ __launch_bounds__(kRouteThreads) void k_route_place(
+    const int32_t *__restrict__ ids, int T, int E, int k, int split /* log2 of S */, int n_chunks,
+    const unsigned long long *__restrict__ mask, int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
+    int32_t *__restrict__ perm, unsigned long long *__restrict__ hotness)
 {
+    __shared__ unsigned long long lds_mask[kRouteThreads];
+    __shared__ int lds_at[kRouteThreads]; // where the chunk's first pair of the expert goes
     __shared__ int lds_tot[kWaves];
-    const int e = threadIdx.x;
-    int run = 0;
+    const int chunk = blockIdx.x, S = 1 << split;
+    const int e = threadIdx.x >> split, part = threadIdx.x & (S - 1);
+    int total = 0, before = 0;
     if (e < E) {
-        // eight independent mask loads in flight per round
-        int c = 0;
-        for (; c + 8 <= n_chunks; c += 8) {
-            unsigned long long m[8];
+        constexpr int U = 8; // independent mask loads in flight
+        for (int c0 = part; c0 < n_chunks; c0 += U * S) {
+            unsigned long long m[U];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) m[i] = mask[(size_t)(c + i) * E + e];
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * S;
+                m[u] = mask[(size_t)(c < n_chunks ? c : n_chunks - 1) * E + e];
+            }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                chunk_base[(size_t)(c + i) * E + e] = run;
-                run += __popcll(m[i]);
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * S;
+                const int n = c < n_chunks ? __popcll(m[u]) : 0;
+                total += n;
+                before += c < chunk ? n : 0;
+                if (c == chunk) lds_mask[e] = m[u];
             }
         }
-        for (; c < n_chunks; ++c) {
-            chunk_base[(size_t)c * E + e] = run;
-            run += __popcll(mask[(size_t)c * E + e]);
+    }
+    for (int o = S >> 1; o > 0; o >>= 1) { // (an expert's threads are neighbours)
+        total += __shfl_xor(total, o, 64);
+        before += __shfl_xor(before, o, 64);
+    }
+    int all;
+    const int off = block_exclusive_scan(part == 0 && e < E ? total : 0, lds_tot, &all);
+    if (part == 0 && e < E) {
+        lds_at[e] = off + before;
+        if (chunk == 0) {
+            counts[e] = total;
+            offsets[e] = off;
+            if (hotness) hotness[e] += (unsigned long long)total;
+            if (e == 0) offsets[E] = all;
         }
     }
-    int total;
-    const int off = block_exclusive_scan(run, lds_tot, &total);
-    if (e < E) {
-        counts[e] = run;
-        offsets[e] = off;
-        if (hotness) hotness[e] += (unsigned long long)run;
+    __syncthreads();
+    const int p0 = chunk * kChunk * k, n = min(T - chunk * kChunk, kChunk) * k;
+    for (int i = threadIdx.x; i < n; i += kRouteThreads) {
+        const int ex = ids[p0 + i];
+        const unsigned long long below = lds_mask[ex] & ((1ull << (i / k)) - 1ull);
+        perm[lds_at[ex] + __popcll(below)] = p0 + i;
     }
-    if (e == 0) offsets[E] = total;
-}
-
-__global__ __launch_bounds__(256) void k_route_place(
-    const int32_t *__restrict__ ids, int P, int E, int k, const unsigned long long *__restrict__ mask,
-    const int32_t *__restrict__ chunk_base, const int32_t *__restrict__ offsets, int32_t *__restrict__ perm)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    const int t = p / k;
-    const int c = t / kChunk, bit = t % kChunk;
-    const int e = ids[p];
-    const unsigned long long below = mask[(size_t)c * E + e] & ((1ull << bit) - 1ull);
-    perm[offsets[e] + chunk_base[(size_t)c * E + e] + __popcll(below)] = p;
 }
 
 __global__ void k_hotness_add(unsigned long long *__restrict__ counters, const int32_t *__restrict__ counts, int E)
@@ -349,7 +364,8 @@ hipError_t launch_topk(const float *logits, int T, int E, int k, int32_t *ids, f
                        int n_chunks, hipStream_t s)
 {
     const int fused = n_chunks == 1;
-    size_t lds = (size_t)E * 8 + (size_t)(kChunk * k + kWaves + E) * 4;
+    size_t lds = (size_t)E * 8 + (size_t)(kChunk * k + kWaves + (E + 3) / 4 * 4) * 4;
+    if (ROWS16 && NV > 8) lds += (size_t)kWaves * 64 * NV * 4; // the wide selection's keys
     hipLaunchKernelGGL((k_route_topk<NV, ROWS16>), dim3(n_chunks), dim3(kRouteThreads), lds, s, logits, T, E, k, ids, w,
                        counts, offsets, perm, mask, hotness, fused);
     return hipGetLastError();
@@ -358,8 +374,8 @@ hipError_t launch_topk(const float *logits, int T, int E, int k, int32_t *ids, f
 } // namespace
 
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
-                     int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *chunk_base,
-                     unsigned long long *hotness, hipStream_t s)
+                     int32_t *offsets, int32_t *perm, unsigned long long *mask, unsigned long long *hotness,
+                     hipStream_t s)
 {
     // T == 0 still runs one (empty) chunk so that counts and offsets are written.
     const int n_chunks = T > 0 ? (T + kChunk - 1) / kChunk : 1;
@@ -375,11 +391,10 @@ hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, flo
     else if (E <= 512) e = launch_topk<8, false>(logits, T, E, k, ids, w, counts, offsets, perm, mask, hotness, n_chunks, s);
     else e = launch_topk<16, false>(logits, T, E, k, ids, w, counts, offsets, perm, mask, hotness, n_chunks, s);
     if (e != hipSuccess || n_chunks == 1) return e;
-    hipLaunchKernelGGL(k_route_scan, dim3(1), dim3(kRouteThreads), 0, s, mask, n_chunks, E, chunk_base, counts,
-                       offsets, hotness);
-    const int P = T * k;
-    hipLaunchKernelGGL(k_route_place, dim3((P + 255) / 256), dim3(256), 0, s, ids, P, E, k, mask, chunk_base,
-                       offsets, perm);
+    int split = 0; // threads per expert
+    while ((E << (split + 1)) <= kRouteThreads && split < 6) ++split;
+    hipLaunchKernelGGL(k_route_place, dim3(n_chunks), dim3(kRouteThreads), 0, s, ids, T, E, k, split, n_chunks, mask, counts,
+                       offsets, perm, hotness);
     return hipGetLastError();
 }
 
@@ -435,8 +450,7 @@ hipError_t dxk_store_handle(dx_handle *slot, const dx_handle &h, hipStream_t s)
 }
 
 // ---- dx_route for callers that cannot allocate ---------------------------------------------------
-// The routing scratch (per-chunk token masks and per-chunk segment bases, the two arrays dx_create
-// otherwise allocates for a context) lives in a file-scope device array.  Every GPU the library runs
+// The routing scratch (per-chunk token masks, the array dx_create otherwise allocates for a context) lives in a file-scope device array.  Every GPU the library runs
 // on holds its own copy at its own address until the process ends; the address is asked for once per
 // device, with that device current, and kept.  In host code the array's name is only a stand-in for
 // the symbol: kernels get the resolved pointer, never the name.
@@ -445,9 +459,8 @@ namespace {
 constexpr size_t kStaticEntries = DX_ROUTE_STATIC_MAX_ENTRIES; // (chunks of 64 tokens) x experts
 struct route_scratch {
     unsigned long long mask[kStaticEntries];
-    int32_t chunk_base[kStaticEntries];
 };
-static __device__ __align__(256) route_scratch scratch; // 768 KiB per GPU
+static __device__ __align__(256) route_scratch scratch; // 512 KiB per GPU
 
 constexpr int kMaxDevices = 64;
 route_scratch *g_scratch_ptr[kMaxDevices]; // per device, null until resolved
@@ -498,9 +511,8 @@ extern "C" dx_status dx_route_static(const float *logits, int T, int E, int top_
         }
         sp = g_scratch_ptr[dev];
     }
-    // Nothing in the scratch has to start at zero: every chunk's block writes all E masks of its chunk,
-    // and the scan writes every base the placement reads.
-    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, sp->chunk_base, nullptr,
+    // Nothing in the scratch has to start at zero: every chunk's block writes all E masks of its chunk.
+    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, nullptr,
                   static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return static_fail(DX_ERR_HIP, "dx_route_static: launch: %s", hipGetErrorString(e));
     return DX_OK;

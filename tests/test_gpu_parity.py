@@ -173,6 +173,22 @@ def test_route_edge_shapes_and_ties(B, LY, dxo, T, E, k):
     _check_route(B, LY, dxo, logits, k)
 
 
+@pytest.mark.parametrize("T,E,k,coarse", [
+    (65, 1, 1, False), (130, 3, 2, True),          # 64 threads per expert in the placement, more than there are chunks
+    (1300, 600, 3, True), (1400, 1024, 5, False),  # one thread per expert, more chunks than loads in flight
+    (2000, 129, 16, True), (700, 512, 10, False),  # wide layers: the threshold and, on a coarse grid, its fall-back
+    (64, 512, 10, False), (40, 200, 16, True),     # the same in a single chunk
+])
+def test_route_chunks_and_wide_selection(B, LY, dxo, T, E, k, coarse):
+    """The placement's thread splits at both ends of the expert count, and the chunk kernel's selection for layers of more
+    than 128 experts: ids, weights, counts, offsets and permutation as the oracle has them."""
+    g = np.random.default_rng(T + E)
+    logits = g.standard_normal((T, E)).astype(np.float32)
+    if coarse:
+        logits = np.round(logits * 2) / 2
+    _check_route(B, LY, dxo, logits, k)
+
+
 def test_route_rejects_bad_arguments(B, LY):
     ctx = B.Context(L=2, E=8, d=64, f=64, top_k=2, group=32, max_tokens=16)
     rb = LY.RoutingBuffers(16, 8, 2)
