@@ -744,6 +744,7 @@ extern "C" dx_status dx_get_profile(dx_ctx *c, dx_profile *out)
         const int to[4] = {1, 2, 3, 4};
         float t[4] = {0.f, 0.f, 0.f, 0.f};
         for (int i = 0; i < 4; ++i) {
+            if (i == 2 && m.combined) continue;
             hipError_t e = hipEventElapsedTime(&t[i], m.ev[from[i]], m.ev[to[i]]);
             if (e != hipSuccess) t[i] = 0.f; // a call that recorded nothing (T == 0)
         }

@@ -54,6 +54,7 @@ struct dx_transition {
 struct dx_marks {
     hipEvent_t ev[8];
     bool per_kernel;
+    bool combined; // the down kernel wrote y: no combine kernel, ev[6] and ev[3] are not recorded
 };
 
 struct dx_ctx {

@@ -1342,6 +1342,124 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 #endif
 }
 
+// ---- a call of one or two tokens: down projection and combine in one kernel ----------------------------------
+// Bound by latency: a launch of k_stream<down> derives its partition, starts runs and leaves O to a combine kernel (10.4 +
+// 3.9 us for 13 MB of weights at T = 1, a boundary in between).  With so few pairs there is nothing to partition:
+// block (strip, token) computes the token's 16 columns of y.  Its wavefronts take the token's experts (several to
+// an expert when there are fewer than eight), each multiplies its strip by the pair's row of H over all of K with up to
+// six chunks in flight, and the results meet in LDS, where they are weighted and added in the order of the slots as
+// k_combine does.  Contractions that are multiples of 128.  Whole calls, us, before and after: 30B-shaped T = 1 30.1 and
+// 27.0, T = 2 36.2 and 32.3, T = 3 40.0 and 43.5 (tokens that share an expert read its strip once each, and k_stream
+// once for all); 80B-shaped T = 1 53 and 37.5, T = 2 51.6 and 38.2; 16 experts of 4096 x 6400 T = 2 100 and 98.
+constexpr int kFewTokens = 2, kFewTasks = DX_ROUTED_MAX_TOPK + 1;
+
+// o[r] of column r (in lanes 0..15): row of H (m = 1) times the strip's 16 rows over the chunks [c0, c1)
+template <int GPC, int FMT>
+__device__ __forceinline__ f32x4 strip_of_one(gbf16 h_row, gbytes w, gbf16 sc, int K, int G, int c0, int c1, int lane,
+                                              const line_lanes &ll, lds_bytes area)
+{
+    constexpr int NB = 3, NSW = GPC; // stages of two chunks; words of scales per stage
+    constexpr int CB = FMT == 0 ? 256 : (FMT == 1 ? 64 : 32);
+    const uint32_t row_bytes = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4);
+    const int r = lane & 15, q = lane >> 4;
+    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+    for (int c = c0; c < c1; c += 2 * NB) { // wavefront-uniform
+        u32x4 x[NB][2][1][4];
+        line_stage<2, FMT> st[NB];
+        uint32_t scales[NB][NSW];
+        // the row of H first (one line for all rows of the operand), then scales, then weights
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int cc = c + 2 * b + i < c1 ? c + 2 * b + i : c1 - 1;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k0 = FMT == 0 || GPC == 4 ? 32 * j + 8 * q : (GPC == 2 ? 64 * (j >> 1) + 16 * q + 8 * (j & 1) : 32 * q + 8 * j);
+                    x[b][i][0][j] = *reinterpret_cast<gvec16>(h_row + cc * 128 + k0);
+                }
+            }
+        if constexpr (FMT != 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int cb = c + 2 * b < c1 ? c + 2 * b : c1 - 1, cn = cb + 1 < c1 ? cb + 1 : cb;
+                const gbf16 sp = sc + (uint32_t)(r * G);
+                if constexpr (GPC == 1) {
+                    scales[b][0] = (uint32_t)sp[cb] | (uint32_t)sp[cn] << 16;
+                } else {
+#pragma unroll
+                    for (int g = 0; g < GPC; g += 2) {
+                        scales[b][g >> 1] = *reinterpret_cast<gvec4>(sp + cb * GPC + g);
+                        scales[b][(GPC + g) >> 1] = *reinterpret_cast<gvec4>(sp + cn * GPC + g);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const gbytes p = w + (c + 2 * b) * CB;
+            issue_lines<2, FMT>(st[b], p, p + 8 * (size_t)row_bytes, row_bytes, c + 2 * b < c1, c + 2 * b + 1 < c1, lane);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            f32x4 nbias[2][GPC][1];
+            if constexpr (FMT != 0) prepare_line_tokens<GPC, 2, 1, FMT>(x[b], nbias, c + 2 * b, c1);
+            multiply_lines<GPC, 2, FMT, 1>(st[b], x[b], nbias, scales[b], c + 2 * b < c1, c + 2 * b + 1 < c1, ll, lane, area, acc);
+        }
+    }
+    return acc[0];
+}
+
+template <int GPC>
+__global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
+{
+    __shared__ u32x4 stage[kWaves][256]; // a line stage per wavefront
+    __shared__ float part[kFewTasks * 8][16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int t = blockIdx.y, strip = blockIdx.x, P = a.T * a.k; // P <= 64
+    const int tasks = a.k + (a.shared ? 1 : 0);
+    const int split = tasks < kWaves ? kWaves / tasks : 1; // wavefronts per expert
+    const int id_of_pair = lane < P ? a.ids[lane] : 0x7fffffff;
+    const line_lanes ll = line_lanes_of(lane);
+    const lds_bytes area = (lds_bytes)(__attribute__((address_space(3))) void *)&stage[wave][0];
+    for (int item = wave; item < tasks * split; item += kWaves) {
+        const int j = item / split, piece = item % split;
+        const bool shared = j == a.k;
+        const int e = shared ? a.E : __builtin_amdgcn_readlane(id_of_pair, t * a.k + (shared ? 0 : j));
+        const dx_handle hd = shared ? *a.shared : a.table[e];
+        const int K = shared ? a.shared_f : a.f, nc = K / 128, per = (nc + split - 1) / split;
+        const int c0 = piece * per, c1 = c0 + per < nc ? c0 + per : nc;
+        // the pair's place in the segments: pairs of lower experts, and of the same expert from tokens in front
+        const int pos = shared ? P + t
+                               : __popcll(__ballot(id_of_pair < e)) + __popcll(__ballot(id_of_pair == e && lane < t * a.k));
+        const gbf16 h_row = (gbf16)a.h + (size_t)pos * a.fmax;
+        const gbytes w = (gbytes)hd.w_down;
+        const gbf16 sc = (gbf16)hd.s_down;
+        const int G = K / a.group;
+        const size_t row0 = (size_t)strip * 16;
+        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (c0 < c1) {
+            if (hd.fmt == DX_FMT_INT4G) o = strip_of_one<GPC, 1>(h_row, w + row0 * (K / 2), sc + row0 * G, K, G, c0, c1, lane, ll, area);
+            else if (hd.fmt == DX_FMT_INT2G) {
+                if constexpr (GPC < 4) o = strip_of_one<GPC, 2>(h_row, w + row0 * (K / 4), sc + row0 * G, K, G, c0, c1, lane, ll, area);
+            } else o = strip_of_one<GPC, 0>(h_row, w + row0 * K * 2, sc, K, G, c0, c1, lane, ll, area);
+        }
+        if (lane < 16) part[item][lane] = o[0]; // (every row of the operand is the same token: row 0)
+    }
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        float acc = 0.f, sh = 0.f;
+        for (int j = 0; j < tasks; ++j) {
+            float v = 0.f;
+            for (int i = 0; i < split; ++i) v += part[j * split + i][threadIdx.x];
+            if (j < a.k) acc += a.w[t * a.k + j] * v;
+            else sh = v;
+        }
+        if (a.shared) acc += sh;
+        a.y[(size_t)t * a.d + strip * 16 + threadIdx.x] = (dx_bf16)float_to_bf16_rne(acc);
+    }
+}
+
 // ---- combine: y[t] = sum_j w[t,j] * O[t*k+j] (+ O[T*k+t] of the shared expert) ----------
 // The rows are fetched eight at a time before they are added (in the order of j), so that a thread has
 // its loads in flight together instead of one round trip per row.
@@ -1533,7 +1651,8 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
     hipEvent_t combine_start = nullptr, combine_stop = nullptr;
-    if (mk) mk->per_kernel = !mixed;
+    if (mk) mk->per_kernel = !mixed, mk->combined = false;
+    bool combined = false; // y is there already
     if (!mixed) {
         // profiled: every kernel's own start and stop stamps
         const dim3 grid(n_cu);
@@ -1541,9 +1660,18 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         if (marks)
             for (int i = 0; i < 8; ++i) ev[i] = marks[i];
         launch_stream<false>(a, grid, s, ev[0], ev[1], r);
-        launch_stream<true>(a, grid, s, ev[5], ev[2]);
-        combine_start = ev[6];
-        combine_stop = ev[3];
+        if (a.T <= kFewTokens && a.k < kFewTasks && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0)) {
+            const dim3 strips(a.d / 16, a.T), block(kThreads);
+            if (a.group == 128) launch(k_down_few<1>, strips, block, s, ev[5], ev[2], a);
+            else if (a.group == 64) launch(k_down_few<2>, strips, block, s, ev[5], ev[2], a);
+            else launch(k_down_few<4>, strips, block, s, ev[5], ev[2], a);
+            combined = true;
+            if (mk) mk->combined = true;
+        } else {
+            launch_stream<true>(a, grid, s, ev[5], ev[2]);
+            combine_start = ev[6];
+            combine_stop = ev[3];
+        }
     } else {
         // Each phase's streamed experts, then its tiles, one kernel after the other.  (Side by side on three streams they
         // are no faster: 300 tokens of the 30B-shaped layer 159 us against 139, 1000 tokens 220 against 204,
@@ -1558,13 +1686,14 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         dxk_tiles_down(a, s);
         if (marks) (void)hipEventRecord(marks[2], s);
     }
-    if (a.o_bf16) {
+    if (combined) {
+    } else if (a.o_bf16) {
         launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
     } else {
         launch(k_combine, dim3((a.d / 4 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
     }
     if (marks) {
-        if (!combine_stop) (void)hipEventRecord(marks[3], s);
+        if (!combine_stop && !combined) (void)hipEventRecord(marks[3], s);
         (void)hipEventRecord(marks[7], s); // two records back to back: the cost of an event pair itself
         (void)hipEventRecord(marks[4], s);
     }

@@ -1203,6 +1203,47 @@ def test_decode_groups_and_chunk_counts(B, LY, dxo, pair, T, d, f, group):
     ctx.close()
 
 
+@pytest.mark.parametrize("pair,T,E,k,d,f,group,shared_f", [
+    ("bf16-int4", 1, 8, 1, 256, 1664, 128, 0),     # one expert: eight wavefronts share 13 chunks
+    ("bf16-int4", 1, 8, 3, 128, 896, 64, 128),     # two wavefronts to an expert, an odd number of chunks; the shared expert's one
+    ("bf16-int4", 1, 32, 16, 256, 1792, 32, 256),  # more experts than wavefronts, K in three rounds of six chunks
+    ("bf16-int4", 2, 4, 3, 256, 128, 128, 384),    # tokens that share experts: places inside a segment
+    ("bf16-int4", 4, 16, 16, 128, 256, 128, 0),    # 64 pairs, every expert four times
+    ("int4-int2", 1, 8, 2, 256, 640, 64, 0),
+    ("int4-int2", 2, 16, 9, 256, 384, 128, 0),
+])
+def test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, shared_f):
+    """The down projection that combines in place (a call of a few tokens): route_forward and the separate calls give the
+    same bits, and y is the oracle's within the bar, token by token within twice the bar."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group, shared_f=shared_f)
+    x, logits = W.layer_inputs(wl, seed=61)
+    shared = None
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, [0, 2], 61, T)
+    else:
+        masters = W.shared_master(wl, 61, 0) if shared_f else None
+        ly = Layer(B, LY, dxo, wl, [0, 2], seed=61, shared=masters)
+        ctx, keep, versions, shared = ly.ctx, ly, ly.versions, ly.shared
+    rb = LY.RoutingBuffers(T, E, k)
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y1 = torch.empty_like(y)
+    rb.route_forward(ctx, 0, ld, xd, y)
+    rb.route(ctx, 0, ld)
+    rb.forward(ctx, 0, xd, y1)
+    sync()
+    assert torch.equal(y, y1)
+    ids, w, counts, offsets, perm = dxo.route(logits, k)
+    assert np.array_equal(rb.ids.cpu().numpy(), ids) and np.array_equal(rb.perm.cpu().numpy(), perm)
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f if shared else 0)
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(LY.device_to_bits(y), y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    del keep
+    ctx.close()
+
+
 def test_probe_read_runs_and_checks_its_arguments(B):
     ctx = B.Context(L=1, E=8, d=64, f=64, top_k=2, group=32, max_tokens=4)
     buf = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
