@@ -183,8 +183,10 @@ dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router
  *          (+ the layer's shared expert, weight 1, when shared_f > 0)
  * handle_table: dev, E entries of this layer; NULL = the context's own table
  * for `layer`.  x_bf16 dev [T,d]; y_bf16 dev [T,d]; routing arrays as written
- * by dx_route for the same T.  Weights are read through the handles as they
- * are when the kernels run on the compute stream.
+ * by dx_route for the same T.  offsets and perm alone say which expert a pair
+ * goes to, in any order inside a segment; topk_ids is part of the call's
+ * arrays, must not be NULL and is not read.  Weights are read through the
+ * handles as they are when the kernels run on the compute stream.
  * Stream order: the call is asynchronous, all its kernels run on the compute
  * stream (and can be captured in a HIP graph with it as origin).  The H and O
  * scratch buffers belong to the context: calls on one context must not

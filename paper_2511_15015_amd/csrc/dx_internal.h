@@ -82,6 +82,7 @@ struct dx_ctx {
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
     float *d_o = nullptr;   // [max_tokens*(k+1), d]
     struct dx_tile_row *d_tile_rows = nullptr; // row tiles of the tiled experts of one call
+    int32_t *d_place_expert = nullptr; // [DX_FEW_TOKENS * DX_ROUTED_MAX_TOPK]: expert of every place in the segments
     int fmax = 0;
 
     // pools / budget tracker / transitions
@@ -152,6 +153,8 @@ inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)
     const long pairs = (long)T * k, with = pairs / ((long)m_small + 1) < E ? pairs / ((long)m_small + 1) : E;
     return pairs / DX_TILE_ROWS + with + (shared ? (T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0);
 }
+// Calls of so few tokens (and top-k up to DX_ROUTED_MAX_TOPK) run the down projection and the combine in one kernel
+constexpr int DX_FEW_TOKENS = 2;
 struct dx_fwd_args {
     const dx_handle *table;  // E routed entries of the layer
     const dx_handle *shared; // one entry or null
@@ -167,6 +170,7 @@ struct dx_fwd_args {
     int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     dx_tile_row *tile_rows; // mixed batches: the row tiles of the tiled experts (element 0: their number), else null
+    int32_t *place_expert;  // up to DX_FEW_TOKENS tokens on a caller's routing arrays: expert of every place in the segments, else null
 };
 // Decode batches that the gate/up kernel routes itself (dx_route_forward): what its first block reads and
 // writes on top of dx_fwd_args (whose ids, w, offsets and perm point at the same arrays for the kernels

@@ -993,6 +993,10 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
             const int m = tokens_of(e);
             pl.seg_tokens[e] = m;
             pl.seg_start[e] = e == a.E ? a.T * a.k : a.offsets[e];
+            if constexpr (!DOWN) {
+                if (a.place_expert && blockIdx.x == 0 && e < a.E)
+                    for (int at = pl.seg_start[e]; at < pl.seg_start[e] + m && at < a.T * a.k; ++at) a.place_expert[at] = e;
+            }
             if (m > 0)
                 mine[i] = (uint32_t)((m + 31) / 32) * strips_of(e) * units_of<DOWN>(fmt_of(e), m) + kRunUnits<DOWN>;
             local += mine[i];
@@ -1351,7 +1355,12 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 // k_combine does.  Contractions that are multiples of 128.  Whole calls, us, before and after: 30B-shaped T = 1 30.1 and
 // 27.0, T = 2 36.2 and 32.3, T = 3 40.0 and 43.5 (tokens that share an expert read its strip once each, and k_stream
 // once for all); 80B-shaped T = 1 53 and 37.5, T = 2 51.6 and 38.2; 16 experts of 4096 x 6400 T = 2 100 and 98.
-constexpr int kFewTokens = 2, kFewTasks = DX_ROUTED_MAX_TOPK + 1;
+// Which expert a pair belongs to and where its row of H is: ROUTED (the gate/up kernel in front has written the routing
+// arrays itself): from the ids, whose segments are in increasing order.  Else the arrays are the caller's: from `offsets`
+// and `perm` alone, as in the other kernels, in any order inside a segment (the gate/up kernel leaves the expert of every
+// place in a.place_expert; 0.6 us more at T = 1); a pair that is in no segment adds nothing.
+constexpr int kFewTokens = DX_FEW_TOKENS, kFewTasks = DX_ROUTED_MAX_TOPK + 1;
+static_assert(kFewTokens * DX_ROUTED_MAX_TOPK <= 64, "a pair per lane");
 
 // o[r] of column r (in lanes 0..15): row of H (m = 1) times the strip's 16 rows over the chunks [c0, c1)
 template <int GPC, int FMT>
@@ -1410,28 +1419,48 @@ __device__ __forceinline__ f32x4 strip_of_one(gbf16 h_row, gbytes w, gbf16 sc, i
     return acc[0];
 }
 
-template <int GPC>
+template <int GPC, bool ROUTED>
 __global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
 {
     __shared__ u32x4 stage[kWaves][256]; // a line stage per wavefront
-    __shared__ float part[kFewTasks * 8][16];
+    __shared__ float part[kFewTasks][16]; // (a task per item, or at most eight items)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int t = blockIdx.y, strip = blockIdx.x, P = a.T * a.k; // P <= 64
+    const int t = blockIdx.y, strip = blockIdx.x, P = a.T * a.k;
     const int tasks = a.k + (a.shared ? 1 : 0);
     const int split = tasks < kWaves ? kWaves / tasks : 1; // wavefronts per expert
-    const int id_of_pair = lane < P ? a.ids[lane] : 0x7fffffff;
+    // lane i: routed: the expert of pair i; else the expert and the pair of place i
+    const int at_i = lane < P ? lane : 0;
+    int expert_i = ROUTED ? a.ids[at_i] : a.place_expert[at_i], pair_i = -1;
+    if constexpr (ROUTED) {
+        expert_i = lane < P ? expert_i : 0x7fffffff;
+    } else { // (places outside the segments are dropped after the loads)
+        const int p = a.perm[at_i], first = a.offsets[0], end = a.offsets[a.E];
+        pair_i = lane >= first && lane < min(P, end) ? p : -1;
+    }
     const line_lanes ll = line_lanes_of(lane);
     const lds_bytes area = (lds_bytes)(__attribute__((address_space(3))) void *)&stage[wave][0];
     for (int item = wave; item < tasks * split; item += kWaves) {
         const int j = item / split, piece = item % split;
         const bool shared = j == a.k;
-        const int e = shared ? a.E : __builtin_amdgcn_readlane(id_of_pair, t * a.k + (shared ? 0 : j));
+        // the expert, and the pair's place in the segments
+        int e = a.E, pos = P + t;
+        if (!shared) {
+            if constexpr (ROUTED) { // pairs of lower experts, and of the same expert from tokens in front
+                e = __builtin_amdgcn_readlane(expert_i, t * a.k + j);
+                pos = __popcll(__ballot(expert_i < e)) + __popcll(__ballot(expert_i == e && lane < t * a.k));
+            } else {
+                const unsigned long long at = __ballot(pair_i == t * a.k + j);
+                if (at == 0ull) {
+                    if (lane < 16) part[item][lane] = 0.f;
+                    continue;
+                }
+                pos = __builtin_ctzll(at);
+                e = __builtin_amdgcn_readlane(expert_i, pos);
+            }
+        }
         const dx_handle hd = shared ? *a.shared : a.table[e];
         const int K = shared ? a.shared_f : a.f, nc = K / 128, per = (nc + split - 1) / split;
         const int c0 = piece * per, c1 = c0 + per < nc ? c0 + per : nc;
-        // the pair's place in the segments: pairs of lower experts, and of the same expert from tokens in front
-        const int pos = shared ? P + t
-                               : __popcll(__ballot(id_of_pair < e)) + __popcll(__ballot(id_of_pair == e && lane < t * a.k));
         const gbf16 h_row = (gbf16)a.h + (size_t)pos * a.fmax;
         const gbytes w = (gbytes)hd.w_down;
         const gbf16 sc = (gbf16)hd.s_down;
@@ -1643,6 +1672,8 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
     if (!mixed) a.tile_rows = nullptr;
+    const bool few = !mixed && a.T <= kFewTokens && a.k < kFewTasks && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0);
+    if (!few || r) a.place_expert = nullptr;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
@@ -1660,11 +1691,16 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         if (marks)
             for (int i = 0; i < 8; ++i) ev[i] = marks[i];
         launch_stream<false>(a, grid, s, ev[0], ev[1], r);
-        if (a.T <= kFewTokens && a.k < kFewTasks && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0)) {
+        if (few) {
             const dim3 strips(a.d / 16, a.T), block(kThreads);
-            if (a.group == 128) launch(k_down_few<1>, strips, block, s, ev[5], ev[2], a);
-            else if (a.group == 64) launch(k_down_few<2>, strips, block, s, ev[5], ev[2], a);
-            else launch(k_down_few<4>, strips, block, s, ev[5], ev[2], a);
+            auto run = [&](auto routed_c) {
+                constexpr bool R = decltype(routed_c)::value;
+                if (a.group == 128) launch(k_down_few<1, R>, strips, block, s, ev[5], ev[2], a);
+                else if (a.group == 64) launch(k_down_few<2, R>, strips, block, s, ev[5], ev[2], a);
+                else launch(k_down_few<4, R>, strips, block, s, ev[5], ev[2], a);
+            };
+            if (r) run(std::true_type{});
+            else run(std::false_type{});
             combined = true;
             if (mk) mk->combined = true;
         } else {

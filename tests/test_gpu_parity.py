@@ -1244,6 +1244,33 @@ def test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, sh
     ctx.close()
 
 
+@pytest.mark.parametrize("T,E,k", [(1, 8, 3), (2, 4, 3), (2, 6, 6), (3, 4, 3)])
+def test_forward_goes_by_offsets_and_perm_alone(B, LY, dxo, T, E, k):
+    """dx_moe_forward on a permutation in another order inside the segments and with ids that say nothing: the pairs'
+    experts are those of the segments, at every batch size (one and two tokens have a down kernel of their own)."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=256, f=128, group=64)
+    x, logits = W.layer_inputs(wl, seed=67)
+    ly = Layer(B, LY, dxo, wl, [0, 2], seed=67)
+    ctx, rb = ly.ctx, ly.rb
+    rb.route(ctx, 0, torch.from_numpy(logits).cuda(), T)
+    sync()
+    offsets, perm = rb.offsets.cpu().numpy(), rb.perm.cpu().numpy()
+    for e in range(E):
+        perm[offsets[e]:offsets[e + 1]] = perm[offsets[e]:offsets[e + 1]][::-1].copy()
+    rb.perm.copy_(torch.from_numpy(perm))
+    rb.ids.fill_(0)
+    y = torch.full((T, wl.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    rb.forward(ctx, 0, LY.bits_to_device(x), y, None, T)
+    sync()
+    ids, w, *_ = dxo.route(logits, k)
+    y_ref = dxo.moe_forward(ly.versions, wl.d, wl.f, wl.group, x, ids, w)
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert tok.max() <= 2 * REL_L2_TOL
+    ctx.close()
+
+
 def test_probe_read_runs_and_checks_its_arguments(B):
     ctx = B.Context(L=1, E=8, d=64, f=64, top_k=2, group=32, max_tokens=4)
     buf = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
