@@ -172,7 +172,9 @@ const char *dx_route_static_last_error(void);
  *   logits[t,e] = sum_c x[t,c] * w_router[e,c] (+ bias[e])
  * x_bf16 dev [T,d], w_router dev bf16 [E,d] row-major, bias dev fp32 [E] or
  * NULL, logits dev fp32 [T,E].  bf16 products accumulated in fp32 on the
- * matrix cores in a fixed order.  0 <= T <= max_tokens. */
+ * matrix cores, in an order that T, E and d determine (a repeated call gives
+ * the same bits; a token's logits may differ in the last bits between batch
+ * sizes).  0 <= T <= max_tokens. */
 dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router, const float *bias,
                            int T, float *logits);
 
