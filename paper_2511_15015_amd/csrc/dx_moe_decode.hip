@@ -1667,8 +1667,9 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
 {
     dx_fwd_args a = a_in;
     // Few tokens per call (decode): the streaming kernels take every expert.  Otherwise experts above
-    // 32 tokens go to the tiled MFMA kernels (when the shapes fit their tiles).
-    const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0);
+    // 32 tokens go to the tiled MFMA kernels (when the shapes fit their tiles, and x starts at a multiple of the 16 bytes
+    // that a lane of their memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address).
+    const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
     if (!mixed) a.tile_rows = nullptr;

@@ -1271,6 +1271,33 @@ def test_forward_goes_by_offsets_and_perm_alone(B, LY, dxo, T, E, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [2, 40, 200])
+def test_forward_takes_tokens_that_start_inside_16_bytes(B, LY, dxo, T):
+    """x as a view that starts 4 bytes into a buffer: the same bits as an aligned copy where the streaming kernels run in both
+    cases, within the bar of the oracle's where the copy would go to the tile kernels."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=4, k=2, d=256, f=128, group=64)
+    x, logits = W.layer_inputs(wl, seed=69)
+    ly = Layer(B, LY, dxo, wl, [0, 2], seed=69)
+    buf = torch.zeros(T * wl.d + 8, dtype=torch.bfloat16, device="cuda")
+    assert buf.data_ptr() % 16 == 0
+    xv = buf[2:2 + T * wl.d].view(T, wl.d)
+    xv.copy_(LY.bits_to_device(x))
+    y = torch.full((T, wl.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y_copy = torch.empty_like(y)
+    ly.rb.route(ly.ctx, 0, torch.from_numpy(logits).cuda(), T)
+    ly.rb.forward(ly.ctx, 0, xv, y, None, T)
+    ly.rb.forward(ly.ctx, 0, xv.clone(), y_copy, None, T)
+    sync()
+    if T <= 128:
+        assert torch.equal(y, y_copy)
+    ids, w, *_ = dxo.route(logits, wl.k)
+    y_ref = dxo.moe_forward(ly.versions, wl.d, wl.f, wl.group, x, ids, w)
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    assert (np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)).max() <= 2 * REL_L2_TOL
+    ly.ctx.close()
+
+
 def test_probe_read_runs_and_checks_its_arguments(B):
     ctx = B.Context(L=1, E=8, d=64, f=64, top_k=2, group=32, max_tokens=4)
     buf = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
