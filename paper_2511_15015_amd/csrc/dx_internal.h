@@ -81,8 +81,7 @@ struct dx_ctx {
     // forward scratch
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
     float *d_o = nullptr;   // [max_tokens*(k+1), d]
-    struct dx_tile_row *d_tile_rows = nullptr; // row tiles of the tiled experts of one call
-    int32_t *d_place_expert = nullptr; // [DX_FEW_TOKENS * DX_ROUTED_MAX_TOPK]: expert of every place in the segments
+    struct dx_tile_row *d_tile_rows = nullptr; // row tiles of the tiled experts of one call (or the experts of its few places)
     int fmax = 0;
 
     // pools / budget tracker / transitions
@@ -169,8 +168,10 @@ struct dx_fwd_args {
     int T, E, k, d, f, group, shared_f, fmax;
     int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
-    dx_tile_row *tile_rows; // mixed batches: the row tiles of the tiled experts (element 0: their number), else null
-    int32_t *place_expert;  // up to DX_FEW_TOKENS tokens on a caller's routing arrays: expert of every place in the segments, else null
+    // A list that the gate/up kernel of the streamed experts leaves for the kernels behind it, or null: mixed batches (m_small
+    // is a bound): the row tiles of the tiled experts (element 0: their number); up to DX_FEW_TOKENS tokens on a caller's
+    // routing arrays: the expert of every place in the segments, as int32_t.
+    dx_tile_row *tile_rows;
 };
 // Decode batches that the gate/up kernel routes itself (dx_route_forward): what its first block reads and
 // writes on top of dx_fwd_args (whose ids, w, offsets and perm point at the same arrays for the kernels

@@ -993,10 +993,6 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
             const int m = tokens_of(e);
             pl.seg_tokens[e] = m;
             pl.seg_start[e] = e == a.E ? a.T * a.k : a.offsets[e];
-            if constexpr (!DOWN) {
-                if (a.place_expert && blockIdx.x == 0 && e < a.E)
-                    for (int at = pl.seg_start[e]; at < pl.seg_start[e] + m && at < a.T * a.k; ++at) a.place_expert[at] = e;
-            }
             if (m > 0)
                 mine[i] = (uint32_t)((m + 31) / 32) * strips_of(e) * units_of<DOWN>(fmt_of(e), m) + kRunUnits<DOWN>;
             local += mine[i];
@@ -1071,6 +1067,14 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
     const int n_shared = a.shared && a.T > a.m_small ? (a.T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0;
     for (int mt = tid; mt < n_shared; mt += kThreads) a.tile_rows[1 + total + mt] = dx_tile_row{a.E, mt, a.T, a.T * a.k};
     if (tid == 0) a.tile_rows[0] = dx_tile_row{(int)total, n_shared, 0, 0};
+}
+
+// The expert of every place in the segments, for the down kernel of a call of a few tokens (one block).
+__device__ __forceinline__ void write_place_experts(const dx_fwd_args &a)
+{
+    int32_t *out = reinterpret_cast<int32_t *>(a.tile_rows);
+    for (int e = threadIdx.x; e < a.E; e += kThreads)
+        for (int at = a.offsets[e]; at < a.offsets[e + 1] && at < a.T * a.k; ++at) out[at] = e;
 }
 
 // This block's share: the strips whose first unit lies in [ub0, ub1), run by run.
@@ -1152,7 +1156,10 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
     const unsigned long long trace_t1 = wall_clock64();
 #endif
     if constexpr (!DOWN) {
-        if (a.tile_rows && blockIdx.x + 1 == gridDim.x) write_tile_rows(a, pl);
+        if (a.tile_rows && blockIdx.x + 1 == gridDim.x) {
+            if (a.m_small == 0x7fffffff) write_place_experts(a);
+            else write_tile_rows(a, pl);
+        }
     }
     run_share<LK, GPC, CPW, DOWN, FAST>(a, pl, ub0, ub1, nullptr, red);
 #ifdef DX_TRACE
@@ -1358,7 +1365,7 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 // Which expert a pair belongs to and where its row of H is: ROUTED (the gate/up kernel in front has written the routing
 // arrays itself): from the ids, whose segments are in increasing order.  Else the arrays are the caller's: from `offsets`
 // and `perm` alone, as in the other kernels, in any order inside a segment (the gate/up kernel leaves the expert of every
-// place in a.place_expert; 0.6 us more at T = 1); a pair that is in no segment adds nothing.
+// place in the list; 0.6 us more at T = 1); a pair that is in no segment adds nothing.
 constexpr int kFewTokens = DX_FEW_TOKENS, kFewTasks = DX_ROUTED_MAX_TOPK + 1;
 static_assert(kFewTokens * DX_ROUTED_MAX_TOPK <= 64, "a pair per lane");
 
@@ -1430,7 +1437,7 @@ __global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
     const int split = tasks < kWaves ? kWaves / tasks : 1; // wavefronts per expert
     // lane i: routed: the expert of pair i; else the expert and the pair of place i
     const int at_i = lane < P ? lane : 0;
-    int expert_i = ROUTED ? a.ids[at_i] : a.place_expert[at_i], pair_i = -1;
+    int expert_i = ROUTED ? a.ids[at_i] : reinterpret_cast<const int32_t *>(a.tile_rows)[at_i], pair_i = -1;
     if constexpr (ROUTED) {
         expert_i = lane < P ? expert_i : 0x7fffffff;
     } else { // (places outside the segments are dropped after the loads)
@@ -1672,9 +1679,8 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
-    if (!mixed) a.tile_rows = nullptr;
     const bool few = !mixed && a.T <= kFewTokens && a.k < kFewTasks && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0);
-    if (!few || r) a.place_expert = nullptr;
+    if (!mixed && (!few || r)) a.tile_rows = nullptr;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
