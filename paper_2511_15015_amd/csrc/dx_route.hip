@@ -310,6 +310,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_router_gemm(const dx_bf16 *__res
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) // row 8 * i + lane / 8: bit 2 of (row >> 1) & 7 is i & 1
             *reinterpret_cast<rt_u32x4 *>(stage + i * 1024 + (put ^ ((i & 1) * 64))) = v[i];
+        // (no instruction: the wavefront's LDS accesses stay in order in the hardware, and here in the compiler, which sees
+        // that a lane reads other addresses than it wrote)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (2 * l + h >= nsteps) break; // wavefront-uniform
@@ -325,6 +328,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_router_gemm(const dx_bf16 *__res
                 for (int n = 0; n < NT; ++n)
                     acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m].v, b[n].v, acc[m][n], 0, 0, 0);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
     rt_u32x4 v[2][LOADS];
     if (l0 < l1) { // wavefront-uniform
