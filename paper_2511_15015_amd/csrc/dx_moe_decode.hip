@@ -63,6 +63,7 @@ typedef const DX_GLOBAL dx_bf16 *gbf16; // bf16 rows (scales, tokens)
 typedef const DX_GLOBAL u32x4 *gvec16;
 typedef const DX_GLOBAL u32x2 *gvec8;
 typedef const DX_GLOBAL uint32_t *gvec4;
+typedef const DX_GLOBAL uint32_t __attribute__((aligned(2))) *gscales2; // two scales
 typedef const __attribute__((address_space(3))) int *lds_ints; // an int array in LDS
 
 union frag8 {
@@ -139,6 +140,7 @@ __device__ __forceinline__ u32x4 interleave_halves(u32x4 v)
 }
 
 constexpr int kWaves = 8;             // wavefronts per block
+constexpr int kRoundPairs = 4;        // strip pairs that share the tokens of a K round
 constexpr int kThreads = 64 * kWaves; // 512
 constexpr int kMaxExperts = 1024 + 1; // routed + shared
 // Cost units of the partition, from a fit of the blocks' measured times (per-block time stamps of a debug
@@ -705,14 +707,19 @@ __device__ __forceinline__ void finish_batch(const dx_fwd_args &a, const expert_
     }
 }
 
+// How the K extent of a strip is split (pick_split):
+//   kWhole:  one round of whole chunks, K / (4*LK) = WPS * CPW with WPS <= 8;
+//   kRagged: one round of CPW = 2 chunks, of which the last wavefront may have one only;
+//   kRounds: more chunks than the wavefronts take at once.
+enum split_mode { kWhole, kRagged, kRounds };
+
 // One run: strips [h_lo, h_hi) of one expert for one block of up to 32 tokens (mb).
 // All kThreads threads of the block execute this with identical arguments.
 //
-// FAST (K is one round of whole chunks: K / (4*LK) = WPS * CPW with WPS <= 8): the steady-state loop
-// is straight-line code -- every iteration issues the next strip pair's loads unconditionally (the
-// strip index is clamped, so the last iterations of a ragged run fetch a duplicate) -- which lets the
-// compiler wait for exactly the loads it is about to use and keep the prefetch in flight.
-template <int LK, int GPC, int CPW, bool DOWN, int FMT, int MT, bool FAST>
+// With one round the steady-state loop is straight-line code -- every iteration issues the next strip pair's loads
+// unconditionally (the strip index is clamped, so the last iterations of a ragged run fetch a duplicate) -- which
+// lets the compiler wait for exactly the loads it is about to use and keep the prefetch in flight.
+template <int LK, int GPC, int CPW, bool DOWN, int FMT, int MT, int MODE>
 __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ctx &ex, int mb, int h_lo, int h_hi,
                                            f32x4 (*red)[kWaves][4][64], int &pb)
 {
@@ -726,7 +733,8 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     const int per = (nc + CPW - 1) / CPW;
     const int WPS = per < kWaves ? per : kWaves;
     const int SPP = kWaves / WPS;
-    const int rounds = FAST ? 1 : (per + WPS - 1) / WPS;
+    constexpr bool ONE_ROUND = MODE != kRounds;
+    const int rounds = ONE_ROUND ? 1 : (per + WPS - 1) / WPS;
     const int g = wave / WPS, kw = wave % WPS;
     const bool idle = g >= SPP;
     const int npairs = (h_hi - h_lo + 1) / 2;
@@ -749,8 +757,8 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
         return;
     }
 
-    // FAST: nc counts as "unbounded" so that every chunk predicate folds away
-    const int ncp = FAST ? 0x7fffffff : nc;
+    // kWhole: nc counts as "unbounded" so that every chunk predicate folds away
+    const int ncp = MODE == kWhole ? 0x7fffffff : nc;
     constexpr bool LINES = LK == 32;
     constexpr int NSW = (CPW * GPC + 1) / 2; // words of group scales per strip
     u32x4 x[CPW][MT][LK / 8];
@@ -772,7 +780,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     };
 
     // A step is one strip: b = 0 the first strip of a pair, b = 1 the second; the last pair of a run may lack its
-    // second strip (no load, no multiply).  FAST: step t = 2 * batch + b.  Otherwise K goes in rounds of 8 * CPW chunks
+    // second strip (no load, no multiply).  One round: step t = 2 * batch + b.  Otherwise K goes in rounds of 8 * CPW chunks
     // and the tokens are fetched anew in every round, so NB pairs share a round's tokens, each with accumulators
     // of its own: step t = (((batch / NB) * rounds + round) * NB + batch % NB) * 2 + b.  (One pair per fetch moved as
     // many token bytes as weight bytes: 8 tokens of 16 experts of 4096 x 6400 225 us, with NB = 4 185 us.)
@@ -780,7 +788,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     // strip is a quarter of the bytes or less, so it gets a deeper pipeline (four stages; with six or eight
     // the runs of a decode batch, a dozen steps each, spend most of their steps outside the steady loop,
     // which measured slower).
-    constexpr int NB = FAST ? 1 : 4;
+    constexpr int NB = ONE_ROUND ? 1 : kRoundPairs;
     constexpr int NST = FMT ? 4 : 2;
     const int nhalf = (nbatch + NB - 1) / NB * NB * rounds * 2; // steps
     using stage_t = std::conditional_t<LINES, line_stage<CPW, FMT>, wstage<LK, CPW, FMT>>;
@@ -790,10 +798,10 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     // the strip of step t (past the end of the run for the missing half of the last pair and for the pairs of
     // wavefront groups without one in the last batch) and its K round
     auto strip_of = [&](int t) {
-        if constexpr (FAST) return h_lo + 2 * ((t >> 1) * SPP + g) + (t & 1);
+        if constexpr (ONE_ROUND) return h_lo + 2 * ((t >> 1) * SPP + g) + (t & 1);
         else return h_lo + 2 * (((t / (2 * NB) / rounds) * NB + ((t >> 1) % NB)) * SPP + g) + (t & 1);
     };
-    auto chunk_of_step = [&](int t) { return FAST ? kw * CPW : (((t / (2 * NB)) % rounds) * WPS + kw) * CPW; };
+    auto chunk_of_step = [&](int t) { return ONE_ROUND ? kw * CPW : (((t / (2 * NB)) % rounds) * WPS + kw) * CPW; };
     // row r of a strip's tile in the weight (scale) matrices: row index and which of the two matrices
     auto issue_step = [&](int t, stage_t &dst) {
         int s = strip_of(t);
@@ -804,7 +812,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
             constexpr int CB = FMT == 0 ? 256 : (FMT == 1 ? 64 : 32); // bytes of a chunk in a row
             const gbytes lo = weight_rows0 + strip_at + c0 * CB;
             const gbytes hi = (DOWN ? weight_rows0 + 8 * (size_t)ex.row_bytes : weight_rows1) + strip_at + c0 * CB;
-            issue_lines<CPW, FMT>(dst, lo, hi, ex.row_bytes, c0 < ncp, c0 + 1 < ncp, lane);
+            issue_lines<CPW, FMT>(dst, lo, hi, ex.row_bytes, ONE_ROUND || c0 < ncp, c0 + 1 < ncp, lane);
         } else {
             const gbytes p = DOWN ? weight_rows0 + strip_at + lane_row16
                                   : (r < 8 ? weight_rows0 + strip_at : weight_rows1 + strip_at) + lane_row8;
@@ -839,8 +847,8 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
                                 dst[u][(i * GPC + g) >> 1] = *reinterpret_cast<gvec4>(sp + (c0 + i) * GPC + g);
                         }
                 } else if (CPW == 2 && a.group == CHUNK && c0 + 1 < ncp) {
-                    // the two chunks' scales are neighbours (c0 is even, a scale row starts 4-byte aligned)
-                    dst[u][0] = *reinterpret_cast<gvec4>(sp + c0);
+                    // the two chunks' scales are neighbours (a row of an odd number of them may start at any even address)
+                    dst[u][0] = *reinterpret_cast<gscales2>(sp + c0);
                 } else {
                     uint32_t v = 0;
 #pragma unroll
@@ -877,7 +885,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
         }
 #endif
         if (strip_of(t) < h_hi) { // wavefront-uniform; a strip past the end was not fetched either, or is a duplicate
-            if constexpr (LINES) multiply_lines<GPC, CPW, FMT, MT>(cur, x, bias, sc, c0 < ncp, c0 + 1 < ncp, ll, lane, area(), to);
+            if constexpr (LINES) multiply_lines<GPC, CPW, FMT, MT>(cur, x, bias, sc, ONE_ROUND || c0 < ncp, c0 + 1 < ncp, ll, lane, area(), to);
             else multiply<LK, CPW, FMT, MT>(cur, x, bias, sc[0], c0, ncp, to);
         }
     };
@@ -919,7 +927,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
                 arow[mt][h] = (gbf16)a.x + (size_t)tok * ex.K;
             }
         }
-    if constexpr (FAST) {
+    if constexpr (ONE_ROUND) {
         fetch_tokens(kw * CPW);
         auto do_step = [&](int t, const stage_t &cur, const uint32_t (&sc)[NSW],
                            int b /* = t & 1, compile-time at every call */) __attribute__((always_inline)) {
@@ -1092,7 +1100,7 @@ __device__ __forceinline__ void write_place_experts(const dx_fwd_args &a)
 }
 
 // This block's share: the strips whose first unit lies in [ub0, ub1), run by run.
-template <int LK, int GPC, int CPW, bool DOWN, bool FAST>
+template <int LK, int GPC, int CPW, bool DOWN, int MODE>
 __device__ __forceinline__ void run_share(const dx_fwd_args &a, const partition_lds &pl, uint32_t ub0, uint32_t ub1,
                                           lds_ints perm_lds, f32x4 (*red)[kWaves][4][64])
 {
@@ -1139,24 +1147,24 @@ __device__ __forceinline__ void run_share(const dx_fwd_args &a, const partition_
             }
 #endif
             if (ex.fmt == DX_FMT_INT4G) {
-                if (two) run_strips<LK, GPC, CPW, DOWN, 1, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                else run_strips<LK, GPC, CPW, DOWN, 1, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                if (two) run_strips<LK, GPC, CPW, DOWN, 1, 2, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
+                else run_strips<LK, GPC, CPW, DOWN, 1, 1, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
             } else if (ex.fmt == DX_FMT_INT2G) {
                 // (16 codes per word: the library refuses int2 handles when the group is 32)
                 if constexpr (LK >= 16 && GPC < 4) {
-                    if (two) run_strips<LK, GPC, CPW, DOWN, 2, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                    else run_strips<LK, GPC, CPW, DOWN, 2, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                    if (two) run_strips<LK, GPC, CPW, DOWN, 2, 2, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
+                    else run_strips<LK, GPC, CPW, DOWN, 2, 1, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
                 }
             } else {
-                if (two) run_strips<LK, GPC, CPW, DOWN, 0, 2, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
-                else run_strips<LK, GPC, CPW, DOWN, 0, 1, FAST>(a, ex, mb, s_lo, s_hi, red, pb);
+                if (two) run_strips<LK, GPC, CPW, DOWN, 0, 2, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
+                else run_strips<LK, GPC, CPW, DOWN, 0, 1, MODE>(a, ex, mb, s_lo, s_hi, red, pb);
             }
             i = iend;
         }
     }
 }
 
-template <int LK, int GPC, int CPW, bool DOWN, bool FAST>
+template <int LK, int GPC, int CPW, bool DOWN, int MODE>
 __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
 {
     __shared__ f32x4 red[2][kWaves][4][64]; // 64 KB: partial sums, double buffered
@@ -1175,7 +1183,7 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
             else write_tile_rows(a, pl);
         }
     }
-    run_share<LK, GPC, CPW, DOWN, FAST>(a, pl, ub0, ub1, nullptr, red);
+    run_share<LK, GPC, CPW, DOWN, MODE>(a, pl, ub0, ub1, nullptr, red);
 #ifdef DX_TRACE
     if (threadIdx.x == 0 && blockIdx.x < 8192) {
         g_trace[DOWN ? 1 : 0][blockIdx.x][0] = trace_t0;
@@ -1356,7 +1364,7 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 #ifdef DX_TRACE
     trace_t3 = wall_clock64();
 #endif
-    run_share<LK, GPC, CPW, false, true>(a, pl, ub0, ub1, (lds_ints)lds_perm, red);
+    run_share<LK, GPC, CPW, false, kWhole>(a, pl, ub0, ub1, (lds_ints)lds_perm, red);
 #ifdef DX_TRACE
     if (threadIdx.x == 0 && blockIdx.x < 8192) {
         g_trace[0][blockIdx.x][0] = trace_t0;
@@ -1590,7 +1598,7 @@ __global__ __launch_bounds__(256) void k_combine_bf16(dx_fwd_args a)
 // WPS <= 8 wavefronts; prefer the split that leaves the fewest of the 8 wavefronts without a K-part.
 struct split_choice {
     int cpw;
-    bool fast;
+    split_mode mode;
 };
 
 split_choice pick_split(int nc_a, int nc_b)
@@ -1611,8 +1619,9 @@ split_choice pick_split(int nc_a, int nc_b)
             best_busy = busy;
         }
     }
-    if (best) return {best, true};
-    return {1, false};
+    if (best) return {best, kWhole};
+    if (nc_a <= 2 * kWaves && nc_b <= 2 * kWaves) return {2, kRagged};
+    return {1, kRounds};
 }
 
 // A launch, optionally with events that take the start and stop time stamps of the kernel's own dispatch
@@ -1668,12 +1677,10 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
                 return;
             }
         }
-        if (c.fast) {
-            if (c.cpw == 2) launch(k_stream<LK, GPC, 2, DOWN, true>, grid, block, s, start, stop, a);
-            else launch(k_stream<LK, GPC, 1, DOWN, true>, grid, block, s, start, stop, a);
-        } else {
-            launch(k_stream<LK, GPC, 1, DOWN, false>, grid, block, s, start, stop, a);
-        }
+        if (c.mode == kRounds) launch(k_stream<LK, GPC, 1, DOWN, kRounds>, grid, block, s, start, stop, a);
+        else if (c.mode == kRagged) launch(k_stream<LK, GPC, 2, DOWN, kRagged>, grid, block, s, start, stop, a);
+        else if (c.cpw == 2) launch(k_stream<LK, GPC, 2, DOWN, kWhole>, grid, block, s, start, stop, a);
+        else launch(k_stream<LK, GPC, 1, DOWN, kWhole>, grid, block, s, start, stop, a);
     });
 }
 
@@ -1698,7 +1705,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
-        *routed = !mixed && pick_split(nc, nc).fast && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
+        *routed = !mixed && pick_split(nc, nc).mode == kWhole && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
