@@ -140,7 +140,6 @@ __device__ __forceinline__ u32x4 interleave_halves(u32x4 v)
 }
 
 constexpr int kWaves = 8;             // wavefronts per block
-constexpr int kRoundPairs = 4;        // strip pairs that share the tokens of a K round
 constexpr int kThreads = 64 * kWaves; // 512
 constexpr int kMaxExperts = 1024 + 1; // routed + shared
 // Cost units of the partition, from a fit of the blocks' measured times (per-block time stamps of a debug
@@ -712,7 +711,6 @@ __device__ __forceinline__ void finish_batch(const dx_fwd_args &a, const expert_
 //   kRagged: one round of CPW = 2 chunks, of which the last wavefront may have one only;
 //   kRounds: more chunks than the wavefronts take at once.
 enum split_mode { kWhole, kRagged, kRounds };
-
 // One run: strips [h_lo, h_hi) of one expert for one block of up to 32 tokens (mb).
 // All kThreads threads of the block execute this with identical arguments.
 //
@@ -783,12 +781,13 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     // second strip (no load, no multiply).  One round: step t = 2 * batch + b.  Otherwise K goes in rounds of 8 * CPW chunks
     // and the tokens are fetched anew in every round, so NB pairs share a round's tokens, each with accumulators
     // of its own: step t = (((batch / NB) * rounds + round) * NB + batch % NB) * 2 + b.  (One pair per fetch moved as
-    // many token bytes as weight bytes: 8 tokens of 16 experts of 4096 x 6400 225 us, with NB = 4 185 us.)
+    // many token bytes as weight bytes: 8 tokens of 16 experts of 4096 x 6400, bf16/int4 227 us, now 192.  NB = 4 with two chunks of 128 per
+    // wavefront does not fit the registers.)
     // NST register stages: the strip of step t + NST - 1 is fetched while step t is multiplied.  A quantized
     // strip is a quarter of the bytes or less, so it gets a deeper pipeline (four stages; with six or eight
     // the runs of a decode batch, a dozen steps each, spend most of their steps outside the steady loop,
     // which measured slower).
-    constexpr int NB = ONE_ROUND ? 1 : kRoundPairs;
+    constexpr int NB = ONE_ROUND ? 1 : (LK == 32 && CPW == 2 ? 2 : 4);
     constexpr int NST = FMT ? 4 : 2;
     const int nhalf = (nbatch + NB - 1) / NB * NB * rounds * 2; // steps
     using stage_t = std::conditional_t<LINES, line_stage<CPW, FMT>, wstage<LK, CPW, FMT>>;
@@ -1621,7 +1620,15 @@ split_choice pick_split(int nc_a, int nc_b)
     }
     if (best) return {best, kWhole};
     if (nc_a <= 2 * kWaves && nc_b <= 2 * kWaves) return {2, kRagged};
-    return {1, kRounds};
+    // Two chunks per wavefront unless many more wavefronts have work in the rounds with one (the last round of two holds few
+    // chunks).  Layers of 32 experts, us with one and with two chunks: 20 chunks (0.83 and 0.63 of the places in use)
+    // int4 32 tokens 54.9 and 62.4, 24 chunks (1 and 0.75) 61.2 and 65.7; 28 chunks (0.88 both) 66.5 and 69.6, int2 73.1 and
+    // 67.0, 32 chunks int2 80.9 and 70.6, 40 chunks (1 and 0.83) int2 94.6 and 86.8, bf16 141 and 146.
+    auto in_use = [&](int cpw) {
+        const int nc = nc_a > nc_b ? nc_a : nc_b, per = (nc + cpw - 1) / cpw;
+        return (double)per / ((per + kWaves - 1) / kWaves * kWaves);
+    };
+    return {in_use(2) >= 0.8 * in_use(1) ? 2 : 1, kRounds};
 }
 
 // A launch, optionally with events that take the start and stop time stamps of the kernel's own dispatch
@@ -1677,8 +1684,13 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
                 return;
             }
         }
-        if (c.mode == kRounds) launch(k_stream<LK, GPC, 1, DOWN, kRounds>, grid, block, s, start, stop, a);
-        else if (c.mode == kRagged) launch(k_stream<LK, GPC, 2, DOWN, kRagged>, grid, block, s, start, stop, a);
+        if (c.mode == kRounds) {
+            // (a pair of chunks with two or four groups each and its sums do not fit the registers)
+            if constexpr (LK < 32) launch(k_stream<LK, GPC, 2, DOWN, kRounds>, grid, block, s, start, stop, a);
+            else if constexpr (GPC > 1) launch(k_stream<LK, GPC, 1, DOWN, kRounds>, grid, block, s, start, stop, a);
+            else if (c.cpw == 2) launch(k_stream<LK, GPC, 2, DOWN, kRounds>, grid, block, s, start, stop, a);
+            else launch(k_stream<LK, GPC, 1, DOWN, kRounds>, grid, block, s, start, stop, a);
+        } else if (c.mode == kRagged) launch(k_stream<LK, GPC, 2, DOWN, kRagged>, grid, block, s, start, stop, a);
         else if (c.cpw == 2) launch(k_stream<LK, GPC, 2, DOWN, kWhole>, grid, block, s, start, stop, a);
         else launch(k_stream<LK, GPC, 1, DOWN, kWhole>, grid, block, s, start, stop, a);
     });

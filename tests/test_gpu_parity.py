@@ -1173,7 +1173,11 @@ def test_forward_random_shapes_int4_int2_pair(B, LY, dxo):
     ("bf16-int4", 20, 1152, 2176, 32),    # four groups per chunk; 9 and 17 chunks: K in rounds, a last chunk without a pair
     ("bf16-int4", 34, 1920, 1152, 128),   # 15 and 9 chunks
     ("bf16-int4", 7, 128, 896, 32),       # one and seven chunks: a chunk per wavefront
+    ("bf16-int4", 21, 3584, 2560, 128),   # 28 chunks (two per wavefront in rounds, a short last round) and 20 (one per wavefront)
+    ("bf16-int4", 40, 352, 608, 32),      # no multiple of 128: 11 chunks of 32 (one ragged round) and 19 (rounds)
     ("int4-int2", 20, 1152, 2176, 64),
+    ("int4-int2", 35, 4096, 3584, 128),   # 32 and 28 chunks
+    ("int4-int2", 5, 704, 1088, 64),      # 11 and 17 chunks of 64
     ("int4-int2", 33, 1920, 2048, 128),
     ("int4-int2", 3, 128, 896, 64),
     ("int4-int2", 18, 2048, 896, 64),
