@@ -202,7 +202,8 @@ struct wstage {
 // buffer that is next to be filled, unused until the sums are parked), from where the operands are read in the
 // order they are needed.  Reading from LDS also lets every step of the matrix instruction take its elements
 // from one quantization group, whatever the group size: GPC = groups per chunk (1, 2, 4 for groups of 128, 64, 32).
-//   Area: bf16 [line][16 rows][128 B], a chunk at a time; int4 [16 rows][64 * CPW B]; int2 [16 rows][32 * CPW B].
+//   Area: bf16 [line][16 rows][128 B], a chunk at a time; int4 [16 rows][64 * CPW B]; int2 in groups of 64
+//   [16 rows][32 * CPW B] (in groups of 128 it does not pass through LDS).
 //   16-byte piece p of row r sits in slot p ^ ((r >> 1) & 7) of a 128-byte row, p ^ ((r >> 2) & 3) of a 64-byte
 //   row: the 16 lanes that read one piece index of 16 rows hit 16 different bank groups.
 template <typename T>
@@ -243,7 +244,7 @@ struct line_stage {
 
 // `lo`: the strip's first eight rows at the wavefront's first chunk, `hi`: its other eight (in a gate/up strip
 // another matrix); `two`: the second chunk of a CPW = 2 stage exists.
-template <int CPW, int FMT>
+template <int GPC, int CPW, int FMT>
 __device__ __forceinline__ void issue_lines(line_stage<CPW, FMT> &st, gbytes lo, gbytes hi, uint32_t row_bytes, bool one,
                                             bool two, int lane)
 {
@@ -263,6 +264,19 @@ __device__ __forceinline__ void issue_lines(line_stage<CPW, FMT> &st, gbytes lo,
         if (one) {
             st.w[0] = line_load(reinterpret_cast<gvec16>(lo + off));
             st.w[1] = line_load(reinterpret_cast<gvec16>(hi + off));
+        }
+    } else if constexpr (FMT == 2 && GPC == 1) {
+        // Codes of 2 bits in one group per chunk: 8 bytes per lane and chunk, in operand order straight to the registers.  A
+        // strip is so small that the way through LDS costs more than the loads in whole lines gain (30B-shaped layer, all
+        // experts int2, 64 tokens 85.7 us through LDS, 80.7 without).
+        const gbytes base = (lane & 8 ? hi : lo) + (uint32_t)(lane & 7) * row_bytes + (lane >> 4) * 8;
+        if (one) {
+            const u32x2 t = *reinterpret_cast<gvec8>(base);
+            st.w[0].x = t.x, st.w[0].y = t.y;
+        }
+        if (CPW == 2 && two) {
+            const u32x2 t = *reinterpret_cast<gvec8>(base + 32);
+            st.w[0].z = t.x, st.w[0].w = t.y;
         }
     } else if (one) {
         // all 16 rows in one instruction: 64 (int2, one chunk: 32) bytes of each
@@ -406,7 +420,8 @@ __device__ __forceinline__ void multiply_lines(const line_stage<CPW, FMT> &st, c
         }
     } else {
         constexpr bool wide = FMT == 1 && CPW == 2; // 128-byte rows in the area
-        if constexpr (wide) {
+        if constexpr (FMT == 2 && GPC == 1) { // in operand order already
+        } else if constexpr (wide) {
             lds_put(area + ll.put, st.w[0]);
             lds_put(area + 1024 + (ll.put ^ 64), st.w[1]);
         } else if constexpr (FMT == 2 && CPW == 1) {
@@ -437,8 +452,7 @@ __device__ __forceinline__ void multiply_lines(const line_stage<CPW, FMT> &st, c
             } else {
                 const int r = lane & 15, q = lane >> 4;
                 if constexpr (GPC == 1) {
-                    const u32x2 t = lds_get<u32x2>(from + (CPW == 2 ? ll.get64_s ^ (i * 32) : r * 32 + 8 * q));
-                    wq[i][0] = t.x; wq[i][1] = t.y;
+                    wq[i][0] = i ? st.w[0].z : st.w[0].x; wq[i][1] = i ? st.w[0].w : st.w[0].y;
                 } else {
 #pragma unroll
                     for (int g = 0; g < 2; ++g)
@@ -811,7 +825,7 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
             constexpr int CB = FMT == 0 ? 256 : (FMT == 1 ? 64 : 32); // bytes of a chunk in a row
             const gbytes lo = weight_rows0 + strip_at + c0 * CB;
             const gbytes hi = (DOWN ? weight_rows0 + 8 * (size_t)ex.row_bytes : weight_rows1) + strip_at + c0 * CB;
-            issue_lines<CPW, FMT>(dst, lo, hi, ex.row_bytes, ONE_ROUND || c0 < ncp, c0 + 1 < ncp, lane);
+            issue_lines<GPC, CPW, FMT>(dst, lo, hi, ex.row_bytes, ONE_ROUND || c0 < ncp, c0 + 1 < ncp, lane);
         } else {
             const gbytes p = DOWN ? weight_rows0 + strip_at + lane_row16
                                   : (r < 8 ? weight_rows0 + strip_at : weight_rows1 + strip_at) + lane_row8;
@@ -1435,7 +1449,7 @@ __device__ __forceinline__ f32x4 strip_of_one(gbf16 h_row, gbytes w, gbf16 sc, i
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const gbytes p = w + (c + 2 * b) * CB;
-            issue_lines<2, FMT>(st[b], p, p + 8 * (size_t)row_bytes, row_bytes, c + 2 * b < c1, c + 2 * b + 1 < c1, lane);
+            issue_lines<GPC, 2, FMT>(st[b], p, p + 8 * (size_t)row_bytes, row_bytes, c + 2 * b < c1, c + 2 * b + 1 < c1, lane);
         }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
