@@ -1710,6 +1710,25 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
     });
 }
 
+// Whether the down projection and the combine run in k_down_few.  A block reads its token's strips by itself on a grid of
+// d / 16 blocks per token, and an expert that both tokens select is read twice; k_stream spreads the bytes over the whole
+// chip and reads an expert once.  So: at most 240 chunks of a strip per compute unit of the chip (blocks that leave
+// compute units idle count accordingly), and for two tokens at least twice as many experts as pairs, unless a block needs
+// one round of loads only and all blocks run at once (latency).  Whole calls, us, k_stream<down> and this, T = 1: 30B-shaped (96 chunks) 31.3 and
+// 25.7, 80B-shaped (88) 53 and 36, 60 experts of 2048 x 1408 with a shared one (120) 27.6 and 25.3, 16 of 4096 x 6400 (100)
+// 54.9 and 45.4, 8 of 4096 x 14336 (224) 115.8 and 109.4; 8 of 2048 x 2048, top-8 (256) 33.7 and 35.6, 32 of 1024 x 2048,
+// top-8 (512) 26.6 and 30.1.  T = 2, every expert selected by both: 4 of 4096 x 4096 96 and 118, 8 of 2048 x 768 (one
+// round, 256 blocks) 29.7 and 27.1, 4 of 4096 x 2048, top-2 (one round, 512 blocks) 34.8 and 36.4.
+bool takes_few(const dx_fwd_args &a, int n_cu)
+{
+    if (a.T > kFewTokens || a.k >= kFewTasks || a.f % 128 || (a.shared && a.shared_f % 128)) return false;
+    const int tasks = a.k + (a.shared ? 1 : 0), split = tasks < kWaves ? kWaves / tasks : 1;
+    const int nc = a.f / 128, nc_shared = a.shared ? a.shared_f / 128 : 0, most = nc > nc_shared ? nc : nc_shared;
+    if ((long)(a.k * nc + nc_shared) * n_cu > 240L * (a.d / 16) * a.T) return false;
+    const bool one_round = tasks * split <= kWaves && (most + split - 1) / split <= 6 && a.d / 16 * a.T <= n_cu;
+    return a.T == 1 || 2 * a.T * a.k <= a.E || one_round;
+}
+
 // Up to this many tokens per call the streaming kernels alone are faster than streamed experts and tiles (30B-shaped
 // layer: T = 100 106 us against 110, T = 128 117 against 114; 80B-shaped: T = 128 106 against 116).
 constexpr int kStreamOnlyTokens = 128;
@@ -1726,7 +1745,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
-    const bool few = !mixed && a.T <= kFewTokens && a.k < kFewTasks && a.f % 128 == 0 && (!a.shared || a.shared_f % 128 == 0);
+    const bool few = !mixed && takes_few(a, n_cu);
     if (!mixed && (!few || r)) a.tile_rows = nullptr;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {

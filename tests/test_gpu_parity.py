@@ -1212,7 +1212,10 @@ def test_decode_groups_and_chunk_counts(B, LY, dxo, pair, T, d, f, group):
     ("bf16-int4", 1, 8, 3, 128, 896, 64, 128),     # two wavefronts to an expert, an odd number of chunks; the shared expert's one
     ("bf16-int4", 1, 32, 16, 256, 1792, 32, 256),  # more experts than wavefronts, K in three rounds of six chunks
     ("bf16-int4", 2, 4, 3, 256, 128, 128, 384),    # tokens that share experts: places inside a segment
-    ("bf16-int4", 4, 16, 16, 128, 256, 128, 0),    # 64 pairs, every expert four times
+    ("bf16-int4", 2, 64, 16, 2048, 128, 128, 128), # the most it takes: 32 pairs, 17 tasks to a block
+    ("bf16-int4", 2, 4, 4, 4096, 1024, 128, 0),    # every expert selected by both tokens: the streaming kernel
+    ("bf16-int4", 1, 8, 8, 128, 4096, 128, 0),     # too much for its eight blocks: the streaming kernel
+    ("bf16-int4", 3, 16, 16, 128, 256, 128, 0),    # a token more than it takes
     ("int4-int2", 1, 8, 2, 256, 640, 64, 0),
     ("int4-int2", 2, 16, 9, 256, 384, 128, 0),
 ])
