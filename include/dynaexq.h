@@ -150,8 +150,8 @@ dx_status dx_route_forward(dx_ctx *ctx, int layer, const dx_handle *handle_table
 /* dx_route for callers that cannot allocate device memory or create a context
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and the same outputs as dx_route, with the
- * routing scratch (per-chunk token masks) in a static device array of
- * DX_ROUTE_STATIC_MAX_ENTRIES entries (512 KiB per GPU, held
+ * routing scratch (per-chunk token masks and their sums) in a static device
+ * array for DX_ROUTE_STATIC_MAX_ENTRIES entries (524 KiB per GPU, held
  * until the process ends) instead of a context's buffers.  The call allocates
  * nothing, frees nothing and needs no context; it runs on the current device,
  * on hip_stream (NULL = the null stream), and never touches hotness counters.

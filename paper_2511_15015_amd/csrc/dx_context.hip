@@ -278,6 +278,8 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
     if ((e = hipHostMalloc(&c->h_counters, (size_t)g.L * g.E * 8, hipHostMallocDefault)) != hipSuccess)
         return fail(e, "pinned counters");
     if ((e = hipMalloc(&c->d_mask, (size_t)c->n_chunks_max * g.E * 8)) != hipSuccess) return fail(e, "route masks");
+    const size_t n_sums = ((size_t)c->n_chunks_max + DX_SUM_CHUNKS - 1) / DX_SUM_CHUNKS * g.E;
+    if ((e = hipMalloc(&c->d_mask_sums, n_sums * 4)) != hipSuccess) return fail(e, "route sums");
     if ((e = hipMalloc(&c->d_h, n_rows * c->fmax * sizeof(dx_bf16))) != hipSuccess) return fail(e, "H scratch");
     if ((e = hipMalloc(&c->d_o, n_rows * (size_t)g.d * sizeof(float))) != hipSuccess) return fail(e, "O scratch");
     // (for the smallest m_small a call can have; 1 + top_k elements or more, so the at most 2 * top_k places of a few
@@ -329,6 +331,7 @@ extern "C" void dx_destroy(dx_ctx *c)
     if (c->d_counters) (void)hipFree(c->d_counters);
     if (c->h_counters) (void)hipHostFree(c->h_counters);
     if (c->d_mask) (void)hipFree(c->d_mask);
+    if (c->d_mask_sums) (void)hipFree(c->d_mask_sums);
     if (c->d_h) (void)hipFree(c->d_h);
     if (c->d_o) (void)hipFree(c->d_o);
     if (c->d_tile_rows) (void)hipFree(c->d_tile_rows);
@@ -347,7 +350,7 @@ extern "C" dx_status dx_route(dx_ctx *c, int layer, const float *logits, int T, 
     if (!counts || !offsets || (T > 0 && (!logits || !ids || !w || !perm)))
         DX_FAIL(c, DX_ERR_INVALID, "dx_route: null pointer");
     unsigned long long *hot = c->cfg.route_updates_hotness ? c->d_counters + (size_t)layer * c->cfg.E : nullptr;
-    DX_HIP(c, dxk_route(logits, T, c->cfg.E, c->cfg.top_k, ids, w, counts, offsets, perm, c->d_mask,
+    DX_HIP(c, dxk_route(logits, T, c->cfg.E, c->cfg.top_k, ids, w, counts, offsets, perm, c->d_mask, c->d_mask_sums,
                         hot, c->compute));
     return DX_OK;
 }

@@ -77,6 +77,7 @@ struct dx_ctx {
     // routing scratch (chunks of 64 tokens)
     int n_chunks_max = 0;
     unsigned long long *d_mask = nullptr; // [n_chunks_max, E]
+    int32_t *d_mask_sums = nullptr;       // [ceil(n_chunks_max / DX_SUM_CHUNKS), E]
 
     // forward scratch
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
@@ -122,10 +123,11 @@ struct dx_ctx {
                     __FILE__, __LINE__);                                                   \
     } while (0)
 
+constexpr int DX_SUM_CHUNKS = 32; // chunks whose population counts are added up together in large batches
 // ---- kernel launchers (each validates nothing; callers validate) ----------
 // dx_route.hip
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
-                     int32_t *offsets, int32_t *perm, unsigned long long *mask,
+                     int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *sums,
                      unsigned long long *hotness /* window counters of the layer, or null */, hipStream_t s);
 hipError_t dxk_router_gemm(const dx_bf16 *x, const dx_bf16 *w_r, const float *bias, int T, int E, int d, float *logits,
                            int n_cu, hipStream_t s);

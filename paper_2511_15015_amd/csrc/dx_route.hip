@@ -145,14 +145,41 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_topk(
 }
 
 // Batches of several chunks: a block per chunk places the chunk's pairs.  It needs every expert's count and what the
-// chunks before its own hold of it, i.e. the population counts of all chunk masks; every block adds them up by
-// itself (64 KB from L2 for 4096 tokens on 128 experts), S threads to an expert so that one round of loads in flight covers
-// them, because a scan kernel in between costs more (30B-shaped layer: a pass of 4096 tokens 492 us with it, 482 without; of
-// 300 tokens 140 and 138).
+// chunks before its own hold of it.  Every block adds up the population counts of all chunk masks by itself (64 KB from L2
+// for 4096 tokens on 128 experts), S threads to an expert, because a kernel in between costs more (30B-shaped layer: a
+// pass of 4096 tokens 492 us with a scan kernel, 482 without; of 300 tokens 140 and 138).  That work grows with the square
+// of the batch: in large ones k_route_sums adds up groups of kSumChunks chunks first, and a block reads the sums and the
+// masks of its own group.
+constexpr int kSumChunks = DX_SUM_CHUNKS;
+
+// threads per expert in a block of kRouteThreads (log2)
+inline int route_split(int E)
+{
+    int split = 0;
+    while ((E << (split + 1)) <= kRouteThreads && split < 6) ++split;
+    return split;
+}
+
+__global__ __launch_bounds__(kRouteThreads) void k_route_sums(int E, int split, int n_chunks,
+                                                              const unsigned long long *__restrict__ mask,
+                                                              int32_t *__restrict__ sums)
+{
+    const int S = 1 << split, e = threadIdx.x >> split, part = threadIdx.x & (S - 1);
+    const int c0 = blockIdx.x * kSumChunks, c1 = min(n_chunks, c0 + kSumChunks);
+    int n = 0;
+    if (e < E) {
+#pragma unroll 8
+        for (int c = c0 + part; c < c1; c += S) n += __popcll(mask[(size_t)c * E + e]);
+    }
+    for (int o = S >> 1; o > 0; o >>= 1) n += __shfl_xor(n, o, 64); // (an expert's threads are neighbours)
+    if (part == 0 && e < E) sums[(size_t)blockIdx.x * E + e] = n;
+}
+
+// sums: of the groups of chunks (k_route_sums), or null
 __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     const int32_t *__restrict__ ids, int T, int E, int k, int split /* log2 of S */, int n_chunks,
-    const unsigned long long *__restrict__ mask, int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
-    int32_t *__restrict__ perm, unsigned long long *__restrict__ hotness)
+    const unsigned long long *__restrict__ mask, const int32_t *__restrict__ sums, int32_t *__restrict__ counts,
+    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, unsigned long long *__restrict__ hotness)
 {
     __shared__ unsigned long long lds_mask[kRouteThreads];
     __shared__ int lds_at[kRouteThreads]; // where the chunk's first pair of the expert goes
@@ -161,19 +188,39 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     const int e = threadIdx.x >> split, part = threadIdx.x & (S - 1);
     int total = 0, before = 0;
     if (e < E) {
-        constexpr int U = 8; // independent mask loads in flight
-        for (int c0 = part; c0 < n_chunks; c0 += U * S) {
+        constexpr int U = 8; // independent loads in flight
+        const int group = chunk / kSumChunks;
+        if (sums) {
+            const int n_groups = (n_chunks + kSumChunks - 1) / kSumChunks;
+            for (int g0 = part; g0 < n_groups; g0 += U * S) {
+                int m[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int g = g0 + u * S;
+                    m[u] = sums[(size_t)(g < n_groups ? g : n_groups - 1) * E + e];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int g = g0 + u * S;
+                    const int n = g < n_groups ? m[u] : 0;
+                    total += n;
+                    before += g < group ? n : 0;
+                }
+            }
+        }
+        const int first = sums ? group * kSumChunks : 0, end = sums ? chunk + 1 : n_chunks; // masks to read
+        for (int c0 = first + part; c0 < end; c0 += U * S) {
             unsigned long long m[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int c = c0 + u * S;
-                m[u] = mask[(size_t)(c < n_chunks ? c : n_chunks - 1) * E + e];
+                m[u] = mask[(size_t)(c < end ? c : end - 1) * E + e];
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int c = c0 + u * S;
-                const int n = c < n_chunks ? __popcll(m[u]) : 0;
-                total += n;
+                const int n = c < end ? __popcll(m[u]) : 0;
+                if (!sums) total += n;
                 before += c < chunk ? n : 0;
                 if (c == chunk) lds_mask[e] = m[u];
             }
@@ -378,7 +425,7 @@ hipError_t launch_topk(const float *logits, int T, int E, int k, int32_t *ids, f
 } // namespace
 
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
-                     int32_t *offsets, int32_t *perm, unsigned long long *mask, unsigned long long *hotness,
+                     int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *sums, unsigned long long *hotness,
                      hipStream_t s)
 {
     // T == 0 still runs one (empty) chunk so that counts and offsets are written.
@@ -395,10 +442,19 @@ hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, flo
     else if (E <= 512) e = launch_topk<8, false>(logits, T, E, k, ids, w, counts, offsets, perm, mask, hotness, n_chunks, s);
     else e = launch_topk<16, false>(logits, T, E, k, ids, w, counts, offsets, perm, mask, hotness, n_chunks, s);
     if (e != hipSuccess || n_chunks == 1) return e;
-    int split = 0; // threads per expert
-    while ((E << (split + 1)) <= kRouteThreads && split < 6) ++split;
-    hipLaunchKernelGGL(k_route_place, dim3(n_chunks), dim3(kRouteThreads), 0, s, ids, T, E, k, split, n_chunks, mask, counts,
-                       offsets, perm, hotness);
+    const int split = route_split(E);
+    // Mask words that all blocks read without the groups' sums: about 3 million of them (24 MB) cost as much as the sums (more
+    // where every expert has one thread only, to whom the sums are dear as well).  us without and with them: 128 experts
+    // 8192 tokens (2.1 M) 17.5 and 17.3, 16384 tokens 25.3 and 18.8; 256 experts 4096 tokens (1 M) 18.1 and 21.2, 8192 tokens
+    // (4.2 M) 25.7 and 20.9; 512 experts 4096 tokens (2.1 M) 22.7 and 25.4, 8192 tokens 30.4 and 27.4; 1024 experts 4096 tokens
+    // (4.2 M) 38.7 and 41.9, 8192 tokens 48.5 and 43.8; 65536 tokens on 128 to 1024 experts 248 to 590 and 41 to 160.
+    const long long words = (long long)n_chunks * n_chunks * E;
+    const bool direct = words <= (split == 0 ? 5000000 : 3000000);
+    if (!direct)
+        hipLaunchKernelGGL(k_route_sums, dim3((n_chunks + kSumChunks - 1) / kSumChunks), dim3(kRouteThreads), 0, s, E, split,
+                           n_chunks, mask, sums);
+    hipLaunchKernelGGL(k_route_place, dim3(n_chunks), dim3(kRouteThreads), 0, s, ids, T, E, k, split, n_chunks, mask,
+                       static_cast<const int32_t *>(direct ? nullptr : sums), counts, offsets, perm, hotness);
     return hipGetLastError();
 }
 
@@ -463,8 +519,9 @@ namespace {
 constexpr size_t kStaticEntries = DX_ROUTE_STATIC_MAX_ENTRIES; // (chunks of 64 tokens) x experts
 struct route_scratch {
     unsigned long long mask[kStaticEntries];
+    int32_t sums[kStaticEntries / kSumChunks + 1024]; // groups of chunks x experts
 };
-static __device__ __align__(256) route_scratch scratch; // 512 KiB per GPU
+static __device__ __align__(256) route_scratch scratch; // 524 KiB per GPU
 
 constexpr int kMaxDevices = 64;
 route_scratch *g_scratch_ptr[kMaxDevices]; // per device, null until resolved
@@ -516,7 +573,7 @@ extern "C" dx_status dx_route_static(const float *logits, int T, int E, int top_
         sp = g_scratch_ptr[dev];
     }
     // Nothing in the scratch has to start at zero: every chunk's block writes all E masks of its chunk.
-    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, nullptr,
+    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, sp->sums, nullptr,
                   static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return static_fail(DX_ERR_HIP, "dx_route_static: launch: %s", hipGetErrorString(e));
     return DX_OK;

@@ -174,6 +174,10 @@ def test_route_edge_shapes_and_ties(B, LY, dxo, T, E, k):
 
 
 @pytest.mark.parametrize("T,E,k,coarse", [
+    # large batches, the chunks' sums in groups of 32: 72 chunks, the third group of eight, the selection of a token per
+    # wavefront; 161 chunks, the sixth group of one, an expert's sums over four threads; 1734 chunks on 64 threads
+    (4580, 1000, 17, False), (10304, 130, 2, True), (110930, 1, 1, False),
+    (4544, 1000, 3, True),     # 71 chunks: the last size without
     (65, 1, 1, False), (130, 3, 2, True),          # 64 threads per expert in the placement, more than there are chunks
     (1300, 600, 3, True), (1400, 1024, 5, False),  # one thread per expert, more chunks than loads in flight
     (2000, 129, 16, True), (700, 512, 10, False),  # wide layers: the threshold and, on a coarse grid, its fall-back
