@@ -141,17 +141,18 @@ hipError_t dxk_quantize(const dx_bf16 *w, int rows, int K, int group, uint8_t *q
 hipError_t dxk_quantize2(const dx_bf16 *w, int rows, int K, int group, uint8_t *q, dx_bf16 *sc, hipStream_t s); // 2-bit
 
 // dx_moe_decode.hip / dx_moe_prefill.hip
-// One row tile of an expert above m_small tokens; in element 0 of the list e is the number of routed row tiles that
-// follow and mt the number of the shared expert's after them.
-constexpr int DX_TILE_ROWS = 128;
+// One row tile of an expert above m_small tokens.  In element 0 of the list e is the number of routed 128-row tiles that
+// follow, mt the number of the shared expert's after them, m and seg0 the same for the 256-row tiles behind those.
+constexpr int DX_TILE_ROWS = 128, DX_BIG_ROWS = 256;
 struct dx_tile_row {
-    int e, mt;   // expert (E = shared), row tile of its segment
-    int m, seg0; // rows and first pair slot of the segment
+    int e, mt;   // expert (E = shared), row tile of the rows below
+    int m, seg0; // rows and first pair slot of the segment, or of the part of it that this tile size takes
 };
 // most row tiles a call of T tokens can have (a routed expert has ceil(m / 128) of them, and none up to m_small tokens)
 inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)
 {
     const long pairs = (long)T * k, with = pairs / ((long)m_small + 1) < E ? pairs / ((long)m_small + 1) : E;
+    // (256 rows in one 256-row tile are fewer tiles than in two of 128)
     return pairs / DX_TILE_ROWS + with + (shared ? (T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0);
 }
 // Calls of so few tokens (and top-k up to DX_ROUTED_MAX_TOPK) run the down projection and the combine in one kernel
@@ -169,6 +170,7 @@ struct dx_fwd_args {
     float *o;    // scratch [T*k (+T), d]: fp32, or bf16 in the same allocation when o_bf16
     int T, E, k, d, f, group, shared_f, fmax;
     int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
+    int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     // A list that the gate/up kernel of the streamed experts leaves for the kernels behind it, or null: mixed batches (m_small
     // is a bound): the row tiles of the tiled experts (element 0: their number); up to DX_FEW_TOKENS tokens on a caller's

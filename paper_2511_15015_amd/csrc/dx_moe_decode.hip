@@ -1069,7 +1069,8 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
     __syncthreads();
 }
 
-// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot is free).  Experts above m_small tokens.
+// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot and pl.wave_cnt are free).  Experts above
+// m_small tokens.
 __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1078,30 +1079,47 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
         const int m = a.offsets[e + 1] - a.offsets[e];
         return m > a.m_small ? m : 0;
     };
-    uint32_t local = 0;
+    auto big_rows = [&](int m, uint32_t fmt) { // leading rows that go in 256-row tiles
+        return (a.m_big >> fmt) & 1 ? m / DX_BIG_ROWS * DX_BIG_ROWS : 0;
+    };
+    auto tiles = [](int rows) { return (rows + DX_TILE_ROWS - 1) / DX_TILE_ROWS; };
+    int local = 0, local_big = 0;
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
-        if (e < a.E) local += (uint32_t)((tokens_of(e) + DX_TILE_ROWS - 1) / DX_TILE_ROWS);
+        if (e < a.E) {
+            const int m = tokens_of(e), lead = big_rows(m, a.table[e].fmt);
+            local += tiles(m - lead);
+            local_big += lead / DX_BIG_ROWS;
+        }
     }
-    const uint32_t inc = dx_route_core::wave_scan_inclusive(local);
-    if (lane == 63) pl.wave_tot[wave] = inc;
+    const int inc = dx_route_core::wave_scan_inclusive(local), inc_big = dx_route_core::wave_scan_inclusive(local_big);
+    if (lane == 63) {
+        pl.wave_tot[wave] = (uint32_t)inc;
+        pl.wave_cnt[wave] = inc_big;
+    }
     __syncthreads();
-    uint32_t base = 0, total = 0;
+    int base = 0, total = 0, base_big = 0, total_big = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        const uint32_t t = pl.wave_tot[w];
-        if (w < wave) base += t;
-        total += t;
+        const int t = (int)pl.wave_tot[w], tb = pl.wave_cnt[w];
+        if (w < wave) base += t, base_big += tb;
+        total += t, total_big += tb;
     }
+    const int T_tiled = a.shared && a.T > a.m_small ? a.T : 0, lead_shared = big_rows(T_tiled, DX_FMT_BF16);
+    const int n_shared = tiles(T_tiled - lead_shared), n_big_shared = lead_shared / DX_BIG_ROWS;
     dx_tile_row *out = a.tile_rows + 1 + base + inc - local;
+    dx_tile_row *big = a.tile_rows + 1 + total + n_shared, *out_big = big + base_big + inc_big - local_big;
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
-        const int m = e < a.E ? tokens_of(e) : 0;
-        for (int mt = 0; mt * DX_TILE_ROWS < m; ++mt) *out++ = dx_tile_row{e, mt, m, a.offsets[e]};
+        if (e >= a.E) continue;
+        const int m = tokens_of(e), lead = big_rows(m, a.table[e].fmt), seg0 = a.offsets[e];
+        for (int mt = 0; mt * DX_BIG_ROWS < lead; ++mt) *out_big++ = dx_tile_row{e, mt, lead, seg0};
+        for (int mt = 0; mt * DX_TILE_ROWS < m - lead; ++mt) *out++ = dx_tile_row{e, mt, m - lead, seg0 + lead};
     }
-    const int n_shared = a.shared && a.T > a.m_small ? (a.T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0;
-    for (int mt = tid; mt < n_shared; mt += kThreads) a.tile_rows[1 + total + mt] = dx_tile_row{a.E, mt, a.T, a.T * a.k};
-    if (tid == 0) a.tile_rows[0] = dx_tile_row{(int)total, n_shared, 0, 0};
+    const int seg0 = a.T * a.k;
+    for (int mt = tid; mt < n_shared; mt += kThreads) a.tile_rows[1 + total + mt] = dx_tile_row{a.E, mt, T_tiled - lead_shared, seg0 + lead_shared};
+    for (int mt = tid; mt < n_big_shared; mt += kThreads) big[total_big + mt] = dx_tile_row{a.E, mt, lead_shared, seg0};
+    if (tid == 0) a.tile_rows[0] = dx_tile_row{total, n_shared, total_big, n_big_shared};
 }
 
 // The expert of every place in the segments, for the down kernel of a call of a few tokens (one block).
@@ -1733,6 +1751,24 @@ bool takes_few(const dx_fwd_args &a, int n_cu)
 // layer: T = 100 106 us against 110, T = 128 117 against 114; 80B-shaped: T = 128 106 against 116).
 constexpr int kStreamOnlyTokens = 128;
 
+// The formats whose segments go in 256-row tiles (bits as in a.m_big).  Shapes: whole tiles of columns; the kernel addresses rows
+// with 32-bit byte offsets; it reads the scales of an int4 row as aligned pairs (an even number of groups along both
+// contractions).  Size: the tiles of the down projection fill the chip once, and a segment has 1024 rows on average (bf16)
+// or 512 (int4, whose tiles gain more: a row of codes is expanded for twice the tokens).  Passes of layers of one format,
+// us, 128-row tiles alone and with 256-row ones: bf16, 8 experts of 4096 x 14336, 768 rows on average 2440 and 2560, 1024 rows
+// 3330 and 2930, 4096 rows 12170 and 10100; 30B-shaped 512 rows 889 and 932, 1024 rows 1670 and 1558.  int4, 16 experts of
+// 4096 x 6400 256 rows 995 and 1055, 512 rows 1816 and 1727, 1024 rows 3480 and 3086; 30B-shaped 768 rows 1461 and 1363.  One expert
+// of 4096 x 4096, 1024 rows (64 tiles of the down projection) 122 and 185.
+int big_tile_formats(const dx_fwd_args &a, int n_cu)
+{
+    const uint64_t span_x = (uint64_t)a.T * a.d * 2, span_h = (uint64_t)a.T * (a.k + 1) * a.fmax * 2;
+    if (a.d % 256 || a.f % 128 || (a.shared && a.shared_f % 128) || span_x >= (1ull << 32) || span_h >= (1ull << 32)) return 0;
+    const long pairs = (long)a.T * a.k;
+    if (pairs / DX_BIG_ROWS * (a.d / 256) < n_cu) return 0;
+    const bool pairs_of_scales = (a.d / a.group) % 2 == 0 && (a.f / a.group) % 2 == 0;
+    return (pairs >= 1024L * a.E ? 1 << DX_FMT_BF16 : 0) | (pairs >= 512L * a.E && pairs_of_scales ? 1 << DX_FMT_INT4G : 0);
+}
+
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
 // then tells whether it did (if not, nothing has been launched).
 hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks *mk, const dx_route_io *r,
@@ -1747,6 +1783,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     a.m_small = mixed ? 32 : 0x7fffffff;
     const bool few = !mixed && takes_few(a, n_cu);
     if (!mixed && (!few || r)) a.tile_rows = nullptr;
+    a.m_big = mixed ? big_tile_formats(a, n_cu) : 0;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);

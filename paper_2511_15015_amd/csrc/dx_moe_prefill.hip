@@ -95,23 +95,25 @@ __device__ __forceinline__ T uniform_load(const T *p)
 
 struct tile_id {
     int e, mt, nt; // expert (E = shared), row tile, column tile
-    int seg0, m;   // first pair slot and number of rows of the segment
+    int seg0, m;   // first pair slot and number of rows of the segment, or of the part of it that the tile size takes
     bool valid;
 };
 
 // This block's tile.  The row tiles of all experts are listed in a.tile_rows (expert by expert, the shared expert's at
-// the end; written by the gate/up kernel of the streamed experts that runs in front, because a prologue that
-// derives the list from the offsets in every block is 3 of a tile's 20 to 35 us).  The tiles of an expert go in
-// bands of BAND row tiles, inside a band column tile next, row tile innermost: with 8 of them and as many columns
-// next to each other the tiles that run together on an XCD ask for every line about eight times.  (Bands that run on
+// the end, the 256-row tiles behind all others; written by the gate/up kernel of the streamed experts that runs in front,
+// because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us).  The tiles of an
+// expert go in bands of BAND row tiles, inside a band column tile next, row tile innermost: with 8 of them and as many
+// columns next to each other the tiles that run together on an XCD ask for every line about eight times.  (Bands that run on
 // over the experts' borders: 16 experts of 4096 x 6400, 1100 tokens 701 us against 688 -- eight experts' tokens
 // do not stay in an XCD's L2 from one column to the next.)
-constexpr int BAND = 8;
+template <int ROWS, int BAND>
 __device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, int ntn_routed, int ntn_shared)
 {
+    constexpr bool BIG = ROWS == DX_BIG_ROWS;
     tile_id t;
     t.valid = false;
-    const int n_routed = uniform_load(&a.tile_rows[0].e), n_shared = uniform_load(&a.tile_rows[0].mt);
+    const int n_small = uniform_load(&a.tile_rows[0].e), n_small_shared = uniform_load(&a.tile_rows[0].mt);
+    const int n_routed = BIG ? uniform_load(&a.tile_rows[0].m) : n_small, n_shared = BIG ? uniform_load(&a.tile_rows[0].seg0) : n_small_shared;
     const uint32_t routed = (uint32_t)(n_routed * ntn_routed), total = routed + (uint32_t)(n_shared * ntn_shared);
     const uint32_t per_xcd = (total + 7) / 8;
     uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -120,9 +122,9 @@ __device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, int ntn_route
     if (shared) idx -= routed;
     const int ntn = shared ? ntn_shared : ntn_routed;
     const int q = (int)(idx / (uint32_t)ntn); // some row tile of the band that the tile is in
-    const dx_tile_row *row = a.tile_rows + 1 + (shared ? n_routed : 0) + q;
+    const dx_tile_row *row = a.tile_rows + 1 + (BIG ? n_small + n_small_shared : 0) + (shared ? n_routed : 0) + q;
     t.e = uniform_load(&row->e), t.m = uniform_load(&row->m), t.seg0 = uniform_load(&row->seg0);
-    const int mt = uniform_load(&row->mt), mt0 = mt / BAND * BAND, nmt = (t.m + DX_TILE_ROWS - 1) / DX_TILE_ROWS;
+    const int mt = uniform_load(&row->mt), mt0 = mt / BAND * BAND, nmt = (t.m + ROWS - 1) / ROWS;
     const int band = nmt - mt0 < BAND ? nmt - mt0 : BAND, in_band = (int)idx - (q - (mt - mt0)) * ntn;
     t.nt = in_band / band;
     t.mt = mt0 + in_band % band;
@@ -166,6 +168,32 @@ __device__ __forceinline__ void block_barrier()
 {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// A token row's 32 columns (gate/up, after SwiGLU) or 64 (down) of a wavefront, from the accumulators of two MFMA tiles
+// (columns 0..31 and 32..63, or gate and up) to memory at dst + 8 * (lane / 32).  The weights were the first MFMA operand:
+// accumulator element v of a 32 x 32 tile is output column (v/4)*8 + (lane/32)*4 + v%4 of token lane%32.  One swap of the
+// wavefront's halves per pair of words gives every lane eight consecutive columns, 16 bytes.  Both halves of the wavefront
+// must store the same rows.
+template <bool DOWN>
+__device__ __forceinline__ void store_row(const f32x16 &a0, const f32x16 &a1, dx_bf16 *dst)
+{
+#pragma unroll
+    for (int ns = 0; ns < (DOWN ? 2 : 1); ++ns)
+#pragma unroll
+        for (int qp = 0; qp < 2; ++qp) {
+            const f32x16 &acc = ns ? a1 : a0;
+            uint32_t w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { // words (q = 2qp: columns 0, 2), (q = 2qp + 1: columns 0, 2)
+                const int v = 4 * (2 * qp + (u >> 1)) + 2 * (u & 1);
+                if constexpr (DOWN) w[u] = pack_bf16(acc[v], acc[v + 1]);
+                else w[u] = pack_bf16(swiglu_fast(a0[v], a1[v]), swiglu_fast(a0[v + 1], a1[v + 1]));
+            }
+            const auto lo = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+            *reinterpret_cast<u32x4 *>(dst + ns * 32 + qp * 16) = u32x4{lo[0], hi[0], lo[1], hi[1]};
+        }
 }
 
 constexpr int kLine = BK * 2; // 128: bytes of a row per K-step, one line
@@ -232,7 +260,7 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
         if constexpr (DOWN) {
             a_at[i] = (uint64_t)a.h + (uint64_t)(t.seg0 + slot) * a.fmax * 2 + piece * 16;
         } else {
-            const int tok = shared ? slot : a.perm[t.seg0 + slot] / a.k;
+            const int tok = shared ? t.seg0 - a.T * a.k + slot : a.perm[t.seg0 + slot] / a.k;
             a_at[i] = (uint64_t)a.x + (uint64_t)tok * K * 2 + piece * 16;
         }
     }
@@ -446,21 +474,7 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
         } else {
             dst = a.h + (size_t)(t.seg0 + slot) * a.fmax + t.nt * (BN / 2) + wn * 32 + 8 * kq;
         }
-#pragma unroll
-        for (int ns = 0; ns < (DOWN ? 2 : 1); ++ns)
-#pragma unroll
-            for (int qp = 0; qp < 2; ++qp) {
-                uint32_t w[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) { // words (q = 2qp: columns 0, 2), (q = 2qp + 1: columns 0, 2)
-                    const int v = 4 * (2 * qp + (u >> 1)) + 2 * (u & 1);
-                    if constexpr (DOWN) w[u] = pack_bf16(acc[ms][ns][v], acc[ms][ns][v + 1]);
-                    else w[u] = pack_bf16(swiglu_fast(acc[ms][0][v], acc[ms][1][v]), swiglu_fast(acc[ms][0][v + 1], acc[ms][1][v + 1]));
-                }
-                const auto lo = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-                const auto hi = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-                if (slot < t.m) *reinterpret_cast<u32x4 *>(dst + ns * 32 + qp * 16) = u32x4{lo[0], hi[0], lo[1], hi[1]};
-            }
+        if (slot < t.m) store_row<DOWN>(acc[ms][0], acc[ms][1], dst);
     }
     // the redundant loads issued past the end still target this block's LDS: it must not end before they have landed
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -471,13 +485,231 @@ __global__ __launch_bounds__(cfg::THREADS, 2) void k_tiled(dx_fwd_args a)
 {
     // the ring and (down) the pair indices of the wavefronts' rows: 74 KB, two blocks to a compute unit
     __shared__ __attribute__((aligned(1024))) char ring[cfg::RING + (DOWN ? 256 * cfg::WAVES : 0)];
-    const tile_id t = find_tile(a, DOWN ? a.d / BN : a.f / (BN / 2), DOWN ? a.d / BN : a.shared_f / (BN / 2));
+    const tile_id t = find_tile<DX_TILE_ROWS, 8>(a, DOWN ? a.d / BN : a.f / (BN / 2), DOWN ? a.d / BN : a.shared_f / (BN / 2));
     if (!t.valid) return; // block-uniform
     const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
     const int fmt = (int)uniform_load(&h->fmt);
     if (fmt == DX_FMT_INT4G) tile_main<DOWN, 1>(a, t, h, ring);
     else if (fmt == DX_FMT_INT2G) tile_main<DOWN, 2>(a, t, h, ring);
     else tile_main<DOWN, 0>(a, t, h, ring);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Large segments: 256 x 256 output tiles, 8 wavefronts (2 along rows x 4 along columns, each a 128 x 64 sub-tile = 4 x 2
+// MFMA tiles), one block to a compute unit, K in steps of 64 through two stages, one barrier per step.
+// Why beside the 128-row tiles: their operand reads take as many LDS cycles as the matrix instructions (a 64 x 64 sub-tile
+// reads 16 KB per 524 kFLOP) and the fill comes on top; a 128 x 64 sub-tile reads 24 KB per 1.05 MFLOP, and a tile loads half
+// the bytes per FLOP.  With few or ragged row tiles the smaller tiles win all the same: no padding, two blocks whose waits
+// overlap: large segments only (big_tile_formats, with the passes measured on both sides of its lines).
+//   LDS rows and loads as in the other kernel.  Codes (Q4): four bytes per lane into a side ring (per slot and wavefront:
+//   4 x 8 rows x 32 bytes of nibbles, 32 rows x one pair of scales), one step before the wavefront that loaded them expands
+//   them into the weight half of the stage that has just been freed; it expands only what it loaded itself, so the side ring
+//   needs no barrier.
+constexpr int TM = 256, TN = 256, TK = 64;
+constexpr int kBigThreads = 512;
+constexpr int kRowBytes64 = TK * 2;                      // 128: one line of a row per step
+constexpr int kStageBytes = (TM + TN) * kRowBytes64;     // 64 KB: token rows then weight rows
+constexpr int kStages = 2;
+constexpr int kSideWave = 1280;                          // per wavefront: 4 x 256 bytes of nibbles, 256 of scale pairs
+constexpr int kSideStage = (kBigThreads / 64) * kSideWave; // 10 KB
+constexpr int kRingBytes = kStages * (kStageBytes + kSideStage);
+
+template <bool DOWN, bool Q4>
+__device__ __forceinline__ void big_tile(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
+{
+    const bool shared = t.e == a.E;
+    const int fe = shared ? a.shared_f : a.f;
+    const int K = DOWN ? fe : a.d;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+
+    // ---- loader role: wavefront w fills rows [32w, 32w + 32) of the token part and of the weight part ----
+    // A load instruction covers 8 rows x one 128-byte line; lane l writes LDS piece l % 8 of row l / 8 and
+    // fetches the memory piece that belongs there: piece p of row r sits in slot p ^ ((r >> 1) & 7).
+    // weight-tile row -> matrix row: down: TN consecutive rows; gate/up: 128 gate rows, then the same up rows
+    auto wrow = [&](int row) { return DOWN ? t.nt * TN + row : t.nt * (TN / 2) + (row & 127); };
+    uint32_t a_off[4], b_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * wave + 8 * i + (lane >> 3);
+        const uint32_t piece = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));
+        const int slot = t.mt * TM + row; // big tiles are full: slot < t.m
+        if constexpr (DOWN) {
+            a_off[i] = (uint32_t)(t.seg0 + slot) * (uint32_t)a.fmax * 2u + piece * 16u;
+        } else {
+            const int tok = shared ? t.seg0 - a.T * a.k + slot : a.perm[t.seg0 + slot] / a.k;
+            a_off[i] = (uint32_t)tok * (uint32_t)K * 2u + piece * 16u;
+        }
+        // bf16: the lane's 16-byte piece of the row; int4: its four bytes (8 nibbles) of the row's 32 per step
+        b_off[i] = Q4 ? (uint32_t)wrow(row) * (uint32_t)(K / 2) + (uint32_t)(lane & 7) * 4u
+                      : (uint32_t)wrow(row) * (uint32_t)K * 2u + piece * 16u;
+    }
+    const uint64_t a_base = (uint64_t)(DOWN ? (const void *)a.h : (const void *)a.x);
+    const uint64_t b_base = scalar_ptr(uniform_load(DOWN ? &h->w_down : (wave < 4 ? &h->w_gate : &h->w_up)));
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)ring;
+    const uint32_t m0_a = lds0 + wave * 32 * kRowBytes64, m0_b = lds0 + TM * kRowBytes64 + wave * 32 * kRowBytes64;
+    const int nk = K / TK;
+    // int4: scales of the lane's row (lane & 31 of the wavefront's 32 rows), read as the aligned pair that
+    // holds the step's groups (the number of groups per row is even there, so a pair never leaves its row;
+    // with groups of 32 a step spans exactly the two groups of its pair)
+    const int lg = __builtin_ctz((unsigned)a.group);
+    const uint32_t s_off = Q4 ? (uint32_t)wrow(32 * wave + (lane & 31)) * (uint32_t)(K >> lg) * 2u : 0u;
+    const uint64_t s_base = Q4 ? scalar_ptr(uniform_load(DOWN ? &h->s_down : (wave < 4 ? &h->s_gate : &h->s_up))) : 0;
+    const int side_wave = kStages * kStageBytes + wave * kSideWave; // + slot * kSideStage
+    auto clamped = [&](int kt) { return kt < nk ? kt : nk - 1; };
+    auto issue_tokens = [&](int kt, int stage) {
+        const uint64_t kb = (uint64_t)clamped(kt) * kRowBytes64;
+        const uint32_t so = (uint32_t)stage * kStageBytes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds(m0_a + so + 1024 * i, a_off[i], a_base + kb);
+    };
+    auto issue_weights = [&](int kt, int stage) { // bf16
+        const uint64_t kb = (uint64_t)clamped(kt) * kRowBytes64;
+        const uint32_t so = (uint32_t)stage * kStageBytes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds(m0_b + so + 1024 * i, b_off[i], b_base + kb);
+    };
+    auto issue_codes = [&](int kt, int slot) { // int4: nibbles and scale pairs of step kt -> side slot
+        const int kc = clamped(kt);
+        const uint32_t m0 = lds0 + (uint32_t)(side_wave + slot * kSideStage);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds4(m0 + 256 * i, b_off[i], b_base + (uint64_t)kc * (TK / 2));
+        load_to_lds4(m0 + 1024, s_off, s_base + (uint64_t)((((kc * TK) >> lg) * 2) & ~3));
+    };
+    // int4: the wavefront's 32 rows of step kt, from side slot `slot` into the weight half of `stage`
+    auto expand = [&](int kt, int slot, int stage) {
+        const int odd = ((clamped(kt) * TK + 8 * (lane & 7)) >> lg) & 1; // per lane when a group is 32 wide
+        const char *side = ring + side_wave + slot * kSideStage;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t codes = *reinterpret_cast<const uint32_t *>(side + 256 * i + 4 * lane);
+            const uint32_t pair = *reinterpret_cast<const uint32_t *>(side + 1024 + 4 * (8 * i + (lane >> 3)));
+            const float scale = __uint_as_float(odd ? pair & 0xFFFF0000u : pair << 16);
+            const int row = 32 * wave + 8 * i + (lane >> 3);
+            const int pos = (lane & 7) ^ ((row >> 1) & 7);
+            *reinterpret_cast<u32x4 *>(ring + stage * kStageBytes + TM * kRowBytes64 + row * kRowBytes64 + pos * 16) =
+                dequant8(codes, scale);
+        }
+    };
+
+    // ---- MFMA role ----
+    const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
+    const int a_lane = (wm * 128 + r) * kRowBytes64;
+    const int b_lane0 = TM * kRowBytes64 + (DOWN ? wn * 64 + r : wn * 32 + r) * kRowBytes64;
+    const int b_lane1 = TM * kRowBytes64 + (DOWN ? wn * 64 + 32 + r : 128 + wn * 32 + r) * kRowBytes64;
+
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int ms = 0; ms < 4; ++ms)
+#pragma unroll
+        for (int ns = 0; ns < 2; ++ns)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[ms][ns][v] = 0.f;
+
+    // Software pipeline.  Each K-step has four quarters (16 k-values each); the fragments of a quarter sit
+    // in registers before its MFMAs start.  The barrier comes once the last quarter's fragments have been
+    // read, in the shadow of the third quarter's MFMAs: past it every wavefront holds what it needs of
+    // stage S, so S is refilled at once with step kt + 2, and the landed stage of step kt + 1 may be read.
+    frag8 fa[2][4], fb[2][2];
+    auto read_frags = [&](int stage, int quarter, frag8 (&af)[4], frag8 (&bf)[2]) {
+        const char *st = ring + stage * kStageBytes;
+        const int so = ((2 * quarter + kq) ^ swz) * 16;
+#pragma unroll
+        for (int ms = 0; ms < 4; ++ms) af[ms].u = *reinterpret_cast<const u32x4 *>(st + a_lane + ms * 32 * kRowBytes64 + so);
+        bf[0].u = *reinterpret_cast<const u32x4 *>(st + b_lane0 + so);
+        bf[1].u = *reinterpret_cast<const u32x4 *>(st + b_lane1 + so);
+    };
+    auto mma_quarter = [&](const frag8 (&af)[4], const frag8 (&bf)[2]) {
+#pragma unroll
+        for (int ms = 0; ms < 4; ++ms)
+#pragma unroll
+            for (int ns = 0; ns < 2; ++ns)
+                acc[ms][ns] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ns].v, af[ms].v, acc[ms][ns], 0, 0, 0);
+    };
+    if constexpr (Q4) {
+        // The codes of step j are loaded with the tokens of step j - 1 and expanded when step j - 2 frees
+        // its stage.  Start: codes 0, 1 and tokens 0, 1; expand 0, 1 as soon as the codes are there; then
+        // the codes of step 2.
+        issue_codes(0, 0);
+        issue_codes(1, 1);
+        issue_tokens(0, 0);
+        issue_tokens(1, 1);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own codes 0, 1
+        expand(0, 0, 0);
+        expand(1, 1, 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // side slot 0 has been read: refill it
+        issue_codes(2, 0);
+        asm volatile("s_waitcnt vmcnt(9) lgkmcnt(0)" ::: "memory"); // own tokens of step 0; own expansions
+    } else {
+        issue_tokens(0, 0), issue_weights(0, 0);
+        issue_tokens(1, 1), issue_weights(1, 1);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own loads of step 0
+    }
+    block_barrier();
+    read_frags(0, 0, fa[0], fb[0]);
+    auto step = [&](int kt, auto stage_c) {
+        constexpr int S = decltype(stage_c)::value;
+        // (the scheduling fences keep the LDS reads ahead of the MFMAs they overlap with)
+        read_frags(S, 1, fa[1], fb[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_quarter(fa[0], fb[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(S, 2, fa[0], fb[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_quarter(fa[1], fb[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(S, 3, fa[1], fb[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_quarter(fa[0], fb[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        // own loads of step kt + 1 (int4: and the codes of step kt + 2) have landed; own LDS reads of stage S
+        // have returned and own LDS writes are done; after the barrier that holds for every wavefront
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        block_barrier();
+        issue_tokens(kt + 2, S);
+        if constexpr (Q4) {
+            issue_codes(kt + 3, S ^ 1);
+            expand(kt + 2, S, S);
+        } else {
+            issue_weights(kt + 2, S);
+        }
+        read_frags(S ^ 1, 0, fa[0], fb[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_quarter(fa[1], fb[1]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int kt = 0; kt < nk; kt += 2) { // nk is even (K a multiple of 128)
+        step(kt, std::integral_constant<int, 0>{});
+        step(kt + 1, std::integral_constant<int, 1>{});
+    }
+    // the redundant loads issued past the end still target this block's LDS: drain them
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+    // (the tile leaves straight from the registers, as in the other kernel)
+    int o_row[4]; // where its rows go
+#pragma unroll
+    for (int ms = 0; ms < 4; ++ms) {
+        const int slot = t.mt * TM + wm * 128 + ms * 32 + r;
+        o_row[ms] = DOWN && !shared ? a.perm[t.seg0 + slot] : t.seg0 + slot;
+    }
+#pragma unroll
+    for (int ms = 0; ms < 4; ++ms) {
+        dx_bf16 *dst = DOWN ? reinterpret_cast<dx_bf16 *>(a.o) + (size_t)o_row[ms] * a.d + t.nt * TN + wn * 64 + 8 * kq
+                            : a.h + (size_t)o_row[ms] * a.fmax + t.nt * (TN / 2) + wn * 32 + 8 * kq;
+        store_row<DOWN>(acc[ms][0], acc[ms][1], dst);
+    }
+}
+
+template <bool DOWN>
+__global__ __launch_bounds__(kBigThreads) void k_big(dx_fwd_args a)
+{
+    __shared__ __attribute__((aligned(1024))) char ring[kRingBytes]; // 128 KB of stages and 20 KB of side ring
+    const tile_id t = find_tile<DX_BIG_ROWS, 4>(a, DOWN ? a.d / TN : a.f / (TN / 2), DOWN ? a.d / TN : a.shared_f / (TN / 2));
+    if (!t.valid) return; // block-uniform
+    const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
+    if (uniform_load(&h->fmt) == DX_FMT_INT4G) big_tile<DOWN, true>(a, t, h, ring);
+    else big_tile<DOWN, false>(a, t, h, ring);
 }
 
 } // namespace
@@ -491,5 +723,21 @@ static void launch_tiles(const dx_fwd_args &a, hipStream_t s)
     hipLaunchKernelGGL((k_tiled<DOWN>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(cfg::THREADS), 0, s, a);
 }
 
-void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s) { launch_tiles<false>(a, s); }
-void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s) { launch_tiles<true>(a, s); }
+template <bool DOWN>
+static void launch_big_tiles(const dx_fwd_args &a, hipStream_t s)
+{
+    const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
+    const long rows = (long)a.T * a.k / DX_BIG_ROWS + (a.shared ? a.T / DX_BIG_ROWS : 0), tiles = rows * (DOWN ? a.d / TN : fe / (TN / 2));
+    if (a.m_big && tiles) hipLaunchKernelGGL((k_big<DOWN>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(kBigThreads), 0, s, a);
+}
+
+void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s)
+{
+    launch_big_tiles<false>(a, s);
+    launch_tiles<false>(a, s);
+}
+void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s)
+{
+    launch_big_tiles<true>(a, s);
+    launch_tiles<true>(a, s);
+}

@@ -595,6 +595,29 @@ def test_forward_prefill_int4_segments_of_256_rows_and_more(B, LY, dxo, T, E, k,
     ly.ctx.close()
 
 
+@pytest.mark.parametrize("T,E,k,d,f,group,shared_f,resident", [
+    (8330, 2, 2, 1024, 128, 64, 0, [0]),       # bf16 and int4: 32 tiles of 256 rows each and ten rows of a 128-row tile
+    (8192, 1, 1, 2048, 128, 64, 128, []),      # int4, whole tiles only; the shared expert's
+    (16400, 1, 1, 1024, 384, 128, 0, []),      # three groups per row of W_down: int4 stays with the 128-row tiles
+    (16500, 2, 1, 1024, 384, 64, 256, [1]),    # a shared expert of another size
+    (8200, 3, 2, 1024, 128, 32, 0, [1]),       # int4 in groups of 32
+    (8200, 14, 1, 2048, 128, 64, 0, [2, 3]),   # 586 rows on average: int4 only
+])
+def test_forward_prefill_256_row_tiles(B, LY, dxo, T, E, k, d, f, group, shared_f, resident):
+    """Segments of 1024 rows and more on average (int4: 512): their whole 256 rows go in 256-row tiles, the rest in 128-row
+    ones; every seventh token and the last ones against the oracle."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group, shared_f=shared_f)
+    x, logits = W.layer_inputs(wl, seed=71)
+    shared = W.shared_master(wl, 71, 0) if shared_f else None
+    ly = Layer(B, LY, dxo, wl, resident, seed=71, shared=shared)
+    y_gpu, y_ref = ly.run(x, logits, tokens=sorted(set(range(0, T, 7)) | set(range(T - 12, T))))
+    yg = bf16_bits_to_f32(y_gpu).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(y_gpu, y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    ly.ctx.close()
+
+
 @pytest.mark.parametrize("T,E,group,resident", [(150, 16, 128, [0, 5, 9]), (600, 16, 128, [0, 5, 9]),
                                                # 256-row tiles of the shared expert, of a bf16 and of int4 experts in one launch
                                                (1100, 4, 64, [1])])
