@@ -800,9 +800,10 @@ __device__ __forceinline__ void run_strips(const dx_fwd_args &a, const expert_ct
     // NST register stages: the strip of step t + NST - 1 is fetched while step t is multiplied.  A quantized
     // strip is a quarter of the bytes or less, so it gets a deeper pipeline (four stages; with six or eight
     // the runs of a decode batch, a dozen steps each, spend most of their steps outside the steady loop,
-    // which measured slower).
+    // which measured slower).  Not so two chunks of four groups each: their scales and sums leave no registers for four
+    // stages (18 to 36 of them spilled; 30B-shaped layer in groups of 32, 8 tokens 66 us with four, 60 with two).
     constexpr int NB = ONE_ROUND ? 1 : (LK == 32 && CPW == 2 ? 2 : 4);
-    constexpr int NST = FMT ? 4 : 2;
+    constexpr int NST = FMT && !(GPC == 4 && CPW == 2) ? 4 : 2;
     const int nhalf = (nbatch + NB - 1) / NB * NB * rounds * 2; // steps
     using stage_t = std::conditional_t<LINES, line_stage<CPW, FMT>, wstage<LK, CPW, FMT>>;
     stage_t st[NST];
