@@ -595,6 +595,63 @@ def test_forward_prefill_int4_segments_of_256_rows_and_more(B, LY, dxo, T, E, k,
     ly.ctx.close()
 
 
+@pytest.mark.parametrize("pair,T,E,k,d,f,group,shared_f", [
+    ("bf16-int4", 150, 2, 1, 128, 64, 64, 0),      # one K step of 64 in the down projection; one group per row of W_down
+    ("bf16-int4", 150, 2, 1, 128, 64, 32, 0),      # the same with the step's two groups in a word
+    ("int4-int2", 150, 2, 1, 128, 64, 64, 0),
+    ("bf16-int4", 300, 3, 2, 256, 192, 64, 0),     # three steps and three groups per row, half a column tile in gate/up
+    ("int4-int2", 300, 3, 2, 256, 192, 64, 0),
+    ("bf16-int4", 300, 3, 2, 256, 192, 32, 0),
+    ("bf16-int4", 270, 2, 2, 384, 320, 64, 0),     # five steps
+    ("int4-int2", 270, 2, 2, 256, 384, 128, 0),    # three groups of 128 per row: the scale's half by row parity
+    ("bf16-int4", 270, 2, 2, 256, 384, 128, 0),
+    ("bf16-int4", 200, 2, 1, 128, 128, 64, 192),   # the shared expert with another, odd number of steps
+    ("bf16-int4", 200, 2, 1, 128, 192, 64, 64),
+])
+def test_forward_prefill_tiles_k_steps_and_groups(B, LY, dxo, pair, T, E, k, d, f, group, shared_f):
+    """The 128-row tile kernel at one, an odd and an even number of K steps with every format, and at odd numbers of groups
+    per row: every token against the oracle."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group, shared_f=shared_f)
+    x, logits = W.layer_inputs(wl, seed=73)
+    shared = None
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, [0], 73, T)
+    else:
+        masters = W.shared_master(wl, 73, 0) if shared_f else None
+        ly = Layer(B, LY, dxo, wl, [0], seed=73, shared=masters)
+        ctx, keep, versions, shared = ly.ctx, ly, ly.versions, ly.shared
+    ids, w, counts, offsets, perm = dxo.route(logits, k)
+    assert (counts[1:] > 32).any(), "some quantized expert has to take the tiles"
+    rb = LY.RoutingBuffers(T, E, k)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    rb.route_forward(ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+    sync()
+    assert np.array_equal(rb.perm.cpu().numpy(), perm)
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f if shared else 0)
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(LY.device_to_bits(y), y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    del keep
+    ctx.close()
+
+
+def test_forward_prefill_tile_list_at_its_bound(B, LY, dxo):
+    """Segments of 129 rows in a context of exactly that many tokens: the list of row tiles has as many entries as the
+    context holds (two per expert), every one of them in use."""
+    import dataclasses
+    E, T = 5, 5 * 129
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=1, d=128, f=64, group=64)
+    x, logits = W.layer_inputs(wl, seed=79)
+    logits = logits.copy()
+    logits[np.arange(T), np.arange(T) % E] += 100.0
+    ly = Layer(B, LY, dxo, wl, [1, 3], seed=79)
+    y_gpu, y_ref = ly.run(x, logits)
+    yg = bf16_bits_to_f32(y_gpu).astype(np.float64)
+    assert (np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)).max() <= 2 * REL_L2_TOL
+    ly.ctx.close()
+
+
 @pytest.mark.parametrize("T,E,k,d,f,group,shared_f,resident", [
     (8330, 2, 2, 1024, 128, 64, 0, [0]),       # bf16 and int4: 32 tiles of 256 rows each and ten rows of a 128-row tile
     (8192, 1, 1, 2048, 128, 64, 128, []),      # int4, whole tiles only; the shared expert's
