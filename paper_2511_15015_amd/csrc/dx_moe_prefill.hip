@@ -6,9 +6,9 @@
 //
 // Regime: experts with more than a few dozen tokens.  Output tiles with v_mfma_f32_32x32x16_bf16, fp32
 // accumulators and K in steps of 64 (one 128-byte line of a token or weight row), filled by loads from memory
-// to LDS: k_tiled<WM> with 64 * WM rows (128 or 256) and 128 columns, any number of rows, all formats.  Quantized
-// weights are expanded on their way into the stage (code -> fp32 -> times the group's scale -> bf16), so the
-// matrix loop is the same for all formats.
+// to LDS: k_tiled with tiles of 128 rows x 128 columns, any number of rows, all formats; k_big with 256 x 256 for the whole
+// 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way into the stage (code -> fp32 ->
+// times the group's scale -> bf16), so the matrix loop is the same for all formats.
 //   gate/up: half of the tile's columns are gate rows and the other half the up rows of the same
 //            indices, and every wavefront owns matching gate/up columns, so SwiGLU happens on the
 //            accumulators; H is written once as bf16.
@@ -199,9 +199,8 @@ __device__ __forceinline__ void store_row(const f32x16 &a0, const f32x16 &a1, dx
 constexpr int kLine = BK * 2; // 128: bytes of a row per K-step, one line
 
 // ---------------------------------------------------------------------------------------------
-// Output tiles of 64 * WM rows x 128 columns, any number of rows, all formats: 2 * WM wavefronts, each a 64 x 64 sub-tile
-// = 2 x 2 MFMA tiles.  WM = 2: two blocks to a compute unit, which multiply in each other's waits.  WM = 4: one
-// block, 3/4 of the bytes per FLOP.
+// Output tiles of 128 rows x 128 columns, any number of rows, all formats: 4 wavefronts, each a 64 x 64 sub-tile = 2 x 2
+// MFMA tiles; two blocks to a compute unit, which multiply in each other's waits.
 // What bounds it: the fill.  Most of its lines hit in L2, but the tiles that share a line ask for it at the same
 // time, so a step waits as long as a miss takes (1.5 to 2 us in a full launch), and what a compute unit gets is
 // the bytes it has in flight over that time.  So the loads must never stop: a wavefront reads all operands of a step (K = 64)
@@ -219,9 +218,8 @@ constexpr int kLine = BK * 2; // 128: bytes of a row per K-step, one line
 // tiles: 470); of 1000 tokens: 115 us against 160.  256-row tiles with three stages and one block of 8 wavefronts
 // were slower (4096 tokens 572 us a pass against 506): the block's barriers have nothing beside them.  At this load the
 // clock is 1.9 GHz (2.4 idle), i.e. the matrix cores could do 2.0 PFLOP/s.
-constexpr int WM = 2; // wavefronts along the rows, two along the columns
 struct cfg {
-    static constexpr int ROWS = 64 * WM, WAVES = 2 * WM, THREADS = 64 * WAVES;
+    static constexpr int ROWS = DX_TILE_ROWS, WAVES = 4, THREADS = 64 * WAVES;
     static constexpr int STAGES = 2;
     static constexpr int STAGE = (ROWS + BN) * kLine;         // 32 KB: token rows then weight rows
     static constexpr int WROWS = BN / WAVES;                  // weight rows a wavefront loads
@@ -264,8 +262,8 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
             a_at[i] = (uint64_t)a.x + (uint64_t)tok * K * 2 + piece * 16;
         }
     }
-    // bf16: the lane's piece of the row; int4: 16 of the row's 32 bytes per step, two lanes to a row (WROWS = 16: 32
-    // lanes); int2: 4 of its 16 bytes, four lanes to a row
+    // bf16: the lane's piece of the row; int4: 16 of the row's 32 bytes per step, two lanes to a row; int2: 4 of its 16 bytes,
+    // four lanes to a row
     const int w0 = WROWS * wave;
 #pragma unroll
     for (int i = 0; i < (FMT == 0 ? WROWS / 8 : (FMT == 1 ? 1 : WROWS / 16)); ++i) {
@@ -273,7 +271,7 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
             const int row = w0 + 8 * i + (lane >> 3);
             b_off[i] = (uint32_t)wrow(row) * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
         } else if constexpr (FMT == 1) {
-            b_off[i] = (uint32_t)wrow(w0 + ((lane >> 1) & (WROWS - 1))) * row_bytes + (lane & 1) * 16;
+            b_off[i] = (uint32_t)wrow(w0 + (lane >> 1)) * row_bytes + (lane & 1) * 16;
         } else {
             b_off[i] = (uint32_t)wrow(w0 + 16 * i + (lane >> 2)) * row_bytes + (lane & 3) * 4;
         }
@@ -306,7 +304,7 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
         const int kc = clamped(kt);
         const uint32_t m0 = lds0 + (uint32_t)(side_wave + slot * cfg::SIDE);
         if constexpr (FMT == 1) {
-            if (lane < 2 * WROWS) load_to_lds(m0, b_off[0], b_base + (uint64_t)kc * (BK / 2));
+            load_to_lds(m0, b_off[0], b_base + (uint64_t)kc * (BK / 2));
         } else {
 #pragma unroll
             for (int i = 0; i < WROWS / 16; ++i) load_to_lds4(m0 + 256 * i, b_off[i], b_base + (uint64_t)kc * (BK / 4));
@@ -383,23 +381,16 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
         issue_codes(0, 0), issue_codes(1, 1);
 #pragma unroll
         for (int j = 0; j < STAGES; ++j) issue_tokens(j, j);
-        if constexpr (STAGES == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own codes 0, 1
-        else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own codes 0, 1
         expand(0, 0, 0);
         expand(1, 1, 1);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // side slots read
         issue_codes(2, 0);
-        if constexpr (STAGES == 3) {
-            issue_codes(3, 1);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            expand(2, 0, 2);
-        }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); // own tokens and codes; expansions written
     } else {
 #pragma unroll
         for (int j = 0; j < STAGES; ++j) issue_tokens(j, j), issue_weights(j, j);
-        if constexpr (STAGES == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own loads of step 0
-        else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // own loads of step 0
     }
     block_barrier();
 #pragma unroll
@@ -454,7 +445,7 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
         }
         stage = stage + 1 < STAGES ? stage + 1 : 0;
     };
-    static_assert(NA == 4 && WROWS == 32 && cfg::ROWS == DX_TILE_ROWS, "the waits; the row tiles of the list");
+    static_assert(NA == 4 && WROWS == 32 && STAGES == 2, "the waits");
     int kt = 0;
     for (; kt + 1 < nk; kt += 2) {
         step(kt, std::integral_constant<int, 0>{});

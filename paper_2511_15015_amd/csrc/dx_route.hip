@@ -302,7 +302,7 @@ __global__ void k_store_handle(dx_handle *slot, dx_handle h)
 // instruction; the same for lines of 8 rows whose lanes are not neighbours).  So a wavefront loads whole lines
 // (8 rows x 128 bytes per instruction, two lines of every row in flight), passes each line through a stage of
 // LDS of its own (piece p of row r in slot p ^ ((r >> 1) & 7): no bank conflicts) and reads the operands there.
-// Per call, d = 2048: 32 tokens x 512 experts 3.4 us, 4096 x 128 8.9 us (13.4 and 17.6 us with 32 x 32 tiles of 4
+// Per call, d = 2048: 32 tokens x 512 experts 4.2 us, 4096 x 128 9.5 us (13.4 and 17.0 us with 32 x 32 tiles of 4
 // wavefronts straight from global memory).
 typedef __attribute__((ext_vector_type(8))) __bf16 rt_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float rt_f32x4;
