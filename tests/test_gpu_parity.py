@@ -542,10 +542,10 @@ def test_route_can_update_hotness_itself(B, LY, dxo):
 # ------------------------------------------------------- prefill-sized batches
 @pytest.mark.parametrize("T,E,k,resident", [(65, 4, 2, [0, 2]), (128, 4, 2, [0, 2]), (200, 4, 2, [1]), (300, 8, 3, [0, 5, 6]),
                                             (129, 2, 2, [0]), (400, 4, 1, []),
-                                            # bf16 segments of 256 rows and more: 256 x 256 tiles plus a remainder
+                                            # segments of several row tiles
                                             (700, 4, 2, [0, 2]), (1100, 2, 2, [0, 1]), (512, 2, 2, [1]),
                                             (256, 1, 1, [0]),
-                                            # one bf16 expert with 200, 385 = 256 + 129, 384 = 256 + 128 rows; two with 641
+                                            # one bf16 expert with 200, 385 = 3 * 128 + 1, 384 = 3 * 128 rows; two with 641
                                             (200, 1, 1, [0]), (385, 1, 1, [0]), (384, 1, 1, [0]), (641, 2, 2, [0, 1])])
 def test_forward_prefill_tiles_small_shapes(B, LY, dxo, T, E, k, resident):
     """Up to 128 tokens per call the streaming kernels walk each segment in blocks of 32 tokens; above,
@@ -567,17 +567,16 @@ def test_forward_prefill_tiles_small_shapes(B, LY, dxo, T, E, k, resident):
 
 
 @pytest.mark.parametrize("T,E,k,d,f,group,resident", [
-    (600, 2, 2, 256, 128, 32, []),          # both experts int4 with 600 rows: two 256-row tiles and a remainder each
-    (1100, 2, 2, 256, 128, 64, []),         # four tiles each; the down contraction is four steps (one trip of the loop)
-    (520, 2, 1, 512, 256, 128, []),         # about 260 rows each: one tile and a few rows
+    (600, 2, 2, 256, 128, 32, []),          # both experts int4 with 600 rows: four row tiles and a remainder each
+    (1100, 2, 2, 256, 128, 64, []),         # nine tiles each, more than a band; the down contraction is two steps
+    (520, 2, 1, 512, 256, 128, []),         # about 260 rows each: two tiles and a few rows
     (700, 4, 2, 512, 256, 128, [0]),        # bf16 and int4 tiles in one launch
-    (768, 1, 1, 256, 384, 128, []),         # three groups per row of W_down: the int4 experts stay with the 128-row tiles
-    (300, 1, 1, 2048, 768, 128, []),        # the 30B layer's K extents: 64 and 24 steps
+    (768, 1, 1, 256, 384, 128, []),         # three groups per row of W_down
+    (300, 1, 1, 2048, 768, 128, []),        # the 30B layer's K extents: 32 and 12 steps
 ])
 def test_forward_prefill_int4_segments_of_256_rows_and_more(B, LY, dxo, T, E, k, d, f, group, resident):
-    """int4 experts with 256 rows and more: the leading multiple of 256 rows takes the 256 x 256 tile kernel, which
-    expands the codes into its LDS ring (when the number of groups per row is even); every token, and the same
-    bits on a second run."""
+    """int4 experts of several row tiles, whose codes the tile kernel expands into its LDS stages; every token, and the same
+    bits on a second run.  (The 256-row tiles of larger batches: test_forward_prefill_256_row_tiles.)"""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group)
     print(f"prefill int4 tiles T={T} E={E} k={k} d={d} f={f} g={group} resident={resident}", flush=True)
@@ -676,7 +675,7 @@ def test_forward_prefill_256_row_tiles(B, LY, dxo, T, E, k, d, f, group, shared_
 
 
 @pytest.mark.parametrize("T,E,group,resident", [(150, 16, 128, [0, 5, 9]), (600, 16, 128, [0, 5, 9]),
-                                               # 256-row tiles of the shared expert, of a bf16 and of int4 experts in one launch
+                                               # row tiles of the shared expert, of a bf16 and of int4 experts in one launch
                                                (1100, 4, 64, [1])])
 def test_forward_prefill_with_shared_expert(B, LY, dxo, T, E, group, resident):
     import dataclasses
@@ -694,7 +693,7 @@ def test_forward_prefill_with_shared_expert(B, LY, dxo, T, E, group, resident):
 @pytest.mark.parametrize("T,n_hi", [(4096, None), (8192, None), (4096, 0)])
 def test_forward_c3_prefill_sampled_tokens(B, LY, dxo, T, n_hi):
     """The 30B-shaped prefill layer at full size (T=4096) and at twice that (the largest batch the
-    benchmarks use), and with no resident expert (every expert int4, the large segments in 256-row tiles):
+    benchmarks use), and with no resident expert (every expert int4):
     routing bit-exact on all tokens, layer output checked on sampled tokens the oracle computes one by one."""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["C3"], T=T)
@@ -748,7 +747,7 @@ def test_forward_c3_prefill_sampled_tokens(B, LY, dxo, T, n_hi):
 @pytest.mark.parametrize("T,one_call", [(32, False), (300, False), (32, True)])
 def test_route_and_forward_replay_from_a_captured_graph(B, LY, dxo, T, one_call):
     """dx_route + dx_moe_forward (or the two as one dx_route_forward call) recorded into a HIP graph (the
-    decode pass, and the prefill pass with its fork/join over the side streams), replayed several times
+    decode pass, and the prefill pass with its tile kernels), replayed several times
     with eager work and synchronisations in between: every replay reproduces the eager result bit for bit."""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=4 if T > 64 else 8)
@@ -831,7 +830,7 @@ def _quant_pair_layer(B, LY, dxo, wl, hi_ids, seed, T):
     (33, 16, 4, 2048, 768, 128, [2, 3, 5]),    # the 30B layer's K extents
     (300, 4, 2, 256, 128, 64, [0, 2]),         # prefill-sized: 128-row tiles expand int2 on the way to LDS
     (700, 4, 2, 256, 128, 128, [1]),
-    (700, 4, 2, 512, 256, 128, [1, 2]),        # int4 segments of 256 rows and more: 256-row tiles
+    (700, 4, 2, 512, 256, 128, [1, 2]),        # int4 segments of several row tiles
 ])
 def test_forward_int4_int2_pair(B, LY, dxo, T, E, k, d, f, group, hi_ids):
     import dataclasses
@@ -1188,7 +1187,7 @@ def test_route_forward_random_shapes_match_separate_calls(B, LY, dxo):
 
 
 def test_forward_random_shapes_match_oracle(B, LY, dxo):
-    """Seeded random layers in both regimes (1 to 400 tokens; streaming kernels, 128-row and 256-row tiles,
+    """Seeded random layers in both regimes (1 to 400 tokens; streaming kernels, row tiles,
     shapes that fit the tiles and shapes that do not): every layer output within the bar of the oracle's,
     token by token within twice the bar."""
     import dataclasses

@@ -269,8 +269,8 @@ def test_c5_churn_with_ema_and_hysteresis(B, LY, dxo):
 @pytest.mark.parametrize("T", [32, 1536])
 def test_phi35_shaped_layer(B, LY, dxo, T):
     """16 experts of 4096 x 6400, top-2, 4 of them bf16: the decode batch runs the streaming kernels on
-    K = 4096 and 6400 (more K-chunks than wavefronts), the prefill batch the 256-row and 128-row tile
-    kernels with 50 column tiles; sampled tokens against the oracle, routing bit-exact."""
+    K = 4096 and 6400 (more K-chunks than wavefronts), the prefill batch the tile
+    kernel with 100 column tiles; sampled tokens against the oracle, routing bit-exact."""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["X1"], T=T)
     print(f"X1 T={T}: drawing masters", flush=True)
