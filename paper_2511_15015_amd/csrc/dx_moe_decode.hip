@@ -71,8 +71,6 @@ union frag8 {
     bf16x8 v;
 };
 
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
-
 __device__ __forceinline__ uint32_t float_to_bf16_rne(float f)
 {
     uint32_t u = __float_as_uint(f);

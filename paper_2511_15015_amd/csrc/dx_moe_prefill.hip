@@ -26,26 +26,12 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-#define DX_GLOBAL __attribute__((address_space(1)))
-typedef const DX_GLOBAL char *gbytes;
-typedef const DX_GLOBAL dx_bf16 *gbf16;
-typedef const DX_GLOBAL u32x4 *gvec16;
-
 union frag8 {
     u32x4 u;
     bf16x8 v;
 };
 
 constexpr int BN = 128, BK = 64;
-
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
-
-__device__ __forceinline__ uint32_t float_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
 
 // silu(g) * u with the hardware exp2 and reciprocal (their error is far below the bf16 rounding of H)
 __device__ __forceinline__ float swiglu_fast(float g, float u)
@@ -57,7 +43,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 // two fp32 -> two bf16 in one word (the hardware's packed conversion: round to nearest even, the same
-// bits as float_to_bf16_rne for finite values)
+// bits as the decode kernels' integer rounding for finite values)
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
     const f32x2 v{lo, hi};
