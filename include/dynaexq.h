@@ -184,7 +184,8 @@ dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router
  *   y[t] = sum_j topk_w[t,j] * W_down( silu(W_gate x[t]) * (W_up x[t]) )  of expert topk_ids[t,j]
  *          (+ the layer's shared expert, weight 1, when shared_f > 0)
  * handle_table: dev, E entries of this layer; NULL = the context's own table
- * for `layer`.  x_bf16 dev [T,d]; y_bf16 dev [T,d]; routing arrays as written
+ * for `layer`.  x_bf16 dev [T,d] (above 128 tokens faster when it starts at a
+ * multiple of 16 bytes); y_bf16 dev [T,d]; routing arrays as written
  * by dx_route for the same T.  offsets and perm alone say which expert a pair
  * goes to, in any order inside a segment; topk_ids is part of the call's
  * arrays, must not be NULL and is not read.  Weights are read through the
