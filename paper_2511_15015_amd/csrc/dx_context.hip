@@ -282,10 +282,10 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
     if ((e = hipMalloc(&c->d_mask_sums, n_sums * 4)) != hipSuccess) return fail(e, "route sums");
     if ((e = hipMalloc(&c->d_h, n_rows * c->fmax * sizeof(dx_bf16))) != hipSuccess) return fail(e, "H scratch");
     if ((e = hipMalloc(&c->d_o, n_rows * (size_t)g.d * sizeof(float))) != hipSuccess) return fail(e, "O scratch");
-    // (for the smallest m_small a call can have; 1 + top_k elements or more, so the at most 2 * top_k places of a few
-    // tokens fit as well)
-    const size_t n_tile_rows = 1 + (size_t)dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0);
-    if ((e = hipMalloc(&c->d_tile_rows, n_tile_rows * sizeof(dx_tile_row))) != hipSuccess) return fail(e, "tile list");
+    // (for the smallest m_small a call can have)
+    const size_t n_tile_rows = (size_t)dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0);
+    const size_t list_bytes = sizeof(dx_tile_head) + n_tile_rows * sizeof(dx_tile_row), places = (size_t)DX_FEW_TOKENS * g.top_k * sizeof(int32_t);
+    if ((e = hipMalloc(&c->d_tiles, list_bytes > places ? list_bytes : places)) != hipSuccess) return fail(e, "tile list");
     // zero the table and the counters with fill kernels on the compute stream
     if ((e = dxk_fill_u64(reinterpret_cast<unsigned long long *>(c->d_table), n_entries * sizeof(dx_handle) / 8, 0ull,
                           c->compute)) != hipSuccess)
@@ -334,7 +334,7 @@ extern "C" void dx_destroy(dx_ctx *c)
     if (c->d_mask_sums) (void)hipFree(c->d_mask_sums);
     if (c->d_h) (void)hipFree(c->d_h);
     if (c->d_o) (void)hipFree(c->d_o);
-    if (c->d_tile_rows) (void)hipFree(c->d_tile_rows);
+    if (c->d_tiles) (void)hipFree(c->d_tiles);
     delete c;
 }
 
@@ -387,7 +387,7 @@ dx_status forward_args(dx_ctx *c, const char *who, int layer, const dx_handle *t
     a.perm = perm;
     a.h = c->d_h;
     a.o = c->d_o;
-    a.tile_rows = c->d_tile_rows;
+    a.tiles = c->d_tiles;
     a.T = T;
     a.E = g.E;
     a.k = g.top_k;

@@ -82,7 +82,7 @@ struct dx_ctx {
     // forward scratch
     dx_bf16 *d_h = nullptr; // [max_tokens*(k+1), fmax]
     float *d_o = nullptr;   // [max_tokens*(k+1), d]
-    struct dx_tile_row *d_tile_rows = nullptr; // row tiles of the tiled experts of one call (or the experts of its few places)
+    struct dx_tile_head *d_tiles = nullptr; // row tiles of the tiled experts of one call (or the experts of its few places)
     int fmax = 0;
 
     // pools / budget tracker / transitions
@@ -141,12 +141,18 @@ hipError_t dxk_quantize(const dx_bf16 *w, int rows, int K, int group, uint8_t *q
 hipError_t dxk_quantize2(const dx_bf16 *w, int rows, int K, int group, uint8_t *q, dx_bf16 *sc, hipStream_t s); // 2-bit
 
 // dx_moe_decode.hip / dx_moe_prefill.hip
-// One row tile of an expert above m_small tokens.  In element 0 of the list e is the number of routed 128-row tiles that
-// follow, mt the number of the shared expert's after them, m and seg0 the same for the 256-row tiles behind those.
+// The list of row tiles of the experts above m_small tokens: a head, then the rows of the head's counts in their order.
 constexpr int DX_TILE_ROWS = 128, DX_BIG_ROWS = 256;
 struct dx_tile_row {
     int e, mt;   // expert (E = shared), row tile of the rows below
     int m, seg0; // rows and first pair slot of the segment, or of the part of it that this tile size takes
+};
+struct dx_tile_head {
+    int n_routed, n_shared;  // 128-row tiles of the routed experts, of the shared one
+    int n_quant;             // of the former, those of quantized experts
+    int n_big, n_big_shared; // 256-row tiles
+    int n_cu;
+    int unused[2];
 };
 // most row tiles a call of T tokens can have (a routed expert has ceil(m / 128) of them, and none up to m_small tokens)
 inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)
@@ -173,9 +179,9 @@ struct dx_fwd_args {
     int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     // A list that the gate/up kernel of the streamed experts leaves for the kernels behind it, or null: mixed batches (m_small
-    // is a bound): the row tiles of the tiled experts (element 0: their number); up to DX_FEW_TOKENS tokens on a caller's
+    // is a bound): the row tiles of the tiled experts; up to DX_FEW_TOKENS tokens on a caller's
     // routing arrays: the expert of every place in the segments, as int32_t.
-    dx_tile_row *tile_rows;
+    dx_tile_head *tiles;
 };
 // Decode batches that the gate/up kernel routes itself (dx_route_forward): what its first block reads and
 // writes on top of dx_fwd_args (whose ids, w, offsets and perm point at the same arrays for the kernels

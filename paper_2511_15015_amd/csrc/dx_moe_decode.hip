@@ -988,7 +988,7 @@ struct partition_lds {
     uint32_t cum[kMaxExperts + 1];
     int seg_start[kMaxExperts], seg_tokens[kMaxExperts];
     uint32_t wave_tot[kWaves];
-    int wave_cnt[kWaves];
+    int wave_cnt[kWaves], quant_cnt[kWaves];
     int e_first;
 };
 
@@ -1056,7 +1056,7 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
     __syncthreads();
 }
 
-// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot and pl.wave_cnt are free).  Experts above
+// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot, wave_cnt and quant_cnt are free).  Experts above
 // m_small tokens.
 __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
 {
@@ -1070,32 +1070,36 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
         return (a.m_big >> fmt) & 1 ? m / DX_BIG_ROWS * DX_BIG_ROWS : 0;
     };
     auto tiles = [](int rows) { return (rows + DX_TILE_ROWS - 1) / DX_TILE_ROWS; };
-    int local = 0, local_big = 0;
+    int local = 0, local_big = 0, local_quant = 0; // row tiles; 256-row tiles; of the former, those of quantized experts
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
         if (e < a.E) {
-            const int m = tokens_of(e), lead = big_rows(m, a.table[e].fmt);
-            local += tiles(m - lead);
+            const uint32_t fmt = a.table[e].fmt;
+            const int m = tokens_of(e), lead = big_rows(m, fmt), t = tiles(m - lead);
+            local += t;
             local_big += lead / DX_BIG_ROWS;
+            local_quant += fmt == DX_FMT_BF16 ? 0 : t;
         }
     }
     const int inc = dx_route_core::wave_scan_inclusive(local), inc_big = dx_route_core::wave_scan_inclusive(local_big);
+    const int inc_quant = dx_route_core::wave_scan_inclusive(local_quant);
     if (lane == 63) {
         pl.wave_tot[wave] = (uint32_t)inc;
         pl.wave_cnt[wave] = inc_big;
+        pl.quant_cnt[wave] = inc_quant;
     }
     __syncthreads();
-    int base = 0, total = 0, base_big = 0, total_big = 0;
+    int base = 0, total = 0, base_big = 0, total_big = 0, total_quant = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         const int t = (int)pl.wave_tot[w], tb = pl.wave_cnt[w];
         if (w < wave) base += t, base_big += tb;
-        total += t, total_big += tb;
+        total += t, total_big += tb, total_quant += pl.quant_cnt[w];
     }
     const int T_tiled = a.shared && a.T > a.m_small ? a.T : 0, lead_shared = big_rows(T_tiled, DX_FMT_BF16);
     const int n_shared = tiles(T_tiled - lead_shared), n_big_shared = lead_shared / DX_BIG_ROWS;
-    dx_tile_row *out = a.tile_rows + 1 + base + inc - local;
-    dx_tile_row *big = a.tile_rows + 1 + total + n_shared, *out_big = big + base_big + inc_big - local_big;
+    dx_tile_row *rows = reinterpret_cast<dx_tile_row *>(a.tiles + 1), *out = rows + base + inc - local;
+    dx_tile_row *big = rows + total + n_shared, *out_big = big + base_big + inc_big - local_big;
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
         if (e >= a.E) continue;
@@ -1104,15 +1108,15 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
         for (int mt = 0; mt * DX_TILE_ROWS < m - lead; ++mt) *out++ = dx_tile_row{e, mt, m - lead, seg0 + lead};
     }
     const int seg0 = a.T * a.k;
-    for (int mt = tid; mt < n_shared; mt += kThreads) a.tile_rows[1 + total + mt] = dx_tile_row{a.E, mt, T_tiled - lead_shared, seg0 + lead_shared};
+    for (int mt = tid; mt < n_shared; mt += kThreads) rows[total + mt] = dx_tile_row{a.E, mt, T_tiled - lead_shared, seg0 + lead_shared};
     for (int mt = tid; mt < n_big_shared; mt += kThreads) big[total_big + mt] = dx_tile_row{a.E, mt, lead_shared, seg0};
-    if (tid == 0) a.tile_rows[0] = dx_tile_row{total, n_shared, total_big, n_big_shared};
+    if (tid == 0) *a.tiles = dx_tile_head{total, n_shared, total_quant, total_big, n_big_shared, (int)gridDim.x, {}};
 }
 
 // The expert of every place in the segments, for the down kernel of a call of a few tokens (one block).
 __device__ __forceinline__ void write_place_experts(const dx_fwd_args &a)
 {
-    int32_t *out = reinterpret_cast<int32_t *>(a.tile_rows);
+    int32_t *out = reinterpret_cast<int32_t *>(a.tiles);
     for (int e = threadIdx.x; e < a.E; e += kThreads)
         for (int at = a.offsets[e]; at < a.offsets[e + 1] && at < a.T * a.k; ++at) out[at] = e;
 }
@@ -1196,7 +1200,7 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
     const unsigned long long trace_t1 = wall_clock64();
 #endif
     if constexpr (!DOWN) {
-        if (a.tile_rows && blockIdx.x + 1 == gridDim.x) {
+        if (a.tiles && blockIdx.x + 1 == gridDim.x) {
             if (a.m_small == 0x7fffffff) write_place_experts(a);
             else write_tile_rows(a, pl);
         }
@@ -1477,7 +1481,7 @@ __global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
     const int split = tasks < kWaves ? kWaves / tasks : 1; // wavefronts per expert
     // lane i: routed: the expert of pair i; else the expert and the pair of place i
     const int at_i = lane < P ? lane : 0;
-    int expert_i = ROUTED ? a.ids[at_i] : reinterpret_cast<const int32_t *>(a.tile_rows)[at_i], pair_i = -1;
+    int expert_i = ROUTED ? a.ids[at_i] : reinterpret_cast<const int32_t *>(a.tiles)[at_i], pair_i = -1;
     if constexpr (ROUTED) {
         expert_i = lane < P ? expert_i : 0x7fffffff;
     } else { // (places outside the segments are dropped after the loads)
@@ -1769,7 +1773,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
     const bool few = !mixed && takes_few(a, n_cu);
-    if (!mixed && (!few || r)) a.tile_rows = nullptr;
+    if (!mixed && (!few || r)) a.tiles = nullptr;
     a.m_big = mixed ? big_tile_formats(a, n_cu) : 0;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {

@@ -6,9 +6,9 @@
 //
 // Regime: experts with more than a few dozen tokens.  Output tiles with v_mfma_f32_32x32x16_bf16, fp32
 // accumulators and K in steps of 64 (one 128-byte line of a token or weight row), filled by loads from memory
-// to LDS: k_tiled with tiles of 128 rows x 128 columns, any number of rows, all formats; k_big with 256 x 256 for the whole
-// 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way into the stage (code -> fp32 ->
-// times the group's scale -> bf16), so the matrix loop is the same for all formats.
+// to LDS: k_tiled with tiles of 128 rows x 128 or 256 columns, any number of rows, all formats; k_big with 256 x 256 for the
+// whole 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way to the matrix instructions (code ->
+// fp32 -> times the group's scale -> bf16).
 //   gate/up: half of the tile's columns are gate rows and the other half the up rows of the same
 //            indices, and every wavefront owns matching gate/up columns, so SwiGLU happens on the
 //            accumulators; H is written once as bf16.
@@ -31,7 +31,7 @@ union frag8 {
     bf16x8 v;
 };
 
-constexpr int BN = 128, BK = 64;
+constexpr int BN = 128, BNW = 256, BK = 64; // columns of a narrow and of a wide tile, k-values of a step
 
 // silu(g) * u with the hardware exp2 and reciprocal (their error is far below the bf16 rounding of H)
 __device__ __forceinline__ float swiglu_fast(float g, float u)
@@ -85,36 +85,57 @@ struct tile_id {
     bool valid;
 };
 
-// This block's tile.  The row tiles of all experts are listed in a.tile_rows (expert by expert, the shared expert's at
-// the end, the 256-row tiles behind all others; written by the gate/up kernel of the streamed experts that runs in front,
-// because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us).  The tiles of an
-// expert go in bands of BAND row tiles, inside a band column tile next, row tile innermost: with 8 of them and as many
-// columns next to each other the tiles that run together on an XCD ask for every line about eight times.  (Bands that run on
-// over the experts' borders: 16 experts of 4096 x 6400, 1100 tokens 701 us against 688 -- eight experts' tokens
-// do not stay in an XCD's L2 from one column to the next.)
-template <int ROWS, int BAND>
-__device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, int ntn_routed, int ntn_shared)
+// column tiles of a projection with fe rows in W_gate (down: d); the last one may be half a tile
+template <bool DOWN>
+__host__ __device__ __forceinline__ int columns_of(const dx_fwd_args &a, int fe, int width)
 {
-    constexpr bool BIG = ROWS == DX_BIG_ROWS;
+    return DOWN ? (a.d + width - 1) / width : (2 * fe + width - 1) / width;
+}
+
+// Tile number `idx` of the row tiles that are listed from `row` on, `ntn` column tiles each.  The tiles of an expert go in bands of
+// BAND row tiles, inside a band column tile next, row tile innermost: with 8 of them and as many columns next to each other
+// the tiles that run together on an XCD ask for every line about eight times.  (Bands that run on over the experts' borders:
+// 16 experts of 4096 x 6400, 1100 tokens 701 us against 688 -- eight experts' tokens do not stay in an XCD's L2 from
+// one column to the next.)
+template <int ROWS, int BAND>
+__device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx, int ntn)
+{
     tile_id t;
-    t.valid = false;
-    const int n_small = uniform_load(&a.tile_rows[0].e), n_small_shared = uniform_load(&a.tile_rows[0].mt);
-    const int n_routed = BIG ? uniform_load(&a.tile_rows[0].m) : n_small, n_shared = BIG ? uniform_load(&a.tile_rows[0].seg0) : n_small_shared;
-    const uint32_t routed = (uint32_t)(n_routed * ntn_routed), total = routed + (uint32_t)(n_shared * ntn_shared);
-    const uint32_t per_xcd = (total + 7) / 8;
-    uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if ((blockIdx.x >> 3) >= per_xcd || idx >= total) return t;
-    const bool shared = idx >= routed;
-    if (shared) idx -= routed;
-    const int ntn = shared ? ntn_shared : ntn_routed;
     const int q = (int)(idx / (uint32_t)ntn); // some row tile of the band that the tile is in
-    const dx_tile_row *row = a.tile_rows + 1 + (BIG ? n_small + n_small_shared : 0) + (shared ? n_routed : 0) + q;
+    const dx_tile_row *row = rows + q;
     t.e = uniform_load(&row->e), t.m = uniform_load(&row->m), t.seg0 = uniform_load(&row->seg0);
     const int mt = uniform_load(&row->mt), mt0 = mt / BAND * BAND, nmt = (t.m + ROWS - 1) / ROWS;
     const int band = nmt - mt0 < BAND ? nmt - mt0 : BAND, in_band = (int)idx - (q - (mt - mt0)) * ntn;
     t.nt = in_band / band;
     t.mt = mt0 + in_band % band;
     t.valid = true;
+    return t;
+}
+
+// This block's tile.  The row tiles of all experts are in a.tiles (written by the gate/up kernel of the streamed experts that
+// runs in front, because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us): the routed
+// experts', the shared one's, the 256-row tiles behind them.  Each XCD takes an eighth of the list.
+// Wide or narrow: a compute unit holds two tiles of either kind, and a wide one takes nearly as long as two rounds of narrow ones
+// (loads of more than one step do not fit beside it), so few tiles are better narrow.  Many are better wide, and quantized ones
+// much earlier, because what they gain is the expansion.  Gate/up kernels, us, narrow and wide, by narrow tiles per compute
+// unit: 30B-shaped layer bf16/int4 (nearly all row tiles bf16) 2.1 61 and 67, 4.2 90 and 112, 6.6 136 and 131, 9.8 201 and 185, 12.7 260
+// and 235; int4/int2 6.6 170 and 146; 80B-shaped (a quarter quantized) 3.0 85 and 74; 16 experts of 4096 x 6400 (half
+// quantized) 5.5 237 and 223, 10 407 and 321.
+template <bool DOWN>
+__device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, bool &wide)
+{
+    const int n = uniform_load(&a.tiles->n_routed), n_shared = uniform_load(&a.tiles->n_shared), n_cu = uniform_load(&a.tiles->n_cu);
+    const int narrow_tiles = n * columns_of<DOWN>(a, a.f, BN) + n_shared * columns_of<DOWN>(a, a.shared_f, BN);
+    const bool quant_rich = 5 * uniform_load(&a.tiles->n_quant) >= n + n_shared;
+    wide = 2 * narrow_tiles > (quant_rich ? 5 : 11) * n_cu;
+    const int width = wide ? BNW : BN, ntn = columns_of<DOWN>(a, a.f, width), ntn_shared = columns_of<DOWN>(a, a.shared_f, width);
+    const uint32_t routed = (uint32_t)(n * ntn), total = routed + (uint32_t)(n_shared * ntn_shared), per_xcd = (total + 7) / 8;
+    const uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const dx_tile_row *rows = reinterpret_cast<const dx_tile_row *>(a.tiles + 1);
+    if ((blockIdx.x >> 3) < per_xcd && idx < total)
+        return idx < routed ? tile_of<DX_TILE_ROWS, 8>(rows, idx, ntn) : tile_of<DX_TILE_ROWS, 8>(rows + n, idx - routed, ntn_shared);
+    tile_id t;
+    t.valid = false;
     return t;
 }
 
@@ -142,11 +163,16 @@ __device__ __forceinline__ void load_to_lds(uint32_t m0, uint64_t addr)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(addr) : "memory");
 }
-// with 4 bytes per lane: memory (sbase + voff) -> LDS (m0 + 4 * lane)
+// with 4 bytes per lane: memory -> LDS (m0 + 4 * lane)
 __device__ __forceinline__ void load_to_lds4(uint32_t m0, uint32_t voff, uint64_t sbase)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(m0), "v"(voff), "s"(sbase)
                  : "memory");
+}
+
+__device__ __forceinline__ void load_to_lds4(uint32_t m0, uint64_t addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(m0), "v"(addr) : "memory");
 }
 
 // the bare barrier, over which the compiler moves no LDS access
@@ -212,10 +238,14 @@ struct cfg {
     static constexpr int SIDE_WAVE = WROWS * (32 + 4);        // up to 32 bytes of codes and one word of scales per row
     static constexpr int SIDE = WAVES * SIDE_WAVE;
     static constexpr int RING = STAGES * STAGE + 2 * SIDE;
+    // wide tiles: two slots of token rows; for every wavefront its 64 weight rows of a step, or (quantized) two slots of the codes of
+    // two steps of them (int2: half of it) and of two words of scales per row
+    static constexpr int A_SLOT = ROWS * kLine, B_WAVE = 64 * kLine, SIDE_WIDE = 64 * 64 + 2 * 256;
+    static_assert(2 * A_SLOT + WAVES * B_WAVE <= RING && 2 * A_SLOT + WAVES * 2 * SIDE_WIDE <= RING, "the ring");
 };
 
 template <bool DOWN, int FMT>
-__device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
+__device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
     constexpr bool quant = FMT != 0;
     constexpr int ROWS = cfg::ROWS, STAGES = cfg::STAGES, STAGE = cfg::STAGE, WROWS = cfg::WROWS;
@@ -457,18 +487,254 @@ __device__ __forceinline__ void tile_main(const dx_fwd_args &a, const tile_id &t
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// ---------------------------------------------------------------------------------------------
+// Output tiles of 128 rows x 256 columns: 4 wavefronts side by side, each all rows x 64 columns of its own (4 x 2 MFMA tiles); two
+// blocks to a compute unit.
+// Why beside the narrow ones: no weight is shared between wavefronts.  So a wavefront turns its codes into operands in registers,
+// in the shadow of the other block's matrix instructions, where the narrow kernel writes them to LDS for two wavefronts between two
+// barriers; a row group of 32 without rows costs nothing; and a tile reads 24 KB from LDS per wavefront and 1.05 MFLOP (a 64 x 64
+// sub-tile 16 KB per 0.52) and loads three quarters of the bytes per FLOP.  64 int4 experts of 2048 x 1536, 100 rows each: gate/up 148 ->
+// 122 us, down 79 -> 64.  What bounds it: the latency of the weights.  A wavefront's 8 KB of a step (bf16) are read to registers at the
+// step's start and loaded again at once, so they have one step to arrive: 1.9 us a step for one block or two.
+//   LDS: two slots of token rows (laid out as in the other kernel); weights: of the wavefront alone, no barrier.  Codes come for two steps
+//   at a time, 64 (int2: 32) bytes of a row, into two slots; lane half kq takes one half of a step's elements of a row, and a
+//   quarter of the step is eight of them in each half, of the tokens too.
+template <bool DOWN, int FMT>
+__device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
+{
+    constexpr bool quant = FMT != 0;
+    constexpr int ROWS = cfg::ROWS, B0 = 2 * cfg::A_SLOT;
+    const bool shared = t.e == a.E;
+    const int fe = shared ? a.shared_f : a.f;
+    const int K = DOWN ? fe : a.d;
+    const int nk = K / BK;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = t.m - t.mt * ROWS < ROWS ? t.m - t.mt * ROWS : ROWS;
+    const int live = (rows + 31) >> 5; // row groups of 32 with rows
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)ring;
+
+    // ---- loader: wavefront w fills token rows [32w, 32w + 32) and its own 64 weight rows ----
+    uint64_t a_at[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * wave + 8 * i + (lane >> 3);
+        const uint32_t piece = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));
+        int slot = t.mt * ROWS + row;
+        slot = slot < t.m ? slot : t.m - 1;
+        if constexpr (DOWN) {
+            a_at[i] = (uint64_t)a.h + (uint64_t)(t.seg0 + slot) * a.fmax * 2 + piece * 16;
+        } else {
+            const int tok = shared ? t.seg0 - a.T * a.k + slot : a.perm[t.seg0 + slot] / a.k;
+            a_at[i] = (uint64_t)a.x + (uint64_t)tok * K * 2 + piece * 16;
+        }
+    }
+    const bool loads_tokens = wave < live;
+    // weight rows: down: 64 consecutive ones; gate/up: 32 gate rows, then the same up rows.  (The last tile of columns may be half a
+    // tile: the wavefronts of the missing half load the last rows again.)
+    const int N = DOWN ? a.d : fe, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
+    const int row0 = first < N ? first : N - (DOWN ? 64 : 32);
+    const uint32_t rb = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4);
+    const uint64_t w_lo = scalar_ptr(uniform_load(DOWN ? &h->w_down : &h->w_gate)) + (uint64_t)row0 * rb;
+    const uint64_t w_hi = DOWN ? w_lo + (uint64_t)32 * rb : scalar_ptr(uniform_load(&h->w_up)) + (uint64_t)row0 * rb;
+    const int lg = __builtin_ctz((unsigned)a.group), G = K >> lg;
+    uint64_t s_base = 0; // scales of the lane's row `lane`
+    uint32_t s_row = 0, b_off[2] = {0, 0};
+    if constexpr (quant) {
+        const uint64_t s_lo = scalar_ptr(uniform_load(DOWN ? &h->s_down : &h->s_gate)), s_hi = DOWN ? s_lo : scalar_ptr(uniform_load(&h->s_up));
+        s_base = lane < 32 ? s_lo : s_hi;
+        s_row = (uint32_t)(row0 + (DOWN ? lane : lane & 31)) * (uint32_t)G;
+    } else {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) b_off[p] = (uint32_t)(lane >> 3) * rb + (uint32_t)((lane & 7) ^ (4 * p + (lane >> 4))) * 16; // even and odd groups of eight rows
+    }
+    auto issue_token = [&](int slot, int i) { // called for steps 0, 1, 2, ...
+        if (loads_tokens) {
+            load_to_lds(lds0 + (uint32_t)(slot * cfg::A_SLOT + (32 * wave + 8 * i) * kLine), a_at[i]);
+            a_at[i] += kLine;
+        }
+    };
+    auto issue_tokens = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) issue_token(slot, i);
+    };
+    const uint32_t b_at = lds0 + B0 + wave * cfg::B_WAVE;
+    auto issue_weight = [&](int kt, int i) { // bf16
+        load_to_lds(b_at + 1024 * i, b_off[i & 1], (i < 4 ? w_lo : w_hi) + (uint64_t)(8 * (i & 3)) * rb + (uint64_t)kt * kLine);
+    };
+    const uint32_t c_at = lds0 + B0 + wave * 2 * cfg::SIDE_WIDE;
+    // Codes of steps 2c and 2c + 1 (int4: 64 bytes of a row, four lanes to it, piece p of row r in slot p ^ ((r >> 2) & 3); int2: 32 bytes,
+    // two lanes) and the aligned words that their scales are in.  Past the end of an odd number of steps the first half is read again.
+    auto issue_codes = [&](int c, int slot) {
+        const uint32_t m0 = c_at + (uint32_t)(slot * cfg::SIDE_WIDE);
+        const bool whole = 2 * c + 1 < nk; // wave-uniform
+        if constexpr (FMT == 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t piece = (uint32_t)((lane & 3) ^ (lane >> 4)); // row 16 i + lane / 4
+                piece = whole ? piece : piece & 1;
+                load_to_lds(m0 + 1024 * i, (uint32_t)(lane >> 2) * rb + piece * 16, (i < 2 ? w_lo : w_hi) + (uint64_t)(16 * (i & 1)) * rb + (uint64_t)c * 64);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint32_t piece = whole ? lane & 1 : 0;
+                load_to_lds(m0 + 1024 * i, (uint32_t)(lane >> 1) * rb + piece * 16, (i == 0 ? w_lo : w_hi) + (uint64_t)c * 32);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int kt = whole ? 2 * c + u : 2 * c;
+            load_to_lds4(m0 + 64 * 64 + 256 * u, s_base + (((s_row + (uint32_t)((kt * BK) >> lg)) * 2) & ~3u));
+        }
+    };
+
+    // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
+    const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
+    if constexpr (DOWN) { // the pair indices of the tile's rows, where they go
+        if (!shared && wave < 2) {
+            const int slot = t.mt * ROWS + wave * 64 + lane;
+            load_to_lds4(lds0 + cfg::RING + 256 * wave, (uint32_t)(slot < t.m ? slot : t.m - 1) * 4u, scalar_ptr(a.perm + t.seg0));
+        }
+    }
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int ns = 0; ns < 2; ++ns)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][ns][v] = 0.f;
+    frag8 fa[2][4];
+    u32x4 fb[2][quant ? 1 : 4]; // bf16: the step's operands; quantized: its codes
+    uint32_t scales[2] = {0, 0};
+    // Quantized: lane half kq has the codes of elements 32 kq .. 32 kq + 31 of a step; quarter s of the step is eight of them, and so it
+    // is of the tokens.
+    const char *const a_rd = ring + r * kLine;
+    auto read_a = [&](int slot, int s, frag8 (&af)[4]) {
+        const char *p = a_rd + slot * cfg::A_SLOT + (((quant ? 4 * kq + s : 2 * s + kq) ^ swz) * 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i == 0 || i < live) af[i].u = *reinterpret_cast<const u32x4 *>(p + i * 32 * kLine);
+    };
+    auto read_weights = [&](int kt) {
+        if constexpr (!quant) {
+            const char *p = ring + B0 + wave * cfg::B_WAVE + r * kLine;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int ns = 0; ns < 2; ++ns) fb[ns][s] = *reinterpret_cast<const u32x4 *>(p + ns * 32 * kLine + (((2 * s + kq) ^ swz) * 16));
+        } else {
+            const char *p = ring + B0 + wave * 2 * cfg::SIDE_WIDE + ((kt >> 1) & 1) * cfg::SIDE_WIDE;
+#pragma unroll
+            for (int ns = 0; ns < 2; ++ns) {
+                const int row = 32 * ns + r;
+                scales[ns] = *reinterpret_cast<const uint32_t *>(p + 64 * 64 + 256 * (kt & 1) + 4 * row);
+                if constexpr (FMT == 1) {
+                    fb[ns][0] = *reinterpret_cast<const u32x4 *>(p + row * 64 + (((2 * (kt & 1) + kq) ^ ((r >> 2) & 3)) * 16));
+                } else {
+                    uint32_t c[2];
+                    __builtin_memcpy(c, __builtin_assume_aligned(p + row * 32 + 16 * (kt & 1) + 8 * kq, 8), 8);
+                    fb[ns][0].x = c[0], fb[ns][0].y = c[1];
+                }
+            }
+        }
+    };
+    float scale[2] = {0.f, 0.f};
+    auto operand = [&](int ns, int s) {
+        frag8 b;
+        if constexpr (FMT == 0) b.u = fb[ns][s];
+        else if constexpr (FMT == 1) b.u = dequant8(fb[ns][0][s], scale[ns]);
+        else b.u = dequant8_crumbs(fb[ns][0][s >> 1], s & 1, scale[ns]);
+        return b;
+    };
+    if constexpr (quant) {
+        issue_codes(0, 0);
+        issue_tokens(0);
+        if (2 < nk) issue_codes(1, 1);
+    } else {
+        issue_tokens(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) issue_weight(0, i);
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+        // own loads of step kt have landed; after the barrier that holds for every wavefront, and all have read the tokens of step kt - 1
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        block_barrier();
+        const int slot = kt & 1;
+        read_weights(kt);
+        read_a(slot, 0, fa[0]);
+        if (quant && kt + 1 < nk) issue_tokens(slot ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // own weights are in registers: the next ones may come
+        if constexpr (quant) {
+            if ((kt & 1) && kt + 3 < nk) issue_codes((kt + 3) >> 1, (kt >> 1) & 1);
+#pragma unroll
+            for (int ns = 0; ns < 2; ++ns) {
+                // the half of the aligned word that the row's scale is in (groups of 32: the two groups of the step)
+                const bool odd = lg == 5 ? kq : (((G & 1) ? r : 0) ^ ((kt * BK) >> lg)) & 1;
+                scale[ns] = __uint_as_float(odd ? scales[ns] & 0xFFFF0000u : scales[ns] << 16);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s < 3) read_a(slot, s + 1, fa[(s + 1) & 1]);
+            const frag8 b0 = operand(0, s), b1 = operand(1, s);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i == 0 || i < live) {
+                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0.v, fa[s & 1][i].v, acc[i][0], 0, 0, 0);
+                    acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1.v, fa[s & 1][i].v, acc[i][1], 0, 0, 0);
+                }
+                if constexpr (!quant) { // the loads of the next step take turns with the first half's matrix instructions
+                    if (kt + 1 < nk) {
+                        if (s == 0) issue_weight(kt + 1, 2 * i), issue_weight(kt + 1, 2 * i + 1);
+                        else if (s == 1) issue_token(slot ^ 1, i);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // The tile leaves straight from the registers.
+    const int col = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
+    if (col >= N) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * i + r, slot = t.mt * ROWS + row;
+        if (row >= rows) continue;
+        dx_bf16 *dst;
+        if constexpr (DOWN) {
+            const int orow = shared ? t.seg0 + slot : *reinterpret_cast<const int *>(ring + cfg::RING + 4 * row);
+            dst = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)orow * a.d + col + 8 * kq;
+        } else {
+            dst = a.h + (size_t)(t.seg0 + slot) * a.fmax + col + 8 * kq;
+        }
+        store_row<DOWN>(acc[i][0], acc[i][1], dst);
+    }
+}
+
 template <bool DOWN>
 __global__ __launch_bounds__(cfg::THREADS, 2) void k_tiled(dx_fwd_args a)
 {
-    // the ring and (down) the pair indices of the wavefronts' rows: 74 KB, two blocks to a compute unit
+    // the ring and (down) the pair indices of the rows: two blocks to a compute unit
     __shared__ __attribute__((aligned(1024))) char ring[cfg::RING + (DOWN ? 256 * cfg::WAVES : 0)];
-    const tile_id t = find_tile<DX_TILE_ROWS, 8>(a, DOWN ? a.d / BN : a.f / (BN / 2), DOWN ? a.d / BN : a.shared_f / (BN / 2));
+    bool wide;
+    const tile_id t = find_tile<DOWN>(a, wide);
     if (!t.valid) return; // block-uniform
     const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
     const int fmt = (int)uniform_load(&h->fmt);
-    if (fmt == DX_FMT_INT4G) tile_main<DOWN, 1>(a, t, h, ring);
-    else if (fmt == DX_FMT_INT2G) tile_main<DOWN, 2>(a, t, h, ring);
-    else tile_main<DOWN, 0>(a, t, h, ring);
+    if (wide) {
+        if (fmt == DX_FMT_INT4G) wide_tile<DOWN, 1>(a, t, h, ring);
+        else if (fmt == DX_FMT_INT2G) wide_tile<DOWN, 2>(a, t, h, ring);
+        else wide_tile<DOWN, 0>(a, t, h, ring);
+    } else {
+        if (fmt == DX_FMT_INT4G) narrow_tile<DOWN, 1>(a, t, h, ring);
+        else if (fmt == DX_FMT_INT2G) narrow_tile<DOWN, 2>(a, t, h, ring);
+        else narrow_tile<DOWN, 0>(a, t, h, ring);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -682,8 +948,13 @@ template <bool DOWN>
 __global__ __launch_bounds__(kBigThreads) void k_big(dx_fwd_args a)
 {
     __shared__ __attribute__((aligned(1024))) char ring[kRingBytes]; // 128 KB of stages and 20 KB of side ring
-    const tile_id t = find_tile<DX_BIG_ROWS, 4>(a, DOWN ? a.d / TN : a.f / (TN / 2), DOWN ? a.d / TN : a.shared_f / (TN / 2));
-    if (!t.valid) return; // block-uniform
+    const dx_tile_row *rows = reinterpret_cast<const dx_tile_row *>(a.tiles + 1) + uniform_load(&a.tiles->n_routed) + uniform_load(&a.tiles->n_shared);
+    const int n = uniform_load(&a.tiles->n_big), n_shared = uniform_load(&a.tiles->n_big_shared);
+    const int ntn = columns_of<DOWN>(a, a.f, TN), ntn_shared = columns_of<DOWN>(a, a.shared_f, TN);
+    const uint32_t routed = (uint32_t)(n * ntn), total = routed + (uint32_t)(n_shared * ntn_shared), per_xcd = (total + 7) / 8;
+    const uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per_xcd || idx >= total) return; // block-uniform
+    const tile_id t = idx < routed ? tile_of<DX_BIG_ROWS, 4>(rows, idx, ntn) : tile_of<DX_BIG_ROWS, 4>(rows + n, idx - routed, ntn_shared);
     const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
     if (uniform_load(&h->fmt) == DX_FMT_INT4G) big_tile<DOWN, true>(a, t, h, ring);
     else big_tile<DOWN, false>(a, t, h, ring);
@@ -696,7 +967,7 @@ static void launch_tiles(const dx_fwd_args &a, hipStream_t s)
 {
     // an upper bound on the tile count; surplus blocks find no tile and leave
     const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
-    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, a.m_small, a.shared != nullptr) * (DOWN ? a.d / BN : fe / (BN / 2));
+    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, a.m_small, a.shared != nullptr) * columns_of<DOWN>(a, fe, BN);
     hipLaunchKernelGGL((k_tiled<DOWN>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(cfg::THREADS), 0, s, a);
 }
 

@@ -635,6 +635,49 @@ def test_forward_prefill_tiles_k_steps_and_groups(B, LY, dxo, pair, T, E, k, d, 
     ctx.close()
 
 
+@pytest.mark.parametrize("pair,T,E,k,d,f,group,hi", [
+    # gate/up: 40.5 column tiles, 2 K steps; then 82 column tiles and an odd number of groups per row in the down projection
+    ("bf16-int4", 320, 4, 2, 128, 5184, 64, [1]),
+    ("bf16-int4", 170, 5, 2, 384, 10496, 128, [0, 2]),
+    ("int4-int2", 320, 4, 2, 128, 5184, 64, [1]),
+    ("int4-int2", 320, 4, 2, 128, 7168, 128, [0, 3]),
+    # down: 40.5 column tiles, one and three K steps
+    ("bf16-int4", 320, 4, 2, 10368, 64, 32, [1]),
+    ("bf16-int4", 320, 4, 2, 10368, 192, 64, [1]),
+    ("int4-int2", 320, 4, 2, 10368, 192, 64, [1]),
+    # nearly all bf16
+    ("bf16-int4", 700, 3, 2, 256, 8256, 64, [0, 1, 2]),
+])
+def test_forward_prefill_wide_tiles(B, LY, dxo, pair, T, E, k, d, f, group, hi):
+    """The 256-column tiles of calls with many tiles, every format: every seventh token against the oracle."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group)
+    print(f"wide tiles {pair} T={T} E={E} k={k} d={d} f={f} group={group}", flush=True)
+    x, logits = W.layer_inputs(wl, seed=13)
+    ids, w, counts, offsets, perm = dxo.route(logits, k)
+    row_tiles = sum(-(-int(m) // 128) for m in counts if m > 32)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert 2 * row_tiles * max(f // 64, d // 128) > (11 if len(hi) == E else 5) * n_cu, "the call has to be one of many tiles"
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 13, T)
+    else:
+        keep = Layer(B, LY, dxo, wl, hi, seed=13)
+        ctx, versions = keep.ctx, keep.versions
+    rb = LY.RoutingBuffers(T, E, k)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    rb.route_forward(ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+    sync()
+    tokens = np.unique(np.append(np.arange(0, T, 7), T - 1))
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, tokens=tokens)
+    bits = LY.device_to_bits(y)
+    assert np.isfinite(bf16_bits_to_f32(bits)).all()
+    assert rel_l2(bits[tokens], y_ref) <= REL_L2_TOL
+    used = assert_elementwise(dxo, bits[tokens], y_ref, versions, group, x, ids, w, tokens=tokens, T_call=T)
+    print(f"  element-wise: largest error = {used:.2f} of its bound", flush=True)
+    del keep
+    ctx.close()
+
+
 def test_forward_prefill_tile_list_at_its_bound(B, LY, dxo):
     """Segments of 129 rows in a context of exactly that many tokens: the list of row tiles has as many entries as the
     context holds (two per expert), every one of them in use."""
