@@ -193,6 +193,13 @@ def test_route_chunks_and_wide_selection(B, LY, dxo, T, E, k, coarse):
     _check_route(B, LY, dxo, logits, k)
 
 
+@pytest.mark.parametrize("T,E,k", [(79, 128, 8), (80, 16, 2), (81, 512, 10), (113, 300, 4), (575, 128, 17), (128, 1024, 9)])
+def test_route_quarters_of_a_chunk(B, LY, dxo, T, E, k):
+    """Several chunks, 16 tokens to a block: last quarters that are full, begun and empty, for every kind of selection."""
+    logits = np.random.default_rng(T * E).standard_normal((T, E)).astype(np.float32)
+    _check_route(B, LY, dxo, logits, k)
+
+
 def test_route_rejects_bad_arguments(B, LY):
     ctx = B.Context(L=2, E=8, d=64, f=64, top_k=2, group=32, max_tokens=16)
     rb = LY.RoutingBuffers(16, 8, 2)
