@@ -1397,100 +1397,397 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 #endif
 }
 
-// ---- a call of one or two tokens: down projection and combine in one kernel ----------------------------------
-// Bound by latency: a launch of k_stream<down> derives its partition, starts runs and leaves O to a combine kernel (10.4 +
-// 3.9 us for 13 MB of weights at T = 1, a boundary in between).  With so few pairs there is nothing to partition:
-// block (strip, token) computes the token's 16 columns of y.  Its wavefronts take the token's experts (several to
-// an expert when there are fewer than eight), each multiplies its strip by the pair's row of H over all of K with up to
-// six chunks in flight, and the results meet in LDS, where they are weighted and added in the order of the slots as
-// k_combine does.  Contractions that are multiples of 128.  Whole calls, us, before and after: 30B-shaped T = 1 30.1 and
-// 27.0, T = 2 36.2 and 32.3, T = 3 40.0 and 43.5 (tokens that share an expert read its strip once each, and k_stream
-// once for all); 80B-shaped T = 1 53 and 37.5, T = 2 51.6 and 38.2; 16 experts of 4096 x 6400 T = 2 100 and 98.
-// Which expert a pair belongs to and where its row of H is: ROUTED (the gate/up kernel in front has written the routing
+// ---- a call of one or two tokens: gate/up, then down and combine ----------------------------------------------
+// Bound by latency: k_stream spends as long on the partition, on the starts of its runs and on the strips' meetings
+// in LDS as on the few weights, and leaves O to a combine kernel.  With so few pairs there is nothing to partition and
+// nothing that a matrix instruction would share: a lane multiplies and adds what it has loaded.  A wavefront asks for all
+// its weights before it uses the first; the sums over lanes are DPP steps.
+// Whole calls, us, with k_stream for gate/up and a down kernel of 16 columns per block, and now, T = 1: 30B-shaped 28.0 and 23.0 (gate/up
+// 17.9 -> 15.4, down 10.2 -> 7.5; int4/int2 21.9 and 16.1), 80B-shaped 37.2 and 23.2 (27.4 -> 15.6), 16 experts of 4096 x 6400 64.0 and 52.4
+// (with a routing kernel before), 8 of 4096 x 14336 120 and 105, 256 of 7168 x 2048 112 and 86.  T = 2: 32.4 and 30.8, 38.2 and 31.2, 96.7 and 73.0.
+// Three tokens: tokens that share an expert read a strip of W_down once each, and k_stream once for all (30B-shaped 40.0, and 43.5).
+// Which expert a pair belongs to and where its row of H is: ROUTED (the gate/up kernel writes the routing
 // arrays itself): from the ids, whose segments are in increasing order.  Else the arrays are the caller's: from `offsets`
 // and `perm` alone, as in the other kernels, in any order inside a segment (the gate/up kernel leaves the expert of every
-// place in the list; 0.6 us more at T = 1); a pair that is in no segment adds nothing.
+// place in the list); a pair that is in no segment adds nothing.
 constexpr int kFewTokens = DX_FEW_TOKENS, kFewTasks = DX_ROUTED_MAX_TOPK + 1;
 static_assert(kFewTokens * DX_ROUTED_MAX_TOPK <= 64, "a pair per lane");
 
-// o[r] of column r (in lanes 0..15): row of H (m = 1) times the strip's 16 rows over the chunks [c0, c1)
-template <int GPC, int FMT>
-__device__ __forceinline__ f32x4 strip_of_one(gbf16 h_row, gbytes w, gbf16 sc, int K, int G, int c0, int c1, int lane,
-                                              const line_lanes &ll, lds_bytes area)
+// wavefronts per expert of a token in k_down_few
+__host__ __device__ __forceinline__ int few_split(int tasks) { return tasks < kWaves ? kWaves / tasks : 1; }
+
+// ---- gate/up: three rows of W_gate and of W_up per wavefront and round, over all of K in steps of 2048 elements (24 KB of
+// bf16, 96 registers: 3 wavefronts to a SIMD).  Groups of rows go round the experts, so that every compute unit has its part of
+// the bf16 experts; blocks beyond what the chip holds at once would route again, so wavefronts go on to another group instead
+// (30B-shaped, T = 2: 24.6 -> 20.3; with a shared expert of its own width a fixed number of wavefronts per expert is 27.4 against 21.6 of
+// k_stream).  An expert that both tokens select is read once.  K up to what the tokens may take of LDS.
+constexpr int kFewWaves = 4, kFewRows = 3, kFewStep = 2048, kFewMaxK = 8192, kFewBlocks = 3;
+constexpr int kFewPieces = kFewMaxK / 8; // of eight elements of a token row, in LDS
+
+// (so that reads of neighbouring pieces and of every fourth one both spread over the banks)
+__device__ __forceinline__ int few_piece_at(int p) { return p ^ ((p >> 3) & 7); }
+
+// sum[i][0 / 1][n]: this lane's part of rows row0 + i of W_gate / W_up times token n
+template <int FMT, int NT>
+__device__ __forceinline__ void rows_of_few(gbytes gate, gbytes up, gbf16 s_gate, gbf16 s_up, int row0, int N, int K, int lg,
+                                            const u32x4 *x0, const u32x4 *x1, int lane, float (&sum)[kFewRows][2][2])
 {
-    constexpr int NB = 3, NSW = GPC; // stages of two chunks; words of scales per stage
-    constexpr int CB = FMT == 0 ? 256 : (FMT == 1 ? 64 : 32);
-    const uint32_t row_bytes = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4);
-    const int r = lane & 15, q = lane >> 4;
-    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-    for (int c = c0; c < c1; c += 2 * NB) { // wavefront-uniform
-        u32x4 x[NB][2][1][4];
-        line_stage<2, FMT> st[NB];
-        uint32_t scales[NB][NSW];
-        // the row of H first (one line for all rows of the operand), then scales, then weights
+    constexpr int LOADS = FMT == 0 ? 4 : 1;
+    constexpr uint32_t kBias = FMT == 1 ? 8 : 2;
+    const uint32_t row_bytes = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4), G = (uint32_t)K >> lg;
+    for (int c = 0; c < K; c += kFewStep) {
+        u32x4 w[kFewRows][2][LOADS];
+        uint32_t sc[kFewRows][2];
+        const bool ragged = c + kFewStep > K; // wavefront-uniform; lanes past the end read the row's start and count nothing
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int i = 0; i < kFewRows; ++i)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int cc = c + 2 * b + i < c1 ? c + 2 * b + i : c1 - 1;
+            for (int g = 0; g < 2; ++g) {
+                const int row = row0 + i < N ? row0 + i : N - 1;
+                const gbytes at = (g ? up : gate) + (size_t)row * row_bytes;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k0 = FMT == 0 || GPC == 4 ? 32 * j + 8 * q : (GPC == 2 ? 64 * (j >> 1) + 16 * q + 8 * (j & 1) : 32 * q + 8 * j);
-                    x[b][i][0][j] = *reinterpret_cast<gvec16>(h_row + cc * 128 + k0);
+                for (int l = 0; l < LOADS; ++l) {
+                    const int k0 = FMT == 0 ? c + 512 * l + 8 * lane : c + 32 * lane, k = k0 < K ? k0 : 0;
+                    if constexpr (FMT == 0) w[i][g][l] = *reinterpret_cast<gvec16>(at + 2 * k);
+                    else if constexpr (FMT == 1) w[i][g][l] = *reinterpret_cast<gvec16>(at + k / 2);
+                    else {
+                        const u32x2 t = *reinterpret_cast<gvec8>(at + k / 4);
+                        w[i][g][l].x = t.x, w[i][g][l].y = t.y;
+                    }
+                    if constexpr (FMT != 0) sc[i][g] = (g ? s_up : s_gate)[(uint32_t)row * G + ((uint32_t)k >> lg)];
                 }
             }
-        if constexpr (FMT != 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        // eight elements of the lane's tokens: piece l of its four
+        auto load_x = [&](int l, float (&x)[NT][8]) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int cb = c + 2 * b < c1 ? c + 2 * b : c1 - 1, cn = cb + 1 < c1 ? cb + 1 : cb;
-                const gbf16 sp = sc + (uint32_t)(r * G);
-                if constexpr (GPC == 1) {
-                    scales[b][0] = (uint32_t)sp[cb] | (uint32_t)sp[cn] << 16;
-                } else {
+            for (int n = 0; n < NT; ++n) {
+                const u32x4 p = (n ? x1 : x0)[few_piece_at(c / 8 + (FMT == 0 ? 64 * l + lane : 4 * lane + l))];
 #pragma unroll
-                    for (int g = 0; g < GPC; g += 2) {
-                        scales[b][g >> 1] = *reinterpret_cast<gvec4>(sp + cb * GPC + g);
-                        scales[b][(GPC + g) >> 1] = *reinterpret_cast<gvec4>(sp + cn * GPC + g);
+                for (int j = 0; j < 4; ++j) {
+                    x[n][2 * j] = __uint_as_float(p[j] << 16);
+                    x[n][2 * j + 1] = __uint_as_float(p[j] & 0xFFFF0000u);
+                }
+            }
+        };
+        float part[kFewRows][2][NT];
+        if constexpr (FMT == 0) {
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                const bool past = ragged && c + 512 * l + 8 * lane >= K;
+                float x[NT][8];
+                load_x(l, x);
+#pragma unroll
+                for (int i = 0; i < kFewRows; ++i)
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        u32x4 v = w[i][g][l];
+                        if (past) v = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float lo = __uint_as_float(v[j] << 16), hi = __uint_as_float(v[j] & 0xFFFF0000u);
+#pragma unroll
+                            for (int n = 0; n < NT; ++n) sum[i][g][n] = fmaf(hi, x[n][2 * j + 1], fmaf(lo, x[n][2 * j], sum[i][g][n]));
+                        }
+                    }
+            }
+        } else {
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                float x[NT][8], bias[NT];
+                load_x(l, x);
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    bias[n] = 0.f;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) bias[n] += x[n][j];
+                    bias[n] *= -(float)kBias;
+                }
+#pragma unroll
+                for (int i = 0; i < kFewRows; ++i)
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+#pragma unroll
+                        for (int n = 0; n < NT; ++n) part[i][g][n] = l == 0 ? bias[n] : part[i][g][n] + bias[n];
+                        if constexpr (FMT == 1) { // element 2 b in the low nibble of byte b; flipped: code + 8
+                            const uint32_t f = w[i][g][0][l] ^ 0x88888888u, lo = f & 0x0F0F0F0Fu, hi = (f >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+                            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                                for (int n = 0; n < NT; ++n)
+                                    part[i][g][n] = fmaf((float)((hi >> (8 * b)) & 255u), x[n][2 * b + 1],
+                                                         fmaf((float)((lo >> (8 * b)) & 255u), x[n][2 * b], part[i][g][n]));
+                        } else { // element 4 b + q in bits 2 q of byte b of the half word; flipped: code + 2
+                            const uint32_t f = (w[i][g][0][l >> 1] ^ 0xAAAAAAAAu) >> (16 * (l & 1));
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                                    for (int n = 0; n < NT; ++n)
+                                        part[i][g][n] = fmaf((float)((f >> (8 * b + 2 * q)) & 3u), x[n][4 * b + q], part[i][g][n]);
+                        }
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < kFewRows; ++i)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const float scale = ragged && c + 32 * lane >= K ? 0.f : __uint_as_float(sc[i][g] << 16);
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) sum[i][g][n] = fmaf(scale, part[i][g][n], sum[i][g][n]);
+                }
+        }
+    }
+}
+
+template <int NV, bool ROUTED>
+__global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_fwd_args a, dx_route_io r)
+{
+    constexpr int THREADS = 64 * kFewWaves, HOT = (16 * NV + THREADS - 1) / THREADS;
+    __shared__ u32x4 xs[kFewTokens * kFewPieces];
+    static_assert(NV <= 8 || sizeof(xs) >= sizeof(int) * kFewWaves * 64 * NV, "the wide selection's keys fit in front of the tokens");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), P = a.T * a.k;
+    const int pieces = (a.d + kFewStep - 1) / kFewStep * (kFewStep / 8); // of a token, with zeros up to a whole step
+    const bool writer = ROUTED && blockIdx.x == 0;
+    float v[ROUTED ? NV : 1];
+    unsigned long long hot_before[HOT] = {};
+    if constexpr (ROUTED) {
+        const int t = lane >> 4;
+        dx_route_core::load_logits_rows16<NV>(r.logits + (size_t)(t < a.T ? t : a.T - 1) * a.E, lane & 15, a.E, v);
+        if (writer && r.hotness) {
+#pragma unroll
+            for (int i = 0; i < HOT; ++i)
+                if (tid + i * THREADS < a.E) hot_before[i] = r.hotness[tid + i * THREADS];
+        }
+    }
+    auto piece = [&](int i) { // of token i / pieces
+        const int t = i >= pieces, p = t ? i - pieces : i;
+        return p * 8 < a.d ? *reinterpret_cast<gvec16>((gbf16)a.x + (size_t)t * a.d + p * 8) : u32x4{0u, 0u, 0u, 0u};
+    };
+    auto keep = [&](int i, u32x4 x) {
+        const int t = i >= pieces, p = t ? i - pieces : i;
+        xs[t * kFewPieces + few_piece_at(p)] = x;
+    };
+    const u32x4 x_first = piece(tid);
+    // (the handles' lines into L2, while the routing runs)
+    uint32_t touched = 0;
+    if constexpr (ROUTED) {
+#pragma unroll
+        for (int i = 0; i < NV / 8; ++i) touched |= a.table[min(2 * (64 * i + lane), a.E - 1)].fmt;
+    }
+    int my_id = 0;
+    float my_w = 0.f;
+    bool has_pair = false;
+    if constexpr (ROUTED) {
+        if constexpr (NV <= 8) dx_route_core::topk_rows16<NV>(v, a.k, lane, my_id, my_w);
+        else dx_route_core::topk_rows16_filtered<NV, 6>(v, a.k, lane, my_id, my_w, (__attribute__((address_space(3))) int *)xs + wave * 64 * NV);
+        has_pair = (lane >> 4) < a.T && (lane & 15) < a.k;
+    }
+    // ---- the wavefront's groups of rows: the shared expert's first, then those of the pairs (not routed: places) in turn.  Of a
+    // group: the expert, its first place in the segments and its tokens (none: another group has them)
+    const int shared_groups = a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0, groups = shared_groups + P * ((a.f + kFewRows - 1) / kFewRows);
+    int e, pos, n_tok, t0, t1, row0;
+    auto take = [&](int group) {
+        e = a.E, pos = P, n_tok = a.T, t0 = 0, t1 = a.T - 1, row0 = group * kFewRows;
+        if (group < shared_groups) return;
+        const int item = (group - shared_groups) % P;
+        row0 = (group - shared_groups) / P * kFewRows;
+        if constexpr (ROUTED) { // the expert's first pair takes them all
+            const int t = item / a.k, src = 16 * t + item % a.k;
+            e = __builtin_amdgcn_readlane(my_id, src);
+            const unsigned long long same = __ballot(has_pair && my_id == e);
+            pos = __popcll(__ballot(has_pair && my_id < e));
+            n_tok = __builtin_ctzll(same) == src ? __popcll(same) : 0;
+            t0 = t;
+        } else { // places in pairs from the segment's start
+            int begin = 0, end = 0;
+            pos = item, n_tok = 0;
+            for (int e0 = 0; e0 < a.E; e0 += 64) { // wavefront-uniform
+                const int el = e0 + lane < a.E ? e0 + lane : a.E - 1, o0 = a.offsets[el], o1 = a.offsets[el + 1];
+                const unsigned long long in = __ballot(o0 <= pos && pos < o1);
+                if (in != 0ull && n_tok == 0) {
+                    const int l = __builtin_ctzll(in);
+                    e = e0 + l, begin = __builtin_amdgcn_readlane(o0, l), end = __builtin_amdgcn_readlane(o1, l);
+                    n_tok = 1;
+                }
+            }
+            if (n_tok) {
+                if (row0 == 0 && lane == 0) reinterpret_cast<int32_t *>(a.tiles)[pos] = e;
+                end = end < P ? end : P;
+                n_tok = ((pos - begin) & 1) ? 0 : (pos + 1 < end ? 2 : 1);
+                t0 = a.perm[pos] / a.k;
+                t1 = n_tok == 2 ? a.perm[pos + 1] / a.k : t0;
+            }
+        }
+    };
+    const int stride = (int)gridDim.x * kFewWaves;
+    int group = (int)blockIdx.x * kFewWaves + wave;
+    if (group < groups) take(group);
+    asm volatile("" ::"v"(touched));
+    if constexpr (ROUTED && NV > 8) __syncthreads(); // the keys are done with
+    keep(tid, x_first);
+    for (int i = tid + THREADS; i < a.T * pieces; i += THREADS) keep(i, piece(i));
+    __syncthreads();
+    for (; group < groups;) { // wavefront-uniform
+        if (n_tok) {
+            const int N = e == a.E ? a.shared_f : a.f, lg = __builtin_ctz((unsigned)a.group);
+            const dx_handle *h = e == a.E ? a.shared : a.table + e;
+            const dx_handle hd = *h;
+            const u32x4 *x0 = xs + t0 * kFewPieces, *x1 = xs + t1 * kFewPieces;
+            float sum[kFewRows][2][2] = {};
+            auto rows = [&](auto fmt, auto nt) {
+                rows_of_few<decltype(fmt)::value, decltype(nt)::value>((gbytes)hd.w_gate, (gbytes)hd.w_up, (gbf16)hd.s_gate, (gbf16)hd.s_up,
+                                                                       row0, N, a.d, lg, x0, x1, lane, sum);
+            };
+            auto any = [&](auto nt) {
+                if (hd.fmt == DX_FMT_INT4G) rows(std::integral_constant<int, 1>{}, nt);
+                else if (hd.fmt == DX_FMT_INT2G) rows(std::integral_constant<int, 2>{}, nt);
+                else rows(std::integral_constant<int, 0>{}, nt);
+            };
+            if (n_tok == 1) any(std::integral_constant<int, 1>{});
+            else any(std::integral_constant<int, 2>{});
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                if (n < n_tok) {
+                    float hv[kFewRows];
+#pragma unroll
+                    for (int i = 0; i < kFewRows; ++i) {
+                        const float g = dx_route_core::wave_sum(sum[i][0][n]), u = dx_route_core::wave_sum(sum[i][1][n]);
+                        hv[i] = g / (1.f + expf(-g)) * u;
+                    }
+                    if (lane == 0) {
+                        dx_bf16 *out = a.h + (size_t)(pos + n) * a.fmax + row0;
+#pragma unroll
+                        for (int i = 0; i < kFewRows; ++i)
+                            if (row0 + i < N) out[i] = (dx_bf16)float_to_bf16_rne(hv[i]);
                     }
                 }
             }
         }
+        group += stride;
+        if (group < groups) take(group);
+    }
+    if constexpr (ROUTED) { // the routing arrays, for the down kernel and the caller
+        if (writer) {
+            int below[HOT] = {}, count[HOT] = {}, at = 0;
+            for (int t = 0; t < a.T; ++t)
+                for (int j = 0; j < a.k; ++j) {
+                    const int id = __builtin_amdgcn_readlane(my_id, 16 * t + j);
+                    at += id < my_id || (id == my_id && 16 * t + j < lane);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const gbytes p = w + (c + 2 * b) * CB;
-            issue_lines<GPC, 2, FMT>(st[b], p, p + 8 * (size_t)row_bytes, row_bytes, c + 2 * b < c1, c + 2 * b + 1 < c1, lane);
-        }
+                    for (int i = 0; i < HOT; ++i) {
+                        below[i] += id < tid + i * THREADS;
+                        count[i] += id == tid + i * THREADS;
+                    }
+                }
+            if (wave == 0 && has_pair) {
+                const int p = (lane >> 4) * a.k + (lane & 15);
+                r.ids[p] = my_id;
+                r.w[p] = my_w;
+                r.perm[at] = p;
+            }
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            f32x4 nbias[2][GPC][1];
-            if constexpr (FMT != 0) prepare_line_tokens<GPC, 2, 1, FMT>(x[b], nbias, c + 2 * b, c1);
-            multiply_lines<GPC, 2, FMT, 1>(st[b], x[b], nbias, scales[b], c + 2 * b < c1, c + 2 * b + 1 < c1, ll, lane, area, acc);
+            for (int i = 0; i < HOT; ++i) {
+                const int ex = tid + i * THREADS;
+                if (ex < a.E) {
+                    r.counts[ex] = count[i];
+                    r.offsets[ex] = below[i];
+                    if (r.hotness) r.hotness[ex] = hot_before[i] + (unsigned long long)count[i];
+                }
+            }
+            if (tid == 0) r.offsets[a.E] = P;
         }
     }
-    return acc[0];
 }
 
-template <int GPC, bool ROUTED>
-__global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
+// ---- down and combine: block (8 columns, token), a wavefront per expert (several where there are fewer than eight), which
+// multiplies its rows of W_down by the pair's row of H, a 16-lane row to a row, up to six chunks of 128 elements in flight;
+// the results meet in LDS, where they are weighted and added in the order of the slots as k_combine does.  Contractions that
+// are multiples of 128.  (8 columns because d / 16 blocks leave half of the chip idle at d = 2048, and a compute unit takes
+// in 28 GB/s past L2.)
+constexpr int kFewCols = 8, kFewDownWaves = 16, kFewChunks = 6; // columns of a block, wavefronts at most, chunks in flight
+
+// sum[p]: this lane's part of row 4 p + lane / 16 of eight rows of W_down times a row of H, over the chunks [c0, c1) of 128
+// elements, of which a lane has eight
+template <int FMT>
+__device__ __forceinline__ void columns_of_few(gbf16 h_row, gbytes w, gbf16 sc, int K, int lg, int c0, int c1, int lane, float (&sum)[2])
 {
-    __shared__ u32x4 stage[kWaves][256]; // a line stage per wavefront
-    __shared__ float part[kFewTasks][16]; // (a task per item, or at most eight items)
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    constexpr uint32_t kBias = FMT == 1 ? 8 : 2;
+    const uint32_t row_bytes = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4), G = (uint32_t)K >> lg;
+    const int row = lane >> 4, l = lane & 15;
+    for (int c = c0; c < c1; c += kFewChunks) { // wavefront-uniform
+        u32x4 xp[kFewChunks], wp[kFewChunks][2];
+        uint32_t scales[kFewChunks][2];
+#pragma unroll
+        for (int i = 0; i < kFewChunks; ++i) {
+            const int cc = c + i < c1 ? c + i : c1 - 1, k = 128 * cc + 8 * l;
+            xp[i] = *reinterpret_cast<gvec16>(h_row + k);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint32_t r = 4 * p + row;
+                const gbytes at = w + r * row_bytes;
+                if constexpr (FMT == 0) wp[i][p] = *reinterpret_cast<gvec16>(at + 2 * k);
+                else if constexpr (FMT == 1) wp[i][p].x = *reinterpret_cast<gvec4>(at + k / 2);
+                else wp[i][p].x = *reinterpret_cast<gbf16>(at + k / 4);
+                if constexpr (FMT != 0) scales[i][p] = sc[r * G + ((uint32_t)k >> lg)];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kFewChunks; ++i) {
+            if (c + i < c1) { // wavefront-uniform
+                float x[8], bias = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    x[2 * j] = __uint_as_float(xp[i][j] << 16);
+                    x[2 * j + 1] = __uint_as_float(xp[i][j] & 0xFFFF0000u);
+                }
+                if constexpr (FMT != 0) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) bias += x[j];
+                    bias *= -(float)kBias;
+                }
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    if constexpr (FMT == 0) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            sum[p] = fmaf(__uint_as_float(wp[i][p][j] & 0xFFFF0000u), x[2 * j + 1],
+                                          fmaf(__uint_as_float(wp[i][p][j] << 16), x[2 * j], sum[p]));
+                    } else {
+                        float part = bias; // code j in bits BITS * j; flipped: code + kBias
+                        constexpr int BITS = FMT == 1 ? 4 : 2;
+                        const uint32_t f = wp[i][p].x ^ (FMT == 1 ? 0x88888888u : 0xAAAAAAAAu);
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) part = fmaf((float)((f >> (BITS * j)) & ((1u << BITS) - 1)), x[j], part);
+                        sum[p] = fmaf(__uint_as_float(scales[i][p] << 16), part, sum[p]);
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <bool ROUTED>
+__global__ __launch_bounds__(64 * kFewDownWaves) void k_down_few(dx_fwd_args a)
+{
+    __shared__ float part[kFewTasks][kFewCols]; // (a task per item, or at most eight items)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     const int t = blockIdx.y, strip = blockIdx.x, P = a.T * a.k;
     const int tasks = a.k + (a.shared ? 1 : 0);
-    const int split = tasks < kWaves ? kWaves / tasks : 1; // wavefronts per expert
+    const int split = few_split(tasks); // wavefronts per expert
     // lane i: routed: the expert of pair i; else the expert and the pair of place i
     const int at_i = lane < P ? lane : 0;
     int expert_i = ROUTED ? a.ids[at_i] : reinterpret_cast<const int32_t *>(a.tiles)[at_i], pair_i = -1;
+    const float w_j = a.w[t * a.k + (lane < a.k ? lane : 0)];
     if constexpr (ROUTED) {
         expert_i = lane < P ? expert_i : 0x7fffffff;
     } else { // (places outside the segments are dropped after the loads)
         const int p = a.perm[at_i], first = a.offsets[0], end = a.offsets[a.E];
         pair_i = lane >= first && lane < min(P, end) ? p : -1;
     }
-    const line_lanes ll = line_lanes_of(lane);
-    const lds_bytes area = (lds_bytes)(__attribute__((address_space(3))) void *)&stage[wave][0];
-    for (int item = wave; item < tasks * split; item += kWaves) {
+    for (int item = wave; item < tasks * split; item += waves) {
         const int j = item / split, piece = item % split;
         const bool shared = j == a.k;
         // the expert, and the pair's place in the segments
@@ -1502,41 +1799,46 @@ __global__ __launch_bounds__(kThreads) void k_down_few(dx_fwd_args a)
             } else {
                 const unsigned long long at = __ballot(pair_i == t * a.k + j);
                 if (at == 0ull) {
-                    if (lane < 16) part[item][lane] = 0.f;
+                    if (lane < kFewCols) part[item][lane] = 0.f;
                     continue;
                 }
                 pos = __builtin_ctzll(at);
                 e = __builtin_amdgcn_readlane(expert_i, pos);
             }
         }
-        const dx_handle hd = shared ? *a.shared : a.table[e];
+        const dx_handle *h = shared ? a.shared : a.table + e;
+        const dx_handle hd = *h;
         const int K = shared ? a.shared_f : a.f, nc = K / 128, per = (nc + split - 1) / split;
         const int c0 = piece * per, c1 = c0 + per < nc ? c0 + per : nc;
         const gbf16 h_row = (gbf16)a.h + (size_t)pos * a.fmax;
         const gbytes w = (gbytes)hd.w_down;
-        const gbf16 sc = (gbf16)hd.s_down;
-        const int G = K / a.group;
-        const size_t row0 = (size_t)strip * 16;
-        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int lg = __builtin_ctz((unsigned)a.group), G = K >> lg;
+        const gbf16 sc = (gbf16)hd.s_down + (size_t)strip * kFewCols * G;
+        const size_t row0 = (size_t)strip * kFewCols;
+        float sum[2] = {0.f, 0.f};
         if (c0 < c1) {
-            if (hd.fmt == DX_FMT_INT4G) o = strip_of_one<GPC, 1>(h_row, w + row0 * (K / 2), sc + row0 * G, K, G, c0, c1, lane, ll, area);
-            else if (hd.fmt == DX_FMT_INT2G) {
-                if constexpr (GPC < 4) o = strip_of_one<GPC, 2>(h_row, w + row0 * (K / 4), sc + row0 * G, K, G, c0, c1, lane, ll, area);
-            } else o = strip_of_one<GPC, 0>(h_row, w + row0 * K * 2, sc, K, G, c0, c1, lane, ll, area);
+            if (hd.fmt == DX_FMT_INT4G) columns_of_few<1>(h_row, w + row0 * (K / 2), sc, K, lg, c0, c1, lane, sum);
+            else if (hd.fmt == DX_FMT_INT2G) columns_of_few<2>(h_row, w + row0 * (K / 4), sc, K, lg, c0, c1, lane, sum);
+            else columns_of_few<0>(h_row, w + row0 * K * 2, sc, K, lg, c0, c1, lane, sum);
         }
-        if (lane < 16) part[item][lane] = o[0]; // (every row of the operand is the same token: row 0)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const float s = dx_route_core::row_sum(sum[p]);
+            if ((lane & 15) == 15) part[item][4 * p + (lane >> 4)] = s;
+        }
     }
     __syncthreads();
-    if (threadIdx.x < 16) {
+    if (threadIdx.x < 64) {
+        const int col = lane & (kFewCols - 1);
         float acc = 0.f, sh = 0.f;
         for (int j = 0; j < tasks; ++j) {
             float v = 0.f;
-            for (int i = 0; i < split; ++i) v += part[j * split + i][threadIdx.x];
-            if (j < a.k) acc += a.w[t * a.k + j] * v;
+            for (int i = 0; i < split; ++i) v += part[j * split + i][col];
+            if (j < a.k) acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_j), j)) * v;
             else sh = v;
         }
         if (a.shared) acc += sh;
-        a.y[(size_t)t * a.d + strip * 16 + threadIdx.x] = (dx_bf16)float_to_bf16_rne(acc);
+        if (lane < kFewCols) a.y[(size_t)t * a.d + strip * kFewCols + lane] = (dx_bf16)float_to_bf16_rne(acc);
     }
 }
 
@@ -1731,11 +2033,24 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
 bool takes_few(const dx_fwd_args &a, int n_cu)
 {
     if (a.T > kFewTokens || a.k >= kFewTasks || a.f % 128 || (a.shared && a.shared_f % 128)) return false;
-    const int tasks = a.k + (a.shared ? 1 : 0), split = tasks < kWaves ? kWaves / tasks : 1;
+    const int tasks = a.k + (a.shared ? 1 : 0), split = few_split(tasks);
     const int nc = a.f / 128, nc_shared = a.shared ? a.shared_f / 128 : 0, most = nc > nc_shared ? nc : nc_shared;
     if ((long)(a.k * nc + nc_shared) * n_cu > 240L * (a.d / 16) * a.T) return false;
     const bool one_round = tasks * split <= kWaves && (most + split - 1) / split <= 6 && a.d / 16 * a.T <= n_cu;
     return a.T == 1 || 2 * a.T * a.k <= a.E || one_round;
+}
+
+// Whether gate/up run in k_gate_up_few (few: what takes_few says).
+bool few_gate_up(const dx_fwd_args &a, bool few) { return few && a.d % 128 == 0 && a.d <= kFewMaxK; }
+
+void launch_few(const dx_fwd_args &a, int n_cu, hipStream_t s, hipEvent_t start, hipEvent_t stop, const dx_route_io *r)
+{
+    const long waves = (a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0) + (long)a.T * a.k * ((a.f + kFewRows - 1) / kFewRows);
+    const long fits = (long)kFewBlocks * n_cu, blocks = (waves + kFewWaves - 1) / kFewWaves;
+    const dim3 grid((unsigned)(blocks < fits ? blocks : fits)), block(64 * kFewWaves);
+    if (!r) launch(k_gate_up_few<8, false>, grid, block, s, start, stop, a, dx_route_io{});
+    else if (a.E <= 128) launch(k_gate_up_few<8, true>, grid, block, s, start, stop, a, *r);
+    else launch(k_gate_up_few<32, true>, grid, block, s, start, stop, a, *r);
 }
 
 // Up to this many tokens per call the streaming kernels alone are faster than streamed experts and tiles (30B-shaped
@@ -1778,7 +2093,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
-        *routed = !mixed && pick_split(nc, nc).mode == kWhole && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
+        *routed = !mixed && (few_gate_up(a, few) || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
@@ -1791,17 +2106,13 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         hipEvent_t ev[8] = {};
         if (marks)
             for (int i = 0; i < 8; ++i) ev[i] = marks[i];
-        launch_stream<false>(a, grid, s, ev[0], ev[1], r);
+        if (few_gate_up(a, few)) launch_few(a, n_cu, s, ev[0], ev[1], r);
+        else launch_stream<false>(a, grid, s, ev[0], ev[1], r);
         if (few) {
-            const dim3 strips(a.d / 16, a.T), block(kThreads);
-            auto run = [&](auto routed_c) {
-                constexpr bool R = decltype(routed_c)::value;
-                if (a.group == 128) launch(k_down_few<1, R>, strips, block, s, ev[5], ev[2], a);
-                else if (a.group == 64) launch(k_down_few<2, R>, strips, block, s, ev[5], ev[2], a);
-                else launch(k_down_few<4, R>, strips, block, s, ev[5], ev[2], a);
-            };
-            if (r) run(std::true_type{});
-            else run(std::false_type{});
+            const int tasks = a.k + (a.shared ? 1 : 0), items = tasks * few_split(tasks);
+            const dim3 strips(a.d / kFewCols, a.T), block(64 * (items <= kFewDownWaves ? items : (items + 1) / 2));
+            if (r) launch(k_down_few<true>, strips, block, s, ev[5], ev[2], a);
+            else launch(k_down_few<false>, strips, block, s, ev[5], ev[2], a);
             combined = true;
             if (mk) mk->combined = true;
         } else {

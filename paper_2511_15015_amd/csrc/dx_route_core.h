@@ -28,14 +28,18 @@ __device__ __forceinline__ float wave_max(float x)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-__device__ __forceinline__ float wave_sum(float x)
+__device__ __forceinline__ float row_sum(float x) // in lane 15 of every 16-lane row
 {
-    // inclusive scan inside each row by shifts (lanes shifted in from outside the row contribute 0) ...
-    x += dpp_move<0x111, 0xF, true>(0.f, x); // row_shr:1
+    x += dpp_move<0x111, 0xF, true>(0.f, x); // row_shr:1 (lanes shifted in from outside the row contribute 0)
     x += dpp_move<0x112, 0xF, true>(0.f, x); // row_shr:2
     x += dpp_move<0x114, 0xF, true>(0.f, x); // row_shr:4
-    x += dpp_move<0x118, 0xF, true>(0.f, x); // row_shr:8 -> lane 15 of every row holds the row's sum
-    // ... then the row sums travel to lane 63
+    x += dpp_move<0x118, 0xF, true>(0.f, x); // row_shr:8
+    return x;
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+    x = row_sum(x); // ... then the row sums travel to lane 63
     x += dpp_move<0x142, 0xA, false>(0.f, x); // row_bcast:15 into rows 1 and 3
     x += dpp_move<0x143, 0xC, false>(0.f, x); // row_bcast:31 into rows 2 and 3
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));

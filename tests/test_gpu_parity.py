@@ -1384,6 +1384,46 @@ def test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, sh
     ctx.close()
 
 
+@pytest.mark.parametrize("pair,T,E,k,d,f,group,shared_f", [
+    ("bf16-int4", 1, 8, 2, 2176, 128, 64, 0),      # gate/up: a step of 2048 and 128 elements; rows no multiple of three
+    ("int4-int2", 2, 8, 2, 2176, 640, 128, 0),
+    ("bf16-int4", 2, 4, 4, 640, 128, 32, 0),       # every expert of both tokens, K less than a step
+    ("bf16-int4", 2, 300, 10, 2048, 512, 128, 512),  # the wide selection
+    ("bf16-int4", 2, 600, 3, 384, 256, 128, 256),  # more experts than the kernel routes
+    ("bf16-int4", 1, 8, 8, 1536, 1280, 64, 256),   # more groups of rows than wavefronts
+    ("bf16-int4", 2, 16, 2, 8192, 128, 128, 0),    # the longest rows
+    ("bf16-int4", 1, 8, 2, 8320, 128, 128, 0),     # longer ones: the streaming kernel
+    ("bf16-int4", 1, 8, 2, 192, 128, 64, 0),       # gate/up no multiple of 128: likewise
+])
+def test_forward_of_one_or_two_tokens_row_by_row(B, LY, dxo, pair, T, E, k, d, f, group, shared_f):
+    """The edges of the gate/up kernel for one and two tokens, as above."""
+    test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, shared_f)
+
+
+@pytest.mark.parametrize("T,E,k", [(1, 100, 8), (2, 512, 16)])
+def test_hotness_of_one_or_two_tokens(B, LY, dxo, T, E, k):
+    """The kernel that routes and multiplies adds the counts as well, and writes every array."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=256, f=128, group=64)
+    ctx = B.Context(L=1, E=E, d=256, f=128, top_k=k, group=64, max_tokens=T, route_updates_hotness=True)
+    lw = LY.LayerWeights(ctx, 0, *[LY.bits_to_device(m) for m in W.layer_masters(wl, 71, 0)], [0, 3], 64)
+    rb = LY.RoutingBuffers(T, E, k)
+    y = torch.empty((T, 256), dtype=torch.bfloat16, device="cuda")
+    c = np.zeros((1, E), np.int64)
+    for step in range(3):
+        x, logits = W.layer_inputs(wl, seed=71, step=step)
+        rb.route_forward(ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+        sync()
+        ids, w, counts, offsets, perm = dxo.route(logits, k)
+        dxo.hotness_update(c[0], counts)
+        for got, want in ((rb.ids, ids), (rb.counts, counts), (rb.offsets, offsets), (rb.perm, perm)):
+            assert np.array_equal(got.cpu().numpy(), want)
+        assert np.max(np.abs(rb.w.cpu().numpy() - w)) < 1e-6
+    assert np.array_equal(ctx.dx_get_counters(), c)
+    del lw
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,E,k", [(1, 8, 3), (2, 4, 3), (2, 6, 6), (3, 4, 3)])
 def test_forward_goes_by_offsets_and_perm_alone(B, LY, dxo, T, E, k):
     """dx_moe_forward on a permutation in another order inside the segments and with ids that say nothing: the pairs'
