@@ -1420,7 +1420,7 @@ __host__ __device__ __forceinline__ int few_split(int tasks) { return tasks < kW
 // bf16, 96 registers: 3 wavefronts to a SIMD).  Groups of rows go round the experts, so that every compute unit has its part of
 // the bf16 experts; blocks beyond what the chip holds at once would route again, so wavefronts go on to another group instead
 // (30B-shaped, T = 2: 24.6 -> 20.3; with a shared expert of its own width a fixed number of wavefronts per expert is 27.4 against 21.6 of
-// k_stream).  An expert that both tokens select is read once.  K up to what the tokens may take of LDS.
+// k_stream; both tokens' experts listed twice and the second dropped 19.5 against 16.5 where all are shared).  An expert that both tokens select is read once.  K up to what the tokens may take of LDS.
 constexpr int kFewWaves = 4, kFewRows = 3, kFewStep = 2048, kFewMaxK = 8192, kFewBlocks = 3;
 constexpr int kFewPieces = kFewMaxK / 8; // of eight elements of a token row, in LDS
 
@@ -1579,27 +1579,35 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
     int my_id = 0;
     float my_w = 0.f;
     bool has_pair = false;
+    unsigned long long first = 0; // lanes whose pair is its expert's first
+    int tasks = P;
     if constexpr (ROUTED) {
         if constexpr (NV <= 8) dx_route_core::topk_rows16<NV>(v, a.k, lane, my_id, my_w);
         else dx_route_core::topk_rows16_filtered<NV, 6>(v, a.k, lane, my_id, my_w, (__attribute__((address_space(3))) int *)xs + wave * 64 * NV);
         has_pair = (lane >> 4) < a.T && (lane & 15) < a.k;
+        bool again = false; // an earlier token has the expert
+        if (a.T == 2) {
+            for (int j = 0; j < a.k; ++j) again |= lane >= 16 && __builtin_amdgcn_readlane(my_id, j) == my_id;
+        }
+        first = __ballot(has_pair && !again);
+        tasks = __popcll(first);
     }
-    // ---- the wavefront's groups of rows: the shared expert's first, then those of the pairs (not routed: places) in turn.  Of a
-    // group: the expert, its first place in the segments and its tokens (none: another group has them)
-    const int shared_groups = a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0, groups = shared_groups + P * ((a.f + kFewRows - 1) / kFewRows);
+    // ---- the wavefront's groups of rows: the shared expert's first, then those of the experts (not routed: places) in turn.  Of a
+    // group: the expert, its first place in the segments and its tokens (none: another place's group has them)
+    const int shared_groups = a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0, groups = shared_groups + tasks * ((a.f + kFewRows - 1) / kFewRows);
     int e, pos, n_tok, t0, t1, row0;
     auto take = [&](int group) {
         e = a.E, pos = P, n_tok = a.T, t0 = 0, t1 = a.T - 1, row0 = group * kFewRows;
         if (group < shared_groups) return;
-        const int item = (group - shared_groups) % P;
-        row0 = (group - shared_groups) / P * kFewRows;
-        if constexpr (ROUTED) { // the expert's first pair takes them all
-            const int t = item / a.k, src = 16 * t + item % a.k;
+        const int item = (group - shared_groups) % tasks;
+        row0 = (group - shared_groups) / tasks * kFewRows;
+        if constexpr (ROUTED) {
+            const int before = __popcll(first & ((1ull << lane) - 1ull));
+            const int src = __builtin_ctzll(__ballot(((first >> lane) & 1ull) != 0ull && before == item));
             e = __builtin_amdgcn_readlane(my_id, src);
-            const unsigned long long same = __ballot(has_pair && my_id == e);
             pos = __popcll(__ballot(has_pair && my_id < e));
-            n_tok = __builtin_ctzll(same) == src ? __popcll(same) : 0;
-            t0 = t;
+            n_tok = __popcll(__ballot(has_pair && my_id == e));
+            t0 = src >> 4;
         } else { // places in pairs from the segment's start
             int begin = 0, end = 0;
             pos = item, n_tok = 0;
@@ -1628,6 +1636,37 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
     if constexpr (ROUTED && NV > 8) __syncthreads(); // the keys are done with
     keep(tid, x_first);
     for (int i = tid + THREADS; i < a.T * pieces; i += THREADS) keep(i, piece(i));
+    if constexpr (ROUTED) { // the routing arrays, for the down kernel and the caller (here, not behind the rows, whose registers are all in use)
+        if (writer) {
+            int below[HOT] = {}, count[HOT] = {}, at = 0;
+            for (int t = 0; t < a.T; ++t)
+                for (int j = 0; j < a.k; ++j) {
+                    const int id = __builtin_amdgcn_readlane(my_id, 16 * t + j);
+                    at += id < my_id || (id == my_id && 16 * t + j < lane);
+#pragma unroll
+                    for (int i = 0; i < HOT; ++i) {
+                        below[i] += id < tid + i * THREADS;
+                        count[i] += id == tid + i * THREADS;
+                    }
+                }
+            if (wave == 0 && has_pair) {
+                const int p = (lane >> 4) * a.k + (lane & 15);
+                r.ids[p] = my_id;
+                r.w[p] = my_w;
+                r.perm[at] = p;
+            }
+#pragma unroll
+            for (int i = 0; i < HOT; ++i) {
+                const int ex = tid + i * THREADS;
+                if (ex < a.E) {
+                    r.counts[ex] = count[i];
+                    r.offsets[ex] = below[i];
+                    if (r.hotness) r.hotness[ex] = hot_before[i] + (unsigned long long)count[i];
+                }
+            }
+            if (tid == 0) r.offsets[a.E] = P;
+        }
+    }
     __syncthreads();
     for (; group < groups;) { // wavefront-uniform
         if (n_tok) {
@@ -1667,37 +1706,6 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
         }
         group += stride;
         if (group < groups) take(group);
-    }
-    if constexpr (ROUTED) { // the routing arrays, for the down kernel and the caller
-        if (writer) {
-            int below[HOT] = {}, count[HOT] = {}, at = 0;
-            for (int t = 0; t < a.T; ++t)
-                for (int j = 0; j < a.k; ++j) {
-                    const int id = __builtin_amdgcn_readlane(my_id, 16 * t + j);
-                    at += id < my_id || (id == my_id && 16 * t + j < lane);
-#pragma unroll
-                    for (int i = 0; i < HOT; ++i) {
-                        below[i] += id < tid + i * THREADS;
-                        count[i] += id == tid + i * THREADS;
-                    }
-                }
-            if (wave == 0 && has_pair) {
-                const int p = (lane >> 4) * a.k + (lane & 15);
-                r.ids[p] = my_id;
-                r.w[p] = my_w;
-                r.perm[at] = p;
-            }
-#pragma unroll
-            for (int i = 0; i < HOT; ++i) {
-                const int ex = tid + i * THREADS;
-                if (ex < a.E) {
-                    r.counts[ex] = count[i];
-                    r.offsets[ex] = below[i];
-                    if (r.hotness) r.hotness[ex] = hot_before[i] + (unsigned long long)count[i];
-                }
-            }
-            if (tid == 0) r.offsets[a.E] = P;
-        }
     }
 }
 
