@@ -497,8 +497,8 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
 // 122 us, down 79 -> 64.  What bounds it: the latency of the weights.  A wavefront's 8 KB of a step (bf16) are read to registers at the
 // step's start and loaded again at once, so they have one step to arrive: 1.9 us a step for one block or two.
 //   LDS: two slots of token rows (laid out as in the other kernel); weights: of the wavefront alone, no barrier.  Codes come for two steps
-//   at a time, 64 (int2: 32) bytes of a row, into two slots; lane half kq takes one half of a step's elements of a row, and a
-//   quarter of the step is eight of them in each half, of the tokens too.
+//   at a time, 64 (int2: 32) bytes of a row, into two slots.  The matrix instructions take the elements of every format in the order
+//   of the narrow tiles, so a token's result does not depend on which kind a call has.
 template <bool DOWN, int FMT>
 __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
@@ -605,13 +605,11 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][ns][v] = 0.f;
     frag8 fa[2][4];
-    u32x4 fb[2][quant ? 1 : 4]; // bf16: the step's operands; quantized: its codes
+    u32x4 fb[2][quant ? 1 : 4]; // bf16: the step's operands; quantized: the codes of the lane's elements 16 s + 8 kq .. + 7 of quarter s
     uint32_t scales[2] = {0, 0};
-    // Quantized: lane half kq has the codes of elements 32 kq .. 32 kq + 31 of a step; quarter s of the step is eight of them, and so it
-    // is of the tokens.
     const char *const a_rd = ring + r * kLine;
     auto read_a = [&](int slot, int s, frag8 (&af)[4]) {
-        const char *p = a_rd + slot * cfg::A_SLOT + (((quant ? 4 * kq + s : 2 * s + kq) ^ swz) * 16);
+        const char *p = a_rd + slot * cfg::A_SLOT + (((2 * s + kq) ^ swz) * 16);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (i == 0 || i < live) af[i].u = *reinterpret_cast<const u32x4 *>(p + i * 32 * kLine);
@@ -631,20 +629,22 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
                 scales[ns] = *reinterpret_cast<const uint32_t *>(p + 64 * 64 + 256 * (kt & 1) + 4 * row);
                 if constexpr (FMT == 1) {
                     fb[ns][0] = *reinterpret_cast<const u32x4 *>(p + row * 64 + (((2 * (kt & 1) + kq) ^ ((r >> 2) & 3)) * 16));
-                } else {
-                    uint32_t c[2];
-                    __builtin_memcpy(c, __builtin_assume_aligned(p + row * 32 + 16 * (kt & 1) + 8 * kq, 8), 8);
-                    fb[ns][0].x = c[0], fb[ns][0].y = c[1];
+                } else { // (the lane's half of word s)
+                    fb[ns][0] = *reinterpret_cast<const u32x4 *>(p + row * 32 + 16 * (kt & 1));
                 }
             }
         }
     };
-    float scale[2] = {0.f, 0.f};
+    // The half of the aligned word that a scale is in, as v_perm_b32 wants it: (row * groups + group) odd or even (the parity of a
+    // row's place in its matrix is that of its place in the tile); with groups of 32 both groups of a step are in the word.
+    constexpr uint32_t kFirst = 0x01000C0Cu, kOther = 0x02020000u;
+    const uint32_t scale_sel = kFirst ^ (G & r & 1 ? kOther : 0u);
+    float scale[2][2] = {}; // of the first and of the second half of the step's elements
     auto operand = [&](int ns, int s) {
         frag8 b;
         if constexpr (FMT == 0) b.u = fb[ns][s];
-        else if constexpr (FMT == 1) b.u = dequant8(fb[ns][0][s], scale[ns]);
-        else b.u = dequant8_crumbs(fb[ns][0][s >> 1], s & 1, scale[ns]);
+        else if constexpr (FMT == 1) b.u = dequant8(fb[ns][0][s], scale[ns][s >> 1]);
+        else b.u = dequant8_crumbs(fb[ns][0][s], kq, scale[ns][s >> 1]);
         return b;
     };
     if constexpr (quant) {
@@ -668,11 +668,18 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // own weights are in registers: the next ones may come
         if constexpr (quant) {
             if ((kt & 1) && kt + 3 < nk) issue_codes((kt + 3) >> 1, (kt >> 1) & 1);
+            uint32_t sel[2];
+            sel[0] = scale_sel ^ (lg != 5 && ((kt * BK) >> lg & 1) ? kOther : 0u);
+            sel[1] = sel[0] ^ (lg == 5 ? kOther : 0u);
 #pragma unroll
             for (int ns = 0; ns < 2; ++ns) {
-                // the half of the aligned word that the row's scale is in (groups of 32: the two groups of the step)
-                const bool odd = lg == 5 ? kq : (((G & 1) ? r : 0) ^ ((kt * BK) >> lg)) & 1;
-                scale[ns] = __uint_as_float(odd ? scales[ns] & 0xFFFF0000u : scales[ns] << 16);
+                if constexpr (FMT == 1) { // lane half kq has words 4 kq .. 4 kq + 3 of the step's eight; it takes words 2 s + kq
+                    const auto first = __builtin_amdgcn_permlane32_swap(fb[ns][0].x, fb[ns][0].y, false, false);
+                    const auto second = __builtin_amdgcn_permlane32_swap(fb[ns][0].z, fb[ns][0].w, false, false);
+                    fb[ns][0] = u32x4{first[0], second[0], first[1], second[1]};
+                }
+#pragma unroll
+                for (int half = 0; half < 2; ++half) scale[ns][half] = __uint_as_float(__builtin_amdgcn_perm(0u, scales[ns], sel[half]));
             }
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -685,6 +685,57 @@ def test_forward_prefill_wide_tiles(B, LY, dxo, pair, T, E, k, d, f, group, hi):
     ctx.close()
 
 
+def _wide_phases(counts, hi, f, d, T, shared_f=0, hi_quantized=False):
+    """Whether the 128-row tiles of a call (segments below 512 rows, none in 256-row tiles) are 256 columns wide: gate/up, down."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = [-(-int(m) // 128) if m > 32 else 0 for m in counts]
+    shared = -(-T // 128) if shared_f else 0
+    quant = sum(t for e, t in enumerate(tiles) if hi_quantized or e not in hi)
+    line = 5 if 5 * quant >= sum(tiles) + shared else 11
+    narrow = [sum(tiles) * -(-columns // 128) + shared * -(-columns_shared // 128)
+              for columns, columns_shared in ((2 * f, 2 * shared_f), (d, d))]
+    return tuple(2 * n > line * n_cu for n in narrow)
+
+
+@pytest.mark.parametrize("pair,d,f,group", [
+    ("bf16-int4", 128, 5184, 32),    # gate/up in wide tiles: 2 K steps
+    ("bf16-int4", 384, 5184, 64),
+    ("bf16-int4", 1152, 5248, 128),  # 18 steps, an odd number of groups
+    ("int4-int2", 384, 5184, 64),
+    ("int4-int2", 1152, 5248, 128),
+    ("bf16-int4", 10368, 192, 32),   # down: 3 steps, then 11
+    ("bf16-int4", 10368, 704, 64),
+    ("int4-int2", 10368, 704, 64),
+])
+def test_prefill_outputs_do_not_depend_on_the_kind_of_tile(B, LY, dxo, pair, d, f, group):
+    """The same tokens in a call of many tiles (256 columns wide) and in one of few: the same bits, because the sums over K
+    have one order."""
+    import dataclasses
+    T, T_few, E, k = 320, 190, 4, 2
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group)
+    x = W.activations(wl, seed=17)
+    logits = np.random.default_rng(17).standard_normal((T, E)).astype(np.float32)
+    for n, wide in ((T, True), (T_few, False)):
+        counts = dxo.route(logits[:n], k)[2]
+        assert counts.min() > 32
+        assert _wide_phases(counts, [1], f, d, n, hi_quantized=pair == "int4-int2") == (wide and f > d, wide and d > f)
+    if pair == "int4-int2":
+        ctx, keep, _ = _quant_pair_layer(B, LY, dxo, wl, [1], 17, T)
+    else:
+        keep = Layer(B, LY, dxo, wl, [1], seed=17)
+        ctx = keep.ctx
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y_few = torch.full((T_few, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    LY.RoutingBuffers(T, E, k).route_forward(ctx, 0, ld, xd, y)
+    LY.RoutingBuffers(T_few, E, k).route_forward(ctx, 0, ld[:T_few].contiguous(), xd[:T_few].contiguous(), y_few)
+    sync()
+    assert np.isfinite(bf16_bits_to_f32(LY.device_to_bits(y))).all()
+    assert torch.equal(y[:T_few], y_few)
+    del keep
+    ctx.close()
+
+
 def test_forward_prefill_tile_list_at_its_bound(B, LY, dxo):
     """Segments of 129 rows in a context of exactly that many tokens: the list of row tiles has as many entries as the
     context holds (two per expert), every one of them in use."""
