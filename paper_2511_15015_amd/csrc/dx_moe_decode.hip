@@ -1576,11 +1576,13 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
 #pragma unroll
         for (int i = 0; i < NV / 8; ++i) touched |= a.table[min(2 * (64 * i + lane), a.E - 1)].fmt;
     }
-    int my_id = 0;
+    // Of this lane's pair (not routed: of the place of this number in the segments): the expert; whether it has one; its token
+    // (not routed).  Lanes that stand for an item of work: routed: whose pair is its expert's first; else whose place is the first
+    // or at an even distance from it, and those of them with a second place.
+    int my_id = 0, my_t = 0;
     float my_w = 0.f;
     bool has_pair = false;
-    unsigned long long first = 0; // lanes whose pair is its expert's first
-    int tasks = P;
+    unsigned long long first = 0, second = 0;
     if constexpr (ROUTED) {
         if constexpr (NV <= 8) dx_route_core::topk_rows16<NV>(v, a.k, lane, my_id, my_w);
         else dx_route_core::topk_rows16_filtered<NV, 6>(v, a.k, lane, my_id, my_w, (__attribute__((address_space(3))) int *)xs + wave * 64 * NV);
@@ -1590,43 +1592,61 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
             for (int j = 0; j < a.k; ++j) again |= lane >= 16 && __builtin_amdgcn_readlane(my_id, j) == my_id;
         }
         first = __ballot(has_pair && !again);
-        tasks = __popcll(first);
+    } else {
+        // every expert with a segment tells the lane of its first place (lane 63 stands for none: there are at most 32 places);
+        // all loads of a round are asked for before the first is waited for.  (dx_moe_forward, us, with groups of rows dealt out over
+        // places, each group looking for its place in the offsets, and now: two tokens with the same experts, 30B-shaped 22.5 and
+        // 19.5, 80B-shaped 26.5 and 21.3, 8 of 2048 x 768 21.7 and 19.0; 1024 experts of 2048 x 512, T = 1 17.9 and 14.6.)
+        static_assert(kFewTokens * DX_ROUTED_MAX_TOPK < 63, "a place per lane, and one more lane");
+        const int pair = a.perm[lane < P ? lane : 0];
+        const int last = a.offsets[a.E];
+        int told = 0; // 1 + expert
+        for (int e0 = 0; e0 < a.E; e0 += 256) { // wavefront-uniform
+            int o0[4], o1[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int el = min(e0 + 64 * i + lane, a.E - 1);
+                o0[i] = a.offsets[el], o1[i] = a.offsets[el + 1];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int el = e0 + 64 * i + lane;
+                const bool has = (el < a.E) & (0 <= o0[i]) & (o0[i] < o1[i]) & (o0[i] < P);
+                told |= __builtin_amdgcn_ds_permute(4 * (has ? o0[i] : 63), has ? el + 1 : 0);
+            }
+        }
+        const int end = min(P, last);
+        my_t = pair / a.k;
+        const unsigned long long starts = __ballot(told != 0), up_to = starts & (~0ull >> (63 - lane));
+        const int begin = up_to ? 63 - __builtin_clzll(up_to) : 0;
+        my_id = __shfl(told, begin, 64) - 1;
+        has_pair = up_to != 0ull && lane < end;
+        first = __ballot(has_pair && ((lane - begin) & 1) == 0);
+        second = first & __ballot(lane + 1 < end && ((starts >> (lane + 1 & 63)) & 1) == 0ull);
+        if (blockIdx.x == 0 && wave == 0 && has_pair) reinterpret_cast<int32_t *>(a.tiles)[lane] = my_id; // for the down kernel
     }
-    // ---- the wavefront's groups of rows: the shared expert's first, then those of the experts (not routed: places) in turn.  Of a
-    // group: the expert, its first place in the segments and its tokens (none: another place's group has them)
+    const int tasks = __popcll(first);
+    // ---- the wavefront's groups of rows: the shared expert's first, then those of the items in turn.  Of a group: the expert, its
+    // first place in the segments and its tokens
     const int shared_groups = a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0, groups = shared_groups + tasks * ((a.f + kFewRows - 1) / kFewRows);
     int e, pos, n_tok, t0, t1, row0;
     auto take = [&](int group) {
         e = a.E, pos = P, n_tok = a.T, t0 = 0, t1 = a.T - 1, row0 = group * kFewRows;
         if (group < shared_groups) return;
-        const int item = (group - shared_groups) % tasks;
+        const int item = (group - shared_groups) % tasks, before = __popcll(first & ((1ull << lane) - 1ull));
+        const int src = __builtin_ctzll(__ballot(((first >> lane) & 1ull) != 0ull && before == item));
         row0 = (group - shared_groups) / tasks * kFewRows;
+        e = __builtin_amdgcn_readlane(my_id, src);
         if constexpr (ROUTED) {
-            const int before = __popcll(first & ((1ull << lane) - 1ull));
-            const int src = __builtin_ctzll(__ballot(((first >> lane) & 1ull) != 0ull && before == item));
-            e = __builtin_amdgcn_readlane(my_id, src);
             pos = __popcll(__ballot(has_pair && my_id < e));
             n_tok = __popcll(__ballot(has_pair && my_id == e));
             t0 = src >> 4;
-        } else { // places in pairs from the segment's start
-            int begin = 0, end = 0;
-            pos = item, n_tok = 0;
-            for (int e0 = 0; e0 < a.E; e0 += 64) { // wavefront-uniform
-                const int el = e0 + lane < a.E ? e0 + lane : a.E - 1, o0 = a.offsets[el], o1 = a.offsets[el + 1];
-                const unsigned long long in = __ballot(o0 <= pos && pos < o1);
-                if (in != 0ull && n_tok == 0) {
-                    const int l = __builtin_ctzll(in);
-                    e = e0 + l, begin = __builtin_amdgcn_readlane(o0, l), end = __builtin_amdgcn_readlane(o1, l);
-                    n_tok = 1;
-                }
-            }
-            if (n_tok) {
-                if (row0 == 0 && lane == 0) reinterpret_cast<int32_t *>(a.tiles)[pos] = e;
-                end = end < P ? end : P;
-                n_tok = ((pos - begin) & 1) ? 0 : (pos + 1 < end ? 2 : 1);
-                t0 = a.perm[pos] / a.k;
-                t1 = n_tok == 2 ? a.perm[pos + 1] / a.k : t0;
-            }
+        } else {
+            pos = src;
+            n_tok = 1 + (int)((second >> src) & 1ull);
+            t0 = __builtin_amdgcn_readlane(my_t, src);
+            t1 = __builtin_amdgcn_readlane(my_t, src + n_tok - 1);
         }
     };
     const int stride = (int)gridDim.x * kFewWaves;
@@ -1669,38 +1689,36 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
     }
     __syncthreads();
     for (; group < groups;) { // wavefront-uniform
-        if (n_tok) {
-            const int N = e == a.E ? a.shared_f : a.f, lg = __builtin_ctz((unsigned)a.group);
-            const dx_handle *h = e == a.E ? a.shared : a.table + e;
-            const dx_handle hd = *h;
-            const u32x4 *x0 = xs + t0 * kFewPieces, *x1 = xs + t1 * kFewPieces;
-            float sum[kFewRows][2][2] = {};
-            auto rows = [&](auto fmt, auto nt) {
-                rows_of_few<decltype(fmt)::value, decltype(nt)::value>((gbytes)hd.w_gate, (gbytes)hd.w_up, (gbf16)hd.s_gate, (gbf16)hd.s_up,
-                                                                       row0, N, a.d, lg, x0, x1, lane, sum);
-            };
-            auto any = [&](auto nt) {
-                if (hd.fmt == DX_FMT_INT4G) rows(std::integral_constant<int, 1>{}, nt);
-                else if (hd.fmt == DX_FMT_INT2G) rows(std::integral_constant<int, 2>{}, nt);
-                else rows(std::integral_constant<int, 0>{}, nt);
-            };
-            if (n_tok == 1) any(std::integral_constant<int, 1>{});
-            else any(std::integral_constant<int, 2>{});
+        const int N = e == a.E ? a.shared_f : a.f, lg = __builtin_ctz((unsigned)a.group);
+        const dx_handle *h = e == a.E ? a.shared : a.table + e;
+        const dx_handle hd = *h;
+        const u32x4 *x0 = xs + t0 * kFewPieces, *x1 = xs + t1 * kFewPieces;
+        float sum[kFewRows][2][2] = {};
+        auto rows = [&](auto fmt, auto nt) {
+            rows_of_few<decltype(fmt)::value, decltype(nt)::value>((gbytes)hd.w_gate, (gbytes)hd.w_up, (gbf16)hd.s_gate, (gbf16)hd.s_up,
+                                                                   row0, N, a.d, lg, x0, x1, lane, sum);
+        };
+        auto any = [&](auto nt) {
+            if (hd.fmt == DX_FMT_INT4G) rows(std::integral_constant<int, 1>{}, nt);
+            else if (hd.fmt == DX_FMT_INT2G) rows(std::integral_constant<int, 2>{}, nt);
+            else rows(std::integral_constant<int, 0>{}, nt);
+        };
+        if (n_tok == 1) any(std::integral_constant<int, 1>{});
+        else any(std::integral_constant<int, 2>{});
 #pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                if (n < n_tok) {
-                    float hv[kFewRows];
+        for (int n = 0; n < 2; ++n) {
+            if (n < n_tok) {
+                float hv[kFewRows];
 #pragma unroll
-                    for (int i = 0; i < kFewRows; ++i) {
-                        const float g = dx_route_core::wave_sum(sum[i][0][n]), u = dx_route_core::wave_sum(sum[i][1][n]);
-                        hv[i] = g / (1.f + expf(-g)) * u;
-                    }
-                    if (lane == 0) {
-                        dx_bf16 *out = a.h + (size_t)(pos + n) * a.fmax + row0;
+                for (int i = 0; i < kFewRows; ++i) {
+                    const float g = dx_route_core::wave_sum(sum[i][0][n]), u = dx_route_core::wave_sum(sum[i][1][n]);
+                    hv[i] = g / (1.f + expf(-g)) * u;
+                }
+                if (lane == 0) {
+                    dx_bf16 *out = a.h + (size_t)(pos + n) * a.fmax + row0;
 #pragma unroll
-                        for (int i = 0; i < kFewRows; ++i)
-                            if (row0 + i < N) out[i] = (dx_bf16)float_to_bf16_rne(hv[i]);
-                    }
+                    for (int i = 0; i < kFewRows; ++i)
+                        if (row0 + i < N) out[i] = (dx_bf16)float_to_bf16_rne(hv[i]);
                 }
             }
         }

@@ -1502,6 +1502,33 @@ def test_forward_goes_by_offsets_and_perm_alone(B, LY, dxo, T, E, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,E,k,used", [(1, 1, 1, 1), (2, 5, 5, 2), (2, 64, 4, 3), (1, 65, 8, 8), (2, 256, 16, 20), (2, 300, 16, 300), (2, 700, 3, 4)])
+def test_forward_of_one_or_two_tokens_on_any_segments(B, LY, dxo, T, E, k, used):
+    """A caller's routing arrays with segments of any length (a token may name an expert more than once) and of any expert: the
+    kernel for one or two tokens finds the expert of every place from the offsets, 256 experts at a time."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=256, f=128, group=64)
+    g = np.random.default_rng(100 * E + k)
+    x = W.activations(wl, seed=83)
+    some = np.append(g.choice(E - 1, used - 1, replace=False), E - 1)      # the last expert among them
+    ids = some[g.integers(0, used, (T, k))].astype(np.int32)
+    w = g.random((T, k))
+    counts = np.bincount(ids.ravel(), minlength=E)
+    ly = Layer(B, LY, dxo, wl, [0, E - 1], seed=83)
+    rb = ly.rb
+    rb.ids.copy_(torch.from_numpy(ids))
+    rb.w.copy_(torch.from_numpy(w.astype(np.float32)))
+    rb.offsets.copy_(torch.from_numpy(np.append(0, np.cumsum(counts)).astype(np.int32)))
+    rb.perm.copy_(torch.from_numpy(np.argsort(ids.ravel(), kind="stable").astype(np.int32)))
+    y = torch.full((T, wl.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    rb.forward(ly.ctx, 0, LY.bits_to_device(x), y, None, T)
+    sync()
+    y_ref = dxo.moe_forward(ly.versions, wl.d, wl.f, wl.group, x, ids, w.astype(np.float32).astype(np.float64))
+    yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+    assert (np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)).max() <= 2 * REL_L2_TOL
+    ly.ctx.close()
+
+
 @pytest.mark.parametrize("T", [2, 40, 200])
 def test_forward_takes_tokens_that_start_inside_16_bytes(B, LY, dxo, T):
     """x as a view that starts 4 bytes into a buffer: the same bits as an aligned copy where the streaming kernels run in both
