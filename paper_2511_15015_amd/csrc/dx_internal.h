@@ -177,6 +177,7 @@ struct dx_fwd_args {
     int T, E, k, d, f, group, shared_f, fmax;
     int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
     int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
+    int any_quantized; // some routed expert of the table may be (a caller's table: unknown)
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     // A list that the gate/up kernel of the streamed experts leaves for the kernels behind it, or null: mixed batches (m_small
     // is a bound): the row tiles of the tiled experts; up to DX_FEW_TOKENS tokens on a caller's

@@ -44,6 +44,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -1402,10 +1403,11 @@ __global__ __launch_bounds__(kThreads) void k_stream_routed(dx_fwd_args a, dx_ro
 // in LDS as on the few weights, and leaves O to a combine kernel.  With so few pairs there is nothing to partition and
 // nothing that a matrix instruction would share: a lane multiplies and adds what it has loaded.  A wavefront asks for all
 // its weights before it uses the first; the sums over lanes are DPP steps.
-// Whole calls, us, with k_stream for gate/up and a down kernel of 16 columns per block, and now, T = 1: 30B-shaped 28.0 and 23.0 (gate/up
-// 17.9 -> 15.4, down 10.2 -> 7.5; int4/int2 21.9 and 16.1), 80B-shaped 37.2 and 23.2 (27.4 -> 15.6), 16 experts of 4096 x 6400 64.0 and 52.4
-// (with a routing kernel before), 8 of 4096 x 14336 120 and 105, 256 of 7168 x 2048 112 and 86.  T = 2: 32.4 and 30.8, 38.2 and 31.2, 96.7 and 73.0.
-// Three tokens: tokens that share an expert read a strip of W_down once each, and k_stream once for all (30B-shaped 40.0, and 43.5).
+// Whole calls, us, with the streaming kernels and with these, on weights that no cache holds, a quarter of the experts bf16: one token,
+// 30B-shaped 27.9 and 17.8 (int4/int2 26.3 and 15.4), 80B-shaped 55 and 18.9, 16 experts of 4096 x 6400 60 and 38.5, 8 of 4096 x 14336 108 and
+// 71, 256 of 7168 x 2048 116 and 93; two tokens 31.8 and 25.0, 45.8 and 27.3, 93 and 65.  Three tokens with k_stream for gate/up, k_stream and
+// k_down_few behind it: 30B-shaped 36.4 and 32.5, but an expert of all three is read three times: 16 of 4096 x 6400 60.6 and 68.4, 4 of
+// 4096 x 4096 70.9 and 80.5.
 // Which expert a pair belongs to and where its row of H is: ROUTED (the gate/up kernel writes the routing
 // arrays itself): from the ids, whose segments are in increasing order.  Else the arrays are the caller's: from `offsets`
 // and `perm` alone, as in the other kernels, in any order inside a segment (the gate/up kernel leaves the expert of every
@@ -2047,32 +2049,56 @@ void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t st
     });
 }
 
-// Whether the down projection and the combine run in k_down_few.  A block reads its token's strips by itself on a grid of
-// d / 16 blocks per token, and an expert that both tokens select is read twice; k_stream spreads the bytes over the whole
-// chip and reads an expert once.  So: at most 240 chunks of a strip per compute unit of the chip (blocks that leave
-// compute units idle count accordingly), and for two tokens at least twice as many experts as pairs, unless a block needs
-// one round of loads only and all blocks run at once (latency).  Whole calls, us, k_stream<down> and this, T = 1: 30B-shaped (96 chunks) 31.3 and
-// 25.7, 80B-shaped (88) 53 and 36, 60 experts of 2048 x 1408 with a shared one (120) 27.6 and 25.3, 16 of 4096 x 6400 (100)
-// 54.9 and 45.4, 8 of 4096 x 14336 (224) 115.8 and 109.4; 8 of 2048 x 2048, top-8 (256) 33.7 and 35.6, 32 of 1024 x 2048,
-// top-8 (512) 26.6 and 30.1.  T = 2, every expert selected by both: 4 of 4096 x 4096 96 and 118, 8 of 2048 x 768 (one
-// round, 256 blocks) 29.7 and 27.1, 4 of 4096 x 2048, top-2 (one round, 512 blocks) 34.8 and 36.4.
-bool takes_few(const dx_fwd_args &a, int n_cu)
+// groups of rows of k_gate_up_few, at most (no expert of both tokens)
+long few_groups(const dx_fwd_args &a)
 {
-    if (a.T > kFewTokens || a.k >= kFewTasks || a.f % 128 || (a.shared && a.shared_f % 128)) return false;
-    const int tasks = a.k + (a.shared ? 1 : 0), split = few_split(tasks);
-    const int nc = a.f / 128, nc_shared = a.shared ? a.shared_f / 128 : 0, most = nc > nc_shared ? nc : nc_shared;
-    if ((long)(a.k * nc + nc_shared) * n_cu > 240L * (a.d / 16) * a.T) return false;
-    const bool one_round = tasks * split <= kWaves && (most + split - 1) / split <= 6 && a.d / 16 * a.T <= n_cu;
-    return a.T == 1 || 2 * a.T * a.k <= a.E || one_round;
+    auto of = [](int f) { return (f + kFewRows - 1) / kFewRows; };
+    return (a.shared ? of(a.shared_f) : 0) + (long)a.T * a.k * of(a.f);
 }
 
-// Whether gate/up run in k_gate_up_few (few: what takes_few says).
-bool few_gate_up(const dx_fwd_args &a, bool few) { return few && a.d % 128 == 0 && a.d <= kFewMaxK; }
+// Which kernels a call of one or two tokens takes: down, that the down projection and the combine run in k_down_few, and gate_up,
+// that k_gate_up_few is in front of it.  Figures: whole calls, us, the streaming kernel and this one, a quarter of the experts bf16.
+// down: blocks of 8 columns read W_down by themselves, k_stream spreads the bytes over the whole chip and reads an expert once.  So at
+// most 512 chunks of W_down (8 rows of 128) per compute unit where blocks are too few: one token, top-8, f = 4096, d = 1024 (512) 37.2
+// and 34.7, d = 512 (1024) 30.6 and 30.7, d = 128 (4096) 24.6 and 25.5.  And two tokens that may well have the same experts (less than
+// twice as many as pairs) at most 128 chunks per compute unit: all experts the same, 8 of 2048 x 1024 (128) 28.1 and 25.4, 4 of
+// 4096 x 2048, top-2 (128) 30.9 and 29.5, 8 of 4096 x 2048, top-4 (256) 44.9 and 47.2, 16 of 4096 x 1024, top-16 (512) 64 and 84.
+// gate_up: where the streaming kernel needs a routing kernel in front or more than one round for K (two tokens: 64 experts of 4096 x 1024,
+// top-4 41.8 and 31.5, 1024 of 2048 x 512 40.2 and 25.9), except layers without a quantized expert, whose bytes it streams faster (8 of
+// 4096 x 14336 208 and 225).  Else as long as the groups of rows are at most 1.4 times the wavefronts that the chip holds: two tokens,
+// 30B-shaped (1.33) 26.2 and 24.9, 64 of 2048 x 1024, top-8 (1.78) 29.7 and 30.6, 64 of 2048 x 2048, top-8 (3.6) 44.4 and 46.8; rows shorter
+// than a step, which leave lanes without elements, count for more there (32 of 1024 x 512, top-16 22.7 and 25.8, 64 of 512 x 512, top-8 16.0 and 17.2).
+struct few_choice {
+    bool gate_up, down;
+};
+few_choice takes_few(const dx_fwd_args &a, int n_cu)
+{
+    if (a.T > kFewTokens || a.k >= kFewTasks || a.f % 128 || (a.shared && a.shared_f % 128)) return {false, false};
+    const long chunks = (long)a.k * (a.f / 128) + (a.shared ? a.shared_f / 128 : 0), blocks = (long)(a.d / kFewCols) * a.T;
+    const bool down = chunks * n_cu <= 512 * blocks && (a.T == 1 || 2 * a.T * a.k <= a.E || chunks * blocks <= 128L * n_cu);
+    if (!down || a.d % 128 || a.d > kFewMaxK) return {false, down};
+    const int nc = a.d / chunk_of(a.group, a.d, a.d);
+    const bool one_launch = pick_split(nc, nc).mode == kWhole && a.E <= kRoutedExperts; // the streaming kernel would route by itself
+    if (a.E > kRoutedExperts || (!one_launch && a.any_quantized)) return {true, true};
+    const long rows = few_groups(a) * (a.T == 2 && a.d < kFewStep ? kFewStep / a.d : 1);
+    return {5 * rows <= 7L * kFewBlocks * kFewWaves * n_cu, true};
+}
+
+// Wavefronts of a block of k_down_few: as many as let all blocks run at once (a compute unit holds 20 at 100 registers), in one round
+// of items more where that leaves none without work.  T = 2, us, one wavefront to an item (nine to 17 items) and now: 64 experts of
+// 2048 x 768, top-16 40.9 and 38.0, 64 of 4096 x 512, top-16 60.0 and 52.1, 64 of 4096 x 1024, top-8 and a shared one 59.3 and 56.8.
+int few_down_waves(const dx_fwd_args &a, int n_cu)
+{
+    const int tasks = a.k + (a.shared ? 1 : 0), items = tasks * few_split(tasks);
+    const int per_cu = ((a.d / kFewCols) * a.T + n_cu - 1) / n_cu, most = std::max(4, std::min(kFewDownWaves, 20 / per_cu));
+    const int least = (items + most - 1) / most;
+    auto waves = [&](int rounds) { return (items + rounds - 1) / rounds; };
+    return waves(least) * least <= waves(least + 1) * (least + 1) ? waves(least) : waves(least + 1);
+}
 
 void launch_few(const dx_fwd_args &a, int n_cu, hipStream_t s, hipEvent_t start, hipEvent_t stop, const dx_route_io *r)
 {
-    const long waves = (a.shared ? (a.shared_f + kFewRows - 1) / kFewRows : 0) + (long)a.T * a.k * ((a.f + kFewRows - 1) / kFewRows);
-    const long fits = (long)kFewBlocks * n_cu, blocks = (waves + kFewWaves - 1) / kFewWaves;
+    const long fits = (long)kFewBlocks * n_cu, blocks = (few_groups(a) + kFewWaves - 1) / kFewWaves;
     const dim3 grid((unsigned)(blocks < fits ? blocks : fits)), block(64 * kFewWaves);
     if (!r) launch(k_gate_up_few<8, false>, grid, block, s, start, stop, a, dx_route_io{});
     else if (a.E <= 128) launch(k_gate_up_few<8, true>, grid, block, s, start, stop, a, *r);
@@ -2113,13 +2139,13 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
     const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
     const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
     a.m_small = mixed ? 32 : 0x7fffffff;
-    const bool few = !mixed && takes_few(a, n_cu);
-    if (!mixed && (!few || r)) a.tiles = nullptr;
+    const few_choice few = mixed ? few_choice{false, false} : takes_few(a, n_cu);
+    if (!mixed && (!few.down || r)) a.tiles = nullptr;
     a.m_big = mixed ? big_tile_formats(a, n_cu) : 0;
     a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
-        *routed = !mixed && (few_gate_up(a, few) || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
+        *routed = !mixed && (few.gate_up || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
@@ -2132,11 +2158,10 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         hipEvent_t ev[8] = {};
         if (marks)
             for (int i = 0; i < 8; ++i) ev[i] = marks[i];
-        if (few_gate_up(a, few)) launch_few(a, n_cu, s, ev[0], ev[1], r);
+        if (few.gate_up) launch_few(a, n_cu, s, ev[0], ev[1], r);
         else launch_stream<false>(a, grid, s, ev[0], ev[1], r);
-        if (few) {
-            const int tasks = a.k + (a.shared ? 1 : 0), items = tasks * few_split(tasks);
-            const dim3 strips(a.d / kFewCols, a.T), block(64 * (items <= kFewDownWaves ? items : (items + 1) / 2));
+        if (few.down) {
+            const dim3 strips(a.d / kFewCols, a.T), block(64 * few_down_waves(a, n_cu));
             if (r) launch(k_down_few<true>, strips, block, s, ev[5], ev[2], a);
             else launch(k_down_few<false>, strips, block, s, ev[5], ev[2], a);
             combined = true;

@@ -1397,7 +1397,7 @@ def test_decode_groups_and_chunk_counts(B, LY, dxo, pair, T, d, f, group):
     ("bf16-int4", 1, 32, 16, 256, 1792, 32, 256),  # more experts than wavefronts, K in three rounds of six chunks
     ("bf16-int4", 2, 4, 3, 256, 128, 128, 384),    # tokens that share experts: places inside a segment
     ("bf16-int4", 2, 64, 16, 2048, 128, 128, 128), # the most it takes: 32 pairs, 17 tasks to a block
-    ("bf16-int4", 2, 4, 4, 4096, 1024, 128, 0),    # every expert selected by both tokens: the streaming kernel
+    ("bf16-int4", 2, 4, 4, 4096, 1024, 128, 0),    # every expert selected by both tokens: the most chunks it takes then
     ("bf16-int4", 1, 8, 8, 128, 4096, 128, 0),     # too much for its eight blocks: the streaming kernel
     ("bf16-int4", 3, 16, 16, 128, 256, 128, 0),    # a token more than it takes
     ("int4-int2", 1, 8, 2, 256, 640, 64, 0),
@@ -1449,6 +1449,45 @@ def test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, sh
 def test_forward_of_one_or_two_tokens_row_by_row(B, LY, dxo, pair, T, E, k, d, f, group, shared_f):
     """The edges of the gate/up kernel for one and two tokens, as above."""
     test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, shared_f)
+
+
+@pytest.mark.parametrize("pair,T,E,k,d,f,group,shared_f", [
+    ("bf16-int4", 2, 4, 4, 4096, 1152, 128, 0),    # a chunk too many for experts of both tokens: the streaming kernels
+    ("bf16-int4", 2, 32, 8, 256, 256, 64, 0),      # short rows of two tokens: gate/up streams
+    ("bf16-int4", 1, 8, 8, 256, 1024, 128, 0),     # one token, few blocks
+    ("int4-int2", 1, 8, 8, 128, 1024, 128, 0),     # the most chunks for the fewest blocks
+    ("bf16-int4", 1, 8, 8, 6144, 128, 64, 128),    # nine items, wavefronts with three each
+    ("bf16-int4", 2, 16, 7, 4096, 128, 128, 128),  # two tokens, four wavefronts to a block
+    ("bf16-int4", 2, 40, 16, 2048, 128, 128, 0),   # 16 items, eight wavefronts
+])
+def test_forward_of_one_or_two_tokens_choice_of_kernels(B, LY, dxo, pair, T, E, k, d, f, group, shared_f):
+    """Both sides of the lines between the streaming kernels and those for one and two tokens, and blocks of fewer wavefronts than
+    items, as above."""
+    test_forward_of_one_or_few_tokens(B, LY, dxo, pair, T, E, k, d, f, group, shared_f)
+
+
+@pytest.mark.parametrize("T,resident", [(1, [0, 1]), (2, [0, 1]), (2, [1])])
+def test_forward_of_one_or_two_tokens_without_quantized_experts(B, LY, dxo, T, resident):
+    """Rows that the streaming kernel cannot take in one round: layers without a quantized expert stream gate/up where there are
+    many rows; route_forward, the separate calls and a caller's own table give the oracle's y."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=2, k=2, d=2176, f=3328, group=128)
+    x, logits = W.layer_inputs(wl, seed=87)
+    ly = Layer(B, LY, dxo, wl, resident, seed=87)
+    ids, w, *_ = dxo.route(logits, wl.k)
+    y_ref = dxo.moe_forward(ly.versions, wl.d, wl.f, wl.group, x, ids, w)
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    for call in ("one", "two", "table"):
+        y = torch.full((T, wl.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        if call == "one":
+            ly.rb.route_forward(ly.ctx, 0, ld, xd, y)
+        else:
+            ly.rb.route(ly.ctx, 0, ld)
+            ly.rb.forward(ly.ctx, 0, xd, y, table=None if call == "two" else ly.ctx.dx_handle_table(0))
+        sync()
+        yg = bf16_bits_to_f32(LY.device_to_bits(y)).astype(np.float64)
+        assert (np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)).max() <= 2 * REL_L2_TOL
+    ly.ctx.close()
 
 
 @pytest.mark.parametrize("T,E,k", [(1, 100, 8), (2, 512, 16)])
