@@ -150,9 +150,10 @@ struct dx_tile_row {
 struct dx_tile_head {
     int n_routed, n_shared;  // 128-row tiles of the routed experts, of the shared one
     int n_quant;             // of the former, those of quantized experts
+    int n_single;            // and those of experts with one only
     int n_big, n_big_shared; // 256-row tiles
     int n_cu;
-    int unused[2];
+    int unused;
 };
 // most row tiles a call of T tokens can have (a routed expert has ceil(m / 128) of them, and none up to m_small tokens)
 inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)

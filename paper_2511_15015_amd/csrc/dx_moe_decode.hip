@@ -989,7 +989,7 @@ struct partition_lds {
     uint32_t cum[kMaxExperts + 1];
     int seg_start[kMaxExperts], seg_tokens[kMaxExperts];
     uint32_t wave_tot[kWaves];
-    int wave_cnt[kWaves], quant_cnt[kWaves];
+    int wave_cnt[kWaves], quant_cnt[kWaves], single_cnt[kWaves];
     int e_first;
 };
 
@@ -1057,7 +1057,7 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
     __syncthreads();
 }
 
-// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot, wave_cnt and quant_cnt are free).  Experts above
+// The list of row tiles for the tile kernels that follow (one block; the counts of the wavefronts in pl are free).  Experts above
 // m_small tokens.
 __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
 {
@@ -1071,7 +1071,7 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
         return (a.m_big >> fmt) & 1 ? m / DX_BIG_ROWS * DX_BIG_ROWS : 0;
     };
     auto tiles = [](int rows) { return (rows + DX_TILE_ROWS - 1) / DX_TILE_ROWS; };
-    int local = 0, local_big = 0, local_quant = 0; // row tiles; 256-row tiles; of the former, those of quantized experts
+    int local = 0, local_big = 0, local_quant = 0, local_single = 0; // row tiles; 256-row tiles; of the former, of quantized experts, of experts with one
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
         if (e < a.E) {
@@ -1080,22 +1080,24 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
             local += t;
             local_big += lead / DX_BIG_ROWS;
             local_quant += fmt == DX_FMT_BF16 ? 0 : t;
+            local_single += t == 1 && lead == 0;
         }
     }
     const int inc = dx_route_core::wave_scan_inclusive(local), inc_big = dx_route_core::wave_scan_inclusive(local_big);
-    const int inc_quant = dx_route_core::wave_scan_inclusive(local_quant);
+    const int inc_quant = dx_route_core::wave_scan_inclusive(local_quant), inc_single = dx_route_core::wave_scan_inclusive(local_single);
     if (lane == 63) {
         pl.wave_tot[wave] = (uint32_t)inc;
         pl.wave_cnt[wave] = inc_big;
         pl.quant_cnt[wave] = inc_quant;
+        pl.single_cnt[wave] = inc_single;
     }
     __syncthreads();
-    int base = 0, total = 0, base_big = 0, total_big = 0, total_quant = 0;
+    int base = 0, total = 0, base_big = 0, total_big = 0, total_quant = 0, total_single = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         const int t = (int)pl.wave_tot[w], tb = pl.wave_cnt[w];
         if (w < wave) base += t, base_big += tb;
-        total += t, total_big += tb, total_quant += pl.quant_cnt[w];
+        total += t, total_big += tb, total_quant += pl.quant_cnt[w], total_single += pl.single_cnt[w];
     }
     const int T_tiled = a.shared && a.T > a.m_small ? a.T : 0, lead_shared = big_rows(T_tiled, DX_FMT_BF16);
     const int n_shared = tiles(T_tiled - lead_shared), n_big_shared = lead_shared / DX_BIG_ROWS;
@@ -1111,7 +1113,7 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
     const int seg0 = a.T * a.k;
     for (int mt = tid; mt < n_shared; mt += kThreads) rows[total + mt] = dx_tile_row{a.E, mt, T_tiled - lead_shared, seg0 + lead_shared};
     for (int mt = tid; mt < n_big_shared; mt += kThreads) big[total_big + mt] = dx_tile_row{a.E, mt, lead_shared, seg0};
-    if (tid == 0) *a.tiles = dx_tile_head{total, n_shared, total_quant, total_big, n_big_shared, (int)gridDim.x, {}};
+    if (tid == 0) *a.tiles = dx_tile_head{total, n_shared, total_quant, total_single, total_big, n_big_shared, (int)gridDim.x, 0};
 }
 
 // The expert of every place in the segments, for the down kernel of a call of a few tokens (one block).

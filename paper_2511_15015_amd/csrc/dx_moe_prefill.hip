@@ -115,19 +115,25 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
 // This block's tile.  The row tiles of all experts are in a.tiles (written by the gate/up kernel of the streamed experts that
 // runs in front, because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us): the routed
 // experts', the shared one's, the 256-row tiles behind them.  Each XCD takes an eighth of the list.
-// Wide or narrow: a compute unit holds two tiles of either kind, and a wide one takes nearly as long as two rounds of narrow ones
-// (loads of more than one step do not fit beside it), so few tiles are better narrow.  Many are better wide, and quantized ones
-// much earlier, because what they gain is the expansion.  Gate/up kernels, us, narrow and wide, by narrow tiles per compute
-// unit: 30B-shaped layer bf16/int4 (nearly all row tiles bf16) 2.1 61 and 67, 4.2 90 and 112, 6.6 136 and 131, 9.8 201 and 185, 12.7 260
-// and 235; int4/int2 6.6 170 and 146; 80B-shaped (a quarter quantized) 3.0 85 and 74; 16 experts of 4096 x 6400 (half
-// quantized) 5.5 237 and 223, 10 407 and 321.
+// Wide or narrow: a compute unit holds two tiles of either kind.  Figures: the phase's kernels, us, narrow and wide, by narrow tiles
+// per compute unit; the same lines hold for both phases.
+//   Quantized weights gain by the expansion as soon as there is more than one round: all int4, 128 experts of 2048 x 768, 110 rows each, gate/up
+//   2.6 76 and 75, 4.3 123 and 122, 6.0 153 and 134, down 3.4 48 and 40, 8.0 96 and 78; 8 of 4096 x 4096, down 2.0 96 and 102, 3.0 141 and 141.
+//   bf16 weights gain by the loads, and a round of wide tiles takes as long as 1.7 to 1.9 of narrow ones: one for two of them (3 to 4) 8 of
+//   4096 x 4096, gate/up 4.0 188 and 157, down 2.0 90 and 104, 3.0 126 and 137; two for three (4 to 6) 64 of 2048 x 1536, gate/up 6.0 191 and 224,
+//   30B-shaped 4.5 128 and 145, down 4.5 71 and 77; two for four and more (from 6) 30B-shaped 6.8 167 and 162, 10.5 233 and 219, 12.9 273 and 253,
+//   down 7.6 100 and 91.
+//   Mixed: as quantized ones from 45 % of the row tiles on (half: 4.0 109 and 96, 6.0 162 and 161), and from 20 % on where most experts have several
+//   row tiles, which ask for the same weights (80B-shaped, a third, 3.2 123 and 106, 5.2 168 and 149, down 6.4 81 and 70); with one row tile to an expert bf16
+//   weights come from memory alone, and narrow tiles take in more (a third, 4.3 132 and 157, 6.0 174 and 185).
 template <bool DOWN>
 __device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, bool &wide)
 {
     const int n = uniform_load(&a.tiles->n_routed), n_shared = uniform_load(&a.tiles->n_shared), n_cu = uniform_load(&a.tiles->n_cu);
     const int narrow_tiles = n * columns_of<DOWN>(a, a.f, BN) + n_shared * columns_of<DOWN>(a, a.shared_f, BN);
-    const bool quant_rich = 5 * uniform_load(&a.tiles->n_quant) >= n + n_shared;
-    wide = 2 * narrow_tiles > (quant_rich ? 5 : 11) * n_cu;
+    const int quant = uniform_load(&a.tiles->n_quant), single = uniform_load(&a.tiles->n_single);
+    const bool as_quantized = 20 * quant >= 9 * (n + n_shared) || (5 * quant >= n + n_shared && 5 * single <= 2 * n);
+    wide = as_quantized ? 2 * narrow_tiles > 5 * n_cu : narrow_tiles > 6 * n_cu || (narrow_tiles > 3 * n_cu && narrow_tiles <= 4 * n_cu);
     const int width = wide ? BNW : BN, ntn = columns_of<DOWN>(a, a.f, width), ntn_shared = columns_of<DOWN>(a, a.shared_f, width);
     const uint32_t routed = (uint32_t)(n * ntn), total = routed + (uint32_t)(n_shared * ntn_shared), per_xcd = (total + 7) / 8;
     const uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);

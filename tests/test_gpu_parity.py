@@ -643,7 +643,7 @@ def test_forward_prefill_tiles_k_steps_and_groups(B, LY, dxo, pair, T, E, k, d, 
 
 
 @pytest.mark.parametrize("pair,T,E,k,d,f,group,hi", [
-    # gate/up: 40.5 column tiles, 2 K steps; then 82 column tiles and an odd number of groups per row in the down projection
+    # gate/up: 40.5 column tiles, 2 K steps; then 82 column tiles, 6 steps and an odd number of groups per row
     ("bf16-int4", 320, 4, 2, 128, 5184, 64, [1]),
     ("bf16-int4", 170, 5, 2, 384, 10496, 128, [0, 2]),
     ("int4-int2", 320, 4, 2, 128, 5184, 64, [1]),
@@ -662,9 +662,7 @@ def test_forward_prefill_wide_tiles(B, LY, dxo, pair, T, E, k, d, f, group, hi):
     print(f"wide tiles {pair} T={T} E={E} k={k} d={d} f={f} group={group}", flush=True)
     x, logits = W.layer_inputs(wl, seed=13)
     ids, w, counts, offsets, perm = dxo.route(logits, k)
-    row_tiles = sum(-(-int(m) // 128) for m in counts if m > 32)
-    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    assert 2 * row_tiles * max(f // 64, d // 128) > (11 if len(hi) == E else 5) * n_cu, "the call has to be one of many tiles"
+    assert _wide_phases(counts, hi, f, d, T, hi_quantized=pair == "int4-int2") == (f > d, d > f)
     if pair == "int4-int2":
         ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 13, T)
     else:
@@ -691,10 +689,78 @@ def _wide_phases(counts, hi, f, d, T, shared_f=0, hi_quantized=False):
     tiles = [-(-int(m) // 128) if m > 32 else 0 for m in counts]
     shared = -(-T // 128) if shared_f else 0
     quant = sum(t for e, t in enumerate(tiles) if hi_quantized or e not in hi)
-    line = 5 if 5 * quant >= sum(tiles) + shared else 11
+    all_tiles = sum(tiles) + shared
+    as_quantized = 20 * quant >= 9 * all_tiles or (5 * quant >= all_tiles and 5 * tiles.count(1) <= 2 * sum(tiles))
     narrow = [sum(tiles) * -(-columns // 128) + shared * -(-columns_shared // 128)
               for columns, columns_shared in ((2 * f, 2 * shared_f), (d, d))]
-    return tuple(2 * n > line * n_cu for n in narrow)
+    return tuple(2 * n > 5 * n_cu if as_quantized else n > 6 * n_cu or 3 * n_cu < n <= 4 * n_cu for n in narrow)
+
+
+@pytest.mark.parametrize("pair,d,f,group,shared_f", [
+    ("int4-int2", 384, 5184, 64, 0),      # gate/up: 6 K steps, so every slot of codes is filled again
+    ("int4-int2", 10368, 512, 128, 0),    # down: 8 steps
+    ("int4-int2", 10368, 704, 64, 0),     # 11
+    ("bf16-int4", 10368, 704, 32, 0),
+    ("bf16-int4", 128, 3840, 64, 5184),   # gate/up with a shared expert of another width, half a tile of columns at its end
+    ("bf16-int4", 10368, 192, 64, 320),   # down: 5 steps for the shared expert, 3 for the others
+])
+def test_forward_prefill_wide_tiles_many_steps_and_shared_expert(B, LY, dxo, pair, d, f, group, shared_f):
+    """As above: rings that are filled several times, and the shared expert's tiles behind the routed ones'."""
+    import dataclasses
+    T, E, k, hi = 320, 4, 2, [1]
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=group, shared_f=shared_f)
+    print(f"wide tiles {pair} d={d} f={f} group={group} shared_f={shared_f}", flush=True)
+    x = W.activations(wl, seed=19)
+    logits = np.random.default_rng(19).standard_normal((T, E)).astype(np.float32)
+    ids, w, counts, offsets, perm = dxo.route(logits, k)
+    assert _wide_phases(counts, hi, f, d, T, shared_f, hi_quantized=pair == "int4-int2") == (f > d, d > f)
+    shared = None
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 19, T)
+    else:
+        keep = Layer(B, LY, dxo, wl, hi, seed=19, shared=W.shared_master(wl, 19, 0) if shared_f else None)
+        ctx, versions, shared = keep.ctx, keep.versions, keep.shared
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    LY.RoutingBuffers(T, E, k).route_forward(ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+    sync()
+    tokens = np.unique(np.append(np.arange(0, T, 7), T - 1))
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f, tokens=tokens)
+    bits = LY.device_to_bits(y)
+    assert np.isfinite(bf16_bits_to_f32(bits)).all()
+    assert rel_l2(bits[tokens], y_ref) <= REL_L2_TOL
+    used = assert_elementwise(dxo, bits[tokens], y_ref, versions, group, x, ids, w, shared=shared, tokens=tokens, T_call=T)
+    print(f"  element-wise: largest error = {used:.2f} of its bound", flush=True)
+    del keep
+    ctx.close()
+
+
+@pytest.mark.parametrize("E,k,T,d,f,hi,wide", [
+    (4, 1, 250, 128, 6144, [0, 1, 2, 3], (False, False)),   # bf16, 4 x 96 narrow tiles: 1.5 per compute unit
+    (8, 1, 500, 128, 8192, list(range(8)), (True, False)),  # 4
+    (8, 1, 500, 128, 8256, list(range(8)), (False, False)), # a little more than 4
+    (12, 1, 750, 128, 8192, list(range(12)), (False, False)),  # 6
+    (12, 1, 750, 128, 8256, list(range(12)), (True, False)),   # a little more than 6
+    (8, 1, 500, 128, 9216, [0, 1, 2, 3, 4, 5], (False, False)),  # a quarter quantized, a row tile each, 4.5
+    (4, 1, 900, 128, 9216, [0, 1, 2], (True, False)),          # the same with two row tiles each
+])
+def test_prefill_lines_between_narrow_and_wide_tiles(B, LY, dxo, E, k, T, d, f, hi, wide):
+    """Calls on both sides of every line between the kinds of tiles, rows evenly spread: every 16th token against the oracle."""
+    import dataclasses
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k, d=d, f=f, group=64)
+    x = W.activations(wl, seed=23)
+    logits = np.random.default_rng(23).standard_normal((T, E)).astype(np.float32)
+    logits[np.arange(T), np.arange(T) % E] += 100.0
+    ids, w, counts, offsets, perm = dxo.route(logits, k)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert _wide_phases(counts, hi, f, d, T) == wide
+    ly = Layer(B, LY, dxo, wl, hi, seed=23)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ly.rb.route_forward(ly.ctx, 0, torch.from_numpy(logits).cuda(), LY.bits_to_device(x), y)
+    sync()
+    tokens = np.arange(0, T, 16)
+    y_ref = dxo.moe_forward(ly.versions, d, f, 64, x, ids, w, tokens=tokens)
+    assert rel_l2(LY.device_to_bits(y)[tokens], y_ref) <= REL_L2_TOL
+    ly.ctx.close()
 
 
 @pytest.mark.parametrize("pair,d,f,group", [
