@@ -61,6 +61,18 @@ __device__ __forceinline__ u32x4 dequant8(uint32_t word, float scale)
     return u32x4{p[0], p[1], p[2], p[3]};
 }
 
+// The same from 16ths of the scale (exact: a bf16 scale has eight significant bits): the nibbles as the upper halves of signed bytes,
+// which the conversion takes out of their word by itself.
+__device__ __forceinline__ u32x4 dequant8_bytes(uint32_t word, float scale16)
+{
+    const uint32_t even = (word << 4) & 0xF0F0F0F0u, odd = word & 0xF0F0F0F0u;
+    uint32_t p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        p[i] = pack_bf16((float)(int8_t)(even >> (8 * i)) * scale16, (float)(int8_t)(odd >> (8 * i)) * scale16);
+    return u32x4{p[0], p[1], p[2], p[3]};
+}
+
 // 8 two-bit codes (bits 16*half .. of `word`) times scale -> 8 bf16 in element order
 __device__ __forceinline__ u32x4 dequant8_crumbs(uint32_t word, int half, float scale)
 {
@@ -70,6 +82,13 @@ __device__ __forceinline__ u32x4 dequant8_crumbs(uint32_t word, int half, float 
     for (int i = 0; i < 4; ++i)
         p[i] = pack_bf16((float)((int)(h << (30 - 4 * i)) >> 30) * scale, (float)((int)(h << (28 - 4 * i)) >> 30) * scale);
     return u32x4{p[0], p[1], p[2], p[3]};
+}
+
+// 8 two-bit codes at bits at[0..7] of `word` times scale -> 8 bf16 in element order
+__device__ __forceinline__ u32x4 dequant8_crumbs_at(uint32_t word, const uint32_t (&at)[8], float scale)
+{
+    auto code = [&](int j) { return (float)(int)__builtin_amdgcn_sbfe((int)word, at[j], 2) * scale; };
+    return u32x4{pack_bf16(code(0), code(1)), pack_bf16(code(2), code(3)), pack_bf16(code(4), code(5)), pack_bf16(code(6), code(7))};
 }
 
 // Reads of what the kernel never writes at a wave-uniform index, as scalar loads.
@@ -504,7 +523,10 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
 // step's start and loaded again at once, so they have one step to arrive: 1.9 us a step for one block or two.
 //   LDS: two slots of token rows (laid out as in the other kernel); weights: of the wavefront alone, no barrier.  Codes come for two steps
 //   at a time, 64 (int2: 32) bytes of a row, into two slots.  The matrix instructions take the elements of every format in the order
-//   of the narrow tiles, so a token's result does not depend on which kind a call has.
+//   of the narrow tiles, so a token's result does not depend on which kind a call has.  What that costs (swaps, shifts, a scale more) the
+//   expansion makes up for: nibbles as bytes that the conversion picks, crumbs at positions kept in registers.  Calls, us, with the lanes'
+//   own order, in order, and in order with this expansion: all int4, 16 experts of 4096 x 6400, 200 rows each 689, 691 and 663, 128 of 2048 x 768,
+//   40 rows 166, 168 and 161; int2 616, 614 and 612, 147, 148 and 145.
 template <bool DOWN, int FMT>
 __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
@@ -645,12 +667,18 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
     // row's place in its matrix is that of its place in the tile); with groups of 32 both groups of a step are in the word.
     constexpr uint32_t kFirst = 0x01000C0Cu, kOther = 0x02020000u;
     const uint32_t scale_sel = kFirst ^ (G & r & 1 ? kOther : 0u);
+    uint32_t crumb_at[8]; // bit positions of the lane's codes in a word (int2)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        crumb_at[j] = 16 * kq + 2 * j;
+        if constexpr (FMT == 2) asm volatile("" : "+v"(crumb_at[j])); // (kept, not derived again at every use)
+    }
     float scale[2][2] = {}; // of the first and of the second half of the step's elements
     auto operand = [&](int ns, int s) {
         frag8 b;
         if constexpr (FMT == 0) b.u = fb[ns][s];
-        else if constexpr (FMT == 1) b.u = dequant8(fb[ns][0][s], scale[ns][s >> 1]);
-        else b.u = dequant8_crumbs(fb[ns][0][s], kq, scale[ns][s >> 1]);
+        else if constexpr (FMT == 1) b.u = dequant8_bytes(fb[ns][0][s], scale[ns][s >> 1]);
+        else b.u = dequant8_crumbs_at(fb[ns][0][s], crumb_at, scale[ns][s >> 1]);
         return b;
     };
     if constexpr (quant) {
@@ -685,7 +713,7 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
                     fb[ns][0] = u32x4{first[0], second[0], first[1], second[1]};
                 }
 #pragma unroll
-                for (int half = 0; half < 2; ++half) scale[ns][half] = __uint_as_float(__builtin_amdgcn_perm(0u, scales[ns], sel[half]));
+                for (int half = 0; half < 2; ++half) scale[ns][half] = __uint_as_float(__builtin_amdgcn_perm(0u, scales[ns], sel[half])) * (FMT == 1 ? 0.0625f : 1.f);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
