@@ -989,7 +989,7 @@ struct partition_lds {
     uint32_t cum[kMaxExperts + 1];
     int seg_start[kMaxExperts], seg_tokens[kMaxExperts];
     uint32_t wave_tot[kWaves];
-    int wave_cnt[kWaves], quant_cnt[kWaves], single_cnt[kWaves];
+    int wave_cnt[kWaves];
     int e_first;
 };
 
@@ -1057,7 +1057,7 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
     __syncthreads();
 }
 
-// The list of row tiles for the tile kernels that follow (one block; the counts of the wavefronts in pl are free).  Experts above
+// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot and pl.wave_cnt are free).  Experts above
 // m_small tokens.
 __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
 {
@@ -1071,6 +1071,7 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
         return (a.m_big >> fmt) & 1 ? m / DX_BIG_ROWS * DX_BIG_ROWS : 0;
     };
     auto tiles = [](int rows) { return (rows + DX_TILE_ROWS - 1) / DX_TILE_ROWS; };
+    __shared__ int quant_cnt[kWaves], single_cnt[kWaves]; // (not in pl, which kernels without a list have as well)
     int local = 0, local_big = 0, local_quant = 0, local_single = 0; // row tiles; 256-row tiles; of the former, of quantized experts, of experts with one
     for (int i = 0; i < R; ++i) {
         const int e = tid * R + i;
@@ -1088,8 +1089,8 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
     if (lane == 63) {
         pl.wave_tot[wave] = (uint32_t)inc;
         pl.wave_cnt[wave] = inc_big;
-        pl.quant_cnt[wave] = inc_quant;
-        pl.single_cnt[wave] = inc_single;
+        quant_cnt[wave] = inc_quant;
+        single_cnt[wave] = inc_single;
     }
     __syncthreads();
     int base = 0, total = 0, base_big = 0, total_big = 0, total_quant = 0, total_single = 0;
@@ -1097,7 +1098,7 @@ __device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_
     for (int w = 0; w < kWaves; ++w) {
         const int t = (int)pl.wave_tot[w], tb = pl.wave_cnt[w];
         if (w < wave) base += t, base_big += tb;
-        total += t, total_big += tb, total_quant += pl.quant_cnt[w], total_single += pl.single_cnt[w];
+        total += t, total_big += tb, total_quant += quant_cnt[w], total_single += single_cnt[w];
     }
     const int T_tiled = a.shared && a.T > a.m_small ? a.T : 0, lead_shared = big_rows(T_tiled, DX_FMT_BF16);
     const int n_shared = tiles(T_tiled - lead_shared), n_big_shared = lead_shared / DX_BIG_ROWS;
