@@ -190,6 +190,9 @@ dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router
  * goes to, in any order inside a segment; topk_ids is part of the call's
  * arrays, must not be NULL and is not read.  Weights are read through the
  * handles as they are when the kernels run on the compute stream.
+ * Sums are taken in fp32 in an order that the batch size, the shapes and the
+ * counts determine: a repeated call gives the same bits, a token's y may
+ * differ in the last bits between batches.
  * Stream order: the call is asynchronous, all its kernels run on the compute
  * stream (and can be captured in a HIP graph with it as origin).  The H and O
  * scratch buffers belong to the context: calls on one context must not
