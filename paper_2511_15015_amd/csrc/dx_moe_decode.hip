@@ -1732,11 +1732,11 @@ __global__ __launch_bounds__(64 * kFewWaves, kFewBlocks) void k_gate_up_few(dx_f
     }
 }
 
-// ---- down and combine: block (8 columns, token), a wavefront per expert (several where there are fewer than eight), which
-// multiplies its rows of W_down by the pair's row of H, a 16-lane row to a row, up to six chunks of 128 elements in flight;
-// the results meet in LDS, where they are weighted and added in the order of the slots as k_combine does.  Contractions that
-// are multiples of 128.  (8 columns because d / 16 blocks leave half of the chip idle at d = 2048, and a compute unit takes
-// in 28 GB/s past L2.)
+// ---- down and combine: block (8 columns, token).  Its items, an expert each (or a part of K where there are fewer than eight), go round
+// its wavefronts: an expert's rows of W_down times the pair's row of H, a 16-lane row to a row, up to six chunks of 128 elements
+// in flight; the results meet in LDS, where they are weighted and added in the order of the slots as k_combine does.  Contractions
+// that are multiples of 128.  (8 columns because d / 16 blocks leave half of the chip idle at d = 2048, and a compute unit takes
+// in 28 GB/s past L2.  One token of the 30B-shaped layer: 7.7 us for 25 MB, 10.2 with 16 columns.)
 constexpr int kFewCols = 8, kFewDownWaves = 16, kFewChunks = 6; // columns of a block, wavefronts at most, chunks in flight
 
 // sum[p]: this lane's part of row 4 p + lane / 16 of eight rows of W_down times a row of H, over the chunks [c0, c1) of 128
