@@ -384,7 +384,7 @@ def main():
             # decode, whole layer call: all three matrices of every activated expert (+ the shared expert) once,
             # x and the logits in, y and the routing arrays out
             step_bytes += n_hi_act * b_hi + n_lo_act * b_lo + b_sh + 2 * T * d * 2 + T * E * 4 + T * k * 12 + E * 8
-            # prefill, gate/up phase (streamed experts, then tiles): 2 * rows * d * 2f over all routed rows
+            # prefill, gate/up phase (the tiles): 2 * rows * d * 2f over all routed rows
             alg_flops += float(counts.sum()) * 2.0 * d * 2 * f
         alg_per_launch, flops_per_launch, step_bytes_per_call = alg_bytes / L, alg_flops / L, step_bytes / L
 
@@ -445,11 +445,10 @@ def main():
         routed = False
         achieved = flops_per_launch / (gate_up_us * 1e-6) / 1e12
         step_flops = float(T * k) * 2.0 * d * 3 * f      # all routed pairs through gate, up and down
-        roofline = {"bound": "mfma", "kernel": "gate/up phase: k_stream<gate/up> + k_tiled<gate/up>", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS,
+        roofline = {"bound": "mfma", "kernel": "gate/up phase: k_tiled<gate/up>", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                     "algorithmic_flops_per_launch": flops_per_launch, "avg_launch_us": gate_up_us,
-                    "note": "both kernels of the phase, the streamed experts (up to 32 tokens) and the tiled ones, with "
-                            "the kernel boundary between them",
+                    "note": "all row tiles of the phase, thin ones (segments of up to 32 tokens) among them",
                     "whole_step_tflops": step_flops / (ms_per_step * 1e-3) / 1e12}
     # HBM traffic of the dominant kernel from the committed counter summary; the summary names the commit
     # whose kernels it was taken on, printed next to it (this tree may have moved on since)

@@ -282,7 +282,6 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
     if ((e = hipMalloc(&c->d_mask_sums, n_sums * 4)) != hipSuccess) return fail(e, "route sums");
     if ((e = hipMalloc(&c->d_h, n_rows * c->fmax * sizeof(dx_bf16))) != hipSuccess) return fail(e, "H scratch");
     if ((e = hipMalloc(&c->d_o, n_rows * (size_t)g.d * sizeof(float))) != hipSuccess) return fail(e, "O scratch");
-    // (for the smallest m_small a call can have)
     const size_t n_tile_rows = (size_t)dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0);
     const size_t list_bytes = sizeof(dx_tile_head) + n_tile_rows * sizeof(dx_tile_row), places = (size_t)DX_FEW_TOKENS * g.top_k * sizeof(int32_t);
     if ((e = hipMalloc(&c->d_tiles, list_bytes > places ? list_bytes : places)) != hipSuccess) return fail(e, "tile list");
@@ -351,7 +350,7 @@ extern "C" dx_status dx_route(dx_ctx *c, int layer, const float *logits, int T, 
         DX_FAIL(c, DX_ERR_INVALID, "dx_route: null pointer");
     unsigned long long *hot = c->cfg.route_updates_hotness ? c->d_counters + (size_t)layer * c->cfg.E : nullptr;
     DX_HIP(c, dxk_route(logits, T, c->cfg.E, c->cfg.top_k, ids, w, counts, offsets, perm, c->d_mask, c->d_mask_sums,
-                        hot, c->compute));
+                        hot, dx_list_args{}, c->compute));
     return DX_OK;
 }
 
@@ -423,6 +422,22 @@ dx_status take_marks(dx_ctx *c, dx_marks &m)
     return DX_OK;
 }
 
+// the forward pass of validated arguments
+dx_status forward(dx_ctx *c, const char *who, const dx_fwd_args &a)
+{
+    if (!c->profiling) {
+        DX_HIP(c, dxk_moe_forward(a, c->n_cu, c->compute, nullptr));
+        return DX_OK;
+    }
+    dx_marks m;
+    dx_status st = take_marks(c, m);
+    if (st != DX_OK) return st;
+    hipError_t e = dxk_moe_forward(a, c->n_cu, c->compute, &m);
+    c->marks.push_back(m);
+    if (e != hipSuccess) DX_FAIL(c, DX_ERR_HIP, "%s: %s", who, hipGetErrorString(e));
+    return DX_OK;
+}
+
 } // namespace
 
 extern "C" dx_status dx_moe_forward(dx_ctx *c, int layer, const dx_handle *table, const void *x, int T,
@@ -436,17 +451,7 @@ extern "C" dx_status dx_moe_forward(dx_ctx *c, int layer, const dx_handle *table
     if (T == 0) return DX_OK;
     dx_fwd_args a;
     dx_status st = forward_args(c, "dx_moe_forward", layer, table, x, T, ids, w, offsets, perm, y, a);
-    if (st != DX_OK) return st;
-    if (!c->profiling) {
-        DX_HIP(c, dxk_moe_forward(a, c->n_cu, c->compute, nullptr));
-        return DX_OK;
-    }
-    dx_marks m;
-    if ((st = take_marks(c, m)) != DX_OK) return st;
-    hipError_t e = dxk_moe_forward(a, c->n_cu, c->compute, &m);
-    c->marks.push_back(m);
-    if (e != hipSuccess) DX_FAIL(c, DX_ERR_HIP, "dx_moe_forward: %s", hipGetErrorString(e));
-    return DX_OK;
+    return st != DX_OK ? st : forward(c, "dx_moe_forward", a);
 }
 
 extern "C" dx_status dx_route_forward(dx_ctx *c, int layer, const dx_handle *table, const float *logits, const void *x,
@@ -459,9 +464,11 @@ extern "C" dx_status dx_route_forward(dx_ctx *c, int layer, const dx_handle *tab
         DX_FAIL(c, DX_ERR_INVALID, "dx_route_forward: T=%d outside [0,%d]", T, c->cfg.max_tokens);
     if (!counts || !offsets || (T > 0 && (!logits || !ids || !w || !perm)))
         DX_FAIL(c, DX_ERR_INVALID, "dx_route_forward: null pointer");
+    if (T == 0) return dx_route(c, layer, logits, T, ids, w, counts, offsets, perm);
     bool routed = false;
-    if (T > 0) {
-        dx_fwd_args a;
+    dx_fwd_args a;
+    unsigned long long *hot = c->cfg.route_updates_hotness ? c->d_counters + (size_t)layer * c->cfg.E : nullptr;
+    {
         dx_status st = forward_args(c, "dx_route_forward", layer, table, x, T, ids, w, offsets, perm, y, a);
         if (st != DX_OK) return st;
         dx_route_io r{};
@@ -471,7 +478,7 @@ extern "C" dx_status dx_route_forward(dx_ctx *c, int layer, const dx_handle *tab
         r.counts = counts;
         r.offsets = offsets;
         r.perm = perm;
-        r.hotness = c->cfg.route_updates_hotness ? c->d_counters + (size_t)layer * c->cfg.E : nullptr;
+        r.hotness = hot;
         dx_marks m;
         if (c->profiling && (st = take_marks(c, m)) != DX_OK) return st;
         hipError_t e = dxk_route_forward(a, r, c->n_cu, c->compute, c->profiling ? &m : nullptr, &routed);
@@ -482,10 +489,11 @@ extern "C" dx_status dx_route_forward(dx_ctx *c, int layer, const dx_handle *tab
         if (e != hipSuccess) DX_FAIL(c, DX_ERR_HIP, "dx_route_forward: %s", hipGetErrorString(e));
     }
     if (routed) return DX_OK;
-    // shapes the self-routing kernel does not take: the two separate calls
-    dx_status st = dx_route(c, layer, logits, T, ids, w, counts, offsets, perm);
-    if (st != DX_OK) return st;
-    return dx_moe_forward(c, layer, table, x, T, ids, w, offsets, perm, y);
+    // shapes the self-routing kernel does not take: routing, which lists the row tiles of a call on tiles as well, and forward pass
+    const dx_list_args list = dxk_list_args(a, c->n_cu);
+    DX_HIP(c, dxk_route(logits, T, c->cfg.E, c->cfg.top_k, ids, w, counts, offsets, perm, c->d_mask, c->d_mask_sums, hot, list, c->compute));
+    a.listed = list.tiles != nullptr;
+    return forward(c, "dx_route_forward", a);
 }
 
 extern "C" dx_status dx_router_logits(dx_ctx *c, const void *x, const void *w_router, const float *bias, int T,

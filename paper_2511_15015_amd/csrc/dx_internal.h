@@ -124,11 +124,19 @@ struct dx_ctx {
     } while (0)
 
 constexpr int DX_SUM_CHUNKS = 32; // chunks whose population counts are added up together in large batches
+// What the list of row tiles is made from, beside the segments
+struct dx_list_args {
+    const dx_handle *table;
+    struct dx_tile_head *tiles; // null: no list
+    int T, E, k, m_big, n_cu;
+    int shared; // the layer has a shared expert
+};
 // ---- kernel launchers (each validates nothing; callers validate) ----------
 // dx_route.hip
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
                      int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *sums,
-                     unsigned long long *hotness /* window counters of the layer, or null */, hipStream_t s);
+                     unsigned long long *hotness /* window counters of the layer, or null */,
+                     const dx_list_args &list /* of row tiles; batches of several chunks write it too */, hipStream_t s);
 hipError_t dxk_router_gemm(const dx_bf16 *x, const dx_bf16 *w_r, const float *bias, int T, int E, int d, float *logits,
                            int n_cu, hipStream_t s);
 hipError_t dxk_hotness_add(unsigned long long *counters, const int32_t *counts, int E, hipStream_t s);
@@ -141,8 +149,8 @@ hipError_t dxk_quantize(const dx_bf16 *w, int rows, int K, int group, uint8_t *q
 hipError_t dxk_quantize2(const dx_bf16 *w, int rows, int K, int group, uint8_t *q, dx_bf16 *sc, hipStream_t s); // 2-bit
 
 // dx_moe_decode.hip / dx_moe_prefill.hip
-// The list of row tiles of the experts above m_small tokens: a head, then the rows of the head's counts in their order.
-constexpr int DX_TILE_ROWS = 128, DX_BIG_ROWS = 256;
+// The list of row tiles of a call: a head, then the rows: 128-row tiles of the routed experts, of the shared one, 256-row tiles likewise, thin tiles.
+constexpr int DX_TILE_ROWS = 128, DX_BIG_ROWS = 256, DX_THIN_ROWS = 32;
 struct dx_tile_row {
     int e, mt;   // expert (E = shared), row tile of the rows below
     int m, seg0; // rows and first pair slot of the segment, or of the part of it that this tile size takes
@@ -152,13 +160,13 @@ struct dx_tile_head {
     int n_quant;             // of the former, those of quantized experts
     int n_single;            // and those of experts with one only
     int n_big, n_big_shared; // 256-row tiles
+    int n_thin, n_thin_quant; // segments of up to DX_THIN_ROWS rows, bf16 and quantized ones
     int n_cu;
-    int unused;
 };
-// most row tiles a call of T tokens can have (a routed expert has ceil(m / 128) of them, and none up to m_small tokens)
-inline long dxk_tile_rows_max(int T, int k, int E, int m_small, bool shared)
+// most row tiles that segments of more than m_min rows can have in a call of T tokens (a routed expert has ceil(m / 128) of them)
+inline long dxk_tile_rows_max(int T, int k, int E, int m_min, bool shared)
 {
-    const long pairs = (long)T * k, with = pairs / ((long)m_small + 1) < E ? pairs / ((long)m_small + 1) : E;
+    const long pairs = (long)T * k, with = pairs / ((long)m_min + 1) < E ? pairs / ((long)m_min + 1) : E;
     // (256 rows in one 256-row tile are fewer tiles than in two of 128)
     return pairs / DX_TILE_ROWS + with + (shared ? (T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0);
 }
@@ -174,16 +182,14 @@ struct dx_fwd_args {
     const int32_t *offsets;
     const int32_t *perm;
     dx_bf16 *h;  // scratch [T*k (+T), fmax]
-    float *o;    // scratch [T*k (+T), d]: fp32, or bf16 in the same allocation when o_bf16
+    float *o;    // scratch [T*k (+T), d]: fp32, or (tiles) bf16 in the same allocation
     int T, E, k, d, f, group, shared_f, fmax;
-    int m_small; // experts with at most this many tokens take the streaming kernels, the others the tiled ones
     int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
     int any_quantized; // some routed expert of the table may be (a caller's table: unknown)
-    int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
-    // A list that the gate/up kernel of the streamed experts leaves for the kernels behind it, or null: mixed batches (m_small
-    // is a bound): the row tiles of the tiled experts; up to DX_FEW_TOKENS tokens on a caller's
-    // routing arrays: the expert of every place in the segments, as int32_t.
+    // A list for the kernels of a call, or null: calls on tiles: the row tiles; up to DX_FEW_TOKENS tokens on a caller's
+    // routing arrays: the expert of every place in the segments, as int32_t, which the gate/up kernel leaves for the down kernel.
     dx_tile_head *tiles;
+    bool listed; // the row tiles are listed already (by the routing kernels in front)
 };
 // Decode batches that the gate/up kernel routes itself (dx_route_forward): what its first block reads and
 // writes on top of dx_fwd_args (whose ids, w, offsets and perm point at the same arrays for the kernels
@@ -198,12 +204,15 @@ struct dx_route_io {
     int32_t *perm;       // [T * k]
     unsigned long long *hotness; // the layer's window counters, or null
 };
+// The list that a call's tiles need (tiles null: the call does not run on tiles)
+dx_list_args dxk_list_args(const dx_fwd_args &a, int n_cu);
 hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, dx_marks *marks);
 // Routing and forward pass in one call.  Returns true in *routed when the gate/up kernel did the routing
 // (small decode batches whose shapes fit); otherwise nothing was launched and the caller runs dxk_route
 // and dxk_moe_forward.
 hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_cu, hipStream_t s, dx_marks *marks,
                              bool *routed);
-// dx_moe_prefill.hip: gate/up, and down, of the experts above a.m_small tokens
+// dx_moe_prefill.hip: the list of row tiles of a call, and gate/up and down of its experts
+void dxk_tile_list(const dx_list_args &l, const int32_t *offsets, hipStream_t s);
 void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s);
 void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s);

@@ -37,8 +37,8 @@
 //     the matrix instruction never crosses a quantization group, so the
 //     group's scale multiplies the group's fp32 partial sums once (q*s is
 //     never rounded).
-// Batches of up to 128 tokens run here alone (segments above 32 tokens in
-// blocks of 32); larger ones hand the big segments to the tile kernels.
+// Batches of up to 128 tokens run here (segments above 32 tokens in blocks of 32);
+// larger ones run on tiles.
 #include "dx_internal.h"
 #include "dx_route_core.h"
 
@@ -638,7 +638,7 @@ struct expert_ctx {
 //
 // Add up the partial sums of the pairs that start at strips sb, sb + 2, ... (live_groups of them, side by
 // side across the wavefront groups) in a fixed order and finish the strips below h_hi:
-// gate/up -> H = silu(gate) * up (bf16); down -> O (fp32 or bf16).  All threads.
+// gate/up -> H = silu(gate) * up (bf16); down -> O (fp32).  All threads.
 // Element (group gg, tile mt, accumulator lane L, component i) is token 4*(L/16)+i, tile column L%16.
 // (slot, row of O) of the output elements a thread finishes: idx = threadIdx.x + n * kThreads has the
 // same idx % (MT * 256) for every n, so both are fixed for a whole run and the row lookup in the
@@ -690,14 +690,8 @@ __device__ __forceinline__ void finish_batch(const dx_fwd_args &a, const expert_
         if constexpr (DOWN) {
             const int n = s0 * 16 + (L & 15);
             const bool both = s0 + 1 < h_hi;
-            if (a.o_bf16) {
-                dx_bf16 *ob = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)orow * a.d + n;
-                ob[0] = (dx_bf16)float_to_bf16_rne(v0);
-                if (both) ob[16] = (dx_bf16)float_to_bf16_rne(v1);
-            } else {
-                a.o[(size_t)orow * a.d + n] = v0;
-                if (both) a.o[(size_t)orow * a.d + n + 16] = v1;
-            }
+            a.o[(size_t)orow * a.d + n] = v0;
+            if (both) a.o[(size_t)orow * a.d + n + 16] = v1;
         } else {
             if (s0 + first < h_hi) {
                 const float hv = v0 / (1.f + expf(-v0)) * v1;
@@ -994,16 +988,14 @@ struct partition_lds {
 };
 
 // The partition: cost units of every expert, exclusive prefix, this block's unit range [ub0, ub1) and the
-// first expert in it.  Experts above m_small tokens belong to the tiled kernels: they count as empty
-// here.  All threads; ends with a barrier.
+// first expert in it.  All threads; ends with a barrier.
 template <bool DOWN>
 __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_lds &pl, uint32_t &ub0, uint32_t &ub1)
 {
     const int nE = a.E + (a.shared ? 1 : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto tokens_of = [&](int e) {
-        const int m = e == a.E ? a.T : a.offsets[e + 1] - a.offsets[e];
-        return m <= a.m_small ? m : 0;
+        return e == a.E ? a.T : a.offsets[e + 1] - a.offsets[e];
     };
     auto strips_of = [&](int e) { return DOWN ? a.d / 16 : (e == a.E ? a.shared_f : a.f) / 8; };
     auto fmt_of = [&](int e) { return e == a.E ? (uint32_t)DX_FMT_BF16 : a.table[e].fmt; };
@@ -1055,66 +1047,6 @@ __device__ __forceinline__ void build_partition(const dx_fwd_args &a, partition_
         if (i < R && e < nE && pl.cum[e] <= ub0 && ub0 < pl.cum[e + 1]) pl.e_first = e;
     }
     __syncthreads();
-}
-
-// The list of row tiles for the tile kernels that follow (one block; pl.wave_tot and pl.wave_cnt are free).  Experts above
-// m_small tokens.
-__device__ __forceinline__ void write_tile_rows(const dx_fwd_args &a, partition_lds &pl)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int R = (a.E + kThreads - 1) / kThreads; // experts per thread, consecutive
-    auto tokens_of = [&](int e) {
-        const int m = a.offsets[e + 1] - a.offsets[e];
-        return m > a.m_small ? m : 0;
-    };
-    auto big_rows = [&](int m, uint32_t fmt) { // leading rows that go in 256-row tiles
-        return (a.m_big >> fmt) & 1 ? m / DX_BIG_ROWS * DX_BIG_ROWS : 0;
-    };
-    auto tiles = [](int rows) { return (rows + DX_TILE_ROWS - 1) / DX_TILE_ROWS; };
-    __shared__ int quant_cnt[kWaves], single_cnt[kWaves]; // (not in pl, which kernels without a list have as well)
-    int local = 0, local_big = 0, local_quant = 0, local_single = 0; // row tiles; 256-row tiles; of the former, of quantized experts, of experts with one
-    for (int i = 0; i < R; ++i) {
-        const int e = tid * R + i;
-        if (e < a.E) {
-            const uint32_t fmt = a.table[e].fmt;
-            const int m = tokens_of(e), lead = big_rows(m, fmt), t = tiles(m - lead);
-            local += t;
-            local_big += lead / DX_BIG_ROWS;
-            local_quant += fmt == DX_FMT_BF16 ? 0 : t;
-            local_single += t == 1 && lead == 0;
-        }
-    }
-    const int inc = dx_route_core::wave_scan_inclusive(local), inc_big = dx_route_core::wave_scan_inclusive(local_big);
-    const int inc_quant = dx_route_core::wave_scan_inclusive(local_quant), inc_single = dx_route_core::wave_scan_inclusive(local_single);
-    if (lane == 63) {
-        pl.wave_tot[wave] = (uint32_t)inc;
-        pl.wave_cnt[wave] = inc_big;
-        quant_cnt[wave] = inc_quant;
-        single_cnt[wave] = inc_single;
-    }
-    __syncthreads();
-    int base = 0, total = 0, base_big = 0, total_big = 0, total_quant = 0, total_single = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int t = (int)pl.wave_tot[w], tb = pl.wave_cnt[w];
-        if (w < wave) base += t, base_big += tb;
-        total += t, total_big += tb, total_quant += quant_cnt[w], total_single += single_cnt[w];
-    }
-    const int T_tiled = a.shared && a.T > a.m_small ? a.T : 0, lead_shared = big_rows(T_tiled, DX_FMT_BF16);
-    const int n_shared = tiles(T_tiled - lead_shared), n_big_shared = lead_shared / DX_BIG_ROWS;
-    dx_tile_row *rows = reinterpret_cast<dx_tile_row *>(a.tiles + 1), *out = rows + base + inc - local;
-    dx_tile_row *big = rows + total + n_shared, *out_big = big + base_big + inc_big - local_big;
-    for (int i = 0; i < R; ++i) {
-        const int e = tid * R + i;
-        if (e >= a.E) continue;
-        const int m = tokens_of(e), lead = big_rows(m, a.table[e].fmt), seg0 = a.offsets[e];
-        for (int mt = 0; mt * DX_BIG_ROWS < lead; ++mt) *out_big++ = dx_tile_row{e, mt, lead, seg0};
-        for (int mt = 0; mt * DX_TILE_ROWS < m - lead; ++mt) *out++ = dx_tile_row{e, mt, m - lead, seg0 + lead};
-    }
-    const int seg0 = a.T * a.k;
-    for (int mt = tid; mt < n_shared; mt += kThreads) rows[total + mt] = dx_tile_row{a.E, mt, T_tiled - lead_shared, seg0 + lead_shared};
-    for (int mt = tid; mt < n_big_shared; mt += kThreads) big[total_big + mt] = dx_tile_row{a.E, mt, lead_shared, seg0};
-    if (tid == 0) *a.tiles = dx_tile_head{total, n_shared, total_quant, total_single, total_big, n_big_shared, (int)gridDim.x, 0};
 }
 
 // The expert of every place in the segments, for the down kernel of a call of a few tokens (one block).
@@ -1204,10 +1136,7 @@ __global__ __launch_bounds__(kThreads) void k_stream(dx_fwd_args a)
     const unsigned long long trace_t1 = wall_clock64();
 #endif
     if constexpr (!DOWN) {
-        if (a.tiles && blockIdx.x + 1 == gridDim.x) {
-            if (a.m_small == 0x7fffffff) write_place_experts(a);
-            else write_tile_rows(a, pl);
-        }
+        if (a.tiles && blockIdx.x + 1 == gridDim.x) write_place_experts(a);
     }
     run_share<LK, GPC, CPW, DOWN, MODE>(a, pl, ub0, ub1, nullptr, red);
 #ifdef DX_TRACE
@@ -2130,32 +2059,34 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
     return (pairs >= 1024L * a.E ? 1 << DX_FMT_BF16 : 0) | (pairs >= 512L * a.E && pairs_of_scales ? 1 << DX_FMT_INT4G : 0);
 }
 
+// Whether a call runs on tiles.  Otherwise (few tokens: decode, or shapes that do not fit the tiles) the streaming kernels take every
+// expert.  (x starts at a multiple of the 16 bytes that a lane of the tiles' memory-to-LDS loads fetches; the streaming kernels'
+// loads to registers take any address.)
+bool takes_tiles(const dx_fwd_args &a)
+{
+    return a.T > kStreamOnlyTokens && a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
+}
+
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
 // then tells whether it did (if not, nothing has been launched).
 hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks *mk, const dx_route_io *r,
                       bool *routed)
 {
     dx_fwd_args a = a_in;
-    // Few tokens per call (decode): the streaming kernels take every expert.  Otherwise experts above
-    // 32 tokens go to the tiled MFMA kernels (when the shapes fit their tiles, and x starts at a multiple of the 16 bytes
-    // that a lane of their memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address).
-    const bool tiles_fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
-    const bool mixed = a.T > kStreamOnlyTokens && tiles_fit;
-    a.m_small = mixed ? 32 : 0x7fffffff;
-    const few_choice few = mixed ? few_choice{false, false} : takes_few(a, n_cu);
-    if (!mixed && (!few.down || r)) a.tiles = nullptr;
-    a.m_big = mixed ? big_tile_formats(a, n_cu) : 0;
-    a.o_bf16 = mixed; // d % 128 == 0 there, so rows split into 8-column pieces
+    const bool tiled = takes_tiles(a);
+    const few_choice few = tiled ? few_choice{false, false} : takes_few(a, n_cu);
+    if (!tiled && (!few.down || r)) a.tiles = nullptr;
+    a.m_big = tiled ? big_tile_formats(a, n_cu) : 0;
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
-        *routed = !mixed && (few.gate_up || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
+        *routed = !tiled && (few.gate_up || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
     hipEvent_t combine_start = nullptr, combine_stop = nullptr;
-    if (mk) mk->per_kernel = !mixed, mk->combined = false;
+    if (mk) mk->per_kernel = !tiled, mk->combined = false;
     bool combined = false; // y is there already
-    if (!mixed) {
+    if (!tiled) {
         // profiled: every kernel's own start and stop stamps
         const dim3 grid(n_cu);
         hipEvent_t ev[8] = {};
@@ -2175,21 +2106,15 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
             combine_stop = ev[3];
         }
     } else {
-        // Each phase's streamed experts, then its tiles, one kernel after the other.  (Side by side on three streams they
-        // are no faster: 300 tokens of the 30B-shaped layer 159 us against 139, 1000 tokens 220 against 204,
-        // 4096 tokens 576 against 516; the streamed experts
-        // and the tiles ask for the same memory, and a fork and a join cost more than a kernel boundary.)
-        const dim3 grid(n_cu);
         if (marks) (void)hipEventRecord(marks[0], s);
-        launch_stream<false>(a, grid, s);
+        if (!a.listed) dxk_tile_list(dxk_list_args(a, n_cu), a.offsets, s);
         dxk_tiles_gate_up(a, s);
         if (marks) (void)hipEventRecord(marks[1], s);
-        launch_stream<true>(a, grid, s);
         dxk_tiles_down(a, s);
         if (marks) (void)hipEventRecord(marks[2], s);
     }
     if (combined) {
-    } else if (a.o_bf16) {
+    } else if (tiled) { // O in bf16: half the traffic between the down kernel and the combine (d % 128 == 0: 8 columns per thread)
         launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
     } else {
         launch(k_combine, dim3((a.d / 4 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
@@ -2226,6 +2151,12 @@ extern "C" int dx_debug_read_steps(void *dst, void *counts)
     return rc;
 }
 #endif
+
+dx_list_args dxk_list_args(const dx_fwd_args &a, int n_cu)
+{
+    if (!takes_tiles(a)) return dx_list_args{};
+    return dx_list_args{a.table, a.tiles, a.T, a.E, a.k, big_tile_formats(a, n_cu), n_cu, a.shared != nullptr};
+}
 
 hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, dx_marks *marks)
 {

@@ -4,10 +4,10 @@
 // Paper: Sec. 3.2 (the compute path resolves the handle and runs the kernel of
 // the active version).  The paper gives no kernel; this one is built for gfx950.
 //
-// Regime: experts with more than a few dozen tokens.  Output tiles with v_mfma_f32_32x32x16_bf16, fp32
+// Regime: calls of more than a hundred tokens.  Output tiles with v_mfma_f32_32x32x16_bf16, fp32
 // accumulators and K in steps of 64 (one 128-byte line of a token or weight row), filled by loads from memory
-// to LDS: k_tiled with tiles of 128 rows x 128 or 256 columns, any number of rows, all formats; k_big with 256 x 256 for the
-// whole 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way to the matrix instructions (code ->
+// to LDS: k_tiled with tiles of 128 rows x 128 or 256 columns, any number of rows, all formats, and thin ones for segments of up to 32
+// rows; k_big with 256 x 256 for the whole 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way to the matrix instructions (code ->
 // fp32 -> times the group's scale -> bf16).
 //   gate/up: half of the tile's columns are gate rows and the other half the up rows of the same
 //            indices, and every wavefront owns matching gate/up columns, so SwiGLU happens on the
@@ -17,6 +17,7 @@
 // the list is cut into 8 contiguous ranges, one per XCD (block b works in range b % 8), so the tiles that
 // share token and weight lines run at the same time on the same L2.
 #include "dx_internal.h"
+#include "dx_tile_list.h"
 
 #include <type_traits>
 
@@ -25,6 +26,8 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+#define DX_GLOBAL __attribute__((address_space(1)))
 
 union frag8 {
     u32x4 u;
@@ -91,6 +94,23 @@ __device__ __forceinline__ u32x4 dequant8_crumbs_at(uint32_t word, const uint32_
     return u32x4{pack_bf16(code(0), code(1)), pack_bf16(code(2), code(3)), pack_bf16(code(4), code(5)), pack_bf16(code(6), code(7))};
 }
 
+// 8 two-bit codes (half `half` of `word`) as bf16 integers, 64 times the code, in element order: crumb i of every byte as its upper
+// two bits, which the conversion takes out of their word by itself
+__device__ __forceinline__ u32x4 crumbs_as_integers(uint32_t word, int half)
+{
+    const uint32_t h = word >> (16 * half);
+    uint32_t at[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at[i] = (h << (6 - 2 * i)) & 0xC0C0u;
+    uint32_t p[4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            p[2 * b + i] = pack_bf16((float)(int8_t)(at[2 * i] >> (8 * b)), (float)(int8_t)(at[2 * i + 1] >> (8 * b)));
+    return u32x4{p[0], p[1], p[2], p[3]};
+}
+
 // Reads of what the kernel never writes at a wave-uniform index, as scalar loads.
 template <typename T>
 __device__ __forceinline__ T uniform_load(const T *p)
@@ -131,9 +151,17 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
     return t;
 }
 
-// This block's tile.  The row tiles of all experts are in a.tiles (written by the gate/up kernel of the streamed experts that
-// runs in front, because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us): the routed
-// experts', the shared one's, the 256-row tiles behind them.  Each XCD takes an eighth of the list.
+// This block's tile.  The row tiles of all experts are in a.tiles (written in front, by the routing's placement kernel or by k_tile_list,
+// because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us): the routed
+// experts', the shared one's, the 256-row tiles behind them, the thin tiles.  Each XCD takes an eighth of the former.
+// Thin tiles in this launch (before: segments of up to 32 rows in the streaming kernels, a launch per phase in front, during which the matrix
+// cores had little to do).  A layer, us, streaming kernels in front and now: 30B-shaped 300 tokens 140 and 121, 1000 tokens 204 and 192, 4096
+// tokens 464 and 432, int4/int2 150 tokens 101 and 81; 80B-shaped 150 tokens 111 and 92, 1000 tokens 204 and 178; 16 experts of 4096 x 6400,
+// 150 tokens 412 and 311, 1100 tokens 602 and 539; 30B-shaped 130 and 190 tokens the same.  First or last: last, because they are short and fill
+// the last round; first where bf16 weights from memory are all there is (up to four narrow tiles per compute unit): 30B-shaped 300 tokens
+// 132 first and 143 last, 500 tokens 146 and 157, 16 of 4096 x 6400 150 tokens 320 and 339; but int4/int2 150 tokens 84 and 79, 1100 tokens of
+// the 16 556 and 550, 80B-shaped 1000 tokens 187 and 178, and with few other tiles: first only where a good part of the thin ones is bf16 as well (80B-shaped 150
+// tokens, none 94 and 92; 30B-shaped 130 tokens 103 and 107).
 // Wide or narrow: a compute unit holds two tiles of either kind.  Figures: the phase's kernels, us, narrow and wide, by narrow tiles
 // per compute unit; the same lines hold for both phases.
 //   Quantized weights gain by the expansion as soon as there is more than one round: all int4, 128 experts of 2048 x 768, 110 rows each, gate/up
@@ -145,22 +173,42 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
 //   Mixed: as quantized ones from 45 % of the row tiles on (half: 4.0 109 and 96, 6.0 162 and 161), and from 20 % on where most experts have several
 //   row tiles, which ask for the same weights (80B-shaped, a third, 3.2 123 and 106, 5.2 168 and 149, down 6.4 81 and 70); with one row tile to an expert bf16
 //   weights come from memory alone, and narrow tiles take in more (a third, 4.3 132 and 157, 6.0 174 and 185).
+enum tile_kind { kNarrow, kWide, kThin };
 template <bool DOWN>
-__device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, bool &wide)
+__device__ __forceinline__ tile_id find_tile(const dx_fwd_args &a, tile_kind &kind)
 {
     const int n = uniform_load(&a.tiles->n_routed), n_shared = uniform_load(&a.tiles->n_shared), n_cu = uniform_load(&a.tiles->n_cu);
     const int narrow_tiles = n * columns_of<DOWN>(a, a.f, BN) + n_shared * columns_of<DOWN>(a, a.shared_f, BN);
     const int quant = uniform_load(&a.tiles->n_quant), single = uniform_load(&a.tiles->n_single);
+    const int thin_bf16 = uniform_load(&a.tiles->n_thin), n_thin = thin_bf16 + uniform_load(&a.tiles->n_thin_quant), ntn_thin = columns_of<DOWN>(a, a.f, BNW);
     const bool as_quantized = 20 * quant >= 9 * (n + n_shared) || (5 * quant >= n + n_shared && 5 * single <= 2 * n);
-    wide = as_quantized ? 2 * narrow_tiles > 5 * n_cu : narrow_tiles > 6 * n_cu || (narrow_tiles > 3 * n_cu && narrow_tiles <= 4 * n_cu);
+    const bool wide = as_quantized ? 2 * narrow_tiles > 5 * n_cu : narrow_tiles > 6 * n_cu || (narrow_tiles > 3 * n_cu && narrow_tiles <= 4 * n_cu);
     const int width = wide ? BNW : BN, ntn = columns_of<DOWN>(a, a.f, width), ntn_shared = columns_of<DOWN>(a, a.shared_f, width);
     const uint32_t routed = (uint32_t)(n * ntn), total = routed + (uint32_t)(n_shared * ntn_shared), per_xcd = (total + 7) / 8;
-    const uint32_t idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const uint32_t thin = (uint32_t)(n_thin * ntn_thin), thin_per_xcd = (thin + 15) / 16 * 2;
     const dx_tile_row *rows = reinterpret_cast<const dx_tile_row *>(a.tiles + 1);
-    if ((blockIdx.x >> 3) < per_xcd && idx < total)
-        return idx < routed ? tile_of<DX_TILE_ROWS, 8>(rows, idx, ntn) : tile_of<DX_TILE_ROWS, 8>(rows + n, idx - routed, ntn_shared);
+    const uint32_t xcd = blockIdx.x & 7;
+    uint32_t at = blockIdx.x >> 3;
     tile_id t;
     t.valid = false;
+    const bool thin_first = !as_quantized && narrow_tiles <= 4 * n_cu && (narrow_tiles > n_cu || 2 * thin_bf16 > n + n_shared);
+    const bool is_thin = thin_first ? at < thin_per_xcd : at >= per_xcd;
+    if (thin_first != is_thin) at -= thin_first ? thin_per_xcd : per_xcd; // behind the other kind
+    if (is_thin) {
+        kind = kThin;
+        // (two at a time to an XCD, so that every one has its share of the bf16 ones, which are listed first: a list in eight parts of
+        // unlike weight 30B-shaped, 130 tokens 104 us a layer against 101)
+        const uint32_t idx = ((at >> 1) * 8 + xcd) * 2 + (at & 1);
+        if (idx >= thin) return t;
+        const dx_tile_row *of = rows + n + n_shared + uniform_load(&a.tiles->n_big) + uniform_load(&a.tiles->n_big_shared) + idx / (uint32_t)ntn_thin;
+        t.e = uniform_load(&of->e), t.m = uniform_load(&of->m), t.seg0 = uniform_load(&of->seg0);
+        t.mt = 0, t.nt = (int)(idx % (uint32_t)ntn_thin);
+        t.valid = true;
+        return t;
+    }
+    kind = wide ? kWide : kNarrow;
+    const uint32_t idx = xcd * per_xcd + at;
+    if (at < per_xcd && idx < total) t = idx < routed ? tile_of<DX_TILE_ROWS, 8>(rows, idx, ntn) : tile_of<DX_TILE_ROWS, 8>(rows + n, idx - routed, ntn_shared);
     return t;
 }
 
@@ -267,6 +315,10 @@ struct cfg {
     // two steps of them (int2: half of it) and of two words of scales per row
     static constexpr int A_SLOT = ROWS * kLine, B_WAVE = 64 * kLine, SIDE_WIDE = 64 * 64 + 2 * 256;
     static_assert(2 * A_SLOT + WAVES * B_WAVE <= RING && 2 * A_SLOT + WAVES * 2 * SIDE_WIDE <= RING, "the ring");
+    // thin tiles, quantized: three slots of the token rows and codes of two steps
+    static constexpr int THIN_SLOTS = 3, THIN_A = DX_THIN_ROWS * kLine, THIN = THIN_SLOTS * (2 * THIN_A + WAVES * SIDE_WIDE);
+    static constexpr int LDS = THIN > RING ? THIN : RING;
+    static_assert(2 * (LDS + 256 * WAVES) <= 160 * 1024, "two blocks to a compute unit");
 };
 
 template <bool DOWN, int FMT>
@@ -385,7 +437,7 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
     if constexpr (DOWN) {
         if (!shared) {
             const int slot = t.mt * ROWS + wm * 64 + lane;
-            load_to_lds4(lds0 + cfg::RING + 256 * wave, (uint32_t)(slot < t.m ? slot : t.m - 1) * 4u, scalar_ptr(a.perm + t.seg0));
+            load_to_lds4(lds0 + cfg::LDS + 256 * wave, (uint32_t)(slot < t.m ? slot : t.m - 1) * 4u, scalar_ptr(a.perm + t.seg0));
         }
     }
     f32x16 acc[2][2];
@@ -501,7 +553,7 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
         const int slot = t.mt * ROWS + wm * 64 + ms * 32 + r;
         dx_bf16 *dst;
         if constexpr (DOWN) {
-            const int orow = shared ? t.seg0 + slot : *reinterpret_cast<const int *>(ring + cfg::RING + 256 * wave + 4 * (ms * 32 + r));
+            const int orow = shared ? t.seg0 + slot : *reinterpret_cast<const int *>(ring + cfg::LDS + 256 * wave + 4 * (ms * 32 + r));
             dst = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)orow * a.d + t.nt * BN + wn * 64 + 8 * kq;
         } else {
             dst = a.h + (size_t)(t.seg0 + slot) * a.fmax + t.nt * (BN / 2) + wn * 32 + 8 * kq;
@@ -511,6 +563,92 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
     // the redundant loads issued past the end still target this block's LDS: it must not end before they have landed
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
+
+// ---------------------------------------------------------------------------------------------
+// The 64 weight rows of a wavefront in the wide and the thin tiles and their way to the registers: down: 64 consecutive ones;
+// gate/up: 32 gate rows, then the same up rows.
+template <bool DOWN, int FMT>
+struct weight_rows {
+    uint64_t lo, hi, s_base = 0; // rows 0 .. 31 and 32 .. 63; scales of the matrix that row `lane` is in
+    uint32_t rb, s_row = 0;      // bytes of a row; first scale of row `lane`
+    uint32_t off[2] = {0, 0};    // bf16: even and odd groups of eight rows
+    uint32_t scale_sel = 0;
+    int lg;                      // group = 2^lg
+    // The half of the aligned word that a scale is in, as v_perm_b32 wants it: (row * groups + group) odd or even (the parity of a
+    // row's place in its matrix is that of its place in the tile); with groups of 32 both groups of a step are in the word.
+    static constexpr uint32_t kFirst = 0x01000C0Cu, kOther = 0x02020000u;
+
+    __device__ __forceinline__ weight_rows(const dx_handle *h, int row0, int K, int group, int lane)
+    {
+        rb = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4);
+        lo = scalar_ptr(uniform_load(DOWN ? &h->w_down : &h->w_gate)) + (uint64_t)row0 * rb;
+        hi = DOWN ? lo + (uint64_t)32 * rb : scalar_ptr(uniform_load(&h->w_up)) + (uint64_t)row0 * rb;
+        lg = __builtin_ctz((unsigned)group);
+        const int G = K >> lg;
+        if constexpr (FMT != 0) {
+            const uint64_t s_lo = scalar_ptr(uniform_load(DOWN ? &h->s_down : &h->s_gate)), s_hi = DOWN ? s_lo : scalar_ptr(uniform_load(&h->s_up));
+            s_base = lane < 32 ? s_lo : s_hi;
+            s_row = (uint32_t)(row0 + (DOWN ? lane : lane & 31)) * (uint32_t)G;
+            scale_sel = kFirst ^ (G & lane & 1 ? kOther : 0u);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) off[p] = (uint32_t)(lane >> 3) * rb + (uint32_t)((lane & 7) ^ (4 * p + (lane >> 4))) * 16;
+        }
+    }
+    // bf16: eight rows (i = 0 .. 7) of step kt, laid out as the token rows: + off[i & 1]
+    __device__ __forceinline__ uint64_t rows_base(int kt, int i) const { return (i < 4 ? lo : hi) + (uint64_t)(8 * (i & 3)) * rb + (uint64_t)kt * kLine; }
+    // Codes of steps 2c and 2c + 1: int4: 64 bytes of a row, four lanes to it, piece p of row r in slot p ^ ((r >> 2) & 3), i = 0 .. 3; int2: 32 bytes,
+    // two lanes, i = 0, 1.  Past the end of an odd number of steps (not `whole`) the first half is read again.
+    __device__ __forceinline__ uint64_t codes_base(int i, int c) const
+    {
+        if constexpr (FMT == 1) return (i < 2 ? lo : hi) + (uint64_t)(16 * (i & 1)) * rb + (uint64_t)c * 64;
+        else return (i == 0 ? lo : hi) + (uint64_t)c * 32;
+    }
+    __device__ __forceinline__ uint32_t codes_off(bool whole, int lane) const
+    {
+        if constexpr (FMT == 1) {
+            const uint32_t piece = (uint32_t)((lane & 3) ^ (lane >> 4)); // row 16 i + lane / 4
+            return (uint32_t)(lane >> 2) * rb + (whole ? piece : piece & 1) * 16;
+        } else {
+            return (uint32_t)(lane >> 1) * rb + (whole ? lane & 1 : 0) * 16;
+        }
+    }
+    // the aligned word that the scale of step kt is in
+    __device__ __forceinline__ uint64_t scales_at(int kt) const { return s_base + (((s_row + (uint32_t)((kt * BK) >> lg)) * 2) & ~3u); }
+    // both, to LDS
+    __device__ __forceinline__ void issue_codes(uint32_t m0, int c, int nk, int lane) const
+    {
+        const bool whole = 2 * c + 1 < nk; // wave-uniform
+#pragma unroll
+        for (int i = 0; i < (FMT == 1 ? 4 : 2); ++i) load_to_lds(m0 + 1024 * i, codes_off(whole, lane), codes_base(i, c));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) load_to_lds4(m0 + 64 * 64 + 256 * u, scales_at(whole ? 2 * c + u : 2 * c));
+    }
+    // step kt of the codes at p: of each tile of 32 rows the lane's elements 16 q + 8 kq .. + 7 of quarter q (int2: in half kq of word q), and
+    // the scales of the first and of the second half of the step
+    __device__ __forceinline__ void read_codes(const char *p, int kt, int lane, u32x4 (&codes)[2], float (&scale)[2][2]) const
+    {
+        const int r = lane & 31, kq = lane >> 5;
+        uint32_t sel[2];
+        sel[0] = scale_sel ^ (lg != 5 && ((kt * BK) >> lg & 1) ? kOther : 0u);
+        sel[1] = sel[0] ^ (lg == 5 ? kOther : 0u);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const int row = 32 * n + r;
+            const uint32_t word = *reinterpret_cast<const uint32_t *>(p + 64 * 64 + 256 * (kt & 1) + 4 * row);
+            if constexpr (FMT == 1) { // lane half kq has words 4 kq .. 4 kq + 3 of the step's eight; it takes words 2 q + kq
+                const u32x4 c = *reinterpret_cast<const u32x4 *>(p + row * 64 + (((2 * (kt & 1) + kq) ^ ((r >> 2) & 3)) * 16));
+                const auto first = __builtin_amdgcn_permlane32_swap(c.x, c.y, false, false);
+                const auto second = __builtin_amdgcn_permlane32_swap(c.z, c.w, false, false);
+                codes[n] = u32x4{first[0], second[0], first[1], second[1]};
+            } else {
+                codes[n] = *reinterpret_cast<const u32x4 *>(p + row * 32 + 16 * (kt & 1));
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) scale[half][n] = __uint_as_float(__builtin_amdgcn_perm(0u, word, sel[half]));
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------------------------
 // Output tiles of 128 rows x 256 columns: 4 wavefronts side by side, each all rows x 64 columns of its own (4 x 2 MFMA tiles); two
@@ -558,24 +696,10 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
         }
     }
     const bool loads_tokens = wave < live;
-    // weight rows: down: 64 consecutive ones; gate/up: 32 gate rows, then the same up rows.  (The last tile of columns may be half a
-    // tile: the wavefronts of the missing half load the last rows again.)
+    // (the last tile of columns may be half a tile: the wavefronts of the missing half load the last rows again)
     const int N = DOWN ? a.d : fe, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
     const int row0 = first < N ? first : N - (DOWN ? 64 : 32);
-    const uint32_t rb = FMT == 0 ? (uint32_t)K * 2 : (FMT == 1 ? (uint32_t)K / 2 : (uint32_t)K / 4);
-    const uint64_t w_lo = scalar_ptr(uniform_load(DOWN ? &h->w_down : &h->w_gate)) + (uint64_t)row0 * rb;
-    const uint64_t w_hi = DOWN ? w_lo + (uint64_t)32 * rb : scalar_ptr(uniform_load(&h->w_up)) + (uint64_t)row0 * rb;
-    const int lg = __builtin_ctz((unsigned)a.group), G = K >> lg;
-    uint64_t s_base = 0; // scales of the lane's row `lane`
-    uint32_t s_row = 0, b_off[2] = {0, 0};
-    if constexpr (quant) {
-        const uint64_t s_lo = scalar_ptr(uniform_load(DOWN ? &h->s_down : &h->s_gate)), s_hi = DOWN ? s_lo : scalar_ptr(uniform_load(&h->s_up));
-        s_base = lane < 32 ? s_lo : s_hi;
-        s_row = (uint32_t)(row0 + (DOWN ? lane : lane & 31)) * (uint32_t)G;
-    } else {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) b_off[p] = (uint32_t)(lane >> 3) * rb + (uint32_t)((lane & 7) ^ (4 * p + (lane >> 4))) * 16; // even and odd groups of eight rows
-    }
+    const weight_rows<DOWN, FMT> w(h, row0, K, a.group, lane);
     auto issue_token = [&](int slot, int i) { // called for steps 0, 1, 2, ...
         if (loads_tokens) {
             load_to_lds(lds0 + (uint32_t)(slot * cfg::A_SLOT + (32 * wave + 8 * i) * kLine), a_at[i]);
@@ -588,41 +712,17 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
     };
     const uint32_t b_at = lds0 + B0 + wave * cfg::B_WAVE;
     auto issue_weight = [&](int kt, int i) { // bf16
-        load_to_lds(b_at + 1024 * i, b_off[i & 1], (i < 4 ? w_lo : w_hi) + (uint64_t)(8 * (i & 3)) * rb + (uint64_t)kt * kLine);
+        load_to_lds(b_at + 1024 * i, w.off[i & 1], w.rows_base(kt, i));
     };
     const uint32_t c_at = lds0 + B0 + wave * 2 * cfg::SIDE_WIDE;
-    // Codes of steps 2c and 2c + 1 (int4: 64 bytes of a row, four lanes to it, piece p of row r in slot p ^ ((r >> 2) & 3); int2: 32 bytes,
-    // two lanes) and the aligned words that their scales are in.  Past the end of an odd number of steps the first half is read again.
-    auto issue_codes = [&](int c, int slot) {
-        const uint32_t m0 = c_at + (uint32_t)(slot * cfg::SIDE_WIDE);
-        const bool whole = 2 * c + 1 < nk; // wave-uniform
-        if constexpr (FMT == 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                uint32_t piece = (uint32_t)((lane & 3) ^ (lane >> 4)); // row 16 i + lane / 4
-                piece = whole ? piece : piece & 1;
-                load_to_lds(m0 + 1024 * i, (uint32_t)(lane >> 2) * rb + piece * 16, (i < 2 ? w_lo : w_hi) + (uint64_t)(16 * (i & 1)) * rb + (uint64_t)c * 64);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const uint32_t piece = whole ? lane & 1 : 0;
-                load_to_lds(m0 + 1024 * i, (uint32_t)(lane >> 1) * rb + piece * 16, (i == 0 ? w_lo : w_hi) + (uint64_t)c * 32);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int kt = whole ? 2 * c + u : 2 * c;
-            load_to_lds4(m0 + 64 * 64 + 256 * u, s_base + (((s_row + (uint32_t)((kt * BK) >> lg)) * 2) & ~3u));
-        }
-    };
+    auto issue_codes = [&](int c, int slot) { w.issue_codes(c_at + (uint32_t)(slot * cfg::SIDE_WIDE), c, nk, lane); }; // of steps 2c and 2c + 1
 
     // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
     const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
     if constexpr (DOWN) { // the pair indices of the tile's rows, where they go
         if (!shared && wave < 2) {
             const int slot = t.mt * ROWS + wave * 64 + lane;
-            load_to_lds4(lds0 + cfg::RING + 256 * wave, (uint32_t)(slot < t.m ? slot : t.m - 1) * 4u, scalar_ptr(a.perm + t.seg0));
+            load_to_lds4(lds0 + cfg::LDS + 256 * wave, (uint32_t)(slot < t.m ? slot : t.m - 1) * 4u, scalar_ptr(a.perm + t.seg0));
         }
     }
     f32x16 acc[4][2];
@@ -666,6 +766,7 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
     // The half of the aligned word that a scale is in, as v_perm_b32 wants it: (row * groups + group) odd or even (the parity of a
     // row's place in its matrix is that of its place in the tile); with groups of 32 both groups of a step are in the word.
     constexpr uint32_t kFirst = 0x01000C0Cu, kOther = 0x02020000u;
+    const int lg = w.lg, G = K >> lg;
     const uint32_t scale_sel = kFirst ^ (G & r & 1 ? kOther : 0u);
     uint32_t crumb_at[8]; // bit positions of the lane's codes in a word (int2)
 #pragma unroll
@@ -748,7 +849,7 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
         if (row >= rows) continue;
         dx_bf16 *dst;
         if constexpr (DOWN) {
-            const int orow = shared ? t.seg0 + slot : *reinterpret_cast<const int *>(ring + cfg::RING + 4 * row);
+            const int orow = shared ? t.seg0 + slot : *reinterpret_cast<const int *>(ring + cfg::LDS + 4 * row);
             dst = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)orow * a.d + col + 8 * kq;
         } else {
             dst = a.h + (size_t)(t.seg0 + slot) * a.fmax + col + 8 * kq;
@@ -757,17 +858,223 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Segments of up to 32 rows: 4 wavefronts side by side, each the segment's rows x 64 columns of its own (1 x 2 MFMA tiles); two blocks
+// to a compute unit.  What bounds it: the weights, which nothing else asks for, so a compute unit needs enough of them on their way.
+// Tokens are the first MFMA operand: accumulator element v is token (v / 4) * 8 + (lane / 32) * 4 + v % 4 of weight row lane % 32.
+
+// where a lane's part of token row 8 * wave + lane / 8 comes from (rows past the end repeat the last one)
+template <bool DOWN>
+__device__ __forceinline__ uint64_t thin_token_at(const dx_fwd_args &a, const tile_id &t, int K, int wave, int lane)
+{
+    const int row = 8 * wave + (lane >> 3), slot = row < t.m ? row : t.m - 1;
+    const uint32_t piece = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));
+    if constexpr (DOWN) return (uint64_t)a.h + (uint64_t)(t.seg0 + slot) * a.fmax * 2 + piece * 16;
+    else return (uint64_t)a.x + (uint64_t)(a.perm[t.seg0 + slot] / a.k) * K * 2 + piece * 16;
+}
+
+// row of H or O that token lane % 32 goes to
+template <bool DOWN>
+__device__ __forceinline__ int thin_row(const dx_fwd_args &a, const tile_id &t, int lane)
+{
+    const int r = lane & 31, place = t.seg0 + (r < t.m ? r : t.m - 1);
+    return DOWN ? a.perm[place] : place;
+}
+
+template <bool DOWN>
+__device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &t, const f32x16 (&acc)[2], int row, int first, int lane)
+{
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int token = (v >> 2) * 8 + 4 * (lane >> 5) + (v & 3);
+        const int to = __shfl(row, token);
+        if (token >= t.m) continue;
+        if constexpr (DOWN) {
+            dx_bf16 *dst = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)to * a.d + first + (lane & 31);
+            const uint32_t both = pack_bf16(acc[0][v], acc[1][v]);
+            dst[0] = (dx_bf16)both, dst[32] = (dx_bf16)(both >> 16);
+        } else {
+            a.h[(size_t)to * a.fmax + first + (lane & 31)] = (dx_bf16)pack_bf16(swiglu_fast(acc[0][v], acc[1][v]), 0.f);
+        }
+    }
+}
+
+// Quantized weights.  The codes of two steps (half a line of a row) and their tokens are a slot; two slots are in flight while the third is
+// multiplied.  The values are multiplied as integers, 16 (int4) or 64 (int2) times the code, and the group's scale
+// multiplies the group's fp32 sums once, as in the streaming kernels.  (By way of registers, as bf16 weights come: 5 to 15 % slower.)
+//   LDS: token rows, laid out as in the other kernels, then the codes of each wavefront alone.  One barrier per slot: behind it every
+//   wavefront has read the slot that is filled next.
+template <bool DOWN, int FMT>
+__device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
+{
+    constexpr int SLOTS = cfg::THIN_SLOTS, A_SLOT = 2 * cfg::THIN_A, W_SLOT = cfg::SIDE_WIDE, W0 = SLOTS * A_SLOT;
+    constexpr int LOADS = FMT == 1 ? 8 : 6; // of a wavefront per slot
+    const int K = DOWN ? a.f : a.d, nk = K / BK, ns = (nk + 1) / 2; // steps, slots
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)ring;
+
+    // ---- loader: wavefront w fills token rows [8w, 8w + 8) and its own 64 weight rows ----
+    uint64_t a_at = thin_token_at<DOWN>(a, t, K, wave, lane);
+    // (the last tile of columns may be half a tile: the wavefronts of the missing half load the last rows again)
+    const int N = DOWN ? a.d : a.f, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
+    const weight_rows<DOWN, FMT> w(h, first < N ? first : N - (DOWN ? 64 : 32), K, a.group, lane);
+    auto issue = [&](int s, int slot) { // called for s = 0, 1, 2, ...
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            load_to_lds(lds0 + (uint32_t)(slot * A_SLOT + u * cfg::THIN_A + 1024 * wave), a_at);
+            a_at += 2 * s + u + 1 < nk ? kLine : 0;
+        }
+        w.issue_codes(lds0 + (uint32_t)(W0 + (wave * SLOTS + slot) * W_SLOT), s, nk, lane);
+    };
+
+    // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
+    const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
+    const int row = thin_row<DOWN>(a, t, lane);
+    f32x16 acc[2], part[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[n][v] = part[n][v] = 0.f;
+    constexpr float kUnit = FMT == 1 ? 0.0625f : 0.015625f; // what the integers are multiples of
+    auto flush = [&](const float (&scale)[2]) { // a group is complete
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                acc[n][v] = fmaf(part[n][v], scale[n] * kUnit, acc[n][v]);
+                part[n][v] = 0.f;
+            }
+    };
+    issue(0, 0);
+    if (ns > 1) issue(1, 1);
+    int slot = 0;
+    for (int s = 0; s < ns; ++s) {
+        // own loads of the slot have landed; after the barrier that holds for every wavefront, and all have read the slot before it
+        if (s + 1 < ns) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        block_barrier();
+        if (s + 2 < ns) issue(s + 2, slot == 0 ? SLOTS - 1 : slot - 1);
+        const char *wp = ring + W0 + (wave * SLOTS + slot) * W_SLOT;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int kt = 2 * s + u;
+            if (kt >= nk) break; // wave-uniform
+            frag8 af[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                af[q].u = *reinterpret_cast<const u32x4 *>(ring + slot * A_SLOT + u * cfg::THIN_A + r * kLine + (((2 * q + kq) ^ swz) * 16));
+            u32x4 codes[2];
+            float scale[2][2]; // [first and second half of the step][tile]
+            w.read_codes(wp, kt, lane, codes, scale);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    frag8 b;
+                    if constexpr (FMT == 1) b.u = dequant8_bytes(codes[n][q], 1.f);
+                    else b.u = crumbs_as_integers(codes[n][q], kq);
+                    part[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[q].v, b.v, part[n], 0, 0, 0);
+                }
+                if (q == 1 && w.lg == 5) flush(scale[0]);
+            }
+            if (w.lg < 7 || u || kt + 1 == nk) flush(scale[1]);
+        }
+        slot = slot + 1 < SLOTS ? slot + 1 : 0;
+    }
+    if (first < N) store_thin<DOWN>(a, t, acc, row, first, lane);
+}
+
+// bf16 weights.  They and the token rows come to registers, two steps in flight, and pass through LDS on their way to the operands: with the
+// non-temporal hint, from which loads to LDS gain nothing, a cold stream runs at 6.2 TB/s, by loads to LDS at 5.2 (30B-shaped, 130 tokens: a
+// layer 107 us by loads to LDS, 101 this way; three steps in flight 102).
+//   LDS: two slots of token rows, one barrier per step: behind it every wavefront has read the slot that is filled next; one slot of the
+//   weights of each wavefront alone.
+template <bool DOWN>
+__device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
+{
+    constexpr int DEPTH = 2, W0 = 2 * cfg::THIN_A;
+    static_assert(W0 + cfg::WAVES * cfg::B_WAVE <= cfg::LDS, "the ring");
+    const int K = DOWN ? a.f : a.d, nk = K / BK;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // ---- loader: wavefront w loads token rows [8w, 8w + 8) and its own 64 weight rows (the last tile of columns may be half a tile: the
+    // wavefronts of the missing half load the last rows again) ----
+    const DX_GLOBAL char *const a_at = (const DX_GLOBAL char *)thin_token_at<DOWN>(a, t, K, wave, lane);
+    const int N = DOWN ? a.d : a.f, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
+    const weight_rows<DOWN, 0> w(h, first < N ? first : N - (DOWN ? 64 : 32), K, a.group, lane);
+    struct step_regs {
+        u32x4 tokens, weights[8];
+    } st[DEPTH];
+    auto fetch = [&](int kt, step_regs &to) __attribute__((always_inline)) {
+        to.tokens = *reinterpret_cast<const DX_GLOBAL u32x4 *>(a_at + (uint32_t)(kt * kLine));
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            to.weights[i] = __builtin_nontemporal_load(reinterpret_cast<const DX_GLOBAL u32x4 *>(w.rows_base(kt, i) + w.off[i & 1]));
+    };
+
+    // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
+    const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
+    const int row = thin_row<DOWN>(a, t, lane);
+    f32x16 acc[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
+    char *const w_at = ring + W0 + wave * cfg::B_WAVE;
+    // step kt: to LDS and, behind the barrier, into the products; its registers take step `next` (negative: none)
+    auto consume = [&](int kt, step_regs &from, int next) __attribute__((always_inline)) {
+        char *const a_slot = ring + (kt & 1) * cfg::THIN_A;
+        *reinterpret_cast<u32x4 *>(a_slot + 1024 * wave + 16 * lane) = from.tokens;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4 *>(w_at + 1024 * i + 16 * lane) = from.weights[i];
+        if (next >= 0) fetch(next, from);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // own stores are in LDS; behind the barrier every wavefront's
+        block_barrier();
+        frag8 af[4], b[2][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int at = r * kLine + (((2 * q + kq) ^ swz) * 16);
+            af[q].u = *reinterpret_cast<const u32x4 *>(a_slot + at);
+#pragma unroll
+            for (int n = 0; n < 2; ++n) b[n][q].u = *reinterpret_cast<const u32x4 *>(w_at + 32 * n * kLine + at);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[q].v, b[n][q].v, acc[n], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i)
+        if (i < nk) fetch(i, st[i]);
+    // With every load issued without a branch the compiler waits for the step that it stores only; the last steps apart.
+    int kt = 0;
+    for (; kt + 2 * DEPTH - 1 < nk; kt += DEPTH)
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) consume(kt + i, st[i], kt + i + DEPTH);
+    for (; kt < nk; kt += DEPTH)
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (kt + i < nk) consume(kt + i, st[i], kt + i + DEPTH < nk ? kt + i + DEPTH : -1);
+    if (first < N) store_thin<DOWN>(a, t, acc, row, first, lane);
+}
+
 template <bool DOWN>
 __global__ __launch_bounds__(cfg::THREADS, 2) void k_tiled(dx_fwd_args a)
 {
     // the ring and (down) the pair indices of the rows: two blocks to a compute unit
-    __shared__ __attribute__((aligned(1024))) char ring[cfg::RING + (DOWN ? 256 * cfg::WAVES : 0)];
-    bool wide;
-    const tile_id t = find_tile<DOWN>(a, wide);
+    __shared__ __attribute__((aligned(1024))) char ring[cfg::LDS + (DOWN ? 256 * cfg::WAVES : 0)];
+    tile_kind kind;
+    const tile_id t = find_tile<DOWN>(a, kind);
     if (!t.valid) return; // block-uniform
     const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
     const int fmt = (int)uniform_load(&h->fmt);
-    if (wide) {
+    if (kind == kThin) {
+        if (fmt == DX_FMT_INT4G) thin_codes<DOWN, 1>(a, t, h, ring);
+        else if (fmt == DX_FMT_INT2G) thin_codes<DOWN, 2>(a, t, h, ring);
+        else thin_rows<DOWN>(a, t, h, ring);
+    } else if (kind == kWide) {
         if (fmt == DX_FMT_INT4G) wide_tile<DOWN, 1>(a, t, h, ring);
         else if (fmt == DX_FMT_INT2G) wide_tile<DOWN, 2>(a, t, h, ring);
         else wide_tile<DOWN, 0>(a, t, h, ring);
@@ -1001,6 +1308,16 @@ __global__ __launch_bounds__(kBigThreads) void k_big(dx_fwd_args a)
     else big_tile<DOWN, false>(a, t, h, ring);
 }
 
+// The list of row tiles on a caller's routing arrays (one block).
+constexpr int kListThreads = 1024; // an expert to a thread
+
+__global__ __launch_bounds__(kListThreads) void k_tile_list(dx_list_args l, const int32_t *offsets)
+{
+    __shared__ int sums[kListThreads / 64][dx_tile_list::kCounts];
+    const int e = threadIdx.x < (unsigned)l.E ? (int)threadIdx.x : l.E, seg0 = offsets[e];
+    dx_tile_list::write<kListThreads / 64>(l, e, seg0, e < l.E ? offsets[e + 1] - seg0 : 0, sums);
+}
+
 } // namespace
 
 template <bool DOWN>
@@ -1008,8 +1325,11 @@ static void launch_tiles(const dx_fwd_args &a, hipStream_t s)
 {
     // an upper bound on the tile count; surplus blocks find no tile and leave
     const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
-    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, a.m_small, a.shared != nullptr) * columns_of<DOWN>(a, fe, BN);
-    hipLaunchKernelGGL((k_tiled<DOWN>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(cfg::THREADS), 0, s, a);
+    const long pairs = (long)a.T * a.k, active = pairs < a.E ? pairs : a.E, above = pairs / (DX_THIN_ROWS + 1);
+    const long thin = active - (above < active ? above : active); // beside as many of more rows as there can be
+    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, DX_THIN_ROWS, a.shared != nullptr) * columns_of<DOWN>(a, fe, BN);
+    const long blocks = (tiles + 7) / 8 * 8 + (thin * columns_of<DOWN>(a, a.f, BNW) + 15) / 16 * 16;
+    hipLaunchKernelGGL((k_tiled<DOWN>), dim3((unsigned)blocks), dim3(cfg::THREADS), 0, s, a);
 }
 
 template <bool DOWN>
@@ -1020,6 +1340,10 @@ static void launch_big_tiles(const dx_fwd_args &a, hipStream_t s)
     if (a.m_big && tiles) hipLaunchKernelGGL((k_big<DOWN>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(kBigThreads), 0, s, a);
 }
 
+void dxk_tile_list(const dx_list_args &l, const int32_t *offsets, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_tile_list, dim3(1), dim3(kListThreads), 0, s, l, offsets);
+}
 void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s)
 {
     launch_big_tiles<false>(a, s);

@@ -12,6 +12,7 @@
 // population counts of mask prefixes.  No atomics decide any position.
 #include "dx_internal.h"
 #include "dx_route_core.h"
+#include "dx_tile_list.h"
 
 #include <cfloat>
 #include <cstdarg>
@@ -184,17 +185,18 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_sums(int E, int split, 
 __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     const int32_t *__restrict__ ids, int T, int E, int k, int split /* log2 of S */, int n_chunks,
     const unsigned long long *__restrict__ mask, const int32_t *__restrict__ sums, int32_t *__restrict__ counts,
-    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, unsigned long long *__restrict__ hotness)
+    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, unsigned long long *__restrict__ hotness, dx_list_args list)
 {
     __shared__ unsigned long long lds_mask[kRouteThreads];
     __shared__ int lds_at[kRouteThreads]; // where the chunk's first pair of the expert goes
     __shared__ int lds_tot[kWaves];
-    const int chunk = blockIdx.x, S = 1 << split;
+    const bool lists = (int)blockIdx.x == n_chunks; // a block more: the list of row tiles
+    const int chunk = lists ? 0 : blockIdx.x, S = 1 << split;
     const int p0 = chunk * kChunk * k, n = min(T - chunk * kChunk, kChunk) * k;
     // asked for here because the masks' way to the first use takes as long as theirs: the first pair's expert, the counter
     const int first_id = ids[p0 + min((int)threadIdx.x, n - 1)];
     const int e = threadIdx.x >> split, part = threadIdx.x & (S - 1);
-    const bool counts_hot = chunk == 0 && part == 0 && e < E && hotness;
+    const bool counts_hot = blockIdx.x == 0 && part == 0 && e < E && hotness;
     const unsigned long long hot_before = counts_hot ? hotness[e] : 0ull;
     int total = 0, before = 0;
     if (e < E) {
@@ -242,6 +244,12 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     }
     int all;
     const int off = block_exclusive_scan(part == 0 && e < E ? total : 0, lds_tot, &all);
+    if (lists) { // block-uniform
+        __shared__ int sums_of_list[kWaves][dx_tile_list::kCounts];
+        const bool owner = part == 0 && e < E;
+        dx_tile_list::write<kWaves>(list, owner ? e : E, off, owner ? total : 0, sums_of_list);
+        return;
+    }
     if (part == 0 && e < E) {
         lds_at[e] = off + before;
         if (chunk == 0) {
@@ -438,7 +446,7 @@ hipError_t launch_topk(const float *logits, int T, int E, int k, int32_t *ids, f
 
 hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, float *w, int32_t *counts,
                      int32_t *offsets, int32_t *perm, unsigned long long *mask, int32_t *sums, unsigned long long *hotness,
-                     hipStream_t s)
+                     const dx_list_args &list, hipStream_t s)
 {
     // T == 0 still runs one (empty) chunk so that counts and offsets are written.
     const int n_chunks = T > 0 ? (T + kChunk - 1) / kChunk : 1;
@@ -465,8 +473,8 @@ hipError_t dxk_route(const float *logits, int T, int E, int k, int32_t *ids, flo
     if (!direct)
         hipLaunchKernelGGL(k_route_sums, dim3((n_chunks + kSumChunks - 1) / kSumChunks), dim3(kRouteThreads), 0, s, E, split,
                            n_chunks, mask, sums);
-    hipLaunchKernelGGL(k_route_place, dim3(n_chunks), dim3(kRouteThreads), 0, s, ids, T, E, k, split, n_chunks, mask,
-                       static_cast<const int32_t *>(direct ? nullptr : sums), counts, offsets, perm, hotness);
+    hipLaunchKernelGGL(k_route_place, dim3(n_chunks + (list.tiles ? 1 : 0)), dim3(kRouteThreads), 0, s, ids, T, E, k, split, n_chunks, mask,
+                       static_cast<const int32_t *>(direct ? nullptr : sums), counts, offsets, perm, hotness, list);
     return hipGetLastError();
 }
 
@@ -585,7 +593,7 @@ extern "C" dx_status dx_route_static(const float *logits, int T, int E, int top_
         sp = g_scratch_ptr[dev];
     }
     // Nothing in the scratch has to start at zero: every chunk's block writes all E masks of its chunk.
-    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, sp->sums, nullptr,
+    e = dxk_route(logits, T, E, top_k, ids, w, counts, offsets, perm, sp->mask, sp->sums, nullptr, dx_list_args{},
                   static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return static_fail(DX_ERR_HIP, "dx_route_static: launch: %s", hipGetErrorString(e));
     return DX_OK;

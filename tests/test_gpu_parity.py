@@ -683,6 +683,53 @@ def test_forward_prefill_wide_tiles(B, LY, dxo, pair, T, E, k, d, f, group, hi):
     ctx.close()
 
 
+@pytest.mark.parametrize("pair,d,f,group", [
+    ("bf16-int4", 128, 64, 32),     # two steps and one; a quarter and half of a tile's columns
+    ("bf16-int4", 384, 320, 64),    # six steps and five, odd numbers of groups per row; 2.5 and 1.5 column tiles
+    ("bf16-int4", 640, 384, 128),   # ten steps and six, five and three groups
+    ("bf16-int4", 2048, 768, 128),  # the 30B layer's
+    ("int4-int2", 384, 320, 64),
+    ("int4-int2", 256, 128, 128),
+    ("int4-int2", 2048, 768, 128),
+])
+def test_forward_prefill_thin_segments(B, LY, dxo, pair, d, f, group):
+    """Segments of up to 32 rows in a call on tiles: none, 1, 16, 17, 31 and 32 rows and one above, in both formats, every token
+    against the oracle; the list of tiles from the routing kernels and from the caller's arrays: the same bits."""
+    import dataclasses
+    sizes = [0, 1, 16, 17, 31, 32, 33]
+    E, T = 2 * len(sizes), 2 * sum(sizes)
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=1, d=d, f=f, group=group)
+    x, _ = W.layer_inputs(wl, seed=17)
+    logits = np.zeros((T, E), np.float32)
+    logits[np.arange(T), np.random.default_rng(3).permutation(np.repeat(np.arange(E), np.repeat(sizes, 2)))] = 4.0
+    hi = list(range(0, E, 2))
+    print(f"thin segments {pair} d={d} f={f} group={group} T={T}", flush=True)
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 17, T)
+    else:
+        keep = Layer(B, LY, dxo, wl, hi, seed=17)
+        ctx, versions = keep.ctx, keep.versions
+    ids, w, counts, offsets, perm = dxo.route(logits, 1)
+    assert counts.tolist() == np.repeat(sizes, 2).tolist()
+    rb = LY.RoutingBuffers(T, E, 1)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    rb.route_forward(ctx, 0, ld, xd, y)
+    y1 = torch.full_like(y, float("nan"))
+    rb.route(ctx, 0, ld)
+    rb.forward(ctx, 0, xd, y1)
+    sync()
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w)
+    bits = LY.device_to_bits(y)
+    assert np.array_equal(bits, LY.device_to_bits(y1))
+    yg = bf16_bits_to_f32(bits).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(bits, y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    assert_elementwise(dxo, bits, y_ref, versions, group, x, ids, w, T_call=T)
+    del keep
+    ctx.close()
+
+
 def _wide_phases(counts, hi, f, d, T, shared_f=0, hi_quantized=False):
     """Whether the 128-row tiles of a call (segments below 512 rows, none in 256-row tiles) are 256 columns wide: gate/up, down."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
