@@ -53,20 +53,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// 8 nibbles of `word` times scale -> 8 bf16 in element order
-__device__ __forceinline__ u32x4 dequant8(uint32_t word, float scale)
-{
-    uint32_t p[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        p[i] = pack_bf16((float)((int)(word << (28 - 8 * i)) >> 28) * scale,
-                         (float)((int)(word << (24 - 8 * i)) >> 28) * scale);
-    return u32x4{p[0], p[1], p[2], p[3]};
-}
-
-// The same from 16ths of the scale (exact: a bf16 scale has eight significant bits): the nibbles as the upper halves of signed bytes,
-// which the conversion takes out of their word by itself.
-__device__ __forceinline__ u32x4 dequant8_bytes(uint32_t word, float scale16)
+// 8 nibbles of `word` times 16 * scale16 -> 8 bf16 in element order (16ths of a bf16 scale are exact: it has eight significant bits): the
+// nibbles as the upper halves of signed bytes, which the conversion takes out of their word by itself.
+__device__ __forceinline__ u32x4 dequant8(uint32_t word, float scale16)
 {
     const uint32_t even = (word << 4) & 0xF0F0F0F0u, odd = word & 0xF0F0F0F0u;
     uint32_t p[4];
@@ -76,39 +65,30 @@ __device__ __forceinline__ u32x4 dequant8_bytes(uint32_t word, float scale16)
     return u32x4{p[0], p[1], p[2], p[3]};
 }
 
-// 8 two-bit codes (bits 16*half .. of `word`) times scale -> 8 bf16 in element order
-__device__ __forceinline__ u32x4 dequant8_crumbs(uint32_t word, int half, float scale)
-{
-    const uint32_t h = word >> (16 * half);
-    uint32_t p[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        p[i] = pack_bf16((float)((int)(h << (30 - 4 * i)) >> 30) * scale, (float)((int)(h << (28 - 4 * i)) >> 30) * scale);
-    return u32x4{p[0], p[1], p[2], p[3]};
-}
+// The four products of a two-bit code (0, 1, -2, -1) and a bf16 scale, which are bf16 values: their lower and their upper bytes.
+struct crumb_products {
+    uint32_t lo, hi;
+    __device__ __forceinline__ explicit crumb_products(float scale)
+    {
+        const uint32_t zero = __float_as_uint(0.f * scale), one = __float_as_uint(scale), minus_two = __float_as_uint(-2.f * scale);
+        // bytes (zero, one, minus two, one) of what is in the upper halves; then minus one is one with the other sign
+        const uint32_t los = __builtin_amdgcn_perm(minus_two, one, 0x02060200u), his = __builtin_amdgcn_perm(minus_two, one, 0x03070300u);
+        lo = __builtin_amdgcn_perm(zero, los, 0x03020106u);
+        hi = __builtin_amdgcn_perm(zero, his, 0x03020107u) ^ 0x80000000u;
+    }
+};
 
-// 8 two-bit codes at bits at[0..7] of `word` times scale -> 8 bf16 in element order
-__device__ __forceinline__ u32x4 dequant8_crumbs_at(uint32_t word, const uint32_t (&at)[8], float scale)
+// 8 two-bit codes (`half`: 16 bits) times the scale -> 8 bf16 in element order.  A byte selection looks a pair up: its selector is code a, code a + 4, code b,
+// code b + 4.  (15 vector instructions; by conversions and products 28.  16 experts of 4096 x 6400, int4/int2, a layer, us: 300 tokens 297 and 282, 1100
+// tokens 557 and 542; 30B-shaped, 500 tokens 146 and 141.)
+__device__ __forceinline__ u32x4 dequant8_crumbs(uint32_t half, const crumb_products &of)
 {
-    auto code = [&](int j) { return (float)(int)__builtin_amdgcn_sbfe((int)word, at[j], 2) * scale; };
-    return u32x4{pack_bf16(code(0), code(1)), pack_bf16(code(2), code(3)), pack_bf16(code(4), code(5)), pack_bf16(code(6), code(7))};
-}
-
-// 8 two-bit codes (half `half` of `word`) as bf16 integers, 64 times the code, in element order: crumb i of every byte as its upper
-// two bits, which the conversion takes out of their word by itself
-__device__ __forceinline__ u32x4 crumbs_as_integers(uint32_t word, int half)
-{
-    const uint32_t h = word >> (16 * half);
-    uint32_t at[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) at[i] = (h << (6 - 2 * i)) & 0xC0C0u;
-    uint32_t p[4];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            p[2 * b + i] = pack_bf16((float)(int8_t)(at[2 * i] >> (8 * b)), (float)(int8_t)(at[2 * i + 1] >> (8 * b)));
-    return u32x4{p[0], p[1], p[2], p[3]};
+    const uint32_t w = half | (half << 14), v = w >> 4; // codes 2j and 2j + 1 sixteen bits apart: 0 and 4 (in v: 2 and 6) first
+    auto two = [&](uint32_t from, uint32_t bytes) {
+        const uint32_t sel = (__builtin_amdgcn_perm(from, from, bytes) & 0x03030303u) | 0x04000400u;
+        return __builtin_amdgcn_perm(of.hi, of.lo, sel);
+    };
+    return u32x4{two(w, 0x02020000u), two(v, 0x02020000u), two(w, 0x03030101u), two(v, 0x03030101u)};
 }
 
 // Reads of what the kernel never writes at a wave-uniform index, as scalar loads.
@@ -421,12 +401,13 @@ __device__ __forceinline__ void narrow_tile(const dx_fwd_args &a, const tile_id 
             uint32_t c[PIECES];
             __builtin_memcpy(c, __builtin_assume_aligned(side + 4 * PIECES * lane, 4 * PIECES), 4 * PIECES);
 #pragma unroll
-            for (int i = 0; i < PIECES; ++i) put(i, dequant8(c[i], scale));
+            for (int i = 0; i < PIECES; ++i) put(i, dequant8(c[i], scale * 0.0625f));
         } else { // half a word per piece
+            const crumb_products products(scale);
             uint32_t c[PIECES / 2];
             __builtin_memcpy(c, __builtin_assume_aligned(side + 2 * PIECES * lane, 2 * PIECES), 2 * PIECES);
 #pragma unroll
-            for (int i = 0; i < PIECES; ++i) put(i, dequant8_crumbs(c[i / 2], i & 1, scale));
+            for (int i = 0; i < PIECES; ++i) put(i, dequant8_crumbs(i & 1 ? c[i / 2] >> 16 : c[i / 2] & 0xFFFFu, products));
         }
     };
 
@@ -662,7 +643,7 @@ struct weight_rows {
 //   LDS: two slots of token rows (laid out as in the other kernel); weights: of the wavefront alone, no barrier.  Codes come for two steps
 //   at a time, 64 (int2: 32) bytes of a row, into two slots.  The matrix instructions take the elements of every format in the order
 //   of the narrow tiles, so a token's result does not depend on which kind a call has.  What that costs (swaps, shifts, a scale more) the
-//   expansion makes up for: nibbles as bytes that the conversion picks, crumbs at positions kept in registers.  Calls, us, with the lanes'
+//   expansion makes up for: nibbles as bytes that the conversion picks, pairs of crumbs that a byte selection looks up.  Calls, us, with the lanes'
 //   own order, in order, and in order with this expansion: all int4, 16 experts of 4096 x 6400, 200 rows each 689, 691 and 663, 128 of 2048 x 768,
 //   40 rows 166, 168 and 161; int2 616, 614 and 612, 147, 148 and 145.
 template <bool DOWN, int FMT>
@@ -768,18 +749,13 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
     constexpr uint32_t kFirst = 0x01000C0Cu, kOther = 0x02020000u;
     const int lg = w.lg, G = K >> lg;
     const uint32_t scale_sel = kFirst ^ (G & r & 1 ? kOther : 0u);
-    uint32_t crumb_at[8]; // bit positions of the lane's codes in a word (int2)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        crumb_at[j] = 16 * kq + 2 * j;
-        if constexpr (FMT == 2) asm volatile("" : "+v"(crumb_at[j])); // (kept, not derived again at every use)
-    }
     float scale[2][2] = {}; // of the first and of the second half of the step's elements
+    crumb_products products[2] = {crumb_products(0.f), crumb_products(0.f)}; // int2 (groups of 64 and more: of the whole step)
     auto operand = [&](int ns, int s) {
         frag8 b;
         if constexpr (FMT == 0) b.u = fb[ns][s];
-        else if constexpr (FMT == 1) b.u = dequant8_bytes(fb[ns][0][s], scale[ns][s >> 1]);
-        else b.u = dequant8_crumbs_at(fb[ns][0][s], crumb_at, scale[ns][s >> 1]);
+        else if constexpr (FMT == 1) b.u = dequant8(fb[ns][0][s], scale[ns][s >> 1]);
+        else b.u = dequant8_crumbs(__builtin_amdgcn_ubfe(fb[ns][0][s], 16 * kq, 16), products[ns]);
         return b;
     };
     if constexpr (quant) {
@@ -815,6 +791,7 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
                 }
 #pragma unroll
                 for (int half = 0; half < 2; ++half) scale[ns][half] = __uint_as_float(__builtin_amdgcn_perm(0u, scales[ns], sel[half])) * (FMT == 1 ? 0.0625f : 1.f);
+                if constexpr (FMT == 2) products[ns] = crumb_products(scale[ns][0]);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -900,7 +877,7 @@ __device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &
 }
 
 // Quantized weights.  The codes of two steps (half a line of a row) and their tokens are a slot; two slots are in flight while the third is
-// multiplied.  The values are multiplied as integers, 16 (int4) or 64 (int2) times the code, and the group's scale
+// multiplied.  The values are multiplied as integers (int4: 16 times the code), and the group's scale
 // multiplies the group's fp32 sums once, as in the streaming kernels.  (By way of registers, as bf16 weights come: 5 to 15 % slower.)
 //   LDS: token rows, laid out as in the other kernels, then the codes of each wavefront alone.  One barrier per slot: behind it every
 //   wavefront has read the slot that is filled next.
@@ -936,7 +913,8 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
     for (int n = 0; n < 2; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[n][v] = part[n][v] = 0.f;
-    constexpr float kUnit = FMT == 1 ? 0.0625f : 0.015625f; // what the integers are multiples of
+    const crumb_products crumbs(1.f);
+    constexpr float kUnit = FMT == 1 ? 0.0625f : 1.f; // int4: the integers are 16 times the codes
     auto flush = [&](const float (&scale)[2]) { // a group is complete
 #pragma unroll
         for (int n = 0; n < 2; ++n)
@@ -972,8 +950,8 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
 #pragma unroll
                 for (int n = 0; n < 2; ++n) {
                     frag8 b;
-                    if constexpr (FMT == 1) b.u = dequant8_bytes(codes[n][q], 1.f);
-                    else b.u = crumbs_as_integers(codes[n][q], kq);
+                    if constexpr (FMT == 1) b.u = dequant8(codes[n][q], 1.f);
+                    else b.u = dequant8_crumbs(__builtin_amdgcn_ubfe(codes[n][q], 16 * kq, 16), crumbs);
                     part[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[q].v, b.v, part[n], 0, 0, 0);
                 }
                 if (q == 1 && w.lg == 5) flush(scale[0]);
@@ -1180,7 +1158,7 @@ __device__ __forceinline__ void big_tile(const dx_fwd_args &a, const tile_id &t,
             const int row = 32 * wave + 8 * i + (lane >> 3);
             const int pos = (lane & 7) ^ ((row >> 1) & 7);
             *reinterpret_cast<u32x4 *>(ring + stage * kStageBytes + TM * kRowBytes64 + row * kRowBytes64 + pos * 16) =
-                dequant8(codes, scale);
+                dequant8(codes, scale * 0.0625f);
         }
     };
 
