@@ -282,7 +282,8 @@ extern "C" dx_status dx_create(const dx_config *cfg, void *stream, dx_ctx **out)
     if ((e = hipMalloc(&c->d_mask_sums, n_sums * 4)) != hipSuccess) return fail(e, "route sums");
     if ((e = hipMalloc(&c->d_h, n_rows * c->fmax * sizeof(dx_bf16))) != hipSuccess) return fail(e, "H scratch");
     if ((e = hipMalloc(&c->d_o, n_rows * (size_t)g.d * sizeof(float))) != hipSuccess) return fail(e, "O scratch");
-    const size_t n_tile_rows = (size_t)dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0);
+    const size_t n_tile_rows = (size_t)std::max(dxk_tile_rows_max(g.max_tokens, g.top_k, g.E, 0, g.shared_f > 0),
+                                                dxk_thin_rows_max(std::min(g.max_tokens, DX_FP32_TOKENS), g.top_k, g.E, g.shared_f > 0));
     const size_t list_bytes = sizeof(dx_tile_head) + n_tile_rows * sizeof(dx_tile_row), places = (size_t)DX_FEW_TOKENS * g.top_k * sizeof(int32_t);
     if ((e = hipMalloc(&c->d_tiles, list_bytes > places ? list_bytes : places)) != hipSuccess) return fail(e, "tile list");
     // zero the table and the counters with fill kernels on the compute stream
@@ -492,7 +493,7 @@ extern "C" dx_status dx_route_forward(dx_ctx *c, int layer, const dx_handle *tab
     // shapes the self-routing kernel does not take: routing, which lists the row tiles of a call on tiles as well, and forward pass
     const dx_list_args list = dxk_list_args(a, c->n_cu);
     DX_HIP(c, dxk_route(logits, T, c->cfg.E, c->cfg.top_k, ids, w, counts, offsets, perm, c->d_mask, c->d_mask_sums, hot, list, c->compute));
-    a.listed = list.tiles != nullptr;
+    a.listed = list.tiles && T > DX_ROUTE_CHUNK; // (one chunk: no placement kernel)
     return forward(c, "dx_route_forward", a);
 }
 

@@ -123,13 +123,15 @@ struct dx_ctx {
                     __FILE__, __LINE__);                                                   \
     } while (0)
 
+constexpr int DX_ROUTE_CHUNK = 64; // tokens of a routing chunk; calls of one chunk are routed by one kernel
 constexpr int DX_SUM_CHUNKS = 32; // chunks whose population counts are added up together in large batches
 // What the list of row tiles is made from, beside the segments
 struct dx_list_args {
     const dx_handle *table;
     struct dx_tile_head *tiles; // null: no list
     int T, E, k, m_big, n_cu;
-    int shared; // the layer has a shared expert
+    int shared;    // the layer has a shared expert
+    int thin_only; // all segments in tiles of DX_THIN_ROWS rows
 };
 // ---- kernel launchers (each validates nothing; callers validate) ----------
 // dx_route.hip
@@ -160,7 +162,7 @@ struct dx_tile_head {
     int n_quant;             // of the former, those of quantized experts
     int n_single;            // and those of experts with one only
     int n_big, n_big_shared; // 256-row tiles
-    int n_thin, n_thin_quant; // segments of up to DX_THIN_ROWS rows, bf16 and quantized ones
+    int n_thin, n_thin_quant, n_thin_shared; // thin tiles' rows: of bf16 experts, of quantized ones, of the shared one
     int n_cu;
 };
 // most row tiles that segments of more than m_min rows can have in a call of T tokens (a routed expert has ceil(m / 128) of them)
@@ -170,6 +172,13 @@ inline long dxk_tile_rows_max(int T, int k, int E, int m_min, bool shared)
     // (256 rows in one 256-row tile are fewer tiles than in two of 128)
     return pairs / DX_TILE_ROWS + with + (shared ? (T + DX_TILE_ROWS - 1) / DX_TILE_ROWS : 0);
 }
+// and most rows of thin tiles when all segments are in them
+inline long dxk_thin_rows_max(int T, int k, int E, bool shared)
+{
+    const long pairs = (long)T * k;
+    return pairs / DX_THIN_ROWS + (pairs < E ? pairs : E) + (shared ? (T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0);
+}
+constexpr int DX_FP32_TOKENS = 128; // calls of up to so many tokens keep O in fp32 and never round a quantized weight
 // Calls of so few tokens (and top-k up to DX_ROUTED_MAX_TOPK) run the down projection and the combine in one kernel
 constexpr int DX_FEW_TOKENS = 2;
 struct dx_fwd_args {
@@ -184,6 +193,7 @@ struct dx_fwd_args {
     dx_bf16 *h;  // scratch [T*k (+T), fmax]
     float *o;    // scratch [T*k (+T), d]: fp32, or (tiles) bf16 in the same allocation
     int T, E, k, d, f, group, shared_f, fmax;
+    int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
     int any_quantized; // some routed expert of the table may be (a caller's table: unknown)
     // A list for the kernels of a call, or null: calls on tiles: the row tiles; up to DX_FEW_TOKENS tokens on a caller's

@@ -37,8 +37,8 @@
 //     the matrix instruction never crosses a quantization group, so the
 //     group's scale multiplies the group's fp32 partial sums once (q*s is
 //     never rounded).
-// Batches of up to 128 tokens run here (segments above 32 tokens in blocks of 32);
-// larger ones run on tiles.
+// Segments above 32 tokens go in blocks of 32.  Calls of more than 128 tokens, and of fewer on
+// layers whose K takes several rounds here, run on tiles (takes_tiles).
 #include "dx_internal.h"
 #include "dx_route_core.h"
 
@@ -2037,10 +2037,6 @@ void launch_few(const dx_fwd_args &a, int n_cu, hipStream_t s, hipEvent_t start,
     else launch(k_gate_up_few<32, true>, grid, block, s, start, stop, a, *r);
 }
 
-// Up to this many tokens per call the streaming kernels alone are faster than streamed experts and tiles (30B-shaped
-// layer: T = 100 106 us against 110, T = 128 117 against 114; 80B-shaped: T = 128 106 against 116).
-constexpr int kStreamOnlyTokens = 128;
-
 // The formats whose segments go in 256-row tiles (bits as in a.m_big).  Shapes: whole tiles of columns; the kernel addresses rows
 // with 32-bit byte offsets; it reads the scales of an int4 row as aligned pairs (an even number of groups along both
 // contractions).  Size: the tiles of the down projection fill the chip once, and a segment has 1024 rows on average (bf16)
@@ -2059,24 +2055,34 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
     return (pairs >= 1024L * a.E ? 1 << DX_FMT_BF16 : 0) | (pairs >= 512L * a.E && pairs_of_scales ? 1 << DX_FMT_INT4G : 0);
 }
 
-// Whether a call runs on tiles.  Otherwise (few tokens: decode, or shapes that do not fit the tiles) the streaming kernels take every
-// expert.  (x starts at a multiple of the 16 bytes that a lane of the tiles' memory-to-LDS loads fetches; the streaming kernels'
-// loads to registers take any address.)
-bool takes_tiles(const dx_fwd_args &a)
+// Whether a call runs on tiles.  Otherwise the streaming kernels take every expert.  (x starts at a multiple of the 16 bytes that a lane of the
+// tiles' memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address.)
+// More than 128 tokens: always (30B-shaped, 130 tokens, a layer 104 us either way).  Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up
+// kernel would take K in rounds, each of which fetches the tokens anew.  From 65 tokens on (us per pass, streaming and tiles: 16 experts of 4096 x 6400,
+// top-2, 66 tokens 378 and 348, 128 tokens 497 and 363, int4/int2 298 and 248, 405 and 257; 2 layers of 64 of 4096 x 1024, top-8, 66 tokens 434 and 360;
+// of 32 of 3072 x 1024, top-4, 202 and 187, int4/int2 167 and 163; of 16 of 2560 x 2048, top-4, 231 and 210; but 48 tokens 184 and 200); and fewer tokens with large
+// experts that fill the chip, each with three tokens on average (16 of 4096 x 6400 40 tokens 293 and 260, int4/int2 213 and 197, 10 tokens 233 and 203, but
+// int4/int2 150 and 154; 2 layers of 96 of 7168 x 2048, top-8, 48 tokens 1515 and 1481, int4/int2 1249 and 1104, 24 tokens 1264 and 1321; smaller experts, 64 of
+// 4096 x 1024 12 tokens, int4/int2, 158 and 192; down projections of fewer tiles than compute units, 8 of 4096 x 14336 12 tokens 315 and 370).
+// Where K is one round the streaming kernels are faster or equal up to 128 tokens (30B-shaped 32 tokens 62 and 80, 101 tokens 104 and 109; 80B-shaped
+// 101 tokens 89 and 94).
+bool takes_tiles(const dx_fwd_args &a, int n_cu)
 {
-    return a.T > kStreamOnlyTokens && a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
+    const bool fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
+    if (!fit || a.T > DX_FP32_TOKENS) return fit;
+    if (a.T <= kFewTokens || pick_split(a.d / 128, a.d / 128).mode != kRounds) return false;
+    return a.T > DX_ROUTE_CHUNK || ((long)a.T * a.k >= 3L * a.E && (long)a.E * (a.d / 256) >= n_cu && (long)a.d * a.f >= 12L << 20);
 }
 
-// r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
-// then tells whether it did (if not, nothing has been launched).
 hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks *mk, const dx_route_io *r,
                       bool *routed)
 {
     dx_fwd_args a = a_in;
-    const bool tiled = takes_tiles(a);
+    const bool tiled = takes_tiles(a, n_cu);
     const few_choice few = tiled ? few_choice{false, false} : takes_few(a, n_cu);
     if (!tiled && (!few.down || r)) a.tiles = nullptr;
-    a.m_big = tiled ? big_tile_formats(a, n_cu) : 0;
+    a.o_bf16 = a.T > DX_FP32_TOKENS && tiled; // d % 128 == 0 there, so rows split into 8-column pieces
+    a.m_big = a.o_bf16 ? big_tile_formats(a, n_cu) : 0;
     if (r) {
         const int nc = a.d / chunk_of(a.group, a.d, a.d);
         *routed = !tiled && (few.gate_up || pick_split(nc, nc).mode == kWhole) && a.T >= 1 && a.T <= kRoutedTokens && a.E <= kRoutedExperts && a.k <= kRoutedTopK;
@@ -2114,7 +2120,7 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         if (marks) (void)hipEventRecord(marks[2], s);
     }
     if (combined) {
-    } else if (tiled) { // O in bf16: half the traffic between the down kernel and the combine (d % 128 == 0: 8 columns per thread)
+    } else if (a.o_bf16) {
         launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
     } else {
         launch(k_combine, dim3((a.d / 4 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
@@ -2154,8 +2160,9 @@ extern "C" int dx_debug_read_steps(void *dst, void *counts)
 
 dx_list_args dxk_list_args(const dx_fwd_args &a, int n_cu)
 {
-    if (!takes_tiles(a)) return dx_list_args{};
-    return dx_list_args{a.table, a.tiles, a.T, a.E, a.k, big_tile_formats(a, n_cu), n_cu, a.shared != nullptr};
+    if (!takes_tiles(a, n_cu)) return dx_list_args{};
+    const bool thin_only = a.T <= DX_FP32_TOKENS;
+    return dx_list_args{a.table, a.tiles, a.T, a.E, a.k, thin_only ? 0 : big_tile_formats(a, n_cu), n_cu, a.shared != nullptr, thin_only};
 }
 
 hipError_t dxk_moe_forward(const dx_fwd_args &a, int n_cu, hipStream_t s, dx_marks *marks)

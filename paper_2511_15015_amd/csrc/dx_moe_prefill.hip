@@ -840,33 +840,45 @@ __device__ __forceinline__ void wide_tile(const dx_fwd_args &a, const tile_id &t
 // to a compute unit.  What bounds it: the weights, which nothing else asks for, so a compute unit needs enough of them on their way.
 // Tokens are the first MFMA operand: accumulator element v is token (v / 4) * 8 + (lane / 32) * 4 + v % 4 of weight row lane % 32.
 
+// ALONE: calls of few tokens, which have no other tiles: segments of more rows in several tiles, the shared expert's among them, and O in fp32.
+
+// the shared expert (bf16) in a call of thin tiles alone
+template <bool ALONE>
+__device__ __forceinline__ bool thin_shared(const dx_fwd_args &a, const tile_id &t)
+{
+    return ALONE && t.e == a.E;
+}
+
 // where a lane's part of token row 8 * wave + lane / 8 comes from (rows past the end repeat the last one)
-template <bool DOWN>
+template <bool DOWN, bool ALONE>
 __device__ __forceinline__ uint64_t thin_token_at(const dx_fwd_args &a, const tile_id &t, int K, int wave, int lane)
 {
-    const int row = 8 * wave + (lane >> 3), slot = row < t.m ? row : t.m - 1;
+    const int row = 8 * wave + (lane >> 3), at = (ALONE ? t.mt * DX_THIN_ROWS : 0) + row, slot = at < t.m ? at : t.m - 1;
     const uint32_t piece = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));
     if constexpr (DOWN) return (uint64_t)a.h + (uint64_t)(t.seg0 + slot) * a.fmax * 2 + piece * 16;
-    else return (uint64_t)a.x + (uint64_t)(a.perm[t.seg0 + slot] / a.k) * K * 2 + piece * 16;
+    else return (uint64_t)a.x + (uint64_t)(thin_shared<ALONE>(a, t) ? slot : a.perm[t.seg0 + slot] / a.k) * K * 2 + piece * 16;
 }
 
 // row of H or O that token lane % 32 goes to
-template <bool DOWN>
+template <bool DOWN, bool ALONE>
 __device__ __forceinline__ int thin_row(const dx_fwd_args &a, const tile_id &t, int lane)
 {
-    const int r = lane & 31, place = t.seg0 + (r < t.m ? r : t.m - 1);
-    return DOWN ? a.perm[place] : place;
+    const int at = (ALONE ? t.mt * DX_THIN_ROWS : 0) + (lane & 31), place = t.seg0 + (at < t.m ? at : t.m - 1);
+    return DOWN && !thin_shared<ALONE>(a, t) ? a.perm[place] : place;
 }
 
-template <bool DOWN>
+template <bool DOWN, bool ALONE>
 __device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &t, const f32x16 (&acc)[2], int row, int first, int lane)
 {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int token = (v >> 2) * 8 + 4 * (lane >> 5) + (v & 3);
         const int to = __shfl(row, token);
-        if (token >= t.m) continue;
-        if constexpr (DOWN) {
+        if ((ALONE ? t.mt * DX_THIN_ROWS : 0) + token >= t.m) continue;
+        if constexpr (DOWN && ALONE) {
+            float *dst = a.o + (size_t)to * a.d + first + (lane & 31);
+            dst[0] = acc[0][v], dst[32] = acc[1][v];
+        } else if constexpr (DOWN) {
             dx_bf16 *dst = reinterpret_cast<dx_bf16 *>(a.o) + (size_t)to * a.d + first + (lane & 31);
             const uint32_t both = pack_bf16(acc[0][v], acc[1][v]);
             dst[0] = (dx_bf16)both, dst[32] = (dx_bf16)(both >> 16);
@@ -881,7 +893,7 @@ __device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &
 // multiplies the group's fp32 sums once, as in the streaming kernels.  (By way of registers, as bf16 weights come: 5 to 15 % slower.)
 //   LDS: token rows, laid out as in the other kernels, then the codes of each wavefront alone.  One barrier per slot: behind it every
 //   wavefront has read the slot that is filled next.
-template <bool DOWN, int FMT>
+template <bool DOWN, int FMT, bool ALONE>
 __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
     constexpr int SLOTS = cfg::THIN_SLOTS, A_SLOT = 2 * cfg::THIN_A, W_SLOT = cfg::SIDE_WIDE, W0 = SLOTS * A_SLOT;
@@ -892,7 +904,7 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)ring;
 
     // ---- loader: wavefront w fills token rows [8w, 8w + 8) and its own 64 weight rows ----
-    uint64_t a_at = thin_token_at<DOWN>(a, t, K, wave, lane);
+    uint64_t a_at = thin_token_at<DOWN, ALONE>(a, t, K, wave, lane);
     // (the last tile of columns may be half a tile: the wavefronts of the missing half load the last rows again)
     const int N = DOWN ? a.d : a.f, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
     const weight_rows<DOWN, FMT> w(h, first < N ? first : N - (DOWN ? 64 : 32), K, a.group, lane);
@@ -907,7 +919,7 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
 
     // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
     const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
-    const int row = thin_row<DOWN>(a, t, lane);
+    const int row = thin_row<DOWN, ALONE>(a, t, lane);
     f32x16 acc[2], part[2];
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -960,7 +972,7 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
         }
         slot = slot + 1 < SLOTS ? slot + 1 : 0;
     }
-    if (first < N) store_thin<DOWN>(a, t, acc, row, first, lane);
+    if (first < N) store_thin<DOWN, ALONE>(a, t, acc, row, first, lane);
 }
 
 // bf16 weights.  They and the token rows come to registers, two steps in flight, and pass through LDS on their way to the operands: with the
@@ -968,19 +980,20 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
 // layer 107 us by loads to LDS, 101 this way; three steps in flight 102).
 //   LDS: two slots of token rows, one barrier per step: behind it every wavefront has read the slot that is filled next; one slot of the
 //   weights of each wavefront alone.
-template <bool DOWN>
+template <bool DOWN, bool ALONE>
 __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
     constexpr int DEPTH = 2, W0 = 2 * cfg::THIN_A;
     static_assert(W0 + cfg::WAVES * cfg::B_WAVE <= cfg::LDS, "the ring");
-    const int K = DOWN ? a.f : a.d, nk = K / BK;
+    const int fe = thin_shared<ALONE>(a, t) ? a.shared_f : a.f;
+    const int K = DOWN ? fe : a.d, nk = K / BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- loader: wavefront w loads token rows [8w, 8w + 8) and its own 64 weight rows (the last tile of columns may be half a tile: the
     // wavefronts of the missing half load the last rows again) ----
-    const DX_GLOBAL char *const a_at = (const DX_GLOBAL char *)thin_token_at<DOWN>(a, t, K, wave, lane);
-    const int N = DOWN ? a.d : a.f, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
+    const DX_GLOBAL char *const a_at = (const DX_GLOBAL char *)thin_token_at<DOWN, ALONE>(a, t, K, wave, lane);
+    const int N = DOWN ? a.d : fe, first = DOWN ? t.nt * BNW + 64 * wave : t.nt * (BNW / 2) + 32 * wave;
     const weight_rows<DOWN, 0> w(h, first < N ? first : N - (DOWN ? 64 : 32), K, a.group, lane);
     struct step_regs {
         u32x4 tokens, weights[8];
@@ -994,7 +1007,7 @@ __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t
 
     // ---- MFMA role: all rows x the wavefront's 64 weight rows ----
     const int r = lane & 31, kq = lane >> 5, swz = (r >> 1) & 7;
-    const int row = thin_row<DOWN>(a, t, lane);
+    const int row = thin_row<DOWN, ALONE>(a, t, lane);
     f32x16 acc[2];
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -1035,7 +1048,7 @@ __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t
 #pragma unroll
         for (int i = 0; i < DEPTH; ++i)
             if (kt + i < nk) consume(kt + i, st[i], kt + i + DEPTH < nk ? kt + i + DEPTH : -1);
-    if (first < N) store_thin<DOWN>(a, t, acc, row, first, lane);
+    if (first < N) store_thin<DOWN, ALONE>(a, t, acc, row, first, lane);
 }
 
 template <bool DOWN>
@@ -1049,9 +1062,9 @@ __global__ __launch_bounds__(cfg::THREADS, 2) void k_tiled(dx_fwd_args a)
     const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
     const int fmt = (int)uniform_load(&h->fmt);
     if (kind == kThin) {
-        if (fmt == DX_FMT_INT4G) thin_codes<DOWN, 1>(a, t, h, ring);
-        else if (fmt == DX_FMT_INT2G) thin_codes<DOWN, 2>(a, t, h, ring);
-        else thin_rows<DOWN>(a, t, h, ring);
+        if (fmt == DX_FMT_INT4G) thin_codes<DOWN, 1, false>(a, t, h, ring);
+        else if (fmt == DX_FMT_INT2G) thin_codes<DOWN, 2, false>(a, t, h, ring);
+        else thin_rows<DOWN, false>(a, t, h, ring);
     } else if (kind == kWide) {
         if (fmt == DX_FMT_INT4G) wide_tile<DOWN, 1>(a, t, h, ring);
         else if (fmt == DX_FMT_INT2G) wide_tile<DOWN, 2>(a, t, h, ring);
@@ -1061,6 +1074,26 @@ __global__ __launch_bounds__(cfg::THREADS, 2) void k_tiled(dx_fwd_args a)
         else if (fmt == DX_FMT_INT2G) narrow_tile<DOWN, 2>(a, t, h, ring);
         else narrow_tile<DOWN, 0>(a, t, h, ring);
     }
+}
+
+// Thin tiles alone (calls of few tokens).  The row tiles of a segment, up to four, go next to each other, so that its weights come to one XCD; four tiles at
+// a time to an XCD.  A kernel of its own: as part of k_tiled it cost the calls of more tokens 1 to 4 %.
+template <bool DOWN>
+__global__ __launch_bounds__(cfg::THREADS, 2) void k_thin(dx_fwd_args a)
+{
+    __shared__ __attribute__((aligned(1024))) char ring[cfg::LDS];
+    const int n = uniform_load(&a.tiles->n_thin) + uniform_load(&a.tiles->n_thin_quant), n_shared = uniform_load(&a.tiles->n_thin_shared);
+    const int ntn = columns_of<DOWN>(a, a.f, BNW), ntn_shared = columns_of<DOWN>(a, a.shared_f, BNW);
+    const uint32_t routed = (uint32_t)(n * ntn), total = routed + (uint32_t)(n_shared * ntn_shared);
+    const uint32_t at = blockIdx.x >> 3, idx = ((at >> 2) * 8 + (blockIdx.x & 7)) * 4 + (at & 3);
+    if (idx >= total) return; // block-uniform
+    const dx_tile_row *rows = reinterpret_cast<const dx_tile_row *>(a.tiles + 1);
+    const tile_id t = idx < routed ? tile_of<DX_THIN_ROWS, 4>(rows, idx, ntn) : tile_of<DX_THIN_ROWS, 4>(rows + n, idx - routed, ntn_shared);
+    const dx_handle *h = t.e == a.E ? a.shared : a.table + t.e;
+    const int fmt = (int)uniform_load(&h->fmt);
+    if (fmt == DX_FMT_INT4G) thin_codes<DOWN, 1, true>(a, t, h, ring);
+    else if (fmt == DX_FMT_INT2G) thin_codes<DOWN, 2, true>(a, t, h, ring);
+    else thin_rows<DOWN, true>(a, t, h, ring);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1291,9 +1324,10 @@ constexpr int kListThreads = 1024; // an expert to a thread
 
 __global__ __launch_bounds__(kListThreads) void k_tile_list(dx_list_args l, const int32_t *offsets)
 {
-    __shared__ int sums[kListThreads / 64][dx_tile_list::kCounts];
-    const int e = threadIdx.x < (unsigned)l.E ? (int)threadIdx.x : l.E, seg0 = offsets[e];
-    dx_tile_list::write<kListThreads / 64>(l, e, seg0, e < l.E ? offsets[e + 1] - seg0 : 0, sums);
+    __shared__ dx_tile_list::lds<kListThreads / 64> of_list;
+    const bool owner = threadIdx.x < (unsigned)l.E;
+    const int e = owner ? (int)threadIdx.x : l.E, seg0 = offsets[e];
+    dx_tile_list::write<kListThreads / 64>(l, e, owner ? l.table[e].fmt : (uint32_t)DX_FMT_BF16, seg0, owner ? offsets[e + 1] - seg0 : 0, of_list);
 }
 
 } // namespace
@@ -1304,10 +1338,18 @@ static void launch_tiles(const dx_fwd_args &a, hipStream_t s)
     // an upper bound on the tile count; surplus blocks find no tile and leave
     const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
     const long pairs = (long)a.T * a.k, active = pairs < a.E ? pairs : a.E, above = pairs / (DX_THIN_ROWS + 1);
-    const long thin = active - (above < active ? above : active); // beside as many of more rows as there can be
-    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, DX_THIN_ROWS, a.shared != nullptr) * columns_of<DOWN>(a, fe, BN);
-    const long blocks = (tiles + 7) / 8 * 8 + (thin * columns_of<DOWN>(a, a.f, BNW) + 15) / 16 * 16;
+    const long thin = active - (above < active ? above : active); // beside as many of more rows as there can be (a tile less there: one more here at most)
+    const long tiles = dxk_tile_rows_max(a.T, a.k, a.E, DX_THIN_ROWS, a.shared != nullptr) * columns_of<DOWN>(a, fe, BN) + thin * columns_of<DOWN>(a, a.f, BNW);
+    const long blocks = (tiles + 7 + 15 + 7) / 8 * 8; // the ranges of the XCDs: eighths of the one kind, of thin tiles in twos
     hipLaunchKernelGGL((k_tiled<DOWN>), dim3((unsigned)blocks), dim3(cfg::THREADS), 0, s, a);
+}
+
+template <bool DOWN>
+static void launch_thin(const dx_fwd_args &a, hipStream_t s)
+{
+    const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
+    const long tiles = dxk_thin_rows_max(a.T, a.k, a.E, a.shared != nullptr) * columns_of<DOWN>(a, fe, BNW);
+    hipLaunchKernelGGL((k_thin<DOWN>), dim3((unsigned)((tiles + 31) / 32 * 32)), dim3(cfg::THREADS), 0, s, a);
 }
 
 template <bool DOWN>
@@ -1324,11 +1366,13 @@ void dxk_tile_list(const dx_list_args &l, const int32_t *offsets, hipStream_t s)
 }
 void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s)
 {
+    if (!a.o_bf16) return launch_thin<false>(a, s);
     launch_big_tiles<false>(a, s);
     launch_tiles<false>(a, s);
 }
 void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s)
 {
+    if (!a.o_bf16) return launch_thin<true>(a, s);
     launch_big_tiles<true>(a, s);
     launch_tiles<true>(a, s);
 }

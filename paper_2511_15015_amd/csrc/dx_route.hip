@@ -20,7 +20,7 @@
 
 namespace {
 
-constexpr int kChunk = 64;      // tokens per chunk = bits per mask word
+constexpr int kChunk = DX_ROUTE_CHUNK;      // tokens per chunk = bits per mask word
 constexpr int kRouteThreads = 1024;
 constexpr int kWaves = kRouteThreads / 64;
 
@@ -193,11 +193,13 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     const bool lists = (int)blockIdx.x == n_chunks; // a block more: the list of row tiles
     const int chunk = lists ? 0 : blockIdx.x, S = 1 << split;
     const int p0 = chunk * kChunk * k, n = min(T - chunk * kChunk, kChunk) * k;
-    // asked for here because the masks' way to the first use takes as long as theirs: the first pair's expert, the counter
+    // asked for here because the masks' way to the first use takes as long as theirs: the first pair's expert, the counter,
+    // the expert's format
     const int first_id = ids[p0 + min((int)threadIdx.x, n - 1)];
     const int e = threadIdx.x >> split, part = threadIdx.x & (S - 1);
     const bool counts_hot = blockIdx.x == 0 && part == 0 && e < E && hotness;
     const unsigned long long hot_before = counts_hot ? hotness[e] : 0ull;
+    const uint32_t fmt = lists && part == 0 && e < E ? list.table[e].fmt : (uint32_t)DX_FMT_BF16;
     int total = 0, before = 0;
     if (e < E) {
         constexpr int U = 8; // independent loads in flight
@@ -245,9 +247,9 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_place(
     int all;
     const int off = block_exclusive_scan(part == 0 && e < E ? total : 0, lds_tot, &all);
     if (lists) { // block-uniform
-        __shared__ int sums_of_list[kWaves][dx_tile_list::kCounts];
+        __shared__ dx_tile_list::lds<kWaves> of_list;
         const bool owner = part == 0 && e < E;
-        dx_tile_list::write<kWaves>(list, owner ? e : E, off, owner ? total : 0, sums_of_list);
+        dx_tile_list::write<kWaves>(list, owner ? e : E, fmt, off, owner ? total : 0, of_list);
         return;
     }
     if (part == 0 && e < E) {
