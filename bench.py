@@ -459,7 +459,7 @@ def main():
             if line.startswith("traffic_bytes_per_launch:"):
                 roofline["traffic"] = float(line.split(":")[1])
                 if not decode:
-                    roofline["traffic_of"] = "k_tiled<gate/up> alone (without the phase's streamed experts)"
+                    roofline["traffic_of"] = "k_tiled<gate/up>"
             if line.startswith("kernels_at_commit:"):
                 roofline["traffic_taken_at_commit"] = line.split(":")[1].strip()
 
