@@ -2057,7 +2057,7 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 
 // Whether a call runs on tiles.  Otherwise the streaming kernels take every expert.  (x starts at a multiple of the 16 bytes that a lane of the
 // tiles' memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address.)
-// More than 128 tokens: always (30B-shaped, 130 tokens, a layer 104 us either way).  Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up
+// More than 128 tokens: always (30B-shaped, 128 tokens streamed 115 us a layer, 130 tokens on tiles 106).  Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up
 // kernel would take K in rounds, each of which fetches the tokens anew.  From 65 tokens on (us per pass, streaming and tiles: 16 experts of 4096 x 6400,
 // top-2, 66 tokens 378 and 348, 128 tokens 497 and 363, int4/int2 298 and 248, 405 and 257; 2 layers of 64 of 4096 x 1024, top-8, 66 tokens 434 and 360;
 // of 32 of 3072 x 1024, top-4, 202 and 187, int4/int2 167 and 163; of 16 of 2560 x 2048, top-4, 231 and 210; but 48 tokens 184 and 200); and fewer tokens with large

@@ -137,7 +137,8 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
 // Thin tiles in this launch (before: segments of up to 32 rows in the streaming kernels, a launch per phase in front, during which the matrix
 // cores had little to do).  A layer, us, streaming kernels in front and now: 30B-shaped 300 tokens 140 and 121, 1000 tokens 204 and 192, 4096
 // tokens 464 and 432, int4/int2 150 tokens 101 and 81; 80B-shaped 150 tokens 111 and 92, 1000 tokens 204 and 178; 16 experts of 4096 x 6400,
-// 150 tokens 412 and 311, 1100 tokens 602 and 539; 30B-shaped 130 and 190 tokens the same.  First or last: last, because they are short and fill
+// 150 tokens 412 and 311, 1100 tokens 602 and 539; 30B-shaped 190 tokens the same, 130 to 150 tokens 103 to 106 and 105
+// to 111: 360 tiles in one round, and those of 256 columns of bf16 weights are four times as long as the others.  First or last: last, because they are short and fill
 // the last round; first where bf16 weights from memory are all there is (up to four narrow tiles per compute unit): 30B-shaped 300 tokens
 // 132 first and 143 last, 500 tokens 146 and 157, 16 of 4096 x 6400 150 tokens 320 and 339; but int4/int2 150 tokens 84 and 79, 1100 tokens of
 // the 16 556 and 550, 80B-shaped 1000 tokens 187 and 178, and with few other tiles: first only where a good part of the thin ones is bf16 as well (80B-shaped 150
