@@ -42,6 +42,10 @@ __device__ __forceinline__ float swiglu_fast(float g, float u)
     return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
 }
 
+// The same as the streaming kernels take it, within 3e-7 of its value: the thin tiles' (segments that those kernels have elsewhere).  swiglu_fast is off by up to
+// 3e-6 for large gates, the rounding of the exponent's product, and flushes silu(g) below g = -87.3.
+__device__ __forceinline__ float swiglu(float g, float u) { return g / (1.f + expf(-g)) * u; }
+
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
@@ -884,7 +888,7 @@ __device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &
             const uint32_t both = pack_bf16(acc[0][v], acc[1][v]);
             dst[0] = (dx_bf16)both, dst[32] = (dx_bf16)(both >> 16);
         } else {
-            a.h[(size_t)to * a.fmax + first + (lane & 31)] = (dx_bf16)pack_bf16(swiglu_fast(acc[0][v], acc[1][v]), 0.f);
+            a.h[(size_t)to * a.fmax + first + (lane & 31)] = (dx_bf16)pack_bf16(swiglu(acc[0][v], acc[1][v]), 0.f);
         }
     }
 }

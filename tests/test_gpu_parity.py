@@ -775,6 +775,61 @@ def test_forward_thin_tiles_alone(B, LY, dxo, pair, d, f, group, shared_f):
     ctx.close()
 
 
+def _hard_gates():
+    """bf16 pairs (g, u), g < 0, whose silu(g) * u lies closer than 3e-6 of its value to the border between two bf16 values, but not closer than
+    6e-7, and all u with g = -87.5, -88 and -88.5, where 1 / (1 + e^-g) is below the normal range; and the bf16 value each rounds to (bits)."""
+    g = -np.unique(bf16_bits_to_f32(np.arange(0x4100, 0x42B2, dtype=np.uint16)))    # -8 .. -88.5
+    u = bf16_bits_to_f32(np.arange(0x3F80, 0x4000, dtype=np.uint16))                # 1 .. 2
+    g, u = (a.ravel().astype(np.float64) for a in np.meshgrid(g, u))
+    h = g / (1.0 + np.exp(-g)) * u
+    ulp = 2.0 ** (np.floor(np.log2(np.abs(h))) - 7)
+    border = (np.floor(np.abs(h) / ulp) + 0.5) * ulp
+    off = np.abs(np.abs(h) - border) / np.abs(h)
+    keep = (off > 6e-7) & ((off < 3e-6) | (g < -87.25))
+    up = np.abs(h) > border
+    value = np.sign(h) * (np.floor(np.abs(h) / ulp) + up) * ulp
+    return tuple(f32_to_bf16_bits(a[keep].astype(np.float32)) for a in (g, u, value))
+
+
+@pytest.mark.parametrize("T,E,k,d,f", [
+    (240, 8, 1, 256, 128),      # thin tiles in the launch of the others
+    (128, 256, 8, 2176, 192),   # thin tiles alone
+])
+def test_forward_thin_tiles_swiglu(B, LY, T, E, k, d, f):
+    """SwiGLU of the thin tiles to fp32 accuracy: gates and ups given exactly (a token has one element, so they are a column of the matrices),
+    W_down the identity, and values that an error of 6e-7 may not but one of a few 1e-6 does round to another bf16 value (the exact form:
+    expf one ulp, sum, quotient and product half an ulp each, 3e-7 together)."""
+    g, u, h = _hard_gates()
+    assert len(h) > 400
+    at = (np.arange(f)[:, None] + f * np.arange(d)[None, :]) % len(h)       # pair of (row of W_gate, column)
+    wg, wu = (LY.bits_to_device(a[at]) for a in (g, u))
+    eye = np.zeros((d, f), np.float32)
+    eye[np.arange(f), np.arange(f)] = 1.0
+    wd = LY.bits_to_device(f32_to_bf16_bits(eye))
+    ctx = B.Context(L=1, E=E, d=d, f=f, top_k=k, group=64, max_tokens=T)
+    for e in range(E):
+        ctx.dx_swap_handle(0, e, B.make_handle(B.DX_FMT_BF16, wg, wu, wd))
+    column = np.random.default_rng(1).permutation(d)[:T]
+    x = np.zeros((T, d), np.float32)
+    x[np.arange(T), column] = 1.0
+    pair = np.arange(T * k)
+    expert = (pair // k + pair % k * (E // k)) % E                          # k different ones to a token
+    perm = np.argsort(expert, kind="stable").astype(np.int32)
+    counts = np.bincount(expert, minlength=E)
+    assert counts.max() <= 32
+    w = np.zeros((T, k), np.float32)
+    w[:, 0] = 1.0
+    dev = [torch.from_numpy(a).cuda() for a in (expert.reshape(T, k).astype(np.int32), w, np.r_[0, np.cumsum(counts)].astype(np.int32), perm)]
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"thin SwiGLU T={T} E={E} k={k} d={d} f={f}", flush=True)
+    ctx.dx_moe_forward(0, None, LY.bits_to_device(f32_to_bf16_bits(x)), T, *dev, y)
+    sync()
+    got, want = LY.device_to_bits(y)[:, :f], h[at[:, column]].T
+    bad = np.argwhere(got != want)
+    assert len(bad) == 0, (len(bad), bf16_bits_to_f32(got[tuple(bad[0])][None]), bf16_bits_to_f32(want[tuple(bad[0])][None]))
+    ctx.close()
+
+
 def _wide_phases(counts, hi, f, d, T, shared_f=0, hi_quantized=False):
     """Whether the 128-row tiles of a call (segments below 512 rows, none in 256-row tiles) are 256 columns wide: gate/up, down."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
