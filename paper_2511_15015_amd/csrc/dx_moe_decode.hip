@@ -2056,24 +2056,37 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 }
 
 // Whether a call runs on tiles.  Otherwise the streaming kernels take every expert.  (x starts at a multiple of the 16 bytes that a lane of the
-// tiles' memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address.)
-// More than 128 tokens: always (30B-shaped, 128 tokens streamed 115 us a layer, 130 tokens on tiles 106).  Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up
-// kernel would take K in rounds, each of which fetches the tokens anew.  From 65 tokens on (us per pass, streaming and tiles: 16 experts of 4096 x 6400,
-// top-2, 66 tokens 378 and 348, 128 tokens 497 and 363, int4/int2 298 and 248, 405 and 257; 2 layers of 64 of 4096 x 1024, top-8, 66 tokens 434 and 360;
-// of 32 of 3072 x 1024, top-4, 202 and 187, int4/int2 167 and 163; of 16 of 2560 x 2048, top-4, 231 and 210; but 48 tokens 184 and 200); and fewer tokens with large
-// experts that fill the chip, each with three tokens on average (16 of 4096 x 6400 40 tokens 293 and 260, int4/int2 213 and 197, 10 tokens 233 and 203, but
-// int4/int2 150 and 154; 2 layers of 96 of 7168 x 2048, top-8, 48 tokens 1515 and 1481, int4/int2 1249 and 1104, 24 tokens 1264 and 1321; smaller experts, 64 of
-// 4096 x 1024 12 tokens, int4/int2, 158 and 192; down projections of fewer tiles than compute units, 8 of 4096 x 14336 12 tokens 315 and 370).
-// Where K is one round the streaming kernels are faster or equal up to 128 tokens (30B-shaped 32 tokens 62 and 80, 101 tokens 104 and 109; 80B-shaped
-// 101 tokens 89 and 94).
+// tiles' memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address.)  Figures: us a layer, streaming and tiles.
+// More than 128 tokens: always.  The streaming kernels read the weights of a segment once per 32 tokens (30B-shaped, 129 tokens 115 and 101, 190 tokens 143
+// and 114; 80B-shaped, 129 tokens 99 and 86).
+// Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up kernel takes K in rounds (more than 16 chunks of 128), each of which fetches the tokens
+// anew.  Where K is one round the streaming kernels are faster or equal (30B-shaped 32 tokens 62 and 80, 101 tokens 104 and 109; 80B-shaped 101 tokens 89 and 94).
+// - The tiles have to fill the chip, because each of them goes through all of K one step after the other: by the most row tiles that the pairs can have, two
+//   gate/up tiles and three quarters of a down tile per compute unit.  Top-2, 66 to 128 tokens, tiles per unit: gate/up 0.5 (8 experts of 7168 x 256) 43 and 125, 57 and 130; 1.25
+//   (16 of 8192 x 2048, 64 tokens) 185 and 217; 1.5 (8 of 4096 x 4096, int4/int2) 113 and 128, 2.0 the same 182 and 135; down 0.3 (4 of 2560 x 2048, top-1) 42 and 76,
+//   0.5 (4 of 4096 x 14336) 304 and 313, 0.75 (8 of them) 474 and 408, 128 tokens 728 and 492.
+// - And a tile has to have tokens: three pairs per expert if both contractions take rounds (64 of 4096 x 3072, top-8, 24 tokens 496 and 427; 16 of 4096 x 6400, 24 tokens
+//   285 and 265, 12 tokens, int4/int2 171 and 178), else five, and more than 64 tokens (64 of 4096 x 1024, int4/int2, 3.9 pairs 103 and 131, 128 of them, 4.1 pairs
+//   3 % slower, 6 pairs 7 % faster; up to 64 tokens 32 of 8192 x 1536, 12 pairs 300 and 311).
+// - Not where the gate/up tiles are surely a little more than a round of two per compute unit (2 of 6144 x 8448, top-2, 124 tokens, 528 tiles 276 and 331).
+// - Up to 64 tokens, besides: a down tile per compute unit, a quantized expert (16 of 4096 x 6400, top-4, 64 tokens, all bf16 465 and 499, all int4 326 and 288), and
+//   f in whole chunks (20 of 5504 x 11456, top-6, 10 tokens 852 and 924, x 11392 800 and 752).
 bool takes_tiles(const dx_fwd_args &a, int n_cu)
 {
     const bool fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
     if (!fit || a.T > DX_FP32_TOKENS) return fit;
-    if (a.T <= kFewTokens || pick_split(a.d / 128, a.d / 128).mode != kRounds) return false;
-    return a.T > DX_ROUTE_CHUNK || ((long)a.T * a.k >= 3L * a.E && (long)a.E * (a.d / 256) >= n_cu && (long)a.d * a.f >= 12L << 20);
+    auto in_rounds = [](int K) { return pick_split((K + 127) / 128, (K + 127) / 128).mode == kRounds; };
+    const bool both = in_rounds(a.f), many = a.T > DX_ROUTE_CHUNK;
+    if (a.T <= kFewTokens || !in_rounds(a.d) || (long)a.T * a.k < (both ? 3L : 5L) * a.E) return false;
+    const long rows = dxk_thin_rows_max(a.T, a.k, a.E, false), rows_shared = a.shared ? (a.T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0;
+    const long gate_up = rows * ((a.f + 127) / 128) + rows_shared * ((a.shared_f + 127) / 128), down = (rows + rows_shared) * (a.d / 256);
+    const long least = ((long)a.T * a.k + DX_THIN_ROWS - 1) / DX_THIN_ROWS * ((a.f + 127) / 128); // gate/up tiles when no segment has a remainder
+    if (gate_up < 2L * n_cu || (least > 2L * n_cu && gate_up < 4L * n_cu)) return false;
+    return many ? 4 * down >= 3L * n_cu : both && a.f % 128 == 0 && a.any_quantized && down >= n_cu;
 }
 
+// r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
+// then tells whether it did (if not, nothing has been launched).
 hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks *mk, const dx_route_io *r,
                       bool *routed)
 {

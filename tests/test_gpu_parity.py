@@ -730,49 +730,131 @@ def test_forward_prefill_thin_segments(B, LY, dxo, pair, d, f, group):
     ctx.close()
 
 
-@pytest.mark.parametrize("pair,d,f,group,shared_f", [
-    ("bf16-int4", 2176, 192, 64, 0),    # 34 K steps and three; 1.5 and 8.5 column tiles
-    ("bf16-int4", 2304, 256, 128, 384), # a shared expert of another width, in four row tiles
-    ("bf16-int4", 2176, 64, 32, 64),
-    ("int4-int2", 2176, 192, 64, 0),
-    ("int4-int2", 2304, 256, 128, 0),
-])
-def test_forward_thin_tiles_alone(B, LY, dxo, pair, d, f, group, shared_f):
-    """Calls of up to 128 tokens whose K the streaming kernels would take in rounds run on thin tiles, segments above 32 rows in several,
-    with O in fp32: every token against the oracle; the same bits from both ways of listing the tiles."""
+def _layer_of_few_versions(B, LY, dxo, pair, E, k, d, f, group, T, seed, shared_f=0, n=5, hi=(0, 2)):
+    """A layer of E experts that share n versions: context, what it needs kept, the versions, the shared expert's."""
     import dataclasses
-    sizes = [1, 1, 32, 33, 0, 0, 20, 17, 3, 4]
-    E, T = len(sizes), sum(sizes)
-    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=1, d=d, f=f, group=group, shared_f=shared_f)
-    x, _ = W.layer_inputs(wl, seed=19)
-    logits = np.zeros((T, E), np.float32)
-    logits[np.arange(T), np.random.default_rng(5).permutation(np.repeat(np.arange(E), sizes))] = 4.0
-    hi = list(range(0, E, 2))
-    print(f"thin tiles alone {pair} d={d} f={f} group={group} shared={shared_f} T={T}", flush=True)
-    shared = None
+    wl = dataclasses.replace(WORKLOADS["C1"], T=1, E=n, k=1, d=d, f=f, group=group, shared_f=shared_f)
     if pair == "int4-int2":
-        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 19, T)
+        small, keep, versions = _quant_pair_layer(B, LY, dxo, wl, list(hi), seed, 1)
     else:
-        keep = Layer(B, LY, dxo, wl, hi, seed=19, shared=W.shared_master(wl, 19, 0) if shared_f else None)
-        ctx, versions, shared = keep.ctx, keep.versions, keep.shared
-    ids, w, counts, offsets, perm = dxo.route(logits, 1)
-    assert counts.tolist() == sizes and 64 < T <= 128
-    rb = LY.RoutingBuffers(T, E, 1)
+        keep = Layer(B, LY, dxo, wl, list(hi), seed=seed)
+        small, versions = keep.ctx, keep.versions
+    ctx = B.Context(L=1, E=E, d=d, f=f, top_k=k, group=group, max_tokens=T, shared_f=shared_f,
+                    hi_fmt=B.DX_FMT_INT4G if pair == "int4-int2" else B.DX_FMT_BF16)
+    for e in range(E):
+        ctx.dx_swap_handle(0, e, small.dx_get_handle(0, e % n))
+    shared, shared_dev = None, None
+    if shared_f:
+        masters = W.shared_master(wl, seed, 0)
+        shared_dev = [LY.bits_to_device(m) for m in masters]
+        ctx.dx_swap_handle(0, E, B.make_handle(B.DX_FMT_BF16, *shared_dev))
+        shared = dxo.ExpertVersion.bf16(*masters)
+    return ctx, (keep, small, shared_dev), [versions[e % n] for e in range(E)], shared
+
+
+def _logits_of_segments(sizes, T, k, seed):
+    """Logits [T, E] whose top-k gives expert e sizes[e] tokens (each at most T, T * k together): the tokens in turn."""
+    g = np.random.default_rng(seed)
+    logits = np.full((T, len(sizes)), -8.0, np.float32)
+    at = 0
+    for e, m in enumerate(sizes):
+        logits[(at + np.arange(m)) % T, e] = g.uniform(1.0, 3.0, m)
+        at += m
+    assert at == T * k and max(sizes) <= T
+    return logits[g.permutation(T)]
+
+
+def _moved_by_four_bytes(x):
+    """x where the tiles' loads cannot take it: the call runs on the streaming kernels"""
+    flat = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+    return flat[2:2 + x.numel()].view_as(x).copy_(x)
+
+
+def _check_thin_tiles_alone(LY, dxo, ctx, versions, shared, shared_f, x, logits, k, f, group, tokens=None):
+    """A call that runs on thin tiles alone: one call and two the same bits, `tokens` (all) against the oracle, and all of them against the streaming
+    kernels, from which it differs in some bit (other kernels did run).  Returns y."""
+    T, E, d = *logits.shape, x.shape[1]
+    ids, w, *_ = dxo.route(logits, k)
+    rb = LY.RoutingBuffers(T, E, k)
     xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
-    y, y1 = (torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    y, y1, ys = (torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
     rb.route_forward(ctx, 0, ld, xd, y)
     rb.route(ctx, 0, ld)
     rb.forward(ctx, 0, xd, y1)
+    rb.forward(ctx, 0, _moved_by_four_bytes(xd), ys)
     sync()
-    bits = LY.device_to_bits(y)
+    assert np.array_equal(rb.ids.cpu().numpy(), ids)
+    bits, streamed = LY.device_to_bits(y), LY.device_to_bits(ys)
     assert np.array_equal(bits, LY.device_to_bits(y1))
-    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f if shared else 0)
-    yg = bf16_bits_to_f32(bits).astype(np.float64)
-    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
-    assert rel_l2(bits, y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
-    assert_elementwise(dxo, bits, y_ref, versions, group, x, ids, w, shared=shared, T_call=T)
-    del keep
+    assert not np.array_equal(bits, streamed), "the call did not run on tiles"
+    # (both round H and y to bf16 from fp32 sums in another order: of the values of H and y that lie close to a border one may be off by 2^-8)
+    assert rel_l2(bits, bf16_bits_to_f32(streamed).astype(np.float64)) <= 2.0 ** -8
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f, tokens=tokens)
+    some = bits if tokens is None else bits[tokens]
+    tok = np.linalg.norm(bf16_bits_to_f32(some).astype(np.float64) - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(some, y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    assert_elementwise(dxo, some, y_ref, versions, group, x, ids, w, shared=shared, tokens=tokens, T_call=T)
+    return y
+
+
+@pytest.mark.parametrize("pair,k,d,f,group,shared_f", [
+    ("bf16-int4", 10, 2176, 192, 64, 0),    # 34 K steps and three; 1.5 and 8.5 column tiles
+    ("bf16-int4", 10, 2304, 256, 128, 384), # a shared expert of another width, in four row tiles
+    ("bf16-int4", 64, 2176, 64, 32, 64),    # one K step in the down projection
+    ("int4-int2", 10, 2176, 192, 64, 0),
+    ("int4-int2", 10, 2304, 256, 128, 0),
+])
+def test_forward_thin_tiles_alone(B, LY, dxo, pair, k, d, f, group, shared_f):
+    """Calls of up to 128 tokens whose K the streaming kernels would take in rounds run on thin tiles if they fill the chip, segments above 32 rows
+    in several, with O in fp32: segments at the edges of a tile, every token against the oracle."""
+    T, E = 128, 256
+    edges = [128, 127, 97, 96, 65, 64, 63, 33, 33, 32, 31, 17, 16, 1]
+    n = E - len(edges) - 10
+    each, more = divmod(T * k - sum(edges), n)
+    sizes = edges + [0] * 10 + [each + (i < more) for i in range(n)]
+    print(f"thin tiles alone {pair} k={k} d={d} f={f} group={group} shared={shared_f}", flush=True)
+    ctx, keep, versions, shared = _layer_of_few_versions(B, LY, dxo, pair, E, k, d, f, group, T, 19, shared_f)
+    sizes = np.random.default_rng(5).permutation(sizes).tolist()
+    logits = _logits_of_segments(sizes, T, k, 19)
+    assert dxo.route(logits, k)[2].tolist() == sizes
+    x = f32_to_bf16_bits(np.random.default_rng(19).standard_normal((T, d)).astype(np.float32))
+    _check_thin_tiles_alone(LY, dxo, ctx, versions, shared, shared_f, x, logits, k, f, group)
     ctx.close()
+    del keep
+
+
+@pytest.mark.parametrize("E,k,d,f,T,hi,tiles", [
+    (8, 2, 7168, 256, 66, (0, 2), False),       # 12 row tiles of two columns
+    (4, 1, 2560, 2048, 128, (0, 2), False),
+    (216, 10, 2304, 256, 128, (0, 2), True),    # 512 gate/up tiles, 5.9 pairs per expert
+    (215, 10, 2304, 256, 128, (0, 2), False),   # 510
+    (256, 10, 2304, 256, 128, (0, 2), True),    # five pairs per expert
+    (256, 10, 2304, 256, 127, (0, 2), False),   # a little less
+    (32, 26, 2304, 512, 127, (0, 1, 2, 3, 4), True),    # all bf16: 540 gate/up tiles
+    (26, 26, 2304, 640, 128, (0, 2), False),    # 650 gate/up tiles, at least 520: a round and a little
+    (16, 15, 2304, 2176, 33, (0, 2), True),     # up to 64 tokens: 279 down tiles
+    (16, 15, 2304, 2176, 33, (0, 1, 2, 3, 4), False),   # all bf16
+    (16, 15, 2304, 2112, 33, (0, 2), False),    # f in chunks and a half
+    (16, 15, 2176, 2176, 33, (0, 2), False),    # 248 down tiles
+    (16, 15, 2304, 2048, 64, (0, 2), False),    # the down projection in one round
+])
+def test_forward_up_to_128_tokens_on_tiles_where_they_fill_the_chip(B, LY, dxo, E, k, d, f, T, hi, tiles):
+    """Which calls of up to 128 tokens with K in rounds run on thin tiles: those that do not give the same bits as with an x that only the streaming kernels
+    take."""
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256, "the sizes are those of 256 compute units"
+    ctx, keep, _, _ = _layer_of_few_versions(B, LY, dxo, "bf16-int4", E, k, d, f, 64, T, 23, hi=hi)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    logits = torch.randn((T, E), generator=g, device="cuda")
+    x = torch.randn((T, d), generator=g, device="cuda").to(torch.bfloat16)
+    rb = LY.RoutingBuffers(T, E, k)
+    y, ys = torch.empty_like(x), torch.empty_like(x)
+    rb.route_forward(ctx, 0, logits, x, y)
+    rb.route_forward(ctx, 0, logits, _moved_by_four_bytes(x), ys)
+    sync()
+    assert torch.equal(y, ys) == (not tiles)
+    assert rel_l2(LY.device_to_bits(y), bf16_bits_to_f32(LY.device_to_bits(ys)).astype(np.float64)) <= 2.0 ** -8
+    ctx.close()
+    del keep
 
 
 def _hard_gates():
@@ -793,7 +875,7 @@ def _hard_gates():
 
 @pytest.mark.parametrize("T,E,k,d,f", [
     (240, 8, 1, 256, 128),      # thin tiles in the launch of the others
-    (128, 256, 8, 2176, 192),   # thin tiles alone
+    (128, 256, 10, 2176, 192),  # thin tiles alone
 ])
 def test_forward_thin_tiles_swiglu(B, LY, T, E, k, d, f):
     """SwiGLU of the thin tiles to fp32 accuracy: gates and ups given exactly (a token has one element, so they are a column of the matrices),
