@@ -556,8 +556,8 @@ def test_route_can_update_hotness_itself(B, LY, dxo):
                                             (200, 1, 1, [0]), (385, 1, 1, [0]), (384, 1, 1, [0]), (641, 2, 2, [0, 1])])
 def test_forward_prefill_tiles_small_shapes(B, LY, dxo, T, E, k, resident):
     """Up to 128 tokens per call the streaming kernels walk each segment in blocks of 32 tokens; above,
-    segments of more than 32 tokens take the tiled MFMA kernels (bf16 and int4), the others the
-    streaming ones; ragged row tiles; every token checked."""
+    segments of more than 32 tokens take 128-row tiles (bf16 and int4), the others thin
+    tiles; ragged row tiles; every token checked."""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=k)
     print(f"prefill tiles T={T} E={E} k={k} resident={resident}", flush=True)
@@ -853,6 +853,58 @@ def test_forward_up_to_128_tokens_on_tiles_where_they_fill_the_chip(B, LY, dxo, 
     sync()
     assert torch.equal(y, ys) == (not tiles)
     assert rel_l2(LY.device_to_bits(y), bf16_bits_to_f32(LY.device_to_bits(ys)).astype(np.float64)) <= 2.0 ** -8
+    ctx.close()
+    del keep
+
+
+@pytest.mark.parametrize("pair,T,k", [("bf16-int4", 64, 8), ("bf16-int4", 40, 14), ("int4-int2", 64, 8)])
+def test_forward_thin_tiles_alone_of_one_routing_chunk(B, LY, dxo, pair, T, k):
+    """Up to 64 tokens the routing is one kernel that lists no tiles: the list of the call, not that of the call of 128 tokens in front of it, and calls of
+    few tokens on thin tiles, recorded into a graph and replayed with other calls between."""
+    E, d, f, group = 16, 2304, 2176, 128
+    print(f"thin tiles alone {pair} T={T} k={k}", flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx, keep, versions, _ = _layer_of_few_versions(B, LY, dxo, pair, E, k, d, f, group, 128, 29, n=3, hi=(1,))
+        g = np.random.default_rng(T)
+        inputs = []
+        for n in (128, T):
+            inputs.append((f32_to_bf16_bits(g.standard_normal((n, d)).astype(np.float32)), (2 * g.standard_normal((n, E))).astype(np.float32)))
+        (x0, logits0), (x, logits) = inputs
+        rb0, y0 = LY.RoutingBuffers(128, E, k), torch.empty((128, d), dtype=torch.bfloat16, device="cuda")
+        x0, logits0 = LY.bits_to_device(x0), torch.from_numpy(logits0).cuda()
+
+        def other_call():
+            rb0.route_forward(ctx, 0, logits0, x0, y0)
+            stream.synchronize()
+
+        other_call()
+        tokens = np.sort(g.choice(T, 10, replace=False)).astype(np.int32)
+        eager = _check_thin_tiles_alone(LY, dxo, ctx, versions, None, 0, x, logits, k, f, group, tokens=tokens)
+        rb, y = LY.RoutingBuffers(T, E, k), torch.empty_like(eager)
+        xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            rb.route_forward(ctx, 0, ld, xd, y)
+        for rep in range(4):
+            y.zero_()
+            other_call()
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(y, eager), rep
+        # fewer tokens' worth of segments in the same buffers: the replay follows them
+        ld.copy_(torch.where(torch.arange(E, device="cuda") < k, 1.0, -4.0) + ld * 0.1)
+        rb.route_forward(ctx, 0, ld, xd, y)
+        stream.synchronize()
+        assert rb.counts.cpu().tolist() == [T] * k + [0] * (E - k)
+        want = y.clone()
+        other_call()
+        y.zero_()
+        graph.replay()
+        stream.synchronize()
+        assert torch.equal(y, want)
+        del graph
     ctx.close()
     del keep
 

@@ -266,10 +266,10 @@ def test_c5_churn_with_ema_and_hysteresis(B, LY, dxo):
         ctx.close()
 
 
-@pytest.mark.parametrize("T", [32, 1536])
+@pytest.mark.parametrize("T", [8, 32, 1536])
 def test_phi35_shaped_layer(B, LY, dxo, T):
-    """16 experts of 4096 x 6400, top-2, 4 of them bf16: the decode batch runs the streaming kernels on
-    K = 4096 and 6400 (more K-chunks than wavefronts), the prefill batch the tile
+    """16 experts of 4096 x 6400, top-2, 4 of them bf16: the smallest batch runs the streaming kernels on
+    K = 4096 and 6400 (more K-chunks than wavefronts), 32 tokens thin tiles alone, the prefill batch the tile
     kernel with 100 column tiles; sampled tokens against the oracle, routing bit-exact."""
     import dataclasses
     wl = dataclasses.replace(WORKLOADS["X1"], T=T)
