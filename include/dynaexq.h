@@ -299,9 +299,10 @@ dx_status dx_get_pool(dx_ctx *ctx, int which, void **base, uint64_t *block_bytes
 
 /* Per-kernel timing of dx_moe_forward with HIP events on the compute stream
  * (measurement aid, off by default).  While enabled, every forward call
- * (dx_moe_forward, dx_route_forward) times its kernels: decode batches attach
- * events to each kernel's own dispatch (start and stop stamps of the launch),
- * larger batches record events around the phases (streamed experts and tiles).
+ * (dx_moe_forward, dx_route_forward) times its kernels: up to 128 tokens events
+ * are attached to each kernel's own dispatch (start and stop stamps of the
+ * launch), above, events are recorded around the phases (each one or two
+ * kernels; gate/up with the list of tiles where routing has not written it).
  * dx_get_profile synchronises the compute stream, adds the elapsed times of all
  * calls since the last read and clears them.  Keep profiling off while the
  * compute stream is being captured into a graph (timing events do not belong

@@ -47,9 +47,9 @@ struct dx_transition {
 };
 
 // Timing events of one profiled forward call.  ev[0..3]: before gate/up, after it, after down, after
-// combine; ev[7], ev[4]: two records back to back (what an event pair itself adds).  Decode batches set
-// per_kernel: there ev[0]/ev[1], ev[5]/ev[2] and ev[6]/ev[3] are the start and stop stamps of the three
-// kernels' own dispatches (attached to the launches), not records between them.  Prefill: records between
+// combine; ev[7], ev[4]: two records back to back (what an event pair itself adds).  Calls of the streaming kernels and of
+// thin tiles alone set per_kernel: there ev[0]/ev[1], ev[5]/ev[2] and ev[6]/ev[3] are the start and stop stamps of the three
+// kernels' own dispatches (attached to the launches), not records between them.  Tiles of several kinds: records between
 // the phases.
 struct dx_marks {
     hipEvent_t ev[8];
@@ -224,5 +224,6 @@ hipError_t dxk_route_forward(const dx_fwd_args &a, const dx_route_io &r, int n_c
                              bool *routed);
 // dx_moe_prefill.hip: the list of row tiles of a call, and gate/up and down of its experts
 void dxk_tile_list(const dx_list_args &l, const int32_t *offsets, hipStream_t s);
-void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s);
-void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s);
+// (start, stop: events for the stamps of the kernel of a call of thin tiles alone, or null)
+void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s, hipEvent_t start, hipEvent_t stop);

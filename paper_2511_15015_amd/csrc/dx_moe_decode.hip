@@ -2102,15 +2102,14 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
         if (!*routed) return hipSuccess;
     }
     hipEvent_t *marks = mk ? mk->ev : nullptr;
-    hipEvent_t combine_start = nullptr, combine_stop = nullptr;
-    if (mk) mk->per_kernel = !tiled, mk->combined = false;
+    if (mk) mk->per_kernel = !a.o_bf16, mk->combined = false;
     bool combined = false; // y is there already
+    // profiled: every kernel's own start and stop stamps; with tiles of several kinds, whose phases may be two kernels, records around the phases
+    hipEvent_t ev[8] = {};
+    if (marks && !a.o_bf16)
+        for (int i = 0; i < 8; ++i) ev[i] = marks[i];
     if (!tiled) {
-        // profiled: every kernel's own start and stop stamps
         const dim3 grid(n_cu);
-        hipEvent_t ev[8] = {};
-        if (marks)
-            for (int i = 0; i < 8; ++i) ev[i] = marks[i];
         if (few.gate_up) launch_few(a, n_cu, s, ev[0], ev[1], r);
         else launch_stream<false>(a, grid, s, ev[0], ev[1], r);
         if (few.down) {
@@ -2121,25 +2120,24 @@ hipError_t launch_all(const dx_fwd_args &a_in, int n_cu, hipStream_t s, dx_marks
             if (mk) mk->combined = true;
         } else {
             launch_stream<true>(a, grid, s, ev[5], ev[2]);
-            combine_start = ev[6];
-            combine_stop = ev[3];
         }
     } else {
-        if (marks) (void)hipEventRecord(marks[0], s);
+        const bool records = marks && a.o_bf16;
+        if (records) (void)hipEventRecord(marks[0], s);
         if (!a.listed) dxk_tile_list(dxk_list_args(a, n_cu), a.offsets, s);
-        dxk_tiles_gate_up(a, s);
-        if (marks) (void)hipEventRecord(marks[1], s);
-        dxk_tiles_down(a, s);
-        if (marks) (void)hipEventRecord(marks[2], s);
+        dxk_tiles_gate_up(a, s, ev[0], ev[1]);
+        if (records) (void)hipEventRecord(marks[1], s);
+        dxk_tiles_down(a, s, ev[5], ev[2]);
+        if (records) (void)hipEventRecord(marks[2], s);
     }
     if (combined) {
     } else if (a.o_bf16) {
-        launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
+        launch(k_combine_bf16, dim3((a.d / 8 + 255) / 256, a.T), dim3(256), s, ev[6], ev[3], a);
     } else {
-        launch(k_combine, dim3((a.d / 4 + 255) / 256, a.T), dim3(256), s, combine_start, combine_stop, a);
+        launch(k_combine, dim3((a.d / 4 + 255) / 256, a.T), dim3(256), s, ev[6], ev[3], a);
     }
     if (marks) {
-        if (!combine_stop && !combined) (void)hipEventRecord(marks[3], s);
+        if (a.o_bf16) (void)hipEventRecord(marks[3], s);
         (void)hipEventRecord(marks[7], s); // two records back to back: the cost of an event pair itself
         (void)hipEventRecord(marks[4], s);
     }

@@ -19,6 +19,8 @@
 #include "dx_internal.h"
 #include "dx_tile_list.h"
 
+#include <hip/hip_ext.h>
+
 #include <type_traits>
 
 namespace {
@@ -1350,11 +1352,13 @@ static void launch_tiles(const dx_fwd_args &a, hipStream_t s)
 }
 
 template <bool DOWN>
-static void launch_thin(const dx_fwd_args &a, hipStream_t s)
+static void launch_thin(const dx_fwd_args &a, hipStream_t s, hipEvent_t start, hipEvent_t stop)
 {
     const int fe = a.shared && a.shared_f > a.f ? a.shared_f : a.f;
     const long tiles = dxk_thin_rows_max(a.T, a.k, a.E, a.shared != nullptr) * columns_of<DOWN>(a, fe, BNW);
-    hipLaunchKernelGGL((k_thin<DOWN>), dim3((unsigned)((tiles + 31) / 32 * 32)), dim3(cfg::THREADS), 0, s, a);
+    const dim3 grid((unsigned)((tiles + 31) / 32 * 32)), block(cfg::THREADS);
+    if (start || stop) hipExtLaunchKernelGGL((k_thin<DOWN>), grid, block, 0, s, start, stop, 0, a);
+    else hipLaunchKernelGGL((k_thin<DOWN>), grid, block, 0, s, a);
 }
 
 template <bool DOWN>
@@ -1369,15 +1373,15 @@ void dxk_tile_list(const dx_list_args &l, const int32_t *offsets, hipStream_t s)
 {
     hipLaunchKernelGGL(k_tile_list, dim3(1), dim3(kListThreads), 0, s, l, offsets);
 }
-void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s)
+void dxk_tiles_gate_up(const dx_fwd_args &a, hipStream_t s, hipEvent_t start, hipEvent_t stop)
 {
-    if (!a.o_bf16) return launch_thin<false>(a, s);
+    if (!a.o_bf16) return launch_thin<false>(a, s, start, stop);
     launch_big_tiles<false>(a, s);
     launch_tiles<false>(a, s);
 }
-void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s)
+void dxk_tiles_down(const dx_fwd_args &a, hipStream_t s, hipEvent_t start, hipEvent_t stop)
 {
-    if (!a.o_bf16) return launch_thin<true>(a, s);
+    if (!a.o_bf16) return launch_thin<true>(a, s, start, stop);
     launch_big_tiles<true>(a, s);
     launch_tiles<true>(a, s);
 }

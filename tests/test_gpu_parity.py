@@ -1587,6 +1587,37 @@ def test_profiling_reports_every_kernel_of_a_forward_call(B, LY, dxo):
         ctx.close()
 
 
+def test_profiling_stamps_the_kernels_of_thin_tiles_alone(B, LY, dxo):
+    """A call of up to 128 tokens on tiles reports its kernels' own durations: the gate/up kernel's is the same whether the kernel that lists the tiles (4 us
+    with its launch) runs in front of it, on a caller's routing arrays, or the routing wrote the list."""
+    T, E, k, d, f = 128, 256, 10, 2304, 256
+    ctx, keep, _, _ = _layer_of_few_versions(B, LY, dxo, "bf16-int4", E, k, d, f, 128, T, 37)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    logits, x = torch.randn((T, E), generator=g, device="cuda"), torch.randn((T, d), generator=g, device="cuda").to(torch.bfloat16)
+    rb, y, y1 = LY.RoutingBuffers(T, E, k), torch.empty_like(x), torch.empty_like(x)
+    rb.route_forward(ctx, 0, logits, x, y)
+    ctx.dx_set_profiling(True)
+    us = {True: [], False: []}
+    for rep in range(7):
+        for routed in (True, False):
+            for _ in range(20):
+                if routed:
+                    rb.route_forward(ctx, 0, logits, x, y1)
+                else:
+                    rb.forward(ctx, 0, x, y1)
+            p = ctx.dx_get_profile()
+            assert p["calls"] == 20 and p["down_ms"] > 0.0 and p["combine_ms"] > 0.0
+            us[routed].append(p["gate_up_ms"] * 50)
+    a, b = (float(np.median(v)) for v in us.values())
+    print(f"gate/up behind routing {a:.2f} us, behind the list {b:.2f}", flush=True)
+    assert abs(a - b) < 2.0, us
+    ctx.dx_set_profiling(False)
+    sync()
+    assert torch.equal(y, y1)
+    ctx.close()
+    del keep
+
+
 def test_route_forward_random_shapes_match_separate_calls(B, LY, dxo):
     """Seeded random decode shapes (tokens, experts, top-k, sizes, group, resident sets, with and without a
     shared expert): dx_route_forward gives the routing arrays of the oracle, bit for bit, and the same y
