@@ -877,11 +877,13 @@ __device__ __forceinline__ int thin_row(const dx_fwd_args &a, const tile_id &t, 
 template <bool DOWN, bool ALONE>
 __device__ __forceinline__ void store_thin(const dx_fwd_args &a, const tile_id &t, const f32x16 (&acc)[2], int row, int first, int lane)
 {
+    const int rows = t.m - (ALONE ? t.mt * DX_THIN_ROWS : 0);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
+        if (8 * (v >> 2) >= rows) break; // wave-uniform: most segments have few rows, and an exact SwiGLU is some thirty instructions
         const int token = (v >> 2) * 8 + 4 * (lane >> 5) + (v & 3);
         const int to = __shfl(row, token);
-        if ((ALONE ? t.mt * DX_THIN_ROWS : 0) + token >= t.m) continue;
+        if (token >= rows) continue;
         if constexpr (DOWN && ALONE) {
             float *dst = a.o + (size_t)to * a.d + first + (lane & 31);
             dst[0] = acc[0][v], dst[32] = acc[1][v];
