@@ -984,15 +984,18 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
     if (first < N) store_thin<DOWN, ALONE>(a, t, acc, row, first, lane);
 }
 
-// bf16 weights.  They and the token rows come to registers, two steps in flight, and pass through LDS on their way to the operands: with the
+// bf16 weights.  They and the token rows come to registers, and pass through LDS on their way to the operands: with the
 // non-temporal hint, from which loads to LDS gain nothing, a cold stream runs at 6.2 TB/s, by loads to LDS at 5.2 (30B-shaped, 130 tokens: a
-// layer 107 us by loads to LDS, 101 this way; three steps in flight 102).
+// layer 107 us by loads to LDS, 101 this way).  Three steps are in flight, and every tile starts at another one and goes round: tiles that start together
+// would all ask for the same 128 bytes of rows that lie a power of two apart, which are in few of the memory's channels.  128 experts of 2048 x 768, top-8, a
+// layer, us, balanced routing, 129, 160 and 256 tokens: two steps and the same start 149, 150 and 153, three steps 147, 147 and 148, and starts of their own 138, 138 and
+// 142; Zipf(1.1) 102, 105, 118 and 97, 99, 115.  (Codes, which are a quarter as much, gain nothing by it: 80B-shaped, 150 tokens 88 and 90.)
 //   LDS: two slots of token rows, one barrier per step: behind it every wavefront has read the slot that is filled next; one slot of the
 //   weights of each wavefront alone.
 template <bool DOWN, bool ALONE>
 __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
-    constexpr int DEPTH = 2, W0 = 2 * cfg::THIN_A;
+    constexpr int DEPTH = 3, W0 = 2 * cfg::THIN_A;
     static_assert(W0 + cfg::WAVES * cfg::B_WAVE <= cfg::LDS, "the ring");
     const int fe = thin_shared<ALONE>(a, t) ? a.shared_f : a.f;
     const int K = DOWN ? fe : a.d, nk = K / BK;
@@ -1007,7 +1010,9 @@ __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t
     struct step_regs {
         u32x4 tokens, weights[8];
     } st[DEPTH];
-    auto fetch = [&](int kt, step_regs &to) __attribute__((always_inline)) {
+    const int begin = (int)((uint32_t)(7 * t.nt + 13 * t.e) % (uint32_t)nk);
+    auto fetch = [&](int step, step_regs &to) __attribute__((always_inline)) { // the tile's step: step 0 is the matrix's step `begin`
+        const int kt = step + begin < nk ? step + begin : step + begin - nk;
         to.tokens = *reinterpret_cast<const DX_GLOBAL u32x4 *>(a_at + (uint32_t)(kt * kLine));
 #pragma unroll
         for (int i = 0; i < 8; ++i)
