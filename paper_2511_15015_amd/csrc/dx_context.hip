@@ -364,14 +364,14 @@ dx_status forward_args(dx_ctx *c, const char *who, int layer, const dx_handle *t
 {
     if (!x || !y || !ids || !w || !offsets || !perm) DX_FAIL(c, DX_ERR_INVALID, "%s: null pointer", who);
     const dx_config &g = c->cfg;
-    bool any_quantized = table != nullptr, any_bf16 = table != nullptr;
+    bool any_quantized = table != nullptr;
     if (!table) {
         // the context's own table: every expert of the layer must have a published version
         for (int e = 0; e < g.E; ++e) {
             const auto &entry = c->entries[entry_index(c, layer, e)];
             if (entry.state == DX_STATE_EMPTY)
                 DX_FAIL(c, DX_ERR_INVALID, "%s: expert (%d,%d) has no published version", who, layer, e);
-            (entry.h.fmt == DX_FMT_BF16 ? any_bf16 : any_quantized) = true;
+            any_quantized |= entry.h.fmt != DX_FMT_BF16;
         }
         table = c->d_table + (size_t)layer * g.E;
     }
@@ -401,7 +401,6 @@ dx_status forward_args(dx_ctx *c, const char *who, int layer, const dx_handle *t
     a.shared_f = g.shared_f;
     a.fmax = c->fmax;
     a.any_quantized = any_quantized;
-    a.any_bf16 = any_bf16;
     return DX_OK;
 }
 

@@ -195,7 +195,7 @@ struct dx_fwd_args {
     int T, E, k, d, f, group, shared_f, fmax;
     int o_bf16;  // O rows are bf16 (prefill: halves the traffic between the down kernels and the combine), else fp32
     int m_big;   // formats whose segments' whole 256 rows go in 256-row tiles: bit 0 bf16, bit 1 int4 (the values of dx_fmt)
-    int any_quantized, any_bf16; // some routed expert of the table may be (a caller's table: unknown)
+    int any_quantized; // some routed expert of the table may be (a caller's table: unknown)
     // A list for the kernels of a call, or null: calls on tiles: the row tiles; up to DX_FEW_TOKENS tokens on a caller's
     // routing arrays: the expert of every place in the segments, as int32_t, which the gate/up kernel leaves for the down kernel.
     dx_tile_head *tiles;

@@ -2070,11 +2070,7 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 //   3 % slower, 6 pairs 7 % faster; up to 64 tokens 32 of 8192 x 1536, 12 pairs 300 and 311).
 // - Not where the gate/up tiles are surely a little more than a round of two per compute unit (2 of 6144 x 8448, top-2, 124 tokens, 528 tiles 276 and 331).
 // - Up to 64 tokens, besides: a down tile per compute unit, a quantized expert (16 of 4096 x 6400, top-4, 64 tokens, all bf16 465 and 499, all int4 326 and 288), and
-//   f in whole chunks (20 of 5504 x 11456, top-6, 10 tokens 852 and 924, x 11392 800 and 752).  And, several layers in turn, streaming over tiles (times): more gate/up tiles, because
-//   experts without tokens leave compute units idle (16 of 6144 x 4096, top-2, 2.1 per unit, 24 tokens 0.90 to 0.93, int4/int2 0.95 to 0.98, 2.2, 32 tokens 0.94 to 0.99 and 1.02 to 1.05,
-//   top-4, 2.4, 24 tokens 1.03; 32 of 4096 x 2304, top-4, 2.5, 24 tokens 1.07 to 1.12); and where bf16 experts, whose tiles are the longest, are left alone with
-//   few tokens, top-1 and top-2, four pairs per expert (16 of 4096 x 6400, top-2, 24 tokens 0.95 to 1.06, 26 0.96 to 1.05, 28 0.97 to 1.07, 32 1.00 to 1.09, but int4/int2 24 tokens 1.05 to 1.10;
-//   top-1, 48 tokens 0.98 to 0.99; top-4, 12 tokens 1.05 to 1.09).
+//   f in whole chunks (20 of 5504 x 11456, top-6, 10 tokens 852 and 924, x 11392 800 and 752).
 bool takes_tiles(const dx_fwd_args &a, int n_cu)
 {
     const bool fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
@@ -2086,9 +2082,7 @@ bool takes_tiles(const dx_fwd_args &a, int n_cu)
     const long gate_up = rows * ((a.f + 127) / 128) + rows_shared * ((a.shared_f + 127) / 128), down = (rows + rows_shared) * (a.d / 256);
     const long least = ((long)a.T * a.k + DX_THIN_ROWS - 1) / DX_THIN_ROWS * ((a.f + 127) / 128); // gate/up tiles when no segment has a remainder
     if (gate_up < 2L * n_cu || (least > 2L * n_cu && gate_up < 4L * n_cu)) return false;
-    if (many) return 4 * down >= 3L * n_cu;
-    if (a.any_bf16 ? 3 * gate_up < 7L * n_cu || (a.k <= 2 && (long)a.T * a.k < 4L * a.E) : 4 * gate_up < 9L * n_cu) return false;
-    return both && a.f % 128 == 0 && a.any_quantized && down >= n_cu;
+    return many ? 4 * down >= 3L * n_cu : both && a.f % 128 == 0 && a.any_quantized && down >= n_cu;
 }
 
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed
