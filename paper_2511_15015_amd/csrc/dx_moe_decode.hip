@@ -2057,8 +2057,15 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 
 // Whether a call runs on tiles.  Otherwise the streaming kernels take every expert.  (x starts at a multiple of the 16 bytes that a lane of the
 // tiles' memory-to-LDS loads fetches; the streaming kernels' loads to registers take any address.)  Figures: us a layer, streaming and tiles.
-// More than 128 tokens: always.  The streaming kernels read the weights of a segment once per 32 tokens (30B-shaped, 129 tokens 115 and 101, 190 tokens 143
-// and 114; 80B-shaped, 129 tokens 99 and 86).
+// More than 128 tokens: tiles, because the streaming kernels read the weights of a segment once per 32 tokens (30B-shaped, 129 tokens 115 and 98, 190 tokens 143
+// and 107; 80B-shaped, 129 tokens 99 and 87), but
+// - not where the most row tiles that the pairs can have leave a quarter of the compute units without one, and pairs per expert are few (2048 elements of K and more; Zipf(0.5), 129, 200, 256
+//   tokens: 64 experts of 7168 x 256, top-2, 108 and 132, 112 and 134, 124 and 136, 400 tokens 138 and 142; 16 of 5120 x 512, top-1, 59 and 97, 66 and 99, 75 and 100; 32 of 2048 x 256,
+//   top-2, 37 and 49, 39 and 51, 42 and 52; 16 of 4096 x 1024, top-1, 256 tokens 80 and 90, 400 tokens, 1.1 tiles per compute unit, 103 and 91; many pairs: 8 of 7168 x 128, top-8, 320 tokens 126 and 121);
+// - nor, K in one round and up to 160 tokens, with up to 9/4 tiles per compute unit and 12 pairs per expert (129 and 160 tokens, Zipf(0.5), Zipf(1), Zipf(1.5): 32 experts of 2048 x 1024, top-2, 57 and 67, 60 and
+//   78; 57 and 64, 61 and 62; 55 and 60, 58 and 60; 128 of 2048 x 512, top-2, 63 and 66, 67 and 72; 52 and 55, 55 and 53; 45 and 52, 48 and 50; but 16 to 20 pairs, 32 of 2048 x 768, top-4,
+//   160 tokens 65 and 68, 69 and 64, 67 and 59).
+// With a shared expert always on tiles: all tokens are its segment (16 experts of 4096 x 128 and a shared one of 4096, 129 tokens 158 and 104).
 // Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up kernel takes K in rounds (more than 16 chunks of 128), each of which fetches the tokens
 // anew.  Where K is one round the streaming kernels are faster or equal (30B-shaped 32 tokens 62 and 80, 101 tokens 104 and 109; 80B-shaped 101 tokens 89 and 94).
 // - The tiles have to fill the chip, because each of them goes through all of K one step after the other: by the most row tiles that the pairs can have, two
@@ -2074,13 +2081,20 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 bool takes_tiles(const dx_fwd_args &a, int n_cu)
 {
     const bool fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
-    if (!fit || a.T > DX_FP32_TOKENS) return fit;
+    if (!fit) return false;
+    const long pairs = (long)a.T * a.k, cols = (a.f + 127) / 128, rows = dxk_thin_rows_max(a.T, a.k, a.E, false);
     auto in_rounds = [](int K) { return pick_split((K + 127) / 128, (K + 127) / 128).mode == kRounds; };
+    if (a.T > DX_FP32_TOKENS) {
+        const long tiles = rows * cols;
+        const bool idle = 4 * tiles <= 3L * n_cu && (a.T <= 256 ? pairs <= 48L * a.E : a.T <= 400 && pairs <= 24L * a.E);
+        const bool one_round = !in_rounds(a.d) && a.T <= 160 && 4 * tiles <= 9L * n_cu && pairs <= 12L * a.E;
+        return a.shared || a.d < 2048 || !(idle || one_round);
+    }
     const bool both = in_rounds(a.f), many = a.T > DX_ROUTE_CHUNK;
-    if (a.T <= kFewTokens || !in_rounds(a.d) || (long)a.T * a.k < (both ? 3L : 5L) * a.E) return false;
-    const long rows = dxk_thin_rows_max(a.T, a.k, a.E, false), rows_shared = a.shared ? (a.T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0;
-    const long gate_up = rows * ((a.f + 127) / 128) + rows_shared * ((a.shared_f + 127) / 128), down = (rows + rows_shared) * (a.d / 256);
-    const long least = ((long)a.T * a.k + DX_THIN_ROWS - 1) / DX_THIN_ROWS * ((a.f + 127) / 128); // gate/up tiles when no segment has a remainder
+    if (a.T <= kFewTokens || !in_rounds(a.d) || pairs < (both ? 3L : 5L) * a.E) return false;
+    const long rows_shared = a.shared ? (a.T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0;
+    const long gate_up = rows * cols + rows_shared * ((a.shared_f + 127) / 128), down = (rows + rows_shared) * (a.d / 256);
+    const long least = (pairs + DX_THIN_ROWS - 1) / DX_THIN_ROWS * cols; // gate/up tiles when no segment has a remainder
     if (gate_up < 2L * n_cu || (least > 2L * n_cu && gate_up < 4L * n_cu)) return false;
     return many ? 4 * down >= 3L * n_cu : both && a.f % 128 == 0 && a.any_quantized && down >= n_cu;
 }

@@ -859,6 +859,53 @@ def test_forward_up_to_128_tokens_on_tiles_where_they_fill_the_chip(B, LY, dxo, 
     del keep
 
 
+@pytest.mark.parametrize("E,k,d,f,T,shared_f,tiles", [
+    (80, 2, 2048, 256, 256, 0, False),      # 192 tiles at most
+    (81, 2, 2048, 256, 256, 0, True),       # 194
+    (5, 1, 2048, 256, 240, 0, False),       # 48 pairs per expert
+    (5, 1, 2048, 256, 241, 0, True),
+    (16, 1, 2048, 256, 384, 0, False),      # above 256 tokens 24
+    (16, 1, 2048, 256, 385, 0, True),
+    (32, 1, 2176, 256, 400, 0, False),
+    (32, 1, 2176, 256, 401, 0, True),
+    (16, 1, 1920, 256, 200, 0, True),       # a short K
+    (16, 1, 2048, 256, 200, 64, True),      # a shared expert
+    (128, 2, 2048, 512, 160, 0, False),     # K in one round: 552 tiles
+    (128, 2, 2048, 512, 161, 0, True),
+    (128, 2, 2048, 640, 160, 0, True),      # 690
+    (128, 2, 2176, 512, 160, 0, True),      # K in rounds
+    (22, 2, 2048, 1024, 132, 0, False),     # 12 pairs per expert
+    (22, 2, 2048, 1024, 133, 0, True),
+])
+def test_forward_above_128_tokens_on_streaming_kernels_where_tiles_are_few(B, LY, dxo, E, k, d, f, T, shared_f, tiles):
+    """Which calls of more than 128 tokens run on the streaming kernels: those that give the same bits as with an x that only they take; a dozen tokens
+    against the oracle."""
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256, "the sizes are those of 256 compute units"
+    print(f"above 128 tokens E={E} k={k} d={d} f={f} T={T} shared={shared_f}", flush=True)
+    ctx, keep, versions, shared = _layer_of_few_versions(B, LY, dxo, "bf16-int4", E, k, d, f, 64, T, 31, shared_f)
+    g = np.random.default_rng(T)
+    x, logits = f32_to_bf16_bits(g.standard_normal((T, d)).astype(np.float32)), g.standard_normal((T, E)).astype(np.float32)
+    ids, w, *_ = dxo.route(logits, k)
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    rb = LY.RoutingBuffers(T, E, k)
+    y, y1, ys = (torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    rb.route_forward(ctx, 0, ld, xd, y)
+    rb.route(ctx, 0, ld)
+    rb.forward(ctx, 0, xd, y1)
+    rb.forward(ctx, 0, _moved_by_four_bytes(xd), ys)
+    sync()
+    assert np.array_equal(rb.ids.cpu().numpy(), ids)
+    bits = LY.device_to_bits(y)
+    assert np.array_equal(bits, LY.device_to_bits(y1))
+    assert torch.equal(y, ys) == (not tiles)
+    tokens = np.sort(g.choice(T, 12, replace=False)).astype(np.int32)
+    y_ref = dxo.moe_forward(versions, d, f, 64, x, ids, w, shared=shared, shared_f=shared_f, tokens=tokens)
+    assert rel_l2(bits[tokens], y_ref) <= REL_L2_TOL
+    assert_elementwise(dxo, bits[tokens], y_ref, versions, 64, x, ids, w, shared=shared, tokens=tokens, T_call=T)
+    ctx.close()
+    del keep
+
+
 @pytest.mark.parametrize("pair,T,k", [("bf16-int4", 64, 8), ("bf16-int4", 40, 14), ("int4-int2", 64, 8)])
 def test_forward_thin_tiles_alone_of_one_routing_chunk(B, LY, dxo, pair, T, k):
     """Up to 64 tokens the routing is one kernel that lists no tiles: the list of the call, not that of the call of 128 tokens in front of it, and calls of
