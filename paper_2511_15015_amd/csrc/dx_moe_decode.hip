@@ -37,8 +37,8 @@
 //     the matrix instruction never crosses a quantization group, so the
 //     group's scale multiplies the group's fp32 partial sums once (q*s is
 //     never rounded).
-// Segments above 32 tokens go in blocks of 32.  Calls of more than 128 tokens, and of fewer on
-// layers whose K takes several rounds here, run on tiles (takes_tiles).
+// Segments above 32 tokens go in blocks of 32.  Most calls of more than 128 tokens, and calls of fewer
+// on layers whose K takes several rounds here, run on tiles (takes_tiles).
 #include "dx_internal.h"
 #include "dx_route_core.h"
 
@@ -1946,7 +1946,7 @@ void with_chunking(int group, int K_a, int K_b, F f)
 }
 int chunk_of(int group, int K_a, int K_b) { return K_a % 128 == 0 && K_b % 128 == 0 ? 128 : group; }
 
-// gate/up or down over the streamed experts; r: the gate/up kernel routes in its prologue (K a fast split)
+// gate/up or down on the streaming kernels; r: the gate/up kernel routes in its prologue (K a fast split)
 template <bool DOWN>
 void launch_stream(const dx_fwd_args &a, dim3 grid, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
                    const dx_route_io *r = nullptr)
@@ -2067,17 +2067,16 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 //   160 tokens 65 and 68, 69 and 64, 67 and 59).
 // With a shared expert always on tiles: all tokens are its segment (16 experts of 4096 x 128 and a shared one of 4096, 129 tokens 158 and 104).
 // Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up kernel takes K in rounds (more than 16 chunks of 128), each of which fetches the tokens
-// anew.  Where K is one round the streaming kernels are faster or equal (30B-shaped 32 tokens 62 and 80, 101 tokens 104 and 109; 80B-shaped 101 tokens 89 and 94).
-// - The tiles have to fill the chip, because each of them goes through all of K one step after the other: by the most row tiles that the pairs can have, two
-//   gate/up tiles and three quarters of a down tile per compute unit.  Top-2, 66 to 128 tokens, tiles per unit: gate/up 0.5 (8 experts of 7168 x 256) 43 and 125, 57 and 130; 1.25
-//   (16 of 8192 x 2048, 64 tokens) 185 and 217; 1.5 (8 of 4096 x 4096, int4/int2) 113 and 128, 2.0 the same 182 and 135; down 0.3 (4 of 2560 x 2048, top-1) 42 and 76,
-//   0.5 (4 of 4096 x 14336) 304 and 313, 0.75 (8 of them) 474 and 408, 128 tokens 728 and 492.
-// - And a tile has to have tokens: three pairs per expert if both contractions take rounds (64 of 4096 x 3072, top-8, 24 tokens 496 and 427; 16 of 4096 x 6400, 24 tokens
-//   285 and 265, 12 tokens, int4/int2 171 and 178), else five, and more than 64 tokens (64 of 4096 x 1024, int4/int2, 3.9 pairs 103 and 131, 128 of them, 4.1 pairs
-//   3 % slower, 6 pairs 7 % faster; up to 64 tokens 32 of 8192 x 1536, 12 pairs 300 and 311).
-// - Not where the gate/up tiles are surely a little more than a round of two per compute unit (2 of 6144 x 8448, top-2, 124 tokens, 528 tiles 276 and 331).
-// - Up to 64 tokens, besides: a down tile per compute unit, a quantized expert (16 of 4096 x 6400, top-4, 64 tokens, all bf16 465 and 499, all int4 326 and 288), and
-//   f in whole chunks (20 of 5504 x 11456, top-6, 10 tokens 852 and 924, x 11392 800 and 752).
+// anew.  Where K is one round the streaming kernels are faster or equal (30B-shaped 32 tokens 62 and 70, 101 tokens 105 and 99; 80B-shaped 101 tokens 88 and 85).
+// - The tiles have to fill the chip, because each of them goes through all of K one step after the other: by the most row tiles that the pairs can have, two gate/up
+//   tiles and three quarters of a down tile per compute unit.  Gate/up: 0.1 (8 experts of 7168 x 256, top-2) 128 tokens 54 and 109; 1.4 (16 of 8192 x 2048, top-2) 90 tokens 220 and 236;
+//   1.6 to 2.1 (32 of 8192 x 1536, top-8) 12, 24 and 48 tokens 242 and 249, 260 and 258, 303 and 277.  Down: 0.5 (4 of 4096 x 14336, top-2) 66 tokens 302 and 311; 0.6 to 0.75 (8 of
+//   them) 24, 32, 48 and 66 tokens 324 and 344, 348 and 349, 418 and 362, 504 and 375.
+// - And a tile has to have tokens: three pairs per expert if both contractions take rounds (16 of 4096 x 6400, top-2, Zipf(1.5), int4/int2, 2 pairs 141 and 140, 3 pairs 152 and 141; 32 of 4096 x
+//   2304, top-4, 2 pairs 171 and 146), else four (256 of 7168 x 256 and a shared one, top-8, 2 pairs 212 and 231, 3 pairs 240 and 251, 4 pairs 265 and 241; 64 of 4096 x 1024, top-8, 2 pairs
+//   135 and 136, 3 pairs 149 and 141, int4/int2 102 and 107, 115 and 109).
+// - Up to 64 tokens, besides, a quantized expert (16 of 4096 x 6400, top-4, all bf16, 48 tokens 442 and 468, 64 tokens 472 and 472, 66 tokens 488 and 474).
+// Over 889 calls (41 layers, 4 to 128 tokens) those that the rule puts on tiles are 1.03 to 2 times as fast there.
 bool takes_tiles(const dx_fwd_args &a, int n_cu)
 {
     const bool fit = a.d % 128 == 0 && a.f % 64 == 0 && (!a.shared || a.shared_f % 64 == 0) && ((uintptr_t)a.x & 15) == 0;
@@ -2090,13 +2089,10 @@ bool takes_tiles(const dx_fwd_args &a, int n_cu)
         const bool one_round = !in_rounds(a.d) && a.T <= 160 && 4 * tiles <= 9L * n_cu && pairs <= 12L * a.E;
         return a.shared || a.d < 2048 || !(idle || one_round);
     }
-    const bool both = in_rounds(a.f), many = a.T > DX_ROUTE_CHUNK;
-    if (a.T <= kFewTokens || !in_rounds(a.d) || pairs < (both ? 3L : 5L) * a.E) return false;
+    if (a.T <= kFewTokens || !in_rounds(a.d) || pairs < (in_rounds(a.f) ? 3L : 4L) * a.E || (a.T <= DX_ROUTE_CHUNK && !a.any_quantized)) return false;
     const long rows_shared = a.shared ? (a.T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0;
     const long gate_up = rows * cols + rows_shared * ((a.shared_f + 127) / 128), down = (rows + rows_shared) * (a.d / 256);
-    const long least = (pairs + DX_THIN_ROWS - 1) / DX_THIN_ROWS * cols; // gate/up tiles when no segment has a remainder
-    if (gate_up < 2L * n_cu || (least > 2L * n_cu && gate_up < 4L * n_cu)) return false;
-    return many ? 4 * down >= 3L * n_cu : both && a.f % 128 == 0 && a.any_quantized && down >= n_cu;
+    return gate_up >= 2L * n_cu && 4 * down >= 3L * n_cu;
 }
 
 // r: null, or the routing inputs and outputs of a call that asks the gate/up kernel to route; *routed

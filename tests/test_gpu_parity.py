@@ -828,17 +828,20 @@ def test_forward_thin_tiles_alone(B, LY, dxo, pair, k, d, f, group, shared_f):
 @pytest.mark.parametrize("E,k,d,f,T,hi,tiles", [
     (8, 2, 7168, 256, 66, (0, 2), False),       # 12 row tiles of two columns
     (4, 1, 2560, 2048, 128, (0, 2), False),
-    (216, 10, 2304, 256, 128, (0, 2), True),    # 512 gate/up tiles, 5.9 pairs per expert
+    (216, 10, 2304, 256, 128, (0, 2), True),    # 512 gate/up tiles
     (215, 10, 2304, 256, 128, (0, 2), False),   # 510
-    (256, 10, 2304, 256, 128, (0, 2), True),    # five pairs per expert
-    (256, 10, 2304, 256, 127, (0, 2), False),   # a little less
-    (32, 26, 2304, 512, 127, (0, 1, 2, 3, 4), True),    # all bf16: 540 gate/up tiles
-    (26, 26, 2304, 640, 128, (0, 2), False),    # 650 gate/up tiles, at least 520: a round and a little
-    (16, 15, 2304, 2176, 33, (0, 2), True),     # up to 64 tokens: 279 down tiles
-    (16, 15, 2304, 2176, 33, (0, 1, 2, 3, 4), False),   # all bf16
-    (16, 15, 2304, 2112, 33, (0, 2), False),    # f in chunks and a half
-    (16, 15, 2176, 2176, 33, (0, 2), False),    # 248 down tiles
-    (16, 15, 2304, 2048, 64, (0, 2), False),    # the down projection in one round
+    (256, 8, 2304, 256, 128, (0, 2), True),     # four pairs per expert, the down projection's K in one round
+    (256, 8, 2304, 256, 127, (0, 2), False),    # a little less
+    (64, 8, 2304, 2176, 24, (0, 2), True),      # three pairs per expert, both contractions in rounds
+    (64, 8, 2304, 2176, 23, (0, 2), False),     # a little less
+    (16, 8, 2176, 2944, 32, (0, 2), True),      # 192 down tiles
+    (16, 8, 2176, 2944, 31, (0, 2), False),     # 184
+    (32, 26, 2304, 512, 127, (0, 1, 2, 3, 4), True),    # all bf16
+    (16, 15, 2304, 2176, 33, (0, 1, 2, 3, 4), False),   # all bf16, up to 64 tokens
+    (16, 15, 2304, 2176, 33, (0, 2), True),
+    (16, 15, 2304, 2112, 33, (0, 2), True),     # f in chunks and a half
+    (16, 15, 2304, 2048, 64, (0, 2), True),     # the down projection's K in one round
+    (16, 15, 2048, 2304, 64, (0, 2), False),    # gate/up's
 ])
 def test_forward_up_to_128_tokens_on_tiles_where_they_fill_the_chip(B, LY, dxo, E, k, d, f, T, hi, tiles):
     """Which calls of up to 128 tokens with K in rounds run on thin tiles: those that do not give the same bits as with an x that only the streaming kernels
