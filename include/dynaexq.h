@@ -184,14 +184,17 @@ dx_status dx_router_logits(dx_ctx *ctx, const void *x_bf16, const void *w_router
  *   y[t] = sum_j topk_w[t,j] * W_down( silu(W_gate x[t]) * (W_up x[t]) )  of expert topk_ids[t,j]
  *          (+ the layer's shared expert, weight 1, when shared_f > 0)
  * handle_table: dev, E entries of this layer; NULL = the context's own table
- * for `layer`.  x_bf16 dev [T,d] (above 128 tokens faster when it starts at a
- * multiple of 16 bytes); y_bf16 dev [T,d]; routing arrays as written
+ * for `layer`.  x_bf16 dev [T,d]: the kernels that most calls of more than 128
+ * tokens run on, and fewer on layers of large experts, need a start at a
+ * multiple of 16 bytes; any other start is taken by slower kernels, which add
+ * up in another order.  y_bf16 dev [T,d]; routing arrays as written
  * by dx_route for the same T.  offsets and perm alone say which expert a pair
  * goes to, in any order inside a segment; topk_ids is part of the call's
  * arrays, must not be NULL and is not read.  Weights are read through the
  * handles as they are when the kernels run on the compute stream.
- * Sums are taken in fp32 in an order that the batch size, the shapes and the
- * counts determine: a repeated call gives the same bits, a token's y may
+ * Sums are taken in fp32 in an order that the batch size, the shapes, the
+ * counts and (few tokens) whether the table may hold quantized experts
+ * determine: a repeated call gives the same bits, a token's y may
  * differ in the last bits between batches.
  * Stream order: the call is asynchronous, all its kernels run on the compute
  * stream (and can be captured in a HIP graph with it as origin).  The H and O
@@ -299,10 +302,11 @@ dx_status dx_get_pool(dx_ctx *ctx, int which, void **base, uint64_t *block_bytes
 
 /* Per-kernel timing of dx_moe_forward with HIP events on the compute stream
  * (measurement aid, off by default).  While enabled, every forward call
- * (dx_moe_forward, dx_route_forward) times its kernels: up to 128 tokens events
- * are attached to each kernel's own dispatch (start and stop stamps of the
- * launch), above, events are recorded around the phases (each one or two
- * kernels; gate/up with the list of tiles where routing has not written it).
+ * (dx_moe_forward, dx_route_forward) times its kernels: up to 128 tokens, and
+ * above where a phase is one kernel, events are attached to each kernel's own
+ * dispatch (start and stop stamps of the launch); else they are recorded around
+ * the phases (each one or two kernels; gate/up with the list of tiles where
+ * routing has not written it).
  * dx_get_profile synchronises the compute stream, adds the elapsed times of all
  * calls since the last read and clears them.  Keep profiling off while the
  * compute stream is being captured into a graph (timing events do not belong

@@ -178,7 +178,7 @@ inline long dxk_thin_rows_max(int T, int k, int E, bool shared)
     const long pairs = (long)T * k;
     return pairs / DX_THIN_ROWS + (pairs < E ? pairs : E) + (shared ? (T + DX_THIN_ROWS - 1) / DX_THIN_ROWS : 0);
 }
-constexpr int DX_FP32_TOKENS = 128; // calls of up to so many tokens keep O in fp32 and never round a quantized weight
+constexpr int DX_FP32_TOKENS = 128; // calls of up to so many tokens (and larger ones on the streaming kernels) keep O in fp32 and never round a quantized weight
 // Calls of so few tokens (and top-k up to DX_ROUTED_MAX_TOPK) run the down projection and the combine in one kernel
 constexpr int DX_FEW_TOKENS = 2;
 struct dx_fwd_args {

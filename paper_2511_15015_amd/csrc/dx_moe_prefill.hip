@@ -4,15 +4,17 @@
 // Paper: Sec. 3.2 (the compute path resolves the handle and runs the kernel of
 // the active version).  The paper gives no kernel; this one is built for gfx950.
 //
-// Regime: calls of more than a hundred tokens.  Output tiles with v_mfma_f32_32x32x16_bf16, fp32
-// accumulators and K in steps of 64 (one 128-byte line of a token or weight row), filled by loads from memory
-// to LDS: k_tiled with tiles of 128 rows x 128 or 256 columns, any number of rows, all formats, and thin ones for segments of up to 32
-// rows; k_big with 256 x 256 for the whole 256 rows of large bf16 and int4 segments.  Quantized weights are expanded on their way to the matrix instructions (code ->
-// fp32 -> times the group's scale -> bf16).
+// Regime: calls of more than 128 tokens, and fewer on layers with a long K (takes_tiles in dx_moe_decode.hip).  Output tiles with
+// v_mfma_f32_32x32x16_bf16, fp32 accumulators and K in steps of 64 (one 128-byte line of a token or weight row).
+//   k_tiled: tiles of 128 rows x 128 or 256 columns, any number of rows, all formats, and thin ones for segments of up to 32 rows;
+//   k_big:   256 x 256 for the whole 256 rows of large bf16 and int4 segments;
+//   k_thin:  thin tiles alone, for calls of up to 128 tokens.
+// Quantized weights are expanded on their way to the matrix instructions: code -> fp32 -> times the group's scale -> bf16; in thin tiles the
+// codes are multiplied as integers and the scale goes on the fp32 sums.
 //   gate/up: half of the tile's columns are gate rows and the other half the up rows of the same
 //            indices, and every wavefront owns matching gate/up columns, so SwiGLU happens on the
 //            accumulators; H is written once as bf16.
-//   down:    plain tiles of O = H . W_down^T, written as bf16 rows in pair order for the combine kernel.
+//   down:    plain tiles of O = H . W_down^T, written as rows in pair order for the combine kernel, bf16 (k_thin: fp32).
 // Tiles are listed expert-major, in bands of row tiles, inside a band column tile next, row tile innermost, and
 // the list is cut into 8 contiguous ranges, one per XCD (block b works in range b % 8), so the tiles that
 // share token and weight lines run at the same time on the same L2.
@@ -140,16 +142,17 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
 // This block's tile.  The row tiles of all experts are in a.tiles (written in front, by the routing's placement kernel or by k_tile_list,
 // because a prologue that derives the list from the offsets in every block is 3 of a tile's 20 to 35 us): the routed
 // experts', the shared one's, the 256-row tiles behind them, the thin tiles.  Each XCD takes an eighth of the former.
-// Thin tiles in this launch (before: segments of up to 32 rows in the streaming kernels, a launch per phase in front, during which the matrix
-// cores had little to do).  A layer, us, streaming kernels in front and now: 30B-shaped 300 tokens 140 and 121, 1000 tokens 204 and 192, 4096
-// tokens 464 and 432, int4/int2 150 tokens 101 and 81; 80B-shaped 150 tokens 111 and 92, 1000 tokens 204 and 178; 16 experts of 4096 x 6400,
-// 150 tokens 412 and 311, 1100 tokens 602 and 539; 30B-shaped 190 tokens the same, 130 to 150 tokens 103 to 106 and 105
-// to 111: 360 tiles in one round, and those of 256 columns of bf16 weights are four times as long as the others.  First or last: last, because they are short and fill
-// the last round; first where bf16 weights from memory are all there is (up to four narrow tiles per compute unit): 30B-shaped 300 tokens
-// 132 first and 143 last, 500 tokens 146 and 157, 16 of 4096 x 6400 150 tokens 320 and 339; but int4/int2 150 tokens 84 and 79, 1100 tokens of
-// the 16 556 and 550, 80B-shaped 1000 tokens 187 and 178, and with few other tiles: first only where a good part of the thin ones is bf16 as well (80B-shaped 150
-// tokens, none 94 and 92; 30B-shaped 130 tokens 103 and 107).
-// Wide or narrow: a compute unit holds two tiles of either kind.  Figures: the phase's kernels, us, narrow and wide, by narrow tiles
+// Figures: us a layer.
+// Thin tiles are in the launch of the others.  (Streaming kernels for the segments of up to 32 rows, a launch in front in each phase, and this: 30B-shaped 129
+// tokens 111 and 98, 300 tokens 137 and 116, 1000 tokens 196 and 184, 4096 tokens 456 and 425, int4/int2 150 tokens 101 and 82; 80B-shaped 150 tokens 115 and 86, 1000
+// tokens 200 and 170; 16 experts of 4096 x 6400 150 tokens 397 and 309, 1100 tokens 587 and 532.  But if no segment has more than 32 rows: 30B-shaped, balanced
+// routing, 129 tokens 120 and 137, 200 tokens 128 and 139, 256 tokens 141 and 142; 80B-shaped 129 tokens 217 and 231, 600 tokens 258 and 261.)
+// Thin tiles go last, because they are short and fill the last round.  They go first where bf16 weights from memory are all there is, up to four narrow tiles per compute
+// unit, and with few other tiles (up to one) only if a good part of the thin ones is bf16 as well.
+//   First and last: 30B-shaped 130 tokens 96 and 99, 300 tokens 116 and 124, 500 tokens 139 and 146, int4/int2 150 tokens 86 and 81; 80B-shaped 150 tokens 88 and 84, 1000
+//   tokens 175 and 162; 16 of 4096 x 6400 150 tokens 329 and 297, int4/int2 266 and 244, 1100 tokens 534 and 522.  Over 55 calls of 19 layers the rule takes 0.93 to 1.09 times as
+//   long as last throughout, 0.91 to 1.02 times as long as first; what it gets wrong is a K of 7168 (64 experts of 7168 x 512, top-2, 200 tokens 190 and 176).
+// Wide or narrow: a compute unit holds two tiles of either kind.  Figures: the phase's kernels alone, narrow and wide, by narrow tiles
 // per compute unit; the same lines hold for both phases.
 //   Quantized weights gain by the expansion as soon as there is more than one round: all int4, 128 experts of 2048 x 768, 110 rows each, gate/up
 //   2.6 76 and 75, 4.3 123 and 122, 6.0 153 and 134, down 3.4 48 and 40, 8.0 96 and 78; 8 of 4096 x 4096, down 2.0 96 and 102, 3.0 141 and 141.

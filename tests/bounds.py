@@ -2,7 +2,7 @@
 
 The HIP path computes every product of bf16 values exactly and accumulates in fp32; what separates
 its result from the fp64 oracle's are its bf16 roundings: H = silu(g) * u is stored as bf16 (relative
-error at most 2^-9 per element), y is stored as bf16 (2^-9 of |y|), and batches above 128 tokens also
+error at most 2^-9 per element), y is stored as bf16 (2^-9 of |y|), and most batches above 128 tokens also
 store the expert outputs O as bf16 (2^-9 of |o|).  Propagating the first through the down projection
 and the combine gives, for token t and column c,
 
