@@ -732,6 +732,51 @@ def test_forward_prefill_thin_segments(B, LY, dxo, pair, d, f, group):
     ctx.close()
 
 
+@pytest.mark.parametrize("pair,d,f,group,shared_f", [
+    ("bf16-int4", 2176, 192, 64, 0),    # 34 K steps and three; 1.5 and 8.5 column tiles
+    ("bf16-int4", 2304, 256, 128, 384), # a shared expert of another width, in four row tiles
+    ("bf16-int4", 2176, 64, 32, 64),
+    ("int4-int2", 2176, 192, 64, 0),
+    ("int4-int2", 2304, 256, 128, 0),
+])
+def test_forward_thin_tiles_alone(B, LY, dxo, pair, d, f, group, shared_f):
+    """Calls of up to 128 tokens whose K the streaming kernels take in rounds, ragged segments (too few for thin tiles to fill the chip: the streaming
+    kernels have them), with O in fp32: every token against the oracle; the same bits from one call and from two."""
+    import dataclasses
+    sizes = [1, 1, 32, 33, 0, 0, 20, 17, 3, 4]
+    E, T = len(sizes), sum(sizes)
+    wl = dataclasses.replace(WORKLOADS["C1"], T=T, E=E, k=1, d=d, f=f, group=group, shared_f=shared_f)
+    x, _ = W.layer_inputs(wl, seed=19)
+    logits = np.zeros((T, E), np.float32)
+    logits[np.arange(T), np.random.default_rng(5).permutation(np.repeat(np.arange(E), sizes))] = 4.0
+    hi = list(range(0, E, 2))
+    print(f"thin tiles alone {pair} d={d} f={f} group={group} shared={shared_f} T={T}", flush=True)
+    shared = None
+    if pair == "int4-int2":
+        ctx, keep, versions = _quant_pair_layer(B, LY, dxo, wl, hi, 19, T)
+    else:
+        keep = Layer(B, LY, dxo, wl, hi, seed=19, shared=W.shared_master(wl, 19, 0) if shared_f else None)
+        ctx, versions, shared = keep.ctx, keep.versions, keep.shared
+    ids, w, counts, offsets, perm = dxo.route(logits, 1)
+    assert counts.tolist() == sizes and 64 < T <= 128
+    rb = LY.RoutingBuffers(T, E, 1)
+    xd, ld = LY.bits_to_device(x), torch.from_numpy(logits).cuda()
+    y, y1 = (torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    rb.route_forward(ctx, 0, ld, xd, y)
+    rb.route(ctx, 0, ld)
+    rb.forward(ctx, 0, xd, y1)
+    sync()
+    bits = LY.device_to_bits(y)
+    assert np.array_equal(bits, LY.device_to_bits(y1))
+    y_ref = dxo.moe_forward(versions, d, f, group, x, ids, w, shared=shared, shared_f=shared_f if shared else 0)
+    yg = bf16_bits_to_f32(bits).astype(np.float64)
+    tok = np.linalg.norm(yg - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)
+    assert rel_l2(bits, y_ref) <= REL_L2_TOL and tok.max() <= 2 * REL_L2_TOL
+    assert_elementwise(dxo, bits, y_ref, versions, group, x, ids, w, shared=shared, T_call=T)
+    del keep
+    ctx.close()
+
+
 def _layer_of_few_versions(B, LY, dxo, pair, E, k, d, f, group, T, seed, shared_f=0, n=5, hi=(0, 2)):
     """A layer of E experts that share n versions: context, what it needs kept, the versions, the shared expert's."""
     import dataclasses
@@ -806,7 +851,7 @@ def _check_thin_tiles_alone(LY, dxo, ctx, versions, shared, shared_f, x, logits,
     ("int4-int2", 10, 2176, 192, 64, 0),
     ("int4-int2", 10, 2304, 256, 128, 0),
 ])
-def test_forward_thin_tiles_alone(B, LY, dxo, pair, k, d, f, group, shared_f):
+def test_forward_thin_tiles_alone_at_the_edges_of_a_tile(B, LY, dxo, pair, k, d, f, group, shared_f):
     """Calls of up to 128 tokens whose K the streaming kernels would take in rounds run on thin tiles if they fill the chip, segments above 32 rows
     in several, with O in fp32: segments at the edges of a tile, every token against the oracle."""
     T, E = 128, 256
