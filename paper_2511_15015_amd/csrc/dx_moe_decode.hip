@@ -2067,7 +2067,8 @@ int big_tile_formats(const dx_fwd_args &a, int n_cu)
 //   160 tokens 65 and 68, 69 and 64, 67 and 59).
 // With a shared expert always on tiles: all tokens are its segment (16 experts of 4096 x 128 and a shared one of 4096, 129 tokens 158 and 104).
 // Up to 128 tokens thin tiles alone, O in fp32, where the streaming gate/up kernel takes K in rounds (more than 16 chunks of 128), each of which fetches the tokens
-// anew.  Where K is one round the streaming kernels are faster or equal (30B-shaped 32 tokens 62 and 70, 101 tokens 105 and 99; 80B-shaped 101 tokens 88 and 85).
+// anew.  Where K is one round the streaming kernels take all of them (30B-shaped 32 tokens 62 and 70; but 101 tokens 105 and 99, 80B-shaped 101 tokens 88 and 85: a line
+// below 128 tokens is still to be found).
 // - The tiles have to fill the chip, because each of them goes through all of K one step after the other: by the most row tiles that the pairs can have, two gate/up
 //   tiles and three quarters of a down tile per compute unit.  Gate/up: 0.1 (8 experts of 7168 x 256, top-2) 128 tokens 54 and 109; 1.4 (16 of 8192 x 2048, top-2) 90 tokens 220 and 236;
 //   1.6 to 2.1 (32 of 8192 x 1536, top-8) 12, 24 and 48 tokens 242 and 249, 260 and 258, 303 and 277.  Down: 0.5 (4 of 4096 x 14336, top-2) 66 tokens 302 and 311; 0.6 to 0.75 (8 of
