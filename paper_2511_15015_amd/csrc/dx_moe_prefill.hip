@@ -146,7 +146,7 @@ __device__ __forceinline__ tile_id tile_of(const dx_tile_row *rows, uint32_t idx
 // Thin tiles are in the launch of the others.  (Streaming kernels for the segments of up to 32 rows, a launch in front in each phase, and this: 30B-shaped 129
 // tokens 111 and 98, 300 tokens 137 and 116, 1000 tokens 196 and 184, 4096 tokens 456 and 425, int4/int2 150 tokens 101 and 82; 80B-shaped 150 tokens 115 and 86, 1000
 // tokens 200 and 170; 16 experts of 4096 x 6400 150 tokens 397 and 309, 1100 tokens 587 and 532.  But if no segment has more than 32 rows: 30B-shaped, balanced
-// routing, 129 tokens 120 and 137, 200 tokens 128 and 139, 256 tokens 141 and 142; 80B-shaped 129 tokens 217 and 231, 600 tokens 258 and 261.)
+// routing, 129 tokens 120 and 130, 200 tokens 122 and 130, no bf16 expert 97 and 106; 80B-shaped 129 tokens 225 and 235, 600 tokens 248 and 253: 1.5 rounds of thin tiles in gate/up.)
 // Thin tiles go last, because they are short and fill the last round.  They go first where bf16 weights from memory are all there is, up to four narrow tiles per compute
 // unit, and with few other tiles (up to one) only if a good part of the thin ones is bf16 as well.
 //   First and last: 30B-shaped 130 tokens 96 and 99, 300 tokens 116 and 124, 500 tokens 139 and 146, int4/int2 150 tokens 86 and 81; 80B-shaped 150 tokens 88 and 84, 1000
@@ -989,16 +989,16 @@ __device__ __forceinline__ void thin_codes(const dx_fwd_args &a, const tile_id &
 
 // bf16 weights.  They and the token rows come to registers, and pass through LDS on their way to the operands: with the
 // non-temporal hint, from which loads to LDS gain nothing, a cold stream runs at 6.2 TB/s, by loads to LDS at 5.2 (30B-shaped, 130 tokens: a
-// layer 107 us by loads to LDS, 101 this way).  Three steps are in flight, and every tile starts at another one and goes round: tiles that start together
+// layer 107 us by loads to LDS, 101 this way).  Four steps are in flight (250 registers), and every tile starts at another one and goes round: tiles that start together
 // would all ask for the same 128 bytes of rows that lie a power of two apart, which are in few of the memory's channels.  128 experts of 2048 x 768, top-8, a
 // layer, us, balanced routing, 129, 160 and 256 tokens: two steps and the same start 149, 150 and 153, three steps 147, 147 and 148, and starts of their own 138, 138 and
-// 142; Zipf(1.1) 102, 105, 118 and 97, 99, 115.  (Codes, which are a quarter as much, gain nothing by it: 80B-shaped, 150 tokens 88 and 90.)
+// 142; Zipf(1.1) 102, 105, 118 and 97, 99, 115.  The fourth step: balanced 129 and 200 tokens 136 -> 130, 138 -> 130, 16 of 4096 x 6400 128 tokens 341 -> 338, the others the same.  (Codes, which are a quarter as much, gain nothing by it: 80B-shaped, 150 tokens 88 and 90.)
 //   LDS: two slots of token rows, one barrier per step: behind it every wavefront has read the slot that is filled next; one slot of the
 //   weights of each wavefront alone.
 template <bool DOWN, bool ALONE>
 __device__ __forceinline__ void thin_rows(const dx_fwd_args &a, const tile_id &t, const dx_handle *h, char *ring)
 {
-    constexpr int DEPTH = 3, W0 = 2 * cfg::THIN_A;
+    constexpr int DEPTH = 4, W0 = 2 * cfg::THIN_A;
     static_assert(W0 + cfg::WAVES * cfg::B_WAVE <= cfg::LDS, "the ring");
     const int fe = thin_shared<ALONE>(a, t) ? a.shared_f : a.f;
     const int K = DOWN ? fe : a.d, nk = K / BK;

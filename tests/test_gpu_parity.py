@@ -687,7 +687,7 @@ def test_forward_prefill_wide_tiles(B, LY, dxo, pair, T, E, k, d, f, group, hi):
     ("bf16-int4", 128, 64, 32),     # two steps and one; a quarter and half of a tile's columns
     ("bf16-int4", 384, 320, 64),    # six steps and five, odd numbers of groups per row; 2.5 and 1.5 column tiles
     ("bf16-int4", 640, 384, 128),   # ten steps and six, five and three groups
-    ("bf16-int4", 256, 448, 64),    # four steps and seven: bf16 tiles start at one of them each, and have three in flight
+    ("bf16-int4", 256, 448, 64),    # four steps and seven: bf16 tiles start at one of them each, and have four in flight
     ("bf16-int4", 512, 576, 64),    # eight and nine
     ("bf16-int4", 2048, 768, 128),  # the 30B layer's
     ("int4-int2", 384, 320, 64),
